@@ -30,6 +30,7 @@ struct SampleArgs {
     kge_sampler s;
     uint64_t base[4];  // mix(seed + GOLDEN * tag) per tag, formed on the host
     int64_t first_step, n_steps;
+    int waves_per_step;  // waves of 64 consecutive items (positives, then corrupting slots) that one step takes
     int64_t* h;
     int64_t* r;
     int64_t* t;
@@ -39,39 +40,48 @@ struct SampleArgs {
 
 __device__ __forceinline__ int side_of(int mode, int64_t step) { return mode == 2 ? (int)(step & 1) : mode; }
 
-__device__ __forceinline__ int64_t position(const SampleArgs& a, uint64_t zs, int64_t j) {
-    // zs = mix(base[1] + step); positives use a = 0
-    return scale_to(mix64(mix64(zs + 0) + (uint64_t)j), (uint64_t)a.s.n_triples);
-}
-
+// A wave owns 64 consecutive items of one step, so the step, its side and the first rounds of the key chain are the
+// same in all lanes, and no lane divides by the items per step (one 64-bit division per id took longer than the
+// rest).  Bound by the random 24-byte reads of the triple list (a list of millions of triples lies in the Infinity
+// Cache, and every read pulls a whole line): a triple is read with two requests (16 + 8 bytes) instead of three, and
+// the ids are stored past the caches so that the list keeps them (2 % faster).  1000 steps of 3,200 ids from a list of
+// 1 M triples: 30.8 -> 23.1 us, about 146 MB of list lines at 6.3 TB/s.
 __global__ __launch_bounds__(256) void k_sample(SampleArgs a) {
-    const int b = a.s.batch, k = a.s.neg_per_chunk, per_step = b + a.s.n_chunks * k;
-    const int64_t total = a.n_steps * per_step;
-    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
-        const int64_t si = idx / per_step;
-        const int item = (int)(idx - si * per_step);
+    typedef long long i64x2 __attribute__((ext_vector_type(2), aligned(8)));
+    const int b = a.s.batch, k = a.s.neg_per_chunk, n_neg = a.s.n_chunks * k, lane = threadIdx.x & 63;
+    const float inv_k = 1.f / (float)(k > 0 ? k : 1);
+    const int64_t waves = a.n_steps * a.waves_per_step, stride = (int64_t)gridDim.x * 4;
+    for (int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); w < waves; w += stride) {
+        const int64_t si = w >> 32 ? w / a.waves_per_step : (int64_t)((uint32_t)w / (uint32_t)a.waves_per_step);
+        const int64_t item = (w - si * a.waves_per_step) * 64 + lane;
         const int64_t step = a.first_step + si;
         const int side = side_of(a.s.side_mode, step);
-        const uint64_t zpos = mix64(a.base[1] + (uint64_t)step);
+        const uint64_t zpos = mix64(mix64(a.base[1] + (uint64_t)step));  // positives use a = 0
         if (item < b) {
-            const int64_t p = position(a, zpos, item);
-            a.h[si * b + item] = a.s.triples[3 * p];
-            a.r[si * b + item] = a.s.triples[3 * p + 1];
-            a.t[si * b + item] = a.s.triples[3 * p + 2];
+            const int64_t p = scale_to(mix64(zpos + (uint64_t)item), (uint64_t)a.s.n_triples);
+            const i64x2 hr = *reinterpret_cast<const i64x2*>(a.s.triples + 3 * p);
+            const int64_t t = a.s.triples[3 * p + 2];
+            __builtin_nontemporal_store(hr.x, (long long*)a.h + si * b + item);
+            __builtin_nontemporal_store(hr.y, (long long*)a.r + si * b + item);
+            __builtin_nontemporal_store(t, a.t + si * b + item);
             if (item == 0 && a.sides) a.sides[si] = side;
-        } else {
-            const int q = item - b, c = q / k, j = q - c * k;
+        } else if (item - b < n_neg) {
+            const uint32_t q = (uint32_t)(item - b);
+            uint32_t c = (uint32_t)((float)q * inv_k);  // q / k: the float quotient is off by a few at most
+            while (c * (uint32_t)k > q) --c;
+            while (q - c * (uint32_t)k >= (uint32_t)k) ++c;
+            const uint32_t j = q - c * (uint32_t)k;
             int64_t id;
-            if (j < a.s.n_degree) {
+            if ((int)j < a.s.n_degree) {
                 const uint64_t key = mix64(mix64(mix64(a.base[3] + (uint64_t)step) + (uint64_t)c) + (uint64_t)j);
                 const int64_t pick = scale_to(key, (uint64_t)b);
-                const int64_t p = position(a, zpos, pick);
+                const int64_t p = scale_to(mix64(zpos + (uint64_t)pick), (uint64_t)a.s.n_triples);
                 id = a.s.triples[3 * p + (side == KGE_NEG_HEAD ? 0 : 2)];
             } else {
                 const uint64_t key = mix64(mix64(mix64(a.base[2] + (uint64_t)step) + (uint64_t)c) + (uint64_t)j);
                 id = scale_to(key, (uint64_t)a.s.num_entities);
             }
-            a.neg[si * (int64_t)(a.s.n_chunks * k) + q] = id;
+            __builtin_nontemporal_store(id, a.neg + si * (int64_t)n_neg + q);
         }
     }
 }
@@ -85,8 +95,9 @@ int kge_sample_launch(const kge_sampler* s, int64_t first_step, int64_t n_steps,
     for (int tag = 0; tag < 4; ++tag) a.base[tag] = mix64(s->seed + GOLDEN * (uint64_t)tag);
     a.first_step = first_step; a.n_steps = n_steps;
     a.h = h; a.r = r; a.t = t; a.neg = neg; a.sides = sides;
-    const int64_t total = n_steps * (int64_t)(s->batch + s->n_chunks * s->neg_per_chunk);
-    int64_t blocks = (total + 255) / 256;
+    const int64_t per_step = (int64_t)s->batch + (int64_t)s->n_chunks * s->neg_per_chunk;
+    a.waves_per_step = (int)((per_step + 63) / 64);
+    int64_t blocks = (n_steps * a.waves_per_step + 3) / 4;
     if (blocks > 65536) blocks = 65536;
     hipLaunchKernelGGL(k_sample, dim3((unsigned)blocks), dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? KGE_OK : KGE_ERR_DEVICE;
