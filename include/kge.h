@@ -127,13 +127,14 @@ int kge_train_step(kge_ctx* ctx, float* ent, float* ent_state, float* rel, float
  * (r, t likewise) and neg[s*(b/chunk)*k ..].  neg_sides: (host) array of n_steps kge_neg_side values, or NULL for
  * tail corruption throughout.  loss_out: device float[n_steps] or NULL.  Same result as n_steps calls of
  * kge_train_step; exists so that a whole pass over pre-sampled mini-batches (Sec. 3.1 step 1 done ahead of time)
- * costs one call.  On a stream that can be captured (any stream but the legacy default stream) the steps are
- * replayed from HIP graphs that the context builds on the first call with a given combination of tables, b, k, chunk,
- * gamma and lr (that call creates graph objects) and keeps: the kernels find the id arrays, the sides and the loss
- * array of the running call through a block in the workspace, so later calls with other arrays replay the same
- * graphs and allocate nothing.  The call must not itself be made while the stream is being captured by the caller
- * (then, and on the default stream, and for fewer than 4 steps, it launches kernel by kernel).  The sides are copied
- * into a fixed part of the workspace; a call of more than 65,536 steps with sides runs in segments of that length.
+ * costs one call.  Shorter calls (fewer than 16 steps) and the first steps of every call are launched kernel by
+ * kernel; the last 16 or 32 steps of a call, and from 256 steps on all but its first, are replayed from HIP graphs that
+ * the context builds on the first call that needs them with a given combination of tables, b, k, chunk, gamma and lr
+ * (that call creates graph objects) and keeps: the kernels find the id arrays, the sides and the loss array of the
+ * running call through a block in the workspace, so later calls with other arrays replay the same graphs and allocate
+ * nothing.  On the legacy default stream, which cannot be captured, and while the caller is capturing the stream
+ * itself, every step is launched kernel by kernel.  The sides of a long replay are copied into a fixed part of the
+ * workspace; more than 65,536 replayed steps with sides run in segments of that length.
  */
 int kge_train_steps(kge_ctx* ctx, float* ent, float* ent_state, float* rel, float* rel_state,
                     const int64_t* h, const int64_t* r, const int64_t* t, int64_t b,

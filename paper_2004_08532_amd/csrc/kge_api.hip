@@ -248,31 +248,20 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     return KGE_OK;
 }
 
-// ---- replay: kge_train_steps captures 1, 2, 4, ... 32 consecutive steps into HIP graphs whose kernels take the step
+// ---- replay: kge_train_steps captures 16 or 32 consecutive steps into HIP graphs whose kernels take the step
 // number and the id arrays from device memory (the step block), so the same graphs serve every step of every call
-// of the same shape.  Launching a graph costs the host about 2 us per kernel in it plus a fixed part, and the
-// device starts on a graph only once the whole of it is enqueued, and every graph start costs the device about 8 us
-// of idling: a call therefore starts with a graph of one step (the device is busy after one step's worth of
-// enqueueing), lets the graphs grow as fast as the host can stay ahead, and otherwise uses as few graphs as the step
-// count allows (20 steps: 1, 1, 2, 16).
-constexpr int REPLAY_SIZES = 6;  // graphs of 1 << i steps, i < REPLAY_SIZES (measured per Freebase-scale step in a
-                                 // 10,000-step call: longest graph 8 steps 38.2 us, 16: 37.9, 32: 37.8, 64: 38.4)
-
-// Launches exec[i] (1 << i steps), or, if that graph is too long for its place in the call, its two halves.  Too long:
-// more than RAMP times the steps already enqueued by this call (the first graph of a call is one step).  Enqueueing
-// costs the host about 8 us per step, a step takes the device four times that or more, so the host stays ahead.
-constexpr int64_t RAMP = 4;
-void launch_graphs(hipGraphExec_t* exec, int i, int64_t* done, hipStream_t st, hipError_t* err) {
-    const int64_t len = (int64_t)1 << i, cap = *done > 0 ? RAMP * *done : 1;
-    if (i > 0 && len > cap) {
-        launch_graphs(exec, i - 1, done, st, err);
-        launch_graphs(exec, i - 1, done, st, err);
-        return;
-    }
-    const hipError_t e = hipGraphLaunch(exec[i], st);
-    if (*err == hipSuccess) *err = e;
-    *done += len;
-}
+// of the same shape.  A graph costs the host about 0.7 us per kernel where a plain launch costs 3.7 us, and costs the
+// device about 8 us of idling at its start where plain launches follow each other without a gap as long as the host
+// stays ahead (it does: 15 us of launching per four-kernel step against 20 us and more on the device; and a plain
+// launch carries its id pointers in its arguments, one dependent load less per kernel).  So:
+//   fewer than 16 steps       plain launches
+//   up to REPLAY_LONG steps   plain launches, and one graph for the last 16 or 32 steps (the call returns while they run)
+//   longer calls              plain launches for at least 32 steps, graphs of 32 for the rest
+// Measured per pass (all graphs, growing from one step -> this): 4 TransE-L1 steps 223 -> 201 us, 50 RotatE steps 3940 ->
+// 3890, 100 FB15k-sized DistMult steps 3976 -> 3895.
+constexpr int REPLAY_SIZES = 2;
+constexpr int64_t REPLAY_STEPS[REPLAY_SIZES] = {16, 32};  // (graphs of 64 steps were slower than of 32)
+constexpr int64_t REPLAY_LONG = 256;
 
 // What a captured graph depends on.  The id arrays, the per-step sides and the loss array are not part of it: the
 // kernels find them through the step block.
@@ -286,7 +275,7 @@ struct ReplayKey {
 struct ReplayCache {
     bool valid = false;
     ReplayKey key;
-    hipGraphExec_t exec[REPLAY_SIZES] = {};  // exec[i] runs 1 << i steps
+    hipGraphExec_t exec[REPLAY_SIZES] = {};  // exec[i] runs REPLAY_STEPS[i] steps; captured when first needed
 };
 
 void replay_drop(ReplayCache* rc) {
@@ -487,20 +476,22 @@ int kge_train_steps(kge_ctx* c, float* ent, float* ent_state, float* rel, float*
         const char* e = getenv("KGE_TRAIN_STEPS_REPLAY");  // "0" turns graph replay off (measurement aid)
         return !(e && e[0] == '0');
     }();
-    if (!replay_enabled || c->prof_on || n_steps < 4 || cap != hipStreamCaptureStatusNone || st == nullptr ||
-        st == hipStreamLegacy) {
-        // plain launches: timing mode, very short runs, the caller is capturing this stream itself, or the stream
-        // is the legacy default stream, which cannot be captured
-        for (int64_t s = 0; s < n_steps; ++s) {
-            const StepIds ids = direct_ids(h + s * b, r + s * b, t + s * b, (int)b, neg + s * n_neg, (int)n_neg,
-                                           neg_sides ? neg_sides[s] : KGE_NEG_TAIL, loss_out ? loss_out + s : nullptr);
-            rc = enqueue_step(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st);
-            if (rc != KGE_OK) return rc;
-        }
-        return KGE_OK;
+    const bool may_replay = replay_enabled && !c->prof_on && cap == hipStreamCaptureStatusNone && st != nullptr &&
+                            st != hipStreamLegacy;  // (the legacy default stream cannot be captured)
+    // the first n_plain steps are launched kernel by kernel, the rest is replayed
+    const int which = n_steps < 64 ? 0 : 1;
+    const int64_t unit = REPLAY_STEPS[which];
+    int64_t n_plain = n_steps;
+    if (may_replay && n_steps >= REPLAY_STEPS[0]) n_plain = n_steps < REPLAY_LONG ? n_steps - unit : unit + n_steps % unit;
+    for (int64_t s = 0; s < n_plain; ++s) {
+        const StepIds ids = direct_ids(h + s * b, r + s * b, t + s * b, (int)b, neg + s * n_neg, (int)n_neg,
+                                       neg_sides ? neg_sides[s] : KGE_NEG_TAIL, loss_out ? loss_out + s : nullptr);
+        rc = enqueue_step(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st);
+        if (rc != KGE_OK) return rc;
     }
+    if (n_plain == n_steps) return KGE_OK;
 
-    // replay path: nothing here allocates once the two graphs exist
+    // replay: nothing here allocates once the graph exists
     ReplayKey key;
     memset(&key, 0, sizeof(key));
     key.ent = ent; key.ent_state = ent_state; key.rel = rel; key.rel_state = rel_state;
@@ -510,38 +501,39 @@ int kge_train_steps(kge_ctx* c, float* ent, float* ent_state, float* rel, float*
     if (!cache) return fail(c, KGE_ERR_DEVICE, "out of host memory%s");
     if (!cache->valid || !(cache->key == key)) {
         replay_drop(cache);
-        StepIds ids = direct_ids(nullptr, nullptr, nullptr, (int)b, nullptr, (int)n_neg, KGE_NEG_TAIL, nullptr);
-        ids.blk = c->step_block;
-        for (int i = 0; i < REPLAY_SIZES && rc == KGE_OK; ++i)
-            rc = capture_steps(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st, 1 << i,
-                               &cache->exec[i]);
-        if (rc != KGE_OK) {
-            replay_drop(cache);
-            return rc;
-        }
         cache->key = key;
         cache->valid = true;
         c->graph_captures += 1;
     }
-    // the per-step sides live in a fixed part of the workspace: a longer call runs in segments of that many steps
-    for (int64_t first = 0; first < n_steps; first += KGE_SIDES_CAP) {
+    if (!cache->exec[which]) {
+        StepIds ids = direct_ids(nullptr, nullptr, nullptr, (int)b, nullptr, (int)n_neg, KGE_NEG_TAIL, nullptr);
+        ids.blk = c->step_block;
+        rc = capture_steps(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st, (int)unit,
+                           &cache->exec[which]);
+        if (rc != KGE_OK) {
+            replay_drop(cache);
+            return rc;
+        }
+    }
+    // the sides of a single graph travel as bits of the step block; those of a longer replay live in a fixed part of
+    // the workspace, and one of more than KGE_SIDES_CAP steps runs in segments of that many (a multiple of the unit)
+    for (int64_t first = n_plain; first < n_steps; first += KGE_SIDES_CAP) {
         const int64_t n = n_steps - first < KGE_SIDES_CAP ? n_steps - first : KGE_SIDES_CAP;
-        if (neg_sides)
-            KGE_HIP(c, hipMemcpyAsync(c->sides_dev, neg_sides + first, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
         StepBlock blk;
         blk.step = 0;
         blk.h = h + first * b; blk.r = r + first * b; blk.t = t + first * b; blk.neg = neg + first * n_neg;
-        blk.sides = neg_sides ? c->sides_dev : nullptr;
+        blk.sides = nullptr;
+        blk.side_bits = 0;
+        if (neg_sides && n <= 64) {
+            for (int64_t s = 0; s < n; ++s) blk.side_bits |= (uint64_t)(neg_sides[first + s] == KGE_NEG_HEAD) << s;
+        } else if (neg_sides) {
+            KGE_HIP(c, hipMemcpyAsync(c->sides_dev, neg_sides + first, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
+            blk.sides = c->sides_dev;
+        }
         blk.loss_out = loss_out ? loss_out + first : nullptr;
         hipLaunchKernelGGL(k_set_step_block, dim3(1), dim3(1), 0, st, c->step_block, blk);
-        // As few graphs as possible: the binary digits of n below the longest graph, smallest first, then the
-        // longest graph for the rest.  A graph that is too long for its place in the call (see launch_graphs) is cut
-        // into halves.
-        int64_t done = 0;
         hipError_t herr = hipSuccess;
-        for (int i = 0; i + 1 < REPLAY_SIZES; ++i)
-            if (n & ((int64_t)1 << i)) launch_graphs(cache->exec, i, &done, st, &herr);
-        for (int64_t q = n >> (REPLAY_SIZES - 1); q > 0; --q) launch_graphs(cache->exec, REPLAY_SIZES - 1, &done, st, &herr);
+        for (int64_t q = n / unit; q > 0 && herr == hipSuccess; --q) herr = hipGraphLaunch(cache->exec[which], st);
         KGE_HIP(c, herr);
     }
     KGE_HIP(c, hipGetLastError());

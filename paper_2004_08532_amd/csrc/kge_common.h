@@ -103,8 +103,8 @@ struct kge_ctx {
 // Direct mode: blk == nullptr and h, r, t, neg point at this step's ids, side and loss_out are this step's.
 // Replay mode (one captured HIP graph serves every step of every kge_train_steps call of the same shape): blk points
 // at a block in the workspace that a one-thread kernel fills at the start of every call with the call's id arrays
-// (ids of its step 0; consecutive steps lie b (n_neg) entries apart), its per-step sides (may be null: tail
-// corruption throughout) and its loss array (one float per step, may be null), and whose step counter the last
+// (ids of its step 0; consecutive steps lie b (n_neg) entries apart), its per-step sides and its loss array (one float per
+// step, may be null), and whose step counter the last
 // kernel of every step advances.  The graphs hold only the block's address, so new id arrays need no new capture.
 // ---------------------------------------------------------------------------------------------------------
 struct StepBlock {
@@ -113,7 +113,8 @@ struct StepBlock {
     const int64_t* r;
     const int64_t* t;
     const int64_t* neg;
-    const int32_t* sides;
+    const int32_t* sides;   // null: the sides are side_bits (of up to 64 steps; 0: tail corruption throughout)
+    uint64_t side_bits;
     float* loss_out;
 };
 
@@ -226,7 +227,7 @@ __device__ __forceinline__ StepView step_view(const StepIds& s) {
         v.t = k->t + v.step * s.b;
         v.neg = k->neg + v.step * s.n_neg;
         const int32_t* sides = k->sides;
-        v.side = sides ? sides[v.step] : KGE_NEG_TAIL;
+        v.side = sides ? sides[v.step] : (int)(k->side_bits >> (v.step & 63) & 1);
     } else {
         v.step = 0;
         v.h = s.h; v.r = s.r; v.t = s.t; v.neg = s.neg;

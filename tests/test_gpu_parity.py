@@ -846,3 +846,29 @@ def test_train_steps_graph_replay_equals_step_by_step(kge, variant):
     stream.synchronize()
     ctx.close()
     assert torch.equal(aE, bE) and torch.equal(aSE, bSE) and torch.equal(aR, bR) and torch.equal(aSR, bSR)
+
+
+@pytest.mark.parametrize("n_steps", [1, 15, 16, 17, 63, 64, 255, 256, 289])
+def test_train_steps_at_the_lengths_where_the_launch_schedule_changes(kge, n_steps):
+    """Plain launches, one graph of 16 or 32 steps at the end, graphs of 32 after a plain start: the same bits and losses as
+    the steps run on the default stream, where every step is launched kernel by kernel."""
+    w = configs.TINY.scaled(name="tiny-schedule", batch=64, chunk=16, neg_per_chunk=24, lr=0.01)
+    gen = torch.Generator(device="cuda").manual_seed(n_steps)
+    ids = lambda hi, n: torch.randint(0, hi, (n_steps, n), dtype=torch.int64, device="cuda", generator=gen)
+    H, Rr, T, N = ids(w.n_entities, 64), ids(w.n_relations, 64), ids(w.n_entities, 64), ids(w.n_entities, 4 * 24)
+    sides = [(s % 3 == 1) * 1 for s in range(n_steps)]
+    E0, R0 = configs.init_tables(w)
+    results = []
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        ctx = kge.KgeContext(w.model, w.n_entities, w.n_relations, w.ent_dim, w.rel_dim, max_batch=64, max_neg_per_chunk=24,
+                             max_chunks=4)
+        E, R = dev(E0), dev(R0)
+        SE, SR = torch.zeros_like(E), torch.zeros_like(R)
+        loss = torch.zeros(n_steps, device="cuda")
+        torch.cuda.synchronize()
+        ctx.train_steps(E, SE, R, SR, H, Rr, T, N, 24, 16, sides, w.gamma, w.lr, loss_out=loss, stream=stream)
+        torch.cuda.synchronize()
+        ctx.close()
+        results.append((E, SE, R, SR, loss))
+    for a, b_ in zip(*results):
+        assert torch.isfinite(a).all() and torch.equal(a, b_)
