@@ -479,3 +479,10 @@ void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds
     if (with_keys && 2 * b + n_neg >= RANK_LONG_LIST) launch_model<1024>(c, a, nv, b + n_neg, with_keys, ids, st);
     else launch_model<256>(c, a, nv, b + n_neg, with_keys, ids, st);
 }
+
+void kge_launch_key_order(kge_ctx* c, const StepIds& ids, hipStream_t st) {
+    GatherArgs a = {};
+    a.ids = ids;
+    if (2 * ids.b + ids.n_neg >= RANK_LONG_LIST) launch_model<1024>(c, a, 1, 0, true, ids, st);
+    else launch_model<256>(c, a, 1, 0, true, ids, st);
+}

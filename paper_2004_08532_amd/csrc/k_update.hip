@@ -257,9 +257,9 @@ __global__ __launch_bounds__(UPD_THREADS) void k_update(UpdateArgs a) {
 }  // namespace
 
 void kge_launch_update(kge_ctx* c, float* E, float* SE, float* R, float* SR, const StepIds& ids, float lr,
-                       int n_loss_parts, hipStream_t st) {
+                       int n_loss_parts, bool with_entities, hipStream_t st) {
     UpdateArgs a;
-    const int b = ids.b, n_ent_keys = 2 * ids.b + ids.n_neg, n_rel_keys = ids.b;
+    const int b = ids.b, n_ent_keys = with_entities ? 2 * ids.b + ids.n_neg : 0, n_rel_keys = ids.b;
     float* loss_out = ids.loss_out;
     a.blk = ids.blk;
     a.T[0] = E; a.T[1] = R; a.St[0] = SE; a.St[1] = SR;

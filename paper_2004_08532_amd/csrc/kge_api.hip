@@ -96,6 +96,10 @@ int check_batch(kge_ctx* c, const void* ent, const void* rel, const int64_t* h, 
 void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids, int k, int chunk, float gamma,
              float* pos_out, float* neg_out, int ld_out, int dist_mode, hipStream_t st) {
     if (c->cfg.validate_indices) launch_validate(c, ids, st);
+    if (kge_ind_score_fits(c, chunk)) {
+        kge_ind_score(c, ent, rel, ids, k, gamma, k > 0 ? neg_out : nullptr, ld_out, pos_out, st);
+        return;
+    }
     if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_phi(c, ent, rel, ids, st);
     if (c->cfg.model == KGE_TRANSR) kge_transr_phi(c, ent, rel, ids, gamma, pos_out, st);
     kge_launch_gather(c, ent, rel, ids, gamma, pos_out, false, st);
@@ -154,7 +158,7 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
     }
     {
         ProfScope p(c, KGE_PROF_UPDATE);
-        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, 0, st);
+        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, 0, true, st);
     }
     KGE_HIP(c, hipGetLastError());
     if (c->prof_on) {
@@ -162,6 +166,40 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
         for (int s = 0; s < KGE_PROF_SLOTS; ++s) {
             float ms = 0.f;
             if (s == KGE_PROF_SORT && !long_lists) continue;
+            if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
+        }
+        c->prof_steps += 1;
+    }
+    return KGE_OK;
+}
+
+// Chunks of one positive.  Profile slots: gather = the key order, neg_backward = k_ind, update = the entity rows (without
+// the join of runs that cross tiles), rel_update = relation rows and loss.
+int enqueue_ind_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids, int K,
+                     float gamma, float lr, bool long_lists, hipStream_t st) {
+    if (!long_lists) {
+        ProfScope p(c, KGE_PROF_GATHER);
+        kge_launch_key_order(c, ids, st);
+    }
+    {
+        ProfScope p(c, KGE_PROF_BACKWARD);
+        kge_ind_step(c, ent, rel, ids, K, gamma, st);
+    }
+    if (long_lists) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    {
+        ProfScope p(c, KGE_PROF_UPDATE);
+        kge_launch_update_runs(c, ent, ent_state, ids, K, lr, st);
+    }
+    {
+        ProfScope p(c, KGE_PROF_REL_UPDATE);
+        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, 0, false, st);
+    }
+    KGE_HIP(c, hipGetLastError());
+    if (c->prof_on) {
+        KGE_HIP(c, hipStreamSynchronize(st));
+        const int slots[] = {long_lists ? KGE_PROF_SORT : KGE_PROF_GATHER, KGE_PROF_BACKWARD, KGE_PROF_UPDATE, KGE_PROF_REL_UPDATE};
+        for (int s : slots) {
+            float ms = 0.f;
             if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
         }
         c->prof_steps += 1;
@@ -185,6 +223,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         KGE_HIP(c, hipEventRecord(c->ev_join, c->side_stream));
     }
     if (c->cfg.validate_indices) launch_validate(c, ids, st);
+    if (kge_ind_step_fits(c, G)) return enqueue_ind_rest(c, ent, ent_state, rel, rel_state, ids, K, gamma, lr, long_lists, st);
     if (c->cfg.model == KGE_RESCAL) {
         ProfScope p(c, KGE_PROF_PHI);
         kge_launch_rescal_phi(c, ent, rel, ids, st);
@@ -231,7 +270,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     }
     {
         ProfScope p(c, KGE_PROF_UPDATE);
-        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, n_loss_parts, st);
+        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, n_loss_parts, true, st);
     }
     KGE_HIP(c, hipGetLastError());
     if (c->prof_on) {
@@ -371,10 +410,14 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const bool transr = m == KGE_TRANSR;
     const size_t proj = transr ? B * (size_t)(cfg->max_neg_per_chunk > 0 ? cfg->max_neg_per_chunk : 1) * D * 4 : 0;
     const size_t o_PP = take(transr ? B * D * 4 : 0), o_P3 = take(proj);
-    const size_t sort_slices = (EK + KGE_SORT_SLICE - 1) / KGE_SORT_SLICE + (B + KGE_SORT_SLICE - 1) / KGE_SORT_SLICE;
-    const size_t o_sc = take(sort_slices * 17 * 256 * 4 + 2 * 256 * 4);  // digit counts per wave and per slice + the two lists' digit bases
+    auto sort_digits = [](size_t keys) {  // counts of all slices: 8-bit digits, or 10-bit ones of few slices
+        const size_t slices = (keys + KGE_SORT_SLICE - 1) / KGE_SORT_SLICE, few = (size_t)KGE_SORT_FEW_SLICES << KGE_SORT_MAX_BITS;
+        return slices * 256 > few ? slices * 256 : few;
+    };
+    const size_t o_sc = take((sort_digits(EK) + sort_digits(B) + ((size_t)2 << KGE_SORT_MAX_BITS)) * 4);
     const bool pair_model = m == KGE_ROTATE || m == KGE_TRANSE_L1;
     const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? KGE_PAIR_MAX_PARTS * NR * D * 4 : 0);
+    const size_t o_rpw = take((EK / 4 + 4) * 4);
     c->ws_bytes = (int64_t)off;
 
     hipError_t e = hipMalloc(&c->ws_base, off);
@@ -400,6 +443,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     c->pair_part_o = pair_model ? (float*)(base + o_ppo) : nullptr;
     c->pair_part_n = pair_model ? (float*)(base + o_ppn) : nullptr;
     c->sort_counts = (uint32_t*)(base + o_sc);
+    c->run_part_w = (float*)(base + o_rpw);
     c->flags = (int*)(base + o_flags);
     c->step_block = (StepBlock*)(base + o_step);
     c->sides_dev = (int32_t*)(base + o_sides);
@@ -628,7 +672,7 @@ int kge_rank(kge_ctx* c, const float* ent, const float* rel,
     KGE_HIP(c, hipSetDevice(c->cfg.device));
     const StepIds ids = direct_ids(h, r, t, (int)b, neg, (int)((b / chunk) * k), neg_side, nullptr);
     hipStream_t st = (hipStream_t)hip_stream;
-    if (is_gemm_model(c->cfg.model) && kge_gemm_forward_can_rank(c)) {
+    if (is_gemm_model(c->cfg.model) && kge_gemm_forward_can_rank(c) && !kge_ind_score_fits(c, (int)chunk)) {
         // the gather launch sets every rank to 1, the forward launch adds the candidates that score higher
         c->rank_out = rank_out;
         forward(c, ent, rel, ids, (int)k, (int)chunk, gamma, nullptr, c->S, c->ld_s, 3, st);

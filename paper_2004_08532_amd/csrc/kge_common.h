@@ -51,6 +51,7 @@ struct kge_ctx {
     float* pair_part_n;  //                     [KGE_PAIR_MAX_PARTS][max_neg_rows x D] partial rows of the corrupting entities
     float* Gent;     // [max_ent_keys x D]   gradient rows in key order: heads | tails | corrupting rows
     float* Grel;     // [max_batch x Dr]     gradient rows of the relations
+    float* run_part_w;  // k_update_runs: sums of W that belong to the partial rows of the running step
     float* fpos;     // [max_batch]          positive scores
     float* o_n2;     // [max_batch]          |o_i|^2          (TransE-L2)
     float* n_n2;     // [max_neg_rows]       |n_j|^2          (TransE-L2)
@@ -67,7 +68,7 @@ struct kge_ctx {
                         // forward launch counts); null otherwise
 
     int ebuf, rbuf;                 // which ping-pong half holds the sorted result
-    uint32_t* sort_counts;          // radix sort: digit counts / offsets, [slices of both lists][16 waves][256]
+    uint32_t* sort_counts;          // radix sort: digit counts per slice of both lists, digit bases
     int64_t last_ent_keys, last_rel_keys;  // sizes of the last train step's key lists (0: none yet)
     hipStream_t side_stream;        // runs the key sort beside the forward/backward kernels
     hipEvent_t ev_fork, ev_join;
@@ -136,7 +137,7 @@ struct KeyList {
     const StepBlock* blk;    // replay mode: the arrays come from the block (which == 0: h | t | neg, 1: r)
     int which;
     int n;                   // total number of keys
-    int passes;              // radix passes needed for ids < n_ids (8 bits each)
+    int passes, digit_bits;  // radix passes needed for ids < n_ids, bits per pass
     int64_t n_ids;           // ids are clamped into [0, n_ids)
     uint32_t* key[2];        // sorted ids (ping-pong halves; the rank path writes half 0)
     uint32_t* pos[2];        // position in the key list of each sorted entry
@@ -151,8 +152,19 @@ void kge_make_key_lists(kge_ctx* c, const StepIds& ids, KeyList* ent, KeyList* r
 // KGE_RANK_MAX_KEYS keys; longer lists go through kge_launch_sort)
 void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds& ids, float gamma, float* pos_out,
                        bool with_keys, hipStream_t st);
+void kge_launch_key_order(kge_ctx* c, const StepIds& ids, hipStream_t st);  // the key lists alone
+// chunks of one positive: everything between the ids and the gradient rows of the positives in one launch, and the
+// update of the entity rows that forms the corrupting rows' gradients itself
+bool kge_ind_step_fits(const kge_ctx* c, int g);
+bool kge_ind_score_fits(const kge_ctx* c, int g);
+void kge_ind_step(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, float gamma, hipStream_t st);
+void kge_ind_score(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, float gamma, float* out,
+                   int ld_out, float* pos_out, hipStream_t st);
+void kge_launch_update_runs(kge_ctx* c, float* E, float* SE, const StepIds& ids, int k, float lr, hipStream_t st);
 constexpr int KGE_SIDES_CAP = 65536;  // steps whose sides fit the workspace: longer kge_train_steps calls run in segments
-constexpr int KGE_SORT_SLICE = 4096;  // keys per workgroup of the radix sort of long key lists
+constexpr int KGE_SORT_SLICE = 2048;     // keys per workgroup of the radix sort of long key lists
+constexpr int KGE_SORT_MAX_BITS = 10;    // bits per digit where a list has at most KGE_SORT_FEW_SLICES slices (else 8)
+constexpr int KGE_SORT_FEW_SLICES = 32;
 constexpr int KGE_PAIR_MAX_PARTS = 8;  // partial rows per gradient row in the tiled backward of RotatE / TransE-L1
 constexpr int KGE_RANK_MAX_KEYS = 14336;  // 14 * 1024: positions fit 14 bits, the list and its tables fit 64 KB of LDS
 // a3: negative scores of every chunk into out[b x ld_out]: matrix-product models / elementwise-reduce models
@@ -193,8 +205,9 @@ void kge_gemm_transr_matrix_grad(kge_ctx* c, const StepIds& ids, int k, int g, c
 // a6: sort (id, position) of the entity and relation key lists
 void kge_launch_sort(kge_ctx* c, const StepIds& ids, hipStream_t st);
 // a7: per distinct row, sum its gradient rows and apply Adagrad; also reduces the loss terms
+// (with_entities: false leaves the entity rows to kge_launch_update_runs)
 void kge_launch_update(kge_ctx* c, float* E, float* SE, float* R, float* SR, const StepIds& ids, float lr,
-                       int n_loss_parts, hipStream_t st);
+                       int n_loss_parts, bool with_entities, hipStream_t st);
 // evaluation: ranks of the positives among their negatives (from fpos and the scores in S), and the metrics
 void kge_launch_rank(kge_ctx* c, int b, int k, int32_t* rank_out, hipStream_t st);
 void kge_launch_rank_metrics(const int32_t* ranks, int64_t n, double* out, hipStream_t st);

@@ -174,6 +174,43 @@ def test_independent_negatives(kge, model):
         p.close()
 
 
+INDEPENDENT_SHAPES = {
+    # rows of each lane-group width (16, 32, 64 lanes, two and four pieces per lane), key lists below and above the
+    # radix sort's limit, counts of negatives around the four rows a lane group takes per round
+    "16-lanes": dict(batch=41, neg_per_chunk=9, ent_dim=16),
+    "32-lanes": dict(batch=33, neg_per_chunk=65, ent_dim=136),
+    "two-pieces": dict(batch=24, neg_per_chunk=31, ent_dim=520),
+    "four-pieces": dict(batch=9, neg_per_chunk=5, ent_dim=1024),
+    # 50 entities in 14,848 keys: every row's run crosses tens of tiles of the sorted list
+    "hubs": dict(batch=64, neg_per_chunk=230, ent_dim=48, n_entities=50),
+}
+INDEPENDENT_OPTIONS = {"uniform": {}, "adversarial": dict(adv_temperature=1.0), "ranking": dict(loss="ranking"),
+                       "adversarial-ranking": dict(adv_temperature=0.1, loss="ranking"), "rowwise": {}, "bf16": dict(bf16_inputs=True)}
+
+
+@pytest.mark.parametrize("shape", list(INDEPENDENT_SHAPES))
+@pytest.mark.parametrize("option", list(INDEPENDENT_OPTIONS))
+@pytest.mark.parametrize("model", ["transe_l2", "transe_l1", "distmult", "complex", "rotate"])
+def test_chunks_of_one_positive(kge, model, option, shape):
+    if option == "bf16" and model in ("transe_l1", "rotate"):
+        pytest.skip("no products to round operands for")
+    if model == "transe_l1" and "ranking" in option and shape == "four-pieces":
+        pytest.skip("nine positives: sums of equal +-w cancel exactly in more elements than the family's limit")
+    kw = dict(INDEPENDENT_SHAPES[shape], chunk=1, steps=2, **INDEPENDENT_OPTIONS[option])
+    kw["rel_dim"] = kw["ent_dim"] // 2 if model == "rotate" else kw["ent_dim"]
+    family = "default"
+    if kw.get("loss") == "ranking":
+        kw["gamma"] = RANKING_MARGIN[model]
+        family = {"transe_l1": "ranking-transe_l1", "complex": "ranking-complex"}.get(model, "default")
+    w = ragged(model, **kw)
+    E, R = configs.init_tables(w.scaled(gamma=6.0))
+    p = Pair(w, kge, E=E, R=R, rowwise=option == "rowwise")
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps, check_dedup_at=(0,), family=family)
+    finally:
+        p.close()
+
+
 PAIR_BACKWARD_SHAPES = {
     # chunks of up to 128 positives take the backward in which a workgroup owns 16 positives x a range of negatives
     # and writes partial rows; here with 8 i-tiles of which the last is ragged, and 8 ranges of 22 negatives
