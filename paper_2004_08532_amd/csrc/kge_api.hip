@@ -246,9 +246,9 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     // The matrix-product models fold the loss (uniform weights) and the chain rule (TransE-L2, DistMult) into
     // the backward launch; whatever is not folded runs as its own kernel.
     const bool gemm = is_gemm_model(c->cfg.model);
-    const bool run_loss = !(gemm && kge_gemm_backward_forms_w(c));
+    const bool run_loss = gemm && !kge_gemm_backward_forms_w(c);
     const bool run_chain = !(gemm && kge_gemm_backward_does_chain(c));
-    const int n_loss_parts = gemm ? kge_gemm_loss_parts(c, B, K, G) : 0;
+    int n_loss_parts = gemm ? kge_gemm_loss_parts(c, B, K, G) : 0;
     if (run_loss) {
         ProfScope p(c, KGE_PROF_LOSS);
         kge_launch_loss(c, B, K, gamma, st);
@@ -256,7 +256,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     {
         ProfScope p(c, KGE_PROF_BACKWARD);
         if (gemm) kge_gemm_neg_backward(c, ent, rel, ids, K, G, gamma, st);
-        else kge_pair_neg_backward(c, B, K, G, st);
+        else n_loss_parts = kge_pair_neg_backward(c, B, K, G, gamma, st);
     }
     if (run_chain) {
         ProfScope p(c, KGE_PROF_CHAIN);
@@ -400,7 +400,9 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const size_t o_Ge = take(EK * D * 4), o_Gr = take(B * (m == KGE_RESCAL ? 2 * D : Dr) * 4);  // RESCAL keeps two factor rows per positive
     const size_t o_fpos = take(B * 4), o_on2 = take(B * 4), o_nn2 = take(NR * 4), o_cpos = take(B * 4);
     const size_t o_rl = take(B * 4), o_idp = take(B * 4);
-    const size_t o_nlp = take((B / 32 + cfg->max_chunks + 1) * ((size_t)cfg->max_neg_per_chunk / 32 + 1) * 4);
+    const size_t nlp_gemm = (B / 32 + cfg->max_chunks + 1) * ((size_t)cfg->max_neg_per_chunk / 32 + 1);
+    const size_t nlp_pair = (B / 8 + cfg->max_chunks + 1) * KGE_PAIR_MAX_PARTS;
+    const size_t o_nlp = take((nlp_gemm > nlp_pair ? nlp_gemm : nlp_pair) * 4);
     const size_t o_ek0 = take(EK * 4), o_ek1 = take(EK * 4), o_ep0 = take(EK * 4), o_ep1 = take(EK * 4);
     const size_t o_rk0 = take(B * 4), o_rk1 = take(B * 4), o_rp0 = take(B * 4), o_rp1 = take(B * 4);
     const size_t o_flags = take(256), o_step = take(256), o_sides = take(sizeof(int32_t) * KGE_SIDES_CAP);
@@ -416,8 +418,14 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     };
     const size_t o_sc = take((sort_digits(EK) + sort_digits(B) + ((size_t)2 << KGE_SORT_MAX_BITS)) * 4);
     const bool pair_model = m == KGE_ROTATE || m == KGE_TRANSE_L1;
-    const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? KGE_PAIR_MAX_PARTS * NR * D * 4 : 0);
     const size_t o_rpw = take((EK / 4 + 4) * 4);
+    // partial rows, written before they are read (the fill below leaves them out).  A set of rows of the corrupting
+    // entities per 8 positives and per chunk at most; more than 256 MB only where 8 sets are already more
+    const size_t zeroed = off;
+    const size_t K1 = cfg->max_neg_per_chunk > 0 ? cfg->max_neg_per_chunk : 1;
+    size_t sets_n = (B / 8 + cfg->max_chunks) * K1 * D;
+    if (sets_n > (size_t)64 << 20) sets_n = 8 * NR * D > (size_t)64 << 20 ? 8 * NR * D : (size_t)64 << 20;
+    const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? sets_n * 4 : 0);
     c->ws_bytes = (int64_t)off;
 
     hipError_t e = hipMalloc(&c->ws_base, off);
@@ -442,6 +450,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     c->P3 = transr ? (float*)(base + o_P3) : nullptr;
     c->pair_part_o = pair_model ? (float*)(base + o_ppo) : nullptr;
     c->pair_part_n = pair_model ? (float*)(base + o_ppn) : nullptr;
+    c->pair_part_n_floats = pair_model ? (int64_t)sets_n : 0;
     c->sort_counts = (uint32_t*)(base + o_sc);
     c->run_part_w = (float*)(base + o_rpw);
     c->flags = (int*)(base + o_flags);
@@ -451,7 +460,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     // hipMemset on device memory returns before the fill has run (it is queued on the null stream, behind whatever
     // the caller has there), and the streams that callers pass are not ordered against the null stream: without the
     // wait below the fill could land after the first call has written its step block into the workspace.
-    bool ok = hipMemset(c->ws_base, 0, off) == hipSuccess;
+    bool ok = hipMemset(c->ws_base, 0, zeroed) == hipSuccess;
     ok = ok && hipDeviceSynchronize() == hipSuccess;
     ok = ok && hipStreamCreateWithFlags(&c->side_stream, hipStreamNonBlocking) == hipSuccess;
     ok = ok && hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) == hipSuccess;

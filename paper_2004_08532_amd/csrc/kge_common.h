@@ -24,6 +24,9 @@ struct PartialRows {
     int64_t n4;      // 16-byte pieces per partial
 };
 
+// How the backward launch of RotatE / TransE-L1 is cut for batches of one shape (k_pair.hip).
+struct PairBwdPlan { int b, k, g, ti, n_i, i_parts, pj, tj, n_col, cpp, ng; };
+
 struct StepBlock;
 
 struct kge_ctx {
@@ -46,9 +49,11 @@ struct kge_ctx {
     float* PP;       // TransR: [max_batch x D] p_i = M_i c_i
     float* P3;       // TransR: [max_batch x max_neg_per_chunk x D] projections of the corrupting rows, then dL/dP
     float* GO;       // [max_batch x D]      dL/do_i
-    float* pair_part_o;  // RotatE / TransE-L1: [KGE_PAIR_MAX_PARTS][max_batch x D] partial dL/do rows of the tiled backward
+    float* pair_part_o;  // RotatE / TransE-L1: [KGE_PAIR_MAX_PARTS][max_batch x D] partial dL/do rows
     PartialRows go_partial, neg_partial;  // what the last backward launch left for the chain launch to add up
-    float* pair_part_n;  //                     [KGE_PAIR_MAX_PARTS][max_neg_rows x D] partial rows of the corrupting entities
+    float* pair_part_n;  //                     partial rows of the corrupting entities, a set per tile of positives
+    int64_t pair_part_n_floats;
+    PairBwdPlan pair_plan;  // of the shape that came last
     float* Gent;     // [max_ent_keys x D]   gradient rows in key order: heads | tails | corrupting rows
     float* Grel;     // [max_batch x Dr]     gradient rows of the relations
     float* run_part_w;  // k_update_runs: sums of W that belong to the partial rows of the running step
@@ -165,7 +170,7 @@ constexpr int KGE_SIDES_CAP = 65536;  // steps whose sides fit the workspace: lo
 constexpr int KGE_SORT_SLICE = 2048;     // keys per workgroup of the radix sort of long key lists
 constexpr int KGE_SORT_MAX_BITS = 10;    // bits per digit where a list has at most KGE_SORT_FEW_SLICES slices (else 8)
 constexpr int KGE_SORT_FEW_SLICES = 32;
-constexpr int KGE_PAIR_MAX_PARTS = 8;  // partial rows per gradient row in the tiled backward of RotatE / TransE-L1
+constexpr int KGE_PAIR_MAX_PARTS = 16;  // most partial rows of dL/do in the backward of RotatE / TransE-L1
 constexpr int KGE_RANK_MAX_KEYS = 14336;  // 14 * 1024: positions fit 14 bits, the list and its tables fit 64 KB of LDS
 // a3: negative scores of every chunk into out[b x ld_out]: matrix-product models / elementwise-reduce models
 void kge_gemm_neg_score(kge_ctx* c, int b, int k, int g, float gamma, float* out, int ld_out, int dist_mode,
@@ -180,7 +185,8 @@ bool kge_gemm_forward_can_rank(const kge_ctx* c);  // evaluation without storing
 bool kge_gemm_backward_forms_w(const kge_ctx* c);     // the forward launch stores W and the loss sums (no k_loss)
 bool kge_gemm_backward_does_chain(const kge_ctx* c);  // the backward launch writes the positives' gradient rows
 int kge_gemm_loss_parts(const kge_ctx* c, int b, int k, int g);  // loss sums the forward launch leaves in neg_loss_part
-void kge_pair_neg_backward(kge_ctx* c, int b, int k, int g, hipStream_t st);
+// (also a4: returns how many loss sums the launch leaves in neg_loss_part)
+int kge_pair_neg_backward(kge_ctx* c, int b, int k, int g, float gamma, hipStream_t st);
 // a5: positive-pair term and chain rule through phi -> gradient rows of heads, tails and relations
 void kge_launch_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
 // RESCAL: o_i from the kept entity and the relation's matrix (before the gather launch); chain rule through it

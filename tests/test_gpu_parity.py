@@ -236,6 +236,32 @@ def test_both_forms_of_the_elementwise_backward(kge, model, shape):
         p.close()
 
 
+PAIR_BACKWARD_CUTS = {
+    # one negative per chunk; rows of 8 or 16 coordinates, 64 thread groups, W staged in several blocks; chunks of one
+    # more than a tile of positives with many ranges of negatives
+    "one-negative": dict(batch=34, chunk=17, neg_per_chunk=1),
+    "short-rows": dict(batch=66, chunk=33, neg_per_chunk=700, ent_dim=16, adv_temperature=1.0),
+    "many-ranges": dict(batch=65, chunk=65, neg_per_chunk=449, ent_dim=200, loss="ranking", gamma=0.3, adv_temperature=1.0),
+    # a set of partial rows for each of the 65 tiles of positives does not fit the workspace: workgroups walk several tiles
+    "walks": dict(batch=1040, chunk=1040, neg_per_chunk=1024, ent_dim=1024, steps=1),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(PAIR_BACKWARD_CUTS))
+@pytest.mark.parametrize("model", ["rotate", "transe_l1"])
+def test_cuts_of_the_elementwise_backward(kge, model, shape):
+    if shape == "walks" and model == "transe_l1":
+        pytest.skip("tiles of 32 positives: their partial rows fit")
+    kw = dict(dict(steps=2, ent_dim=72), **PAIR_BACKWARD_CUTS[shape])
+    kw["rel_dim"] = kw["ent_dim"] // 2 if model == "rotate" else kw["ent_dim"]
+    w = ragged(model, **kw)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps, family="ranking-transe_l1" if "loss" in kw and model == "transe_l1" else "default")
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("b,g,k", [(1, 1, 1), (3, 1, 2), (2, 2, 1)])
 @pytest.mark.parametrize("model", MODELS)
 def test_smallest_batches(kge, model, b, g, k):
