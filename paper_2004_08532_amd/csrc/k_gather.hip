@@ -9,6 +9,7 @@
 // In a training step the same launch carries extra blocks that bring the step's key lists into (id, position)
 // order for the duplicate reduction (rank_block below): that work needs only the ids, so it rides along here.
 #include "kge_common.h"
+#include "k_transr_items.h"
 
 namespace {
 
@@ -36,6 +37,9 @@ struct GatherArgs {
     int ent_rank_blocks;     // the first ent_rank_blocks of them order the entity key list, the rest the relation keys
     uint64_t bucket_mul;     // long entity lists: bucket of an id = (id * bucket_mul) >> 32 (0: brute-force blocks)
     KeyList ent, rel;
+    // TransR: workgroups that form the items of the chunks, chunks of g positives
+    int item_blocks, g, max_pblocks;
+    TransrGroups items;
 };
 
 // One block size for both kinds of block in a launch: THREADS = 256 for short key lists, 1024 for long ones.  The
@@ -231,9 +235,17 @@ template <int MODEL, int NV, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
     constexpr int ROWS_PER_BLOCK = THREADS / 64;
     extern __shared__ __attribute__((aligned(16))) uint32_t rank_keys[];  // (read 16 bytes at a time)
+    int block = blockIdx.x;
+    if constexpr (MODEL == KGE_TRANSR) {
+        if (block < a.item_blocks) {
+            transr_items<THREADS>(a.items, step_view(a.ids).r + (int64_t)block * a.g, block, a.g, a.n_rel, a.max_pblocks);
+            return;
+        }
+        block -= a.item_blocks;
+    }
     // the rank blocks come first: they run longest and need nothing but the ids
-    if ((int)blockIdx.x < a.rank_blocks) {
-        const int rb = blockIdx.x;
+    if (block < a.rank_blocks) {
+        const int rb = block;
         if (rb < a.ent_rank_blocks) {
             if (THREADS == 1024 && a.bucket_mul != 0) rank_block_bucketed(a.ent, rb, a.bucket_mul, rank_keys);
             else rank_block<THREADS>(a.ent, rb, rank_keys);
@@ -243,7 +255,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
         return;
     }
     const int lane = threadIdx.x & 63;
-    const int row = (blockIdx.x - a.rank_blocks) * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+    const int row = (block - a.rank_blocks) * ROWS_PER_BLOCK + (threadIdx.x >> 6);
     const int D = a.D;
     constexpr bool CPLX = (MODEL == KGE_COMPLEX || MODEL == KGE_ROTATE);
     const int nvec = CPLX ? D / 8 : D / 4;   // vectors (or re/im vector pairs) per row
@@ -287,7 +299,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
     }
 
     // ---- a positive: rows a (kept entity), r, c (the entity that the negatives replace)
-    if constexpr (MODEL == KGE_TRANSR) return;  // k_transr_phi has done the positives (they need the matrix)
+    if constexpr (MODEL == KGE_TRANSR) return;  // k_transr_phi does the positives (they need the matrix)
     const int i = row;
     const int64_t hid = clamp_id(sv.h[i], a.n_ent), tid = clamp_id(sv.t[i], a.n_ent);
     const int64_t rid = clamp_id(sv.r[i], a.n_rel);
@@ -447,7 +459,7 @@ void launch_model(kge_ctx* c, GatherArgs& a, int nv, int rows, bool with_keys, c
         c->rbuf = 0;
     }
     a.rank_blocks = rank_blocks;
-    const dim3 grid(gather_blocks + rank_blocks);
+    const dim3 grid(gather_blocks + rank_blocks + a.item_blocks);
     switch (c->cfg.model) {
     case KGE_TRANSE_L2: launch_nv<KGE_TRANSE_L2, THREADS>(c, a, nv, grid, lds, st); break;
     case KGE_TRANSE_L1: launch_nv<KGE_TRANSE_L1, THREADS>(c, a, nv, grid, lds, st); break;
@@ -461,7 +473,7 @@ void launch_model(kge_ctx* c, GatherArgs& a, int nv, int rows, bool with_keys, c
 
 }  // namespace
 
-void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds& ids, float gamma, float* pos_out,
+void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int gsz, float gamma, float* pos_out,
                        bool with_keys, hipStream_t st) {
     GatherArgs a;
     const int b = ids.b, n_neg = ids.n_neg;
@@ -473,6 +485,8 @@ void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds
     a.O = c->O; a.Nst = c->Nst; a.fpos = c->fpos; a.pos_out = pos_out; a.o_n2 = c->o_n2; a.n_n2 = c->n_n2;
     a.cpos = c->cpos; a.inv_dpos = c->inv_dpos; a.row_loss = c->row_loss; a.rank_out = c->rank_out;
     const int model = c->cfg.model;
+    a.item_blocks = model == KGE_TRANSR ? b / gsz : 0;
+    a.g = gsz; a.max_pblocks = transr_max_pblocks(gsz, a.n_rel); a.items = c->tr_groups;
     const bool cplx = model == KGE_COMPLEX || model == KGE_ROTATE;
     const int nvec = cplx ? a.D / 8 : a.D / 4;
     const int nv = (nvec + 63) / 64;

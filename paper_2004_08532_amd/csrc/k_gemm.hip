@@ -78,18 +78,17 @@ struct BlockLoader {
             p[it] = base + (int64_t)(major0 + 8 * it) * ld + (any ? gr : 0);
         }
     }
-    // shift: floats from the operand that init was given to the one that block kb is taken from (IND_CHUNK_SUM)
-    __device__ __forceinline__ void issue(int kb, float4 (&reg)[4], int64_t shift = 0) const {
+    __device__ __forceinline__ void issue(int kb, float4 (&reg)[4]) const {
         const int k0 = kb * 32;
         if (KC) {
             const int gk = k0 + minor;
             const int koff = gk < K ? gk : 0;  // the first 16 bytes of a row are always there
 #pragma unroll
-            for (int it = 0; it < 4; ++it) reg[it] = ld4(p[it] + shift + koff);
+            for (int it = 0; it < 4; ++it) reg[it] = ld4(p[it] + koff);
         } else {
 #pragma unroll
             for (int it = 0; it < 4; ++it)
-                reg[it] = ld4(k0 + major0 + 8 * it < K ? p[it] + shift + (int64_t)k0 * ld : p0_safe);
+                reg[it] = ld4(k0 + major0 + 8 * it < K ? p[it] + (int64_t)k0 * ld : p0_safe);
         }
     }
     // validity of element e (0..3) of register it for K-block kb
@@ -136,7 +135,7 @@ __device__ __forceinline__ void lds_frag(const float* region, int lane, int q, f
 }
 
 // One 32x32 output tile: K loop, cross-wave sum, epilogue.
-template <int NW, bool A_KC, bool B_KC, int EPI, bool IS_DO, int IND = IND_NONE>
+template <int NW, bool A_KC, bool B_KC, int EPI, bool IS_DO>
 __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tile, float (*lds)[2][REGION]) {
     constexpr bool CHAIN = EPI == EPI_CHAIN_L2 || EPI == EPI_CHAIN_DM || EPI == EPI_CHAIN_CX;
     constexpr bool CX = EPI == EPI_CHAIN_CX;
@@ -147,13 +146,6 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tile, float (*l
     const int n0 = (tile % g.gx) * TILE, mt = (tile / g.gx) % g.gy, m0 = mt * TILE, c = tile / (g.gx * g.gy);
     const float* A = g.A + c * g.sA;
     const float* B = g.B + c * g.sB;
-    if (IND == IND_CHUNK_REL) A = g.A + (c / g.ind_g) * g.sA;
-    if (IND == IND_CHUNK_REL) {
-        const StepView sv = step_view(g.ids);
-        B = g.B + clamp_id(sv.r[c], g.n_rel) * g.sB + g.b_off;
-    }
-    if (IND == IND_ITEM_CHUNK) B = g.B + (c / g.ind_g) * g.sB;
-    if (IND == IND_CHUNK_SUM) B = g.B + g.b_off;  // relation 0's matrix; a block is shifted to its positive's relation
     float* As = lds[w][0];
     float* Bs = lds[w][1];
     // ComplEx chain rule: the real and the imaginary part of a coordinate have to meet in one tile, so the tile's
@@ -197,7 +189,7 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tile, float (*l
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
     float a_sum = 0.f;  // sum over this lane's K-values of A[m = lane%32][.]  (rowsum / colsum of W)
 
-    const int nblk = (IND == IND_CHUNK_SUM ? g.ind_g : 1) * ((g.K + TILE - 1) / TILE);
+    const int nblk = (g.K + TILE - 1) / TILE;
     float4 ra[4], rb[4];
     BlockLoader<A_KC> la;
     BlockLoader<B_KC> lb;
@@ -207,38 +199,20 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& g, int tile, float (*l
         const int j = 4 * (lane & 7);
         lb.init_rows_at(B, col_of(j), col_in(j) ? (j < TILE / 2 ? g.N / 2 : g.N) : 0);
     }
-    // IND_CHUNK_SUM: block kb is block kb % bpi of positive kb / bpi of the chunk; where its operands lie is looked up
-    // (the positive's relation id) one round before its loads go out
-    const int bpi = (g.K + TILE - 1) / TILE;
-    const StepView sv_sum = IND == IND_CHUNK_SUM ? step_view(g.ids) : StepView();
-    auto place = [&](int blk, int& kl, int64_t& sa, int64_t& sb) {
-        kl = blk; sa = 0; sb = 0;
-        if (IND == IND_CHUNK_SUM) {
-            const int p = blk / bpi;
-            kl = blk - p * bpi;
-            sa = p * g.sA_item;
-            sb = clamp_id(sv_sum.r[c * g.ind_g + p], g.n_rel) * g.sB;
-        }
-    };
-    int kb = w, kl = 0, kl_n = 0;
-    int64_t sa = 0, sb = 0, sa_n = 0, sb_n = 0;
+    int kb = w;
     if (kb < nblk) {
-        place(kb, kl, sa, sb);
-        la.issue(kl, ra, sa);
-        lb.issue(kl, rb, sb);
-        if (kb + NW < nblk) place(kb + NW, kl_n, sa_n, sb_n);
+        la.issue(kb, ra);
+        lb.issue(kb, rb);
     }
     while (kb < nblk) {
-        la.mask(kl, ra);
-        lb.mask(kl, rb);
+        la.mask(kb, ra);
+        lb.mask(kb, rb);
         lds_store<A_KC>(As, lane, ra);
         lds_store<B_KC>(Bs, lane, rb);
         const int nxt = kb + NW;
         if (nxt < nblk) {  // next block's global loads fly while this block is multiplied
-            la.issue(kl_n, ra, sa_n);
-            lb.issue(kl_n, rb, sb_n);
-            kl = kl_n;
-            if (nxt + NW < nblk) place(nxt + NW, kl_n, sa_n, sb_n);
+            la.issue(nxt, ra);
+            lb.issue(nxt, rb);
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -392,15 +366,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4, 4)))
     }
 }
 
-// One plain product per batch item, operands found as IND says (the TransR products).
-template <int NW, bool A_KC, bool B_KC, int IND>
-__global__ __launch_bounds__(NW * 64) void k_gemm_one(GemmArgs g) {
-    __shared__ __attribute__((aligned(16))) float lds[NW][2][REGION];
-    const int tile = xcd_tile(blockIdx.x >> 3, gridDim.x >> 3);
-    if (tile >= g.tiles) return;
-    gemm_tile<NW, A_KC, B_KC, EPI_PLAIN, false, IND>(g, tile, lds);
-}
-
 // Number of K-splitting waves per tile.  With few tiles every K-block gets its own wave (one round of memory
 // latency, all SIMDs of the CU busy); with thousands of tiles four waves per tile keep the cross-wave sum cheap.
 int pick_nw(int tiles, int nblk, int cap) {
@@ -425,23 +390,6 @@ void launch_fwd(kge_ctx* c, GemmArgs g, int chunks, hipStream_t st) {
     if (nw == 4) KGE_LAUNCH(c, (k_gemm_fwd<4, EPI>), grid, dim3(256), 0, st, g);
     else if (nw == 8) KGE_LAUNCH(c, (k_gemm_fwd<8, EPI>), grid, dim3(512), 0, st, g);
     else KGE_LAUNCH(c, (k_gemm_fwd<16, EPI>), grid, dim3(1024), 0, st, g);
-}
-
-template <bool A_KC, bool B_KC, int IND>
-void launch_one(kge_ctx* c, GemmArgs g, int items, hipStream_t st) {
-    set_tiling(g, items);
-    g.out_mode = OUT_SCORE;
-    const dim3 grid(8 * ((g.tiles + 7) / 8));
-    const int nblk = (IND == IND_CHUNK_SUM ? g.ind_g : 1) * ((g.K + TILE - 1) / TILE);
-    int nw = pick_nw(g.tiles, nblk, IND == IND_CHUNK_SUM ? 16 : 8);
-    // thousands of tiles with a short K loop (rows of 100 floats are 4 K-blocks): one wave per tile, which multiplies
-    // all the blocks between the tile's set-up and its epilogue, and sixteen tiles share a CU (measured on the
-    // FB15k-sized TransR step: 113 us per product against 117 with two waves per tile and 134 with four)
-    if (g.tiles >= 1024 && nblk <= 8) nw = 1;
-    if (nw == 1) KGE_LAUNCH(c, (k_gemm_one<1, A_KC, B_KC, IND>), grid, dim3(64), 0, st, g);
-    else if (nw == 4) KGE_LAUNCH(c, (k_gemm_one<4, A_KC, B_KC, IND>), grid, dim3(256), 0, st, g);
-    else if (nw == 8) KGE_LAUNCH(c, (k_gemm_one<8, A_KC, B_KC, IND>), grid, dim3(512), 0, st, g);
-    else KGE_LAUNCH(c, (k_gemm_one<16, A_KC, B_KC, IND>), grid, dim3(1024), 0, st, g);
 }
 
 template <int EPI_O, int EPI_N>
@@ -546,44 +494,4 @@ void kge_gemm_neg_backward(kge_ctx* c, const float* E, const float* R, const Ste
     else if (model == KGE_COMPLEX && !bf) launch_bwd<EPI_CHAIN_CX, EPI_PLAIN>(c, g, q, chunks, st);
     else KGE_BWD(EPI_PLAIN, EPI_PLAIN);
 #undef KGE_BWD
-}
-
-// ---- TransR: f = gamma - |M_r h + r - M_r t|^2 (Table 1).  Every positive i has its own projection matrix M_i (D x D,
-// behind the D numbers of r in its relation row), so the products are batched over positives:
-//   P_i = N_c M_i^T   [k x D]  projections of the chunk's corrupting rows              (forward)
-//   sum_i U_i M_i     [k x D]  with U_i = dL/dP_i, over the chunk's positives i: one product per chunk whose K range
-//                              is the concatenation of the positives' D values -> gradient rows of the negatives
-//   G_i = U_i^T N_c   [D x D]  the negatives' share of dL/dM_i
-void kge_gemm_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, float* P, hipStream_t st) {
-    const int D = c->cfg.ent_dim;
-    GemmArgs g = {};
-    g.A = c->Nst; g.B = R; g.C = P;
-    g.M = k; g.N = D; g.K = D; g.lda = D; g.ldb = D; g.ldc = D;
-    g.sA = (int64_t)k * D; g.sB = c->cfg.rel_dim; g.sC = (int64_t)k * D;
-    g.ids = ids; g.n_rel = c->cfg.num_relations; g.ind_g = gsz; g.b_off = D;
-    launch_one<true, true, IND_CHUNK_REL>(c, g, ids.b, st);
-}
-
-// dL/dn for the corrupting rows of every chunk in one product per chunk: sum over the chunk's positives i of U_i M_i,
-// i.e. the K range is the concatenation of the positives' D values; out = the gradient rows of the corrupting entities.
-void kge_gemm_transr_back_project_sum(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, const float* U,
-                                      float* out, hipStream_t st) {
-    const int D = c->cfg.ent_dim;
-    GemmArgs g = {};
-    g.A = U; g.B = R; g.C = out;
-    g.M = k; g.N = D; g.K = D; g.lda = D; g.ldb = D; g.ldc = D;
-    g.sA = (int64_t)gsz * k * D; g.sA_item = (int64_t)k * D; g.sB = c->cfg.rel_dim; g.sC = (int64_t)k * D;
-    g.ids = ids; g.n_rel = c->cfg.num_relations; g.ind_g = gsz; g.b_off = D;
-    launch_one<true, false, IND_CHUNK_SUM>(c, g, ids.b / gsz, st);
-}
-
-void kge_gemm_transr_matrix_grad(kge_ctx* c, const StepIds& ids, int k, int gsz, const float* U, float* GM,
-                                 hipStream_t st) {
-    const int D = c->cfg.ent_dim;
-    GemmArgs g = {};
-    g.A = U; g.B = c->Nst; g.C = GM;
-    g.M = D; g.N = D; g.K = k; g.lda = D; g.ldb = D; g.ldc = D;
-    g.sA = (int64_t)k * D; g.sB = (int64_t)k * D; g.sC = (int64_t)D * D;
-    g.ids = ids; g.n_rel = c->cfg.num_relations; g.ind_g = gsz;
-    launch_one<false, false, IND_ITEM_CHUNK>(c, g, ids.b, st);
 }

@@ -178,53 +178,12 @@ struct ChainArgs {
     int rest_share;  // threads that share the partial rows of one 16-byte piece
 };
 
-// sum of `parts` 16-byte pieces `stride` floats apart, in order; eight of them are asked for before the first is added (a
-// part that does not exist is read from part 0 and left out of the sum)
-__device__ __forceinline__ float4 ld4_parts(const float* p, int parts, int64_t stride) {
-    if (parts <= 1) return ld4(p);  // (the same for every thread)
-    float4 s = f4(0.f);
-    for (int q0 = 0; q0 < parts; q0 += 8) {
-        float4 v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = ld4(p + (q0 + q < parts ? q0 + q : 0) * stride);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            if (q0 + q < parts) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
-        }
-    }
-    return s;
-}
-
 __device__ __forceinline__ int64_t clamp_id(int64_t id, int64_t n) { return id < 0 ? 0 : (id >= n ? n - 1 : id); }
 
 template <int MODEL, int NV>
 __global__ __launch_bounds__(256) void k_chain(ChainArgs a) {
     if ((int)blockIdx.x >= a.chain_blocks) {  // partial rows of the corrupting entities -> their gradient rows
-        // `share` threads per 16 bytes, each a contiguous range of the partial rows; their sums meet in LDS in order
-        __shared__ __attribute__((aligned(16))) float4 sums[256];
-        const int share = a.rest_share, cols = 256 / share, per = (a.rest.parts + share - 1) / share;
-        const int grp = threadIdx.x / cols, ln = threadIdx.x % cols;
-        const int q0 = grp * per, n = min(per, a.rest.parts - q0);
-        const int64_t step = (int64_t)(gridDim.x - a.chain_blocks) * cols;
-        for (int64_t e0 = (int64_t)(blockIdx.x - a.chain_blocks) * cols; e0 < a.rest.n4; e0 += step) {
-            const int64_t e = e0 + ln;
-            float4 s = f4(0.f);
-            if (e < a.rest.n4 && n > 0) s = ld4_parts(a.rest.src + q0 * a.rest.stride + 4 * e, n, a.rest.stride);
-            if (share == 1) {
-                if (e < a.rest.n4) st4(a.rest.out + 4 * e, s);
-                continue;
-            }
-            __syncthreads();
-            sums[threadIdx.x] = s;
-            __syncthreads();
-            if (grp == 0 && e < a.rest.n4) {
-                for (int g2 = 1; g2 < share; ++g2) {
-                    const float4 v = sums[g2 * cols + ln];
-                    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-                }
-                st4(a.rest.out + 4 * e, s);
-            }
-        }
+        sum_partial_rows<256>(a.rest, a.rest_share, blockIdx.x - a.chain_blocks, gridDim.x - a.chain_blocks);
         return;
     }
     const int lane = threadIdx.x & 63;
@@ -274,7 +233,7 @@ __global__ __launch_bounds__(256) void k_chain(ChainArgs a) {
         for (int it = 0; it < NV; ++it) {
             const int v = lane + it * 64;
             if (v >= nvec) continue;
-            const float4 G = ld4_parts(pg + 4 * v, a.go_parts, a.go_stride);
+            const float4 G = sum_parts(pg + 4 * v, a.go_parts, a.go_stride);
             const float ov[4] = {Ov[it].x, Ov[it].y, Ov[it].z, Ov[it].w};
             const float cv[4] = {Cv[it].x, Cv[it].y, Cv[it].z, Cv[it].w};
             const float gv[4] = {G.x, G.y, G.z, G.w};
@@ -311,8 +270,8 @@ __global__ __launch_bounds__(256) void k_chain(ChainArgs a) {
             if (v >= nvec) continue;
             const float4 Ore = ld4(po + 4 * v), Oim = ld4(po + im_off + 4 * v);
             const float4 Cre = ld4(pc + 4 * v), Cim = ld4(pc + im_off + 4 * v);
-            const float4 Gre = ld4_parts(pg + 4 * v, a.go_parts, a.go_stride);
-            const float4 Gim = ld4_parts(pg + im_off + 4 * v, a.go_parts, a.go_stride);
+            const float4 Gre = sum_parts(pg + 4 * v, a.go_parts, a.go_stride);
+            const float4 Gim = sum_parts(pg + im_off + 4 * v, a.go_parts, a.go_stride);
             const float4 Are = ld4(pa + 4 * v), Aim = ld4(pa + im_off + 4 * v);
             const float ore[4] = {Ore.x, Ore.y, Ore.z, Ore.w}, oim[4] = {Oim.x, Oim.y, Oim.z, Oim.w};
             const float cre[4] = {Cre.x, Cre.y, Cre.z, Cre.w}, cim[4] = {Cim.x, Cim.y, Cim.z, Cim.w};
@@ -406,15 +365,7 @@ void kge_launch_chain(kge_ctx* c, const float* E, const float* R, const StepIds&
     if (c->go_partial.parts > 1) { a.GO = c->go_partial.src; a.go_parts = c->go_partial.parts; a.go_stride = c->go_partial.stride; }
     a.chain_blocks = (b + 3) / 4;
     a.rest = c->neg_partial;
-    // 16 bytes of 8 partial rows or more per thread; a thread per piece where that already makes 2048 blocks, which then
-    // take up to four rounds each
-    int rest_blocks = 0;
-    a.rest_share = 1;
-    if (a.rest.parts > 1) {
-        while (a.rest_share < 16 && a.rest.parts > 8 * a.rest_share && a.rest.n4 * a.rest_share < 2048 * 256) a.rest_share *= 2;
-        const int64_t blocks = (a.rest.n4 * a.rest_share + 255) / 256;
-        rest_blocks = (int)(blocks <= 2048 ? blocks : (blocks + 3) / 4 > 2048 ? (blocks + 3) / 4 : 2048);
-    }
+    const int rest_blocks = partial_rows_blocks(a.rest, a.rest_share);
     const int model = c->cfg.model;
     const bool cplx = model == KGE_COMPLEX || model == KGE_ROTATE;
     const int nvec = cplx ? a.D / 8 : a.D / 4;

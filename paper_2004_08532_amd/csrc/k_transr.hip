@@ -4,317 +4,754 @@
 // With a the entity that is kept, x the one that is replaced (the true one for the positive, a corrupting one for a
 // negative) and sigma = +1 (tail corrupted) or -1 (head corrupted):
 //     o_i = M_i a_i + sigma r_i ,    P(x) = M_i x ,    f = gamma - |o_i - P(x)|^2
-// so a positive's negatives need the chunk's corrupting rows projected with the positive's own matrix: batched products
-// over the positives (k_gemm.hip).  Here are the steps around them, one workgroup per positive unless said otherwise:
-//   k_transr_phi     o_i, p_i = M_i c_i, the positive's score and logistic-loss terms
-//   k_transr_score   S_ij = gamma - |o_i - P_ij|^2 from the projections P_i = N_c M_i^T
-//   (k_loss)         W = dL/df-
-//   k_transr_dp      U_ij = dL/dP_ij = 2 W_ij (o_i - P_ij), in place over P; dL/do_i of the negatives = - sum_j U_ij
-//   (product)        gradient rows of the corrupting entities: sum over the chunk's positives of U_i M_i
-//   k_transr_chain   go = dL/do, gp = dL/dp -> kept entity M^T go, replaced entity M^T gp, translation sigma go,
-//                    matrix += go a^T + gp c^T (on top of the negatives' share U_i^T N_c)
-//   k_transr_update  duplicate reduction and Adagrad for the relation rows [r | M] (Sec. 3.1 step 4): the last sorted
-//                    position of every run of equal relation ids sums the run's gradient rows, slab by slab
-// All sums have a fixed order.
-#include "kge_common.h"
+// so a positive's negatives need the chunk's corrupting rows projected with the positive's own matrix.  Positives of one
+// chunk that share a relation share these projections, and what flows back through them adds up before it is
+// multiplied: the unit of work is an ITEM, a (chunk, relation) that occurs in the mini-batch, with its positives.  The
+// arrays per positive (o, p, gradients, scores, coefficients) are in the order of the items' positives ("members"), so
+// that an item's rows are contiguous; what a caller sees is put back into the order of the mini-batch where it is stored.
+//   (k_gather)        the items of every chunk (k_transr_items.h), beside the corrupting rows and the order of the keys
+//   k_transr_phi      o_i, p_i = M_i c_i: an item's a and c rows times M^T; the positive's score and logistic-loss terms
+//   k_transr_project  P_t = N_c M_t^T, and in its epilogue S_ij = gamma - |o_i - P_tj|^2 for the item's positives
+//                     (logistic loss with uniform weights: W = dL/df-, no loss kernel)
+//   (k_loss)          W otherwise
+//   k_transr_dp       V_tj = sum over the item's positives of 2 W_ij (o_i - P_tj); dL/do_i = - sum_j of the same terms
+//                     - 2 cpos (o - p), dL/dp_i = 2 cpos (o - p), gradient of the translation (k_transr_go ends these for
+//                     items of few positives)
+//   k_transr_back     sum over a chunk's items of V_t M_t (partial over ranges of items); M^T dL/do_i, M^T dL/dp_i
+//   k_transr_mgrad    dL/dM of an item: V_t^T N_c + sum over its positives of dL/do a^T + dL/dp c^T, one product whose
+//                     K range is the corrupting rows and the positives
+//   k_transr_update   duplicate reduction and Adagrad for the relation rows [r | M] (Sec. 3.1 step 4); the partial sums
+//                     of k_transr_back
+// The products run on v_mfma_f32_16x16x4_f32: a workgroup owns 64 rows x up to 128 columns (whole matrices at D <= 128),
+// K in blocks of 32 staged in LDS for its four waves (16 rows each), the next block's global loads in flight while one is
+// multiplied.  (128 rows per workgroup were measured: equal or slower, half as many waves fit a SIMD.)  All sums have a
+// fixed order.
+// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 292 us per step, 450 with three products per
+// positive on 32x32 tiles, projections written and read four times; b 798, g 266, k 52, D 56, 21 relations: 192 -> 74.
+// The three large products take 63-71 us each: 29 us of matrix instructions (a quarter of them padding, 100 -> 112 rows and
+// columns), the rest the start of a workgroup (four dependent loads) and an uneven number of workgroups per CU.
+#include "k_gemm_shared.h"
+#include "k_transr_items.h"
 
 namespace {
 
 constexpr int RT = 256;
-constexpr int MAX_D = 1024;
+constexpr int BM = 64, BN = 128, BK = 32;  // rows, most columns, K per staged block
+constexpr int KP = 36;                     // pitch of a staged [row][k] block: 16-byte reads without bank conflicts
+constexpr int AP = BM + 4, BP = BN + 4;    // pitches of staged [k][row] blocks: 4 * pitch = 16 mod 64 banks
+constexpr int A_FLOATS = BM * KP > BK * AP ? BM * KP : BK * AP, B_FLOATS = BN * KP > BK * BP ? BN * KP : BK * BP;
+constexpr int PB = TRANSR_PB;              // positives per block of an item's positives
+
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 struct TransrArgs {
     const float* E;
     const float* R;
     StepIds ids;
-    int b, D, k, g, ld_s;
+    int b, D, k, g, ld_s, max_items, max_pblocks;  // (the last two per chunk)
     int64_t n_ent, n_rel, rel_dim;
-    float gamma;
-    float* O;        // [b x D]      o_i
-    float* PP;       // [b x D]      p_i = M_i c_i
-    float* P;        // [b x k x D]  projections, then U
+    float gamma, wk;
+    int out_w;       // project: store W = dL/df- instead of the score
+    int train;       // project: keep the projections, scores in the order of the members; phi: likewise
+    int segments;    // back: ranges of a chunk's items
+    TransrGroups q;
+    float* O;        // [b x D]      o
+    float* PP;       // [b x D]      p, then dL/dp
+    float* P;        // [b x k x D]  projections of item slot t
+    float* V;        // [b x k x D]  dL/dP summed over the item's positives
+    const float* N;  // [C*k x D]    corrupting rows
     float* S;        // [b x ld_s]   scores, then W
-    float* GO;       // [b x D]      dL/do_i from the negatives
+    float* GO;       // [b x D]      dL/do
+    float* GOp;      // [ceil(k / 64)][b x D] partial sums of it (items of few positives)
     float* fpos;
+    float* pos_out;
     float* cpos;
     float* row_loss;
+    float* loss_part;
     float* Gent;     // gradient rows in key order: heads | tails | corrupting rows
-    float* Gr;       // [b x D]      gradient of the translation
-    float* GM;       // [b x D x D]  gradient of the matrix
+    float* Gr;       // [b x D]      gradient of the translation, in the order of the mini-batch
+    float* GM;       // [b x D x D]  gradient of the matrix, per item slot
+    float* back_part;  // [segments][C*k x D]
 };
 
-__device__ __forceinline__ int64_t clamp_id(int64_t id, int64_t n) { return id < 0 ? 0 : (id >= n ? n - 1 : id); }
-
-struct Rows {
-    const float* a;  // kept entity
-    const float* c;  // replaced entity
-    const float* r;  // translation
-    const float* M;  // projection
-    float sigma;
-    bool head;
+// ---------------------------------------------------------------------------------------------------------------
+// The product core.  Thread tid stages, per block of 32 values of K, pieces of 16 bytes:
+//   [row][k] operands: row tid / 8 + 32 it, k 4 (tid % 8) ..      (A: 2 pieces, B: 4)
+//   [k][row] operands: A: k tid / 16 + 16 it, row 4 (tid % 16) ..  B: k tid / 32 + 8 it, row 4 (tid % 32) ..
+// load_a / load_b(run, block, piece registers) ask for them; mask_a / mask_b put zeros where k is outside the product, a
+// block later, when they go to LDS (a select right behind the load would wait for it).  Rows outside only reach outputs
+// that are not stored, and read something valid.  No branch stands between the loads of a block, and none between the LDS
+// reads and matrix instructions of one (the number of column tiles NT is a template argument).
+template <int NT>
+struct Tile {
+    float* As;
+    float* Bs;
+    floatx4 acc[NT];
+    float a_sum;  // ASUM: sum over K of the A values of row lane % 16 of the wave's sixteen (complete in every lane)
+    int wave, lane;
+    bool active;  // the wave has rows
+    __device__ __forceinline__ int row(int v) const { return 16 * wave + 4 * (lane >> 4) + v; }  // of accumulator v
 };
-__device__ __forceinline__ Rows rows_of(const TransrArgs& a, int i) {
-    const StepView sv = step_view(a.ids);
-    Rows x;
-    x.head = sv.side == KGE_NEG_HEAD;
-    const int64_t hid = clamp_id(sv.h[i], a.n_ent), tid = clamp_id(sv.t[i], a.n_ent);
-    const int64_t rid = clamp_id(sv.r[i], a.n_rel);
-    x.a = a.E + (x.head ? tid : hid) * (int64_t)a.D;
-    x.c = a.E + (x.head ? hid : tid) * (int64_t)a.D;
-    x.r = a.R + rid * a.rel_dim;
-    x.M = x.r + a.D;
-    x.sigma = x.head ? -1.f : 1.f;
+
+// Waves take the groups of 16 rows in an order that changes from workgroup to workgroup, so that the SIMDs of a CU get about
+// the same number where there are fewer than four.
+__device__ __forceinline__ int row_wave() { return __builtin_amdgcn_readfirstlane(((threadIdx.x >> 6) + blockIdx.x) & 3); }
+template <int NT>
+__device__ __forceinline__ void tile_init(Tile<NT>& t, float* As, float* Bs, int rows) {
+    t.As = As; t.Bs = Bs;
+    t.wave = row_wave(); t.lane = threadIdx.x & 63;
+    t.active = __builtin_amdgcn_readfirstlane(16 * t.wave < rows);
+    t.a_sum = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) t.acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+}
+
+// 16 values of K (from s16 on) of a staged block
+template <bool A_KC, bool B_KC, bool ASUM, int NT>
+__device__ __forceinline__ void tile_mma(Tile<NT>& t, int s16) {
+    const int r16 = t.lane & 15, kk = s16 + 4 * (t.lane >> 4), row = 16 * t.wave + r16;
+    float fa[4];
+    if (A_KC) {
+        const float4 v = ld4(t.As + row * KP + kk);
+        fa[0] = v.x; fa[1] = v.y; fa[2] = v.z; fa[3] = v.w;
+    } else {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) fa[x] = t.As[(kk + x) * AP + row];
+    }
+    if (ASUM) t.a_sum += (fa[0] + fa[1]) + (fa[2] + fa[3]);
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) {
+        float fb[4];
+        if (B_KC) {
+            const float4 v = ld4(t.Bs + (16 * ct + r16) * KP + kk);
+            fb[0] = v.x; fb[1] = v.y; fb[2] = v.z; fb[3] = v.w;
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) fb[x] = t.Bs[(kk + x) * BP + 16 * ct + r16];
+        }
+#pragma unroll
+        for (int x = 0; x < 4; ++x) t.acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[x], fb[x], t.acc[ct], 0, 0, 0);
+    }
+}
+
+// The product over `runs` consecutive ranges of K values each; masks apply to the last block of a run.
+template <bool A_KC, bool B_KC, bool ASUM, int NT, class LoadA, class MaskA, class LoadB, class MaskB>
+__device__ __forceinline__ void tile_run(Tile<NT>& t, int K, int runs, LoadA load_a, MaskA mask_a, LoadB load_b, MaskB mask_b) {
+    constexpr int NB = B_KC ? (NT + 1) / 2 : 4;  // pieces of B that hold columns of the tile
+    const int tid = threadIdx.x;
+    const int bpr = (K + BK - 1) / BK, nblk = bpr * runs;
+    const bool odd = K - BK * (bpr - 1) <= 16;  // the last block of a run is at most 16 values
+    float4 ra[2], rb[4];
+    float* sa = A_KC ? t.As + tid / 8 * KP + 4 * (tid % 8) : t.As + tid / 16 * AP + 4 * (tid % 16);
+    float* sb = B_KC ? t.Bs + tid / 8 * KP + 4 * (tid % 8) : t.Bs + tid / 32 * BP + 4 * (tid % 32);
+    int run = 0, kb = 0;  // of the block that is loaded
+    if (nblk > 0) { load_a(0, 0, ra); load_b(0, 0, rb); }
+    for (int blk = 0; blk < nblk; ++blk) {
+        const bool tail = kb == bpr - 1;
+        __syncthreads();  // the block before has been read
+        if (tail) { mask_a(kb, ra); mask_b(kb, rb); }
+#pragma unroll
+        for (int it = 0; it < 2; ++it) st4(sa + it * (A_KC ? 32 * KP : 16 * AP), ra[it]);
+#pragma unroll
+        for (int it = 0; it < NB; ++it) st4(sb + it * (B_KC ? 32 * KP : 8 * BP), rb[it]);
+        __syncthreads();
+        if (tail) { kb = 0; ++run; } else { ++kb; }
+        if (blk + 1 < nblk) { load_a(run, kb, ra); load_b(run, kb, rb); }
+        if (t.active) {
+            const int ns = tail && odd ? 1 : 2;
+#pragma unroll 1
+            for (int s = 0; s < ns; ++s) tile_mma<A_KC, B_KC, ASUM>(t, 16 * s);
+        }
+    }
+    if (ASUM) {
+        t.a_sum += __shfl_xor(t.a_sum, 16, 64);
+        t.a_sum += __shfl_xor(t.a_sum, 32, 64);
+    }
+}
+
+// pieces of a [row][k] operand whose rows of K floats start at p[it]
+template <int N>
+__device__ __forceinline__ void load_kc(const float* const (&p)[N], int K, int blk, float4* r) {
+    const int k = BK * blk + 4 * (threadIdx.x % 8);
+#pragma unroll
+    for (int it = 0; it < N; ++it) r[it] = ld4(p[it] + (k < K ? k : 0));
+}
+template <int N>
+__device__ __forceinline__ void mask_kc(int K, int blk, float4* r) {
+    const bool out = BK * blk + 4 * (int)(threadIdx.x % 8) >= K;
+#pragma unroll
+    for (int it = 0; it < N; ++it) r[it] = out ? f4(0.f) : r[it];
+}
+// [k][row] operand with rows of `ld` floats from p on (the thread's column included): k of piece it is BK blk + k0 + step it
+template <int N>
+__device__ __forceinline__ void load_mc(const float* p, int64_t ld, int K, int blk, int k0, int step, float4* r) {
+#pragma unroll
+    for (int it = 0; it < N; ++it) r[it] = ld4(p + min(BK * blk + k0 + step * it, K - 1) * ld);
+}
+template <int N>
+__device__ __forceinline__ void mask_mc(int K, int blk, int k0, int step, float4* r) {
+#pragma unroll
+    for (int it = 0; it < N; ++it) r[it] = BK * blk + k0 + step * it >= K ? f4(0.f) : r[it];
+}
+
+// x of the lane that control word CTRL names (within a row of 16 lanes: vector ALU moves, no LDS)
+template <int CTRL> __device__ __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_ROR8 = 0x128;
+__device__ __forceinline__ float sum16(float x) {  // over the 16 lanes of a row, in every lane
+    x += dpp<DPP_ROR8>(x);
+    x += dpp<DPP_HALF_MIRROR>(x);  // (lane i and 7 - i: what they lack of each other's quad the next two steps add)
+    x += dpp<DPP_XOR2>(x);
+    x += dpp<DPP_XOR1>(x);
     return x;
 }
-
-// y1 = M v1, y2 = M v2; v1, v2, y1, y2 in LDS.  Row dots: a group of SUB lanes (the power of two that holds the row's
-// 16-byte pieces, at most a wave) per matrix row, four rows per round so that four loads are in flight, shuffle
-// reductions inside the group.  Rows of more than 256 floats: a wave per row, up to four pieces per lane.
-template <int SUB>
-__device__ __forceinline__ void row_dots_short(const float* M, int D, const float* v1, const float* v2, float* y1, float* y2) {
-    constexpr int GROUPS = RT / SUB;
-    const int grp = threadIdx.x / SUB, ln = threadIdx.x % SUB, lanes = D / 4;
-    const bool act = ln < lanes;
-    const float4 a1 = act ? ld4(v1 + 4 * ln) : f4(0.f), a2 = act ? ld4(v2 + 4 * ln) : f4(0.f);
-    const float* Mc = M + (act ? 4 * ln : 0);
-    for (int r0 = grp; r0 < D; r0 += 4 * GROUPS) {
-        float4 m[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) m[u] = ld4(Mc + (int64_t)(r0 + u * GROUPS < D ? r0 + u * GROUPS : r0) * D);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float s1 = act ? m[u].x * a1.x + m[u].y * a1.y + m[u].z * a1.z + m[u].w * a1.w : 0.f;
-            float s2 = act ? m[u].x * a2.x + m[u].y * a2.y + m[u].z * a2.z + m[u].w * a2.w : 0.f;
-#pragma unroll
-            for (int o = SUB / 2; o > 0; o >>= 1) {
-                s1 += __shfl_xor(s1, o, 64);
-                s2 += __shfl_xor(s2, o, 64);
-            }
-            const int r = r0 + u * GROUPS;
-            if (ln == 0 && r < D) { y1[r] = s1; y2[r] = s2; }
-        }
-    }
+// sums over 16 lanes of four values; lane (of the 16) with bits 3, 2 = (h1, h2) gets value 2 h1 + h2
+__device__ __forceinline__ float sum16x4(const float (&s)[4]) {
+    const bool h1 = threadIdx.x & 8, h2 = threadIdx.x & 4;
+    float x = h1 ? s[2] : s[0], y = h1 ? s[3] : s[1];
+    x += dpp<DPP_ROR8>(h1 ? s[0] : s[2]);
+    y += dpp<DPP_ROR8>(h1 ? s[1] : s[3]);
+    float z = h2 ? y : x;
+    z += dpp<DPP_HALF_MIRROR>(h2 ? x : y);
+    z += dpp<DPP_XOR2>(z);
+    z += dpp<DPP_XOR1>(z);
+    return z;
 }
 
-__device__ __forceinline__ void row_dots_long(const float* M, int D, const float* v1, const float* v2, float* y1, float* y2) {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, lanes = D / 4;
-    float4 a1[4], a2[4];
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int q = lane + 64 * it;
-        a1[it] = q < lanes ? ld4(v1 + 4 * q) : f4(0.f);
-        a2[it] = q < lanes ? ld4(v2 + 4 * q) : f4(0.f);
-    }
-    for (int r = w; r < D; r += RT / 64) {
-        const float* row = M + (int64_t)r * D;
-        float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int q = lane + 64 * it;
-            if (q < lanes) {
-                const float4 m = ld4(row + 4 * q);
-                s1 += m.x * a1[it].x + m.y * a1[it].y + m.z * a1[it].z + m.w * a1[it].w;
-                s2 += m.x * a2[it].x + m.y * a2[it].y + m.z * a2[it].z + m.w * a2[it].w;
-            }
-        }
-        s1 = wave_sum(s1);
-        s2 = wave_sum(s2);
-        if (lane == 0) { y1[r] = s1; y2[r] = s2; }
-    }
+// Workgroup -> (item or block of an item's positives, tile): the tiles of an item run on one XCD (workgroups are dealt to
+// them round-robin) and share its operands there.
+__device__ __forceinline__ int unit_of_block(int block, int tiles, int& tile) {
+    const int xcd = block & 7, n = block >> 3;
+    tile = n % tiles;
+    return n / tiles * 8 + xcd;
+}
+dim3 unit_grid(int units, int tiles) { return dim3((units + 7) / 8 * 8 * tiles); }
+dim3 item_grid(const TransrArgs& a, int tiles) { return unit_grid(a.b / a.g * a.max_items, tiles); }
+dim3 block_grid(const TransrArgs& a, int tiles) { return unit_grid(a.b / a.g * a.max_pblocks, tiles); }
+// The record of the unit and the number of units in its chunk are asked for together.
+__device__ __forceinline__ bool item_of(const TransrArgs& a, int unit, int& c, int& slot, TransrItem& item) {
+    c = unit / a.max_items;
+    const int idx = unit - c * a.max_items;
+    slot = c * a.g + idx;
+    if (c * a.g >= a.b) return false;
+    item = a.q.items[slot];
+    return idx < a.q.n_items[c];
+}
+__device__ __forceinline__ bool pblock_of(const TransrArgs& a, int unit, int& c, TransrBlock& blk) {
+    c = unit / a.max_pblocks;
+    const int e = unit - c * a.max_pblocks;
+    if (c * a.g >= a.b) return false;
+    blk = a.q.pblocks[(int64_t)c * a.max_pblocks + e];
+    return e < a.q.n_pblocks[c];
 }
 
-__device__ __forceinline__ void row_dots(const float* M, int D, const float* v1, const float* v2, float* y1, float* y2) {
-    const int lanes = D / 4;  // (the same for every thread)
-    if (lanes <= 16) row_dots_short<16>(M, D, v1, v2, y1, y2);
-    else if (lanes <= 32) row_dots_short<32>(M, D, v1, v2, y1, y2);
-    else if (lanes <= 64) row_dots_short<64>(M, D, v1, v2, y1, y2);
-    else row_dots_long(M, D, v1, v2, y1, y2);
-}
-
-__global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a, float* pos_out) {
-    __shared__ __attribute__((aligned(16))) float va[MAX_D], vc[MAX_D], yo[MAX_D], yp[MAX_D];
-    __shared__ float part[RT / 64];
-    const int i = blockIdx.x, tid = threadIdx.x, D = a.D;
-    const Rows x = rows_of(a, i);
-    for (int d = tid; d < D; d += RT) { va[d] = x.a[d]; vc[d] = x.c[d]; }
-    __syncthreads();
-    row_dots(x.M, D, va, vc, yo, yp);
-    __syncthreads();
-    float ss = 0.f;
-    for (int d = tid; d < D; d += RT) {
-        const float o = yo[d] + x.sigma * x.r[d], p = yp[d];
-        a.O[(int64_t)i * D + d] = o;
-        a.PP[(int64_t)i * D + d] = p;
-        ss += (o - p) * (o - p);
+// Rows 2 m and 2 m + 1 of the product: a and c of the block's m-th positive.
+template <int NT>
+__global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
+    __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
+    const int D = a.D, tid = threadIdx.x;
+    int c;
+    TransrBlock blk;
+    if (!pblock_of(a, blockIdx.x, c, blk)) return;
+    const int n = blk.n;
+    const StepView sv = step_view(a.ids);
+    const bool head = sv.side == KGE_NEG_HEAD;
+    const float* Rr = a.R + (int64_t)blk.rel * a.rel_dim;
+    const float* M = Rr + D;
+    const float* pa[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const int row = min(tid / 8 + 32 * it, 2 * n - 1), i = a.q.members[blk.off + row / 2];
+        // even rows: the kept entity, odd rows: the replaced one
+        const int64_t id = clamp_id((head == (bool)(row & 1)) ? sv.h[i] : sv.t[i], a.n_ent);
+        pa[it] = a.E + id * D;
+        if (tid % 8 == 0 && row == tid / 8 + 32 * it) a.q.ent[2 * blk.off + row] = (uint32_t)id;
     }
-    ss = wave_sum(ss);
-    if ((tid & 63) == 0) part[tid >> 6] = ss;
-    __syncthreads();
-    if (tid == 0) {
-        float tot = 0.f;
-        for (int w = 0; w < RT / 64; ++w) tot += part[w];
-        const float f = a.gamma - tot;
-        a.fpos[i] = f;
-        if (pos_out) pos_out[i] = f;
-        // positive part of the logistic loss (Sec. 2, y = +1) and its derivative
-        const float invb = 1.f / (float)a.b;
-        const float e = expf(-fabsf(f));
-        a.row_loss[i] = (fmaxf(-f, 0.f) + log1pf(e)) * invb;
-        a.cpos[i] = -((f >= 0.f ? e : 1.f) / (1.f + e)) * invb;
-    }
-}
-
-// Workgroup per positive: S_ij = gamma - |o_i - P_ij|^2.  A row of D floats is D / 4 16-byte pieces; a group of SUB
-// lanes (the power of two that holds them, at most a wave) takes one j at a time, so that short rows do not leave most
-// of a wave idle, and works on four of its j in one round (four loads in flight, then four shuffle reductions).
-template <int SUB>
-__device__ __forceinline__ void transr_score_rows(const TransrArgs& a, float* out, int ld_out) {
-    constexpr int GROUPS = RT / SUB;
-    const int i = blockIdx.x, grp = threadIdx.x / SUB, ln = threadIdx.x % SUB, D = a.D, lanes = D / 4;
-    const bool act = ln < lanes;
-    const float4 ov = act ? ld4(a.O + (int64_t)i * D + 4 * ln) : f4(0.f);
-    const float* P = a.P + (int64_t)i * a.k * D + (act ? 4 * ln : 0);
-    for (int j0 = grp; j0 < a.k; j0 += 4 * GROUPS) {
-        float4 v[4];
+    const float sigma = head ? -1.f : 1.f;
+    const int l16 = tid & 15, quad = (tid & 63) >> 4;
+    float ss[2] = {0.f, 0.f};
+    for (int n0 = 0; n0 < D; n0 += BN) {
+        Tile<NT> t;
+        tile_init(t, As, Bs, 2 * n);
+        const float* pb[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int j = j0 + u * GROUPS;
-            v[u] = ld4(P + (int64_t)(j < a.k ? j : j0) * D);
-        }
+        for (int it = 0; it < 4; ++it) pb[it] = M + (int64_t)min(n0 + tid / 8 + 32 * it, D - 1) * D;
+        float rr[NT];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const float d0 = ov.x - v[u].x, d1 = ov.y - v[u].y, d2 = ov.z - v[u].z, d3 = ov.w - v[u].w;
-            float ss = act ? d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3 : 0.f;
+        for (int ct = 0; ct < NT; ++ct) rr[ct] = sigma * Rr[min(n0 + 16 * ct + l16, D - 1)];
+        tile_run<true, true, false>(t, D, 1, [&](int, int kb, float4* r) { load_kc<2>(pa, D, kb, r); },
+                                    [&](int kb, float4* r) { mask_kc<2>(D, kb, r); },
+                                    [&](int, int kb, float4* r) { load_kc<4>(pb, D, kb, r); },
+                                    [&](int kb, float4* r) { mask_kc<4>(D, kb, r); });
+        if (!t.active) continue;
 #pragma unroll
-            for (int o = SUB / 2; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-            const int j = j0 + u * GROUPS;
-            if (ln == 0 && j < a.k) out[(int64_t)i * ld_out + j] = a.gamma - ss;
-        }
-    }
-}
-
-// rows of more than 256 floats: a wave per j, up to four pieces per lane
-__device__ __forceinline__ void transr_score_long_rows(const TransrArgs& a, float* out, int ld_out) {
-    const int i = blockIdx.x, w = threadIdx.x >> 6, lane = threadIdx.x & 63, D = a.D, lanes = D / 4;
-    const float* o = a.O + (int64_t)i * D;
-    float4 ov[4];
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) {
 #pragma unroll
-    for (int it = 0; it < 4; ++it) ov[it] = lane + 64 * it < lanes ? ld4(o + 4 * (lane + 64 * it)) : f4(0.f);
-    for (int j = w; j < a.k; j += RT / 64) {
-        const float* p = a.P + ((int64_t)i * a.k + j) * D;
-        float ss = 0.f;
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int q = lane + 64 * it;
-            if (q < lanes) {
-                const float4 v = ld4(p + 4 * q);
-                const float d0 = ov[it].x - v.x, d1 = ov[it].y - v.y, d2 = ov[it].z - v.z, d3 = ov[it].w - v.w;
-                ss += d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3;
-            }
-        }
-        ss = wave_sum(ss);
-        if (lane == 0) out[(int64_t)i * ld_out + j] = a.gamma - ss;
-    }
-}
-
-__global__ __launch_bounds__(RT) void k_transr_score(TransrArgs a, float* out, int ld_out) {
-    const int lanes = a.D / 4;  // (the same for every thread)
-    if (lanes <= 16) transr_score_rows<16>(a, out, ld_out);
-    else if (lanes <= 32) transr_score_rows<32>(a, out, ld_out);
-    else if (lanes <= 64) transr_score_rows<64>(a, out, ld_out);
-    else transr_score_long_rows(a, out, ld_out);
-}
-
-// Threads (group, 16 bytes of the row); the groups share out the rows they walk, four loads in flight each, and their
-// sums meet in LDS in group order.
-// U_ij = 2 W_ij (o_i - P_ij) over P_ij; GO_i = - sum_j U_ij
-__global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a) {
-    __shared__ __attribute__((aligned(16))) float4 part[RT];
-    const int i = blockIdx.x, D = a.D, lanes = D / 4, groups = RT / lanes;
-    const int grp = threadIdx.x / lanes, v = threadIdx.x % lanes;
-    const float* W = a.S + (int64_t)i * a.ld_s;
-    float4 go = f4(0.f);
-    if (grp < groups) {
-        const float4 o = ld4(a.O + (int64_t)i * D + 4 * v);
-        float* P = a.P + (int64_t)i * a.k * D + 4 * v;
-        for (int j0 = grp; j0 < a.k; j0 += 4 * groups) {
-            float4 pv[4];
-            float w2[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + u * groups < a.k ? j0 + u * groups : j0;
-                pv[u] = ld4(P + (int64_t)j * D);
-                w2[u] = 2.f * W[j];
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int j = j0 + u * groups;
-                if (j < a.k) {
-                    const float4 q = make_float4(w2[u] * (o.x - pv[u].x), w2[u] * (o.y - pv[u].y), w2[u] * (o.z - pv[u].z),
-                                                 w2[u] * (o.w - pv[u].w));
-                    st4(P + (int64_t)j * D, q);
-                    go.x -= q.x; go.y -= q.y; go.z -= q.z; go.w -= q.w;
+                for (int h = 0; h < 2; ++h) {
+                    const int m = 8 * t.wave + 2 * quad + h;
+                    const float o = t.acc[ct][2 * h] + rr[ct], p = t.acc[ct][2 * h + 1];
+                    ss[h] += (o - p) * (o - p);
+                    if (m < n) {
+                        const int64_t at = (int64_t)(blk.off + m) * D + d;
+                        a.O[at] = o;
+                        a.PP[at] = p;
+                    }
                 }
             }
         }
     }
-    part[threadIdx.x] = go;
-    __syncthreads();
-    if (grp == 0) {
-        float4 t = part[v];
-        for (int g2 = 1; g2 < groups; ++g2) {
-            const float4 q = part[g2 * lanes + v];
-            t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const float s = sum16(ss[h]);
+        const int m = 8 * row_wave() + 2 * quad + h;
+        if (l16 == 0 && m < n) {
+            const int q = blk.off + m, i = a.train ? q : a.q.members[q];
+            const float f = a.gamma - s;
+            a.fpos[i] = f;
+            if (a.pos_out) a.pos_out[i] = f;
+            // positive part of the logistic loss (Sec. 2, y = +1) and its derivative
+            const float invb = 1.f / (float)a.b;
+            const float x = expf(-fabsf(f));
+            a.row_loss[i] = (fmaxf(-f, 0.f) + log1pf(x)) * invb;
+            a.cpos[i] = -((f >= 0.f ? x : 1.f) / (1.f + x)) * invb;
         }
-        st4(a.GO + (int64_t)i * D + 4 * v, t);
     }
 }
 
-__global__ __launch_bounds__(RT) void k_transr_chain(TransrArgs a) {
-    __shared__ __attribute__((aligned(16))) float go[MAX_D], gp[MAX_D];
-    __shared__ __attribute__((aligned(16))) float4 part1[RT], part2[RT];
-    const int i = blockIdx.x, tid = threadIdx.x, D = a.D, lanes = D / 4;
-    const Rows x = rows_of(a, i);
-    const float cp = a.cpos[i];
-    for (int d = tid; d < D; d += RT) {
-        const float q = a.O[(int64_t)i * D + d] - a.PP[(int64_t)i * D + d];
-        const float g1 = a.GO[(int64_t)i * D + d] - 2.f * cp * q;  // df+/do = -2 (o - p)
-        go[d] = g1;
-        gp[d] = 2.f * cp * q;
-        a.Gr[(int64_t)i * D + d] = x.sigma * g1;
-    }
-    __syncthreads();
-    // M^T go and M^T gp (column sums: a thread per 16-byte column slice, rows dealt round-robin to thread groups),
-    // and on the way, row by row, the outer products into the matrix gradient
-    const int groups = RT / lanes, grp = tid / lanes, v = tid % lanes;
-    float4 y1 = f4(0.f), y2 = f4(0.f);
-    if (grp < groups) {
-        const float4 av = ld4(x.a + 4 * v), cv = ld4(x.c + 4 * v);
-        float* gm = a.GM + (int64_t)i * D * D;
-        for (int r = grp; r < D; r += groups) {
-            const float4 m = ld4(x.M + (int64_t)r * D + 4 * v);
-            const float s1 = go[r], s2 = gp[r];
-            y1.x += s1 * m.x; y1.y += s1 * m.y; y1.z += s1 * m.z; y1.w += s1 * m.w;
-            y2.x += s2 * m.x; y2.y += s2 * m.y; y2.z += s2 * m.z; y2.w += s2 * m.w;
-            float4 gv = ld4(gm + (int64_t)r * D + 4 * v);
-            gv.x += s1 * av.x + s2 * cv.x; gv.y += s1 * av.y + s2 * cv.y;
-            gv.z += s1 * av.z + s2 * cv.z; gv.w += s1 * av.w + s2 * cv.w;
-            st4(gm + (int64_t)r * D + 4 * v, gv);
+// 64 corrupting rows x a block of an item's positives: projections, then the scores of the positives against them.  (An
+// item of more than 32 positives is projected once per block: at that size the scores are the larger part of the work.)
+template <int NT>
+__global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a) {
+    __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
+    const int tiles = (a.k + BM - 1) / BM, D = a.D, tid = threadIdx.x;
+    int c, tile;
+    TransrBlock blk;
+    float loss = 0.f;
+    const int unit = unit_of_block(blockIdx.x, tiles, tile);
+    if (pblock_of(a, unit, c, blk)) {
+        const int j0 = tile * BM, rows = min(BM, a.k - j0), n = blk.n;
+        const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D;
+        const float* N = a.N + ((int64_t)c * a.k + j0) * D;
+        float* P = a.P + ((int64_t)blk.slot * a.k + j0) * D;
+        const bool store_p = a.train && blk.first == 0;
+        const float* pa[2];
+#pragma unroll
+        for (int it = 0; it < 2; ++it) pa[it] = N + (int64_t)min(tid / 8 + 32 * it, rows - 1) * D;
+        const int l16 = tid & 15, q = ((tid >> 2) & 1) + 2 * ((tid >> 3) & 1);  // accumulator row this lane ends up with
+        for (int n0 = 0; n0 < D; n0 += BN) {
+            Tile<NT> t;
+            tile_init(t, As, Bs, rows);
+            const float* pb[4];
+#pragma unroll
+            for (int it = 0; it < 4; ++it) pb[it] = M + (int64_t)min(n0 + tid / 8 + 32 * it, D - 1) * D;
+            tile_run<true, true, false>(t, D, 1, [&](int, int kb, float4* r) { load_kc<2>(pa, D, kb, r); },
+                                        [&](int kb, float4* r) { mask_kc<2>(D, kb, r); },
+                                        [&](int, int kb, float4* r) { load_kc<4>(pb, D, kb, r); },
+                                        [&](int kb, float4* r) { mask_kc<4>(D, kb, r); });
+            // the o rows of the block, where the matrix was (zeros past column D)
+            float4 ro[4];
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int d = n0 + 4 * (tid % 32);
+                ro[it] = d < D ? ld4(a.O + (int64_t)(blk.off + min(tid / 32 + 8 * it, n - 1)) * D + d) : f4(0.f);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < 4; ++it) st4(Bs + (tid / 32 + 8 * it) * BN + 4 * (tid % 32), ro[it]);
+            __syncthreads();
+            if (!t.active) continue;
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) {
+                const int d = n0 + 16 * ct + l16;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (d >= D) t.acc[ct][v] = 0.f;
+                    else if (store_p && t.row(v) < rows) P[(int64_t)t.row(v) * D + d] = t.acc[ct][v];
+                }
+            }
+            // four positives per round, so that every lane has a score to finish: positive m0 + lane % 4, row q
+            const int x = tid & 3, j = t.row(q);
+            for (int m0 = 0; m0 < n; m0 += 4) {
+                float r[4];
+#pragma unroll
+                for (int y = 0; y < 4; ++y) {
+                    if (m0 + y >= n) {
+                        r[y] = 0.f;
+                        continue;
+                    }
+                    const float* po = Bs + (m0 + y) * BN + l16;
+                    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int ct = 0; ct < NT; ++ct) {
+                        const float o = po[16 * ct];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const float d = o - t.acc[ct][v];
+                            ss[v] = fmaf(d, d, ss[v]);
+                        }
+                    }
+                    r[y] = sum16x4(ss);
+                }
+                if (m0 + x < n && j < rows) {
+                    float s = x == 0 ? r[0] : x == 1 ? r[1] : x == 2 ? r[2] : r[3];
+                    const int m = blk.off + m0 + x;
+                    float* ps = a.S + (int64_t)(a.train ? m : a.q.members[m]) * a.ld_s + j0 + j;
+                    if (n0 > 0) s += *ps;  // what the columns before contributed
+                    if (n0 + BN >= D) {
+                        s = a.gamma - s;
+                        if (a.out_w) s = w_and_loss<true>(s, a.wk, loss);
+                    }
+                    *ps = s;
+                }
+            }
         }
     }
-    part1[tid] = y1;
-    part2[tid] = y2;
+    if (!a.out_w) return;
+    __shared__ float part[RT / 64];
+    loss = wave_sum(loss);
+    if ((tid & 63) == 0) part[tid >> 6] = loss;
     __syncthreads();
-    if (tid < lanes) {
-        float4 t1 = part1[tid], t2 = part2[tid];
-        for (int g = 1; g < groups; ++g) {
-            const float4 u1 = part1[g * lanes + tid], u2 = part2[g * lanes + tid];
-            t1.x += u1.x; t1.y += u1.y; t1.z += u1.z; t1.w += u1.w;
-            t2.x += u2.x; t2.y += u2.y; t2.z += u2.z; t2.w += u2.w;
+    if (tid == 0) a.loss_part[blockIdx.x] = (part[0] + part[1] + part[2] + part[3]) * a.wk;
+}
+
+// Items of at most DP_FEW positives: the sums over an item's positives and over the corrupting rows on the vector ALUs,
+// both while a row of P is in registers (32 us for the FB15k-sized step, 130 MB of rows; two products took 67, their
+// tiles of sixteen rows nearly empty); others: two products.
+constexpr int DP_FEW = 16, MB = 4, DR = 8;
+
+// 64 corrupting rows of an item.  Thread (group, 16 bytes of the row), DR rows at a time in registers with their sums over
+// the item's positives, which come in batches of MB: the sums for dL/do stay in registers too and meet in LDS in group order.
+__device__ void dp_few(const TransrArgs& a, int slot, int tile, const TransrItem& item, float4 (*part)[RT], float (*W2)[BM]) {
+    const int D = a.D, tid = threadIdx.x, lanes = D / 4, groups = RT / lanes, n = item.n;
+    const int j0 = tile * BM, rows = min(BM, a.k - j0), grp = tid / lanes, v = tid % lanes;
+    const bool act = grp < groups;
+    const int64_t base = ((int64_t)slot * a.k + j0) * D + 4 * v;
+    const float* O = a.O + (int64_t)item.off * D + 4 * v;
+    const int wm = tid / BM, wj = tid % BM;
+    const float* W = a.S + (int64_t)item.off * a.ld_s + j0 + min(wj, rows - 1);
+    for (int r0 = 0; r0 < rows; r0 += DR * groups) {
+        float4 p[DR], s[DR];
+#pragma unroll
+        for (int u = 0; u < DR; ++u) {
+            p[u] = ld4(a.P + base + (int64_t)min(r0 + (act ? grp : 0) + u * groups, rows - 1) * D);
+            s[u] = f4(0.f);
         }
-        // key positions: heads 0 .. b-1, tails b .. 2b-1
-        st4(a.Gent + (int64_t)(x.head ? a.b + i : i) * D + 4 * tid, t1);
-        st4(a.Gent + (int64_t)(x.head ? i : a.b + i) * D + 4 * tid, t2);
+        for (int m0 = 0; m0 < n; m0 += MB) {
+            const int mn = min(MB, n - m0);
+            float4 o[MB], go[MB];
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                o[m] = ld4(O + (int64_t)min(m0 + m, n - 1) * D);
+                go[m] = f4(0.f);
+            }
+            const float w2 = 2.f * W[(int64_t)min(m0 + wm, n - 1) * a.ld_s];
+            __syncthreads();
+            W2[wm][wj] = wm < mn && wj < rows ? w2 : 0.f;  // (rows and positives that do not exist add nothing)
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < DR; ++u) {
+                const int j = r0 + grp + u * groups;
+                if (act && j < rows) {
+#pragma unroll
+                    for (int m = 0; m < MB; ++m) {
+                        const float w = W2[m][j];
+                        const float4 x = make_float4(w * (o[m].x - p[u].x), w * (o[m].y - p[u].y), w * (o[m].z - p[u].z), w * (o[m].w - p[u].w));
+                        s[u].x += x.x; s[u].y += x.y; s[u].z += x.z; s[u].w += x.w;
+                        go[m].x -= x.x; go[m].y -= x.y; go[m].z -= x.z; go[m].w -= x.w;
+                    }
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < MB; ++m) part[m][tid] = go[m];
+            __syncthreads();
+            for (int e = tid; e < mn * lanes; e += RT) {
+                const int m = e / lanes, x = e % lanes;
+                float4 t = part[m][x];
+                for (int g2 = 1; g2 < groups; ++g2) {
+                    const float4 q = part[m][g2 * lanes + x];
+                    t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+                }
+                float* dst = a.GOp + ((int64_t)tile * a.b + item.off + m0 + m) * D + 4 * x;
+                if (r0 > 0) {
+                    const float4 q = ld4(dst);
+                    t.x += q.x; t.y += q.y; t.z += q.z; t.w += q.w;
+                }
+                st4(dst, t);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < DR; ++u) {
+            const int j = r0 + grp + u * groups;
+            if (act && j < rows) st4(a.V + base + (int64_t)j * D, s[u]);
+        }
+    }
+}
+
+// The first workgroups: the gradients of a block of the positives of an item of many x 128 columns, K over the corrupting
+// rows; the others: V of 64 corrupting rows of an item (of many: x 128 columns, K over the item's positives).
+//     V = 2 (W^T O - colsum(W) P) ,   dL/do = 2 (W P - rowsum(W) o)
+template <int NT>
+__global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
+    __shared__ __attribute__((aligned(16))) float lds[A_FLOATS + B_FLOATS];
+    float* As = lds;
+    float* Bs = lds + A_FLOATS;
+    static_assert(sizeof(float4) * MB * RT + sizeof(float) * MB * BM <= sizeof(lds), "");
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15, quad = (tid & 63) >> 4;
+    int c;
+    if ((int)blockIdx.x >= go_blocks) {
+        int slot, tile;
+        TransrItem item;
+        const int tiles = (a.k + BM - 1) / BM * cols;
+        if (!item_of(a, unit_of_block(blockIdx.x - go_blocks, tiles, tile), c, slot, item)) return;
+        const int n0 = tile % cols * BN, j0 = tile / cols * BM, rows = min(BM, a.k - j0), n = item.n;
+        if (n <= DP_FEW) {
+            if (n0 == 0) dp_few(a, slot, tile / cols, item, reinterpret_cast<float4(*)[RT]>(lds), reinterpret_cast<float(*)[BM]>(lds + 4 * MB * RT));
+            return;
+        }
+        const int ja = 4 * (tid % 16), db = n0 + 4 * (tid % 32);
+        const float* W = a.S + (int64_t)item.off * a.ld_s + j0 + (ja < rows ? ja : 0);
+        const float* O = a.O + (int64_t)item.off * D + (db < D ? db : n0);
+        Tile<NT> t;
+        tile_init(t, As, Bs, rows);
+        tile_run<false, false, true>(t, n, 1, [&](int, int kb, float4* r) { load_mc<2>(W, a.ld_s, n, kb, tid / 16, 16, r); },
+                                     [&](int kb, float4* r) { mask_mc<2>(n, kb, tid / 16, 16, r); },
+                                     [&](int, int kb, float4* r) { load_mc<4>(O, D, n, kb, tid / 32, 8, r); },
+                                     [&](int kb, float4* r) { mask_mc<4>(n, kb, tid / 32, 8, r); });
+        const int64_t base = ((int64_t)slot * a.k + j0) * D + n0 + (n0 + l16 < D ? l16 : 0);
+        float w[4], p[NT][4];  // all of P asked for before the first store
+#pragma unroll
+        for (int v = 0; v < 4; ++v) w[v] = __shfl(t.a_sum, 4 * quad + v, 64);
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16 < D ? 16 * ct : 0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) p[ct][v] = a.P[base + (int64_t)min(t.row(v), rows - 1) * D + d];
+        }
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            if (n0 + 16 * ct + l16 < D) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (t.row(v) < rows) a.V[base + (int64_t)t.row(v) * D + 16 * ct] = 2.f * (t.acc[ct][v] - w[v] * p[ct][v]);
+                }
+            }
+        }
+        return;
+    }
+    const int n0 = blockIdx.x % cols * BN;
+    TransrBlock blk;
+    if (!pblock_of(a, blockIdx.x / cols, c, blk) || blk.all <= DP_FEW) return;
+    const int db = n0 + 4 * (tid % 32), n = blk.n;
+    const float* P = a.P + (int64_t)blk.slot * a.k * D + (db < D ? db : n0);
+    const float* W[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) W[it] = a.S + (int64_t)(blk.off + min(tid / 8 + 32 * it, n - 1)) * a.ld_s;
+    Tile<NT> t;
+    tile_init(t, As, Bs, n);
+    tile_run<true, false, true>(t, a.k, 1, [&](int, int kb, float4* r) { load_kc<2>(W, a.k, kb, r); },
+        [&](int kb, float4* r) {
+            const int left = a.k - BK * kb - 4 * (tid % 8);  // (a row of W holds a multiple of four)
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                r[it].x = left <= 0 ? 0.f : r[it].x; r[it].y = left <= 1 ? 0.f : r[it].y;
+                r[it].z = left <= 2 ? 0.f : r[it].z; r[it].w = left <= 3 ? 0.f : r[it].w;
+            }
+        },
+        [&](int, int kb, float4* r) { load_mc<4>(P, D, a.k, kb, tid / 32, 8, r); },
+        [&](int kb, float4* r) { mask_mc<4>(a.k, kb, tid / 32, 8, r); });
+    if (!t.active) return;
+    const float sigma = step_view(a.ids).side == KGE_NEG_HEAD ? -1.f : 1.f;
+    float o[4][NT], p[4][NT];  // all of them asked for before the first store
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int64_t at = (int64_t)(blk.off + min(t.row(v), n - 1)) * D + n0 + (n0 + l16 < D ? l16 : 0);
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16 < D ? 16 * ct : 0;
+            o[v][ct] = a.O[at + d];
+            p[v][ct] = a.PP[at + d];
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const float w = __shfl(t.a_sum, 4 * quad + v, 64);
+        const int m = blk.off + t.row(v);
+        if (t.row(v) >= n) continue;
+        const int64_t at = (int64_t)m * D + n0 + l16, at_r = (int64_t)a.q.members[m] * D + n0 + l16;
+        const float cp2 = 2.f * a.cpos[m];
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            if (n0 + 16 * ct + l16 < D) {
+                const float gp = cp2 * (o[v][ct] - p[v][ct]);  // df+/do = -2 (o - p)
+                const float go = 2.f * (t.acc[ct][v] - w * o[v][ct]) - gp;
+                a.GO[at + 16 * ct] = go;
+                a.PP[at + 16 * ct] = gp;
+                a.Gr[at_r + 16 * ct] = sigma * go;
+            }
+        }
+    }
+}
+
+// what dp_few left in parts: thread per 16 bytes of a positive's row
+__global__ __launch_bounds__(RT) void k_transr_go(TransrArgs a) {
+    const int lanes = a.D / 4, e = blockIdx.x * RT + threadIdx.x, m = e / lanes;
+    if (m >= a.b) return;
+    const int64_t at = (int64_t)m * a.D + 4 * (e % lanes);
+    const int i = a.q.members[m], all = a.q.count[m];
+    const float cp2 = 2.f * a.cpos[m];
+    const float4 o = ld4(a.O + at), p = ld4(a.PP + at);
+    if (all > DP_FEW) return;
+    const float4 s = sum_parts(a.GOp + at, (a.k + BM - 1) / BM, (int64_t)a.b * a.D);
+    const float4 gp = make_float4(cp2 * (o.x - p.x), cp2 * (o.y - p.y), cp2 * (o.z - p.z), cp2 * (o.w - p.w));  // df+/do = -2 (o - p)
+    const float4 go = make_float4(s.x - gp.x, s.y - gp.y, s.z - gp.z, s.w - gp.w);
+    st4(a.GO + at, go);
+    st4(a.PP + at, gp);
+    const float sigma = step_view(a.ids).side == KGE_NEG_HEAD ? -1.f : 1.f;
+    st4(a.Gr + (int64_t)i * a.D + 4 * (e % lanes), make_float4(sigma * go.x, sigma * go.y, sigma * go.z, sigma * go.w));
+}
+
+// V_t M_t.  The first workgroups: 64 corrupting rows of a chunk x 128 columns x a range of the chunk's items; the others:
+// dL/do and dL/dp of a block of an item's positives (rows 2 m, 2 m + 1) x 128 columns, straight into their gradient rows.
+template <int NT>
+__global__ __launch_bounds__(RT, 4) void k_transr_back(TransrArgs a, int neg_blocks) {
+    __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15;
+    Tile<NT> t;
+    const bool neg = (int)blockIdx.x < neg_blocks;
+    const int x = neg ? blockIdx.x : blockIdx.x - neg_blocks;
+    const int n0 = x % cols * BN, col = n0 + 4 * (tid % 32), colc = col < D ? col : n0;  // D is a multiple of 4
+    if (neg) {
+        const int tiles = (a.k + BM - 1) / BM, seg = x / cols % a.segments, y = x / cols / a.segments;
+        const int tile = y % tiles, c = y / tiles, j0 = tile * BM, rows = min(BM, a.k - j0);
+        const int items = a.q.n_items[c], s0 = (int)((int64_t)items * seg / a.segments), s1 = (int)((int64_t)items * (seg + 1) / a.segments);
+        tile_init(t, As, Bs, rows);
+        const float* V[2];
+#pragma unroll
+        for (int it = 0; it < 2; ++it) V[it] = a.V + (((int64_t)c * a.g + s0) * a.k + j0 + min(tid / 8 + 32 * it, rows - 1)) * D;
+        // the matrix of the item at hand and of the next one (its relation id is asked for an item ahead)
+        const TransrItem* item = a.q.items + c * a.g + s0;
+        const int last = s1 - s0 - 1;
+        int cur = 0;
+        const float* here = a.R + D + (last >= 0 ? item[0].rel : 0) * a.rel_dim + colc;
+        uint32_t next = last >= 0 ? item[last > 0].rel : 0;
+        tile_run<true, false, false>(t, D, s1 - s0,
+            [&](int run, int kb, float4* r) {
+                const float* p[2] = {V[0] + (int64_t)run * a.k * D, V[1] + (int64_t)run * a.k * D};
+                load_kc<2>(p, D, kb, r);
+            },
+            [&](int kb, float4* r) { mask_kc<2>(D, kb, r); },
+            [&](int run, int kb, float4* r) {
+                if (run != cur) {
+                    cur = run;
+                    here = a.R + D + next * a.rel_dim + colc;
+                    next = item[min(run + 1, last)].rel;
+                }
+                load_mc<4>(here, D, D, kb, tid / 32, 8, r);
+            },
+            [&](int kb, float4* r) { mask_mc<4>(D, kb, tid / 32, 8, r); });
+        float* out = a.back_part + (((int64_t)seg * (a.b / a.g) + c) * a.k + j0) * D;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (t.row(v) < rows) out[(int64_t)t.row(v) * D + d] = t.acc[ct][v];
+                }
+            }
+        }
+        return;
+    }
+    int c;
+    TransrBlock blk;
+    if (!pblock_of(a, x / cols, c, blk)) return;
+    const int n = blk.n;
+    const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D + colc;
+    const bool head = step_view(a.ids).side == KGE_NEG_HEAD;
+    tile_init(t, As, Bs, 2 * n);
+    const float* pa[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const int row = min(tid / 8 + 32 * it, 2 * n - 1);
+        pa[it] = ((row & 1) ? a.PP : a.GO) + (int64_t)(blk.off + row / 2) * D;
+    }
+    int i[2];  // rows 2 h, 2 h + 1 of the lane's four
+#pragma unroll
+    for (int h = 0; h < 2; ++h) i[h] = a.q.members[blk.off + min(t.row(2 * h) / 2, n - 1)];
+    tile_run<true, false, false>(t, D, 1, [&](int, int kb, float4* r) { load_kc<2>(pa, D, kb, r); },
+                                 [&](int kb, float4* r) { mask_kc<2>(D, kb, r); },
+                                 [&](int, int kb, float4* r) { load_mc<4>(M, D, D, kb, tid / 32, 8, r); },
+                                 [&](int kb, float4* r) { mask_mc<4>(D, kb, tid / 32, 8, r); });
+    if (!t.active) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (t.row(v) >= 2 * n) continue;
+        // key positions: heads 0 .. b-1, tails b .. 2b-1; even rows belong to the kept entity
+        const bool to_head = head == (bool)(v & 1);
+        float* out = a.Gent + ((int64_t)(to_head ? 0 : a.b) + i[v / 2]) * D;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) out[d] = t.acc[ct][v];
+        }
+    }
+}
+
+// 64 rows x 128 columns of dL/dM of an item.  K: the chunk's corrupting rows, then two rows per positive.
+template <int NT>
+__global__ __launch_bounds__(RT, 4) void k_transr_mgrad(TransrArgs a) {
+    __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, tiles = (D + BM - 1) / BM * cols;
+    int c, slot, tile;
+    TransrItem item;
+    if (!item_of(a, unit_of_block(blockIdx.x, tiles, tile), c, slot, item)) return;
+    const int n0 = tile % cols * BN, e0 = tile / cols * BM, n2 = 2 * item.n;
+    const int ca = e0 + 4 * (tid % 16), cb = n0 + 4 * (tid % 32), ka = tid / 16, kb0 = tid / 32;
+    const int cac = ca < D ? ca : e0, cbc = cb < D ? cb : n0;
+    const float* V = a.V + (int64_t)slot * a.k * D + cac;
+    const float* N = a.N + (int64_t)c * a.k * D + cbc;
+    const uint32_t* ent = a.q.ent + 2 * item.off;
+    uint32_t id[4];  // of the first block of positives: there when the corrupting rows are done
+#pragma unroll
+    for (int it = 0; it < 4; ++it) id[it] = ent[min(kb0 + 8 * it, n2 - 1)];
+    Tile<NT> t;
+    tile_init(t, As, Bs, min(BM, D - e0));
+    tile_run<false, false, false>(t, a.k, 1, [&](int, int kb, float4* r) { load_mc<2>(V, D, a.k, kb, ka, 16, r); },
+                                  [&](int kb, float4* r) { mask_mc<2>(a.k, kb, ka, 16, r); },
+                                  [&](int, int kb, float4* r) { load_mc<4>(N, D, a.k, kb, kb0, 8, r); },
+                                  [&](int kb, float4* r) { mask_mc<4>(a.k, kb, kb0, 8, r); });
+    tile_run<false, false, false>(t, n2, 1,
+        [&](int, int kb, float4* r) {
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int kk = min(BK * kb + ka + 16 * it, n2 - 1);
+                r[it] = ld4(((kk & 1) ? a.PP : a.GO) + (int64_t)(item.off + kk / 2) * D + cac);
+            }
+        },
+        [&](int kb, float4* r) { mask_mc<2>(n2, kb, ka, 16, r); },
+        [&](int, int kb, float4* r) {
+            if (kb > 0) {
+#pragma unroll
+                for (int it = 0; it < 4; ++it) id[it] = ent[min(BK * kb + kb0 + 8 * it, n2 - 1)];
+            }
+#pragma unroll
+            for (int it = 0; it < 4; ++it) r[it] = ld4(a.E + (int64_t)id[it] * D + cbc);
+        },
+        [&](int kb, float4* r) { mask_mc<4>(n2, kb, kb0, 8, r); });
+    float* out = a.GM + (int64_t)slot * D * D;
+    const int l16 = tid & 15;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int e = e0 + t.row(v);
+        if (e >= D) continue;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) out[(int64_t)e * D + d] = t.acc[ct][v];
+        }
     }
 }
 
@@ -323,32 +760,41 @@ struct TransrUpdArgs {
     float* St;            // its Adagrad accumulator
     const uint32_t* key;  // sorted relation ids of the step
     const uint32_t* pos;  // position in the mini-batch of each sorted entry
-    int n, D, rows_per_slab;
+    const int* slot_of;   // item slot of the positives that are the first of their item, else -1
+    int n, D, rows_per_slab, slabs;
     int64_t rel_dim;
     const float* Gr;
     const float* GM;
     float lr, eps;
+    PartialRows rest;     // gradient rows of the corrupting entities, still in parts
+    int share;
 };
 
 // Workgroup (p, slab): slab 0 is the translation, slab s > 0 rows (s - 1) * rows_per_slab .. of the matrix.  If sorted
 // position p is the last of its run of equal relation ids, the workgroup sums the run's gradient rows for its slab in
-// sorted order and applies Adagrad.
+// sorted order (translation: a row per positive; matrix: one per item) and applies Adagrad.
 __global__ __launch_bounds__(RT) void k_transr_update(TransrUpdArgs a) {
-    const int p = blockIdx.x, slab = blockIdx.y, tid = threadIdx.x;
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x >= a.n * a.slabs) {
+        sum_partial_rows<RT>(a.rest, a.share, blockIdx.x - a.n * a.slabs, gridDim.x - a.n * a.slabs);
+        return;
+    }
+    const int p = blockIdx.x / a.slabs, slab = blockIdx.x % a.slabs;
     const uint32_t key = a.key[p];
     if (p + 1 < a.n && a.key[p + 1] == key) return;  // the run goes on (same decision in every thread)
-    __shared__ int first_other;
-    __shared__ uint32_t lpos[RT];
+    __shared__ int first_other, n_rows;
+    __shared__ int lrow[RT];
     const int D = a.D;
     const int width = slab == 0 ? D : a.rows_per_slab * D, lanes = width / 4;
-    const bool act = tid < lanes;
-    const int e = act ? 4 * tid : 0;
+    const int groups = RT / lanes, grp = tid / lanes;  // thread groups share out the rows of the run; the first applies the sum
+    const bool act = grp < groups;
+    const int e = act ? 4 * (tid - grp * lanes) : 0;
     const int64_t in_row = slab == 0 ? e : (int64_t)D + (int64_t)(slab - 1) * a.rows_per_slab * D + e;
     const int64_t off = (int64_t)key * a.rel_dim + in_row;
     const float* G = slab == 0 ? a.Gr + e : a.GM + (int64_t)(slab - 1) * a.rows_per_slab * D + e;
     const int64_t g_stride = slab == 0 ? D : (int64_t)D * D;
     float4 x = f4(0.f), s = f4(0.f);
-    if (act) { x = ld4(a.T + off); s = ld4(a.St + off); }
+    if (grp == 0) { x = ld4(a.T + off); s = ld4(a.St + off); }
     if (tid == 0) first_other = 1 << 30;
     __syncthreads();
     for (int base = 1;; base += RT) {
@@ -363,20 +809,42 @@ __global__ __launch_bounds__(RT) void k_transr_update(TransrUpdArgs a) {
     }
     const int start = p - first_other + 1;
     float4 g = f4(0.f);
+    __shared__ __attribute__((aligned(16))) float4 part[RT];
+    __shared__ int wcount[RT / 64];
     for (int c0 = start; c0 <= p; c0 += RT) {
+        // the rows of this part of the run, in order
+        int row = -1;
+        if (c0 + tid <= p) {
+            row = (int)a.pos[c0 + tid];
+            if (slab > 0) row = a.slot_of[row];
+        }
+        const unsigned long long bal = __ballot(row >= 0);
         __syncthreads();
-        lpos[tid] = a.pos[c0 + tid <= p ? c0 + tid : p];
+        if ((tid & 63) == 0) wcount[tid >> 6] = __popcll(bal);
         __syncthreads();
-        const int m = p - c0 + 1 < RT ? p - c0 + 1 : RT;
+        int at = __popcll(bal & ((1ull << (tid & 63)) - 1));
+        for (int w = 0; w < tid >> 6; ++w) at += wcount[w];
+        if (row >= 0) lrow[at] = row;
+        if (tid == 0) { n_rows = 0; for (int w = 0; w < RT / 64; ++w) n_rows += wcount[w]; }
+        __syncthreads();
+        const int m = n_rows;
         if (act) {
 #pragma unroll 4
-            for (int j = 0; j < m; ++j) {
-                const float4 t = ld4(G + (int64_t)lpos[j] * g_stride);
+            for (int j = grp; j < m; j += groups) {
+                const float4 t = ld4(G + (int64_t)lrow[j] * g_stride);
                 g.x += t.x; g.y += t.y; g.z += t.z; g.w += t.w;
             }
         }
     }
-    if (act) {
+    if (groups > 1) {
+        part[tid] = g;
+        __syncthreads();
+        for (int g2 = 1; grp == 0 && g2 < groups; ++g2) {
+            const float4 t = part[g2 * lanes + tid];
+            g.x += t.x; g.y += t.y; g.z += t.z; g.w += t.w;
+        }
+    }
+    if (grp == 0) {
         adagrad4(g, x, s, a.lr, a.eps);
         st4(a.St + off, s);
         st4(a.T + off, x);
@@ -388,38 +856,94 @@ TransrArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& 
     const int D = c->cfg.ent_dim;
     a.E = E; a.R = R; a.ids = ids; a.b = ids.b; a.D = D; a.k = k; a.g = gsz; a.ld_s = c->ld_s;
     a.n_ent = c->cfg.num_entities; a.n_rel = c->cfg.num_relations; a.rel_dim = c->cfg.rel_dim;
-    a.gamma = gamma;
-    a.O = c->O; a.PP = c->PP; a.P = c->P3; a.S = c->S; a.GO = c->GO;
-    a.fpos = c->fpos; a.cpos = c->cpos; a.row_loss = c->row_loss;
+    a.max_items = transr_max_items(gsz, a.n_rel);
+    a.max_pblocks = transr_max_pblocks(gsz, a.n_rel);
+    a.gamma = gamma; a.wk = 1.f / ((float)(k > 0 ? k : 1) * (float)ids.b);
+    a.out_w = 0; a.train = 1; a.segments = 1;
+    a.q = c->tr_groups;
+    a.O = c->O; a.PP = c->PP; a.P = c->P3; a.V = c->P3 + (int64_t)c->cfg.max_batch * c->cfg.max_neg_per_chunk * D;
+    a.N = c->Nst; a.S = c->S; a.GO = c->GO; a.GOp = c->tr_go_part;
+    a.fpos = c->fpos; a.pos_out = nullptr; a.cpos = c->cpos; a.row_loss = c->row_loss; a.loss_part = c->neg_loss_part;
     a.Gent = c->Gent; a.Gr = c->Grel; a.GM = c->Grel + (int64_t)c->cfg.max_batch * D;
+    a.back_part = c->tr_back_part;
     return a;
 }
 
+// Ranges of a chunk's items in the back-projection: about three workgroups per CU, at least one item each.
+int back_segments(const TransrArgs& a) {
+    const int base = (a.b / a.g) * ((a.k + BM - 1) / BM) * ((a.D + BN - 1) / BN);
+    int s = (KGE_TRANSR_BACK_WGS + base - 1) / base;
+    return s > a.max_items ? a.max_items : s;
+}
+
+// column tiles of 16 per workgroup
+#define KGE_BY_COLUMNS(D, LAUNCH)                                                                     \
+    do {                                                                                              \
+        switch (((D) < BN ? (D) + 15 : BN) / 16) {                                                    \
+        case 1: case 2: LAUNCH(2); break;                                                             \
+        case 3: LAUNCH(3); break;                                                                     \
+        case 4: LAUNCH(4); break;                                                                     \
+        case 5: LAUNCH(5); break;                                                                     \
+        case 6: LAUNCH(6); break;                                                                     \
+        case 7: LAUNCH(7); break;                                                                     \
+        default: LAUNCH(8); break;                                                                    \
+        }                                                                                             \
+    } while (0)
+
 }  // namespace
 
-void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, float gamma, float* pos_out,
+// train: what later launches read stays in the order of the items' positives; otherwise the outputs are the caller's
+void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int gsz, float gamma, float* pos_out, bool train,
                     hipStream_t st) {
-    const TransrArgs a = make_args(c, E, R, ids, 0, 1, gamma);
-    KGE_LAUNCH(c, k_transr_phi, dim3(ids.b), dim3(RT), 0, st, a, pos_out);
+    TransrArgs a = make_args(c, E, R, ids, 0, gsz, gamma);
+    a.pos_out = pos_out; a.train = train;
+#define L(NT) KGE_LAUNCH(c, k_transr_phi<NT>, dim3(ids.b / gsz * a.max_pblocks), dim3(RT), 0, st, a)
+    KGE_BY_COLUMNS(a.D, L);
+#undef L
 }
 
-// negative scores from the projections (kge_gemm_transr_project has filled c->P3)
-void kge_transr_score(kge_ctx* c, const StepIds& ids, int k, float gamma, float* out, int ld_out, hipStream_t st) {
-    const TransrArgs a = make_args(c, nullptr, nullptr, ids, k, 1, gamma);
-    KGE_LAUNCH(c, k_transr_score, dim3(ids.b), dim3(RT), 0, st, a, out, ld_out);
+int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* out, int ld_out, bool train,
+                       bool form_w, hipStream_t st) {
+    TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, gamma);
+    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train;
+    const dim3 grid = block_grid(a, (k + BM - 1) / BM);
+#define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, grid, dim3(RT), 0, st, a)
+    KGE_BY_COLUMNS(a.D, L);
+#undef L
+    return form_w ? (int)grid.x : 0;
 }
 
-float* kge_transr_projections(kge_ctx* c) { return c->P3; }
-float* kge_transr_matrix_grads(kge_ctx* c) { return c->Grel + (int64_t)c->cfg.max_batch * c->cfg.ent_dim; }
-
-void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, hipStream_t st) {
-    const TransrArgs a = make_args(c, nullptr, nullptr, ids, k, 1, 0.f);
-    KGE_LAUNCH(c, k_transr_dp, dim3(ids.b), dim3(RT), 0, st, a);
+void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, hipStream_t st) {
+    const TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
+    const int cols = (a.D + BN - 1) / BN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
+    const dim3 grid(go_blocks + item_grid(a, (k + BM - 1) / BM * cols).x);
+#define L(NT) KGE_LAUNCH(c, k_transr_dp<NT>, grid, dim3(RT), 0, st, a, go_blocks)
+    KGE_BY_COLUMNS(a.D, L);
+#undef L
+    hipLaunchKernelGGL(k_transr_go, dim3((ids.b * (a.D / 4) + RT - 1) / RT), dim3(RT), 0, st, a);
 }
 
-void kge_transr_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st) {
-    const TransrArgs a = make_args(c, E, R, ids, 0, 1, 0.f);
-    KGE_LAUNCH(c, k_transr_chain, dim3(ids.b), dim3(RT), 0, st, a);
+void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, hipStream_t st) {
+    TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, 0.f);
+    const int chunks = ids.b / gsz, cols = (a.D + BN - 1) / BN;
+    a.segments = back_segments(a);
+    float* out = a.Gent + (int64_t)2 * ids.b * a.D;
+    const int64_t stride = (int64_t)chunks * k * a.D;
+    c->neg_partial = {c->tr_back_part, out, a.segments, stride, stride / 4};
+    if (a.segments == 1) a.back_part = out;
+    const int neg_blocks = chunks * ((k + BM - 1) / BM) * a.segments * cols;
+    const dim3 grid(neg_blocks + chunks * a.max_pblocks * cols);
+#define L(NT) KGE_LAUNCH(c, k_transr_back<NT>, grid, dim3(RT), 0, st, a, neg_blocks)
+    KGE_BY_COLUMNS(a.D, L);
+#undef L
+}
+
+void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int gsz, hipStream_t st) {
+    const TransrArgs a = make_args(c, E, nullptr, ids, k, gsz, 0.f);
+    const dim3 grid = item_grid(a, ((a.D + BM - 1) / BM) * ((a.D + BN - 1) / BN));
+#define L(NT) KGE_LAUNCH(c, k_transr_mgrad<NT>, grid, dim3(RT), 0, st, a)
+    KGE_BY_COLUMNS(a.D, L);
+#undef L
 }
 
 void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st) {
@@ -427,9 +951,31 @@ void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, floa
     const int D = c->cfg.ent_dim;
     int rows = 1024 / D;  // matrix rows per workgroup: the largest divisor of D that keeps a slab within 1024 floats
     while (D % rows != 0) --rows;
-    a.T = R; a.St = SR; a.key = c->rkey[c->rbuf]; a.pos = c->rpos[c->rbuf];
-    a.n = ids.b; a.D = D; a.rows_per_slab = rows; a.rel_dim = c->cfg.rel_dim;
+    a.T = R; a.St = SR; a.key = c->rkey[c->rbuf]; a.pos = c->rpos[c->rbuf]; a.slot_of = c->tr_groups.slot_of;
+    a.n = ids.b; a.D = D; a.rows_per_slab = rows; a.slabs = D / rows + 1; a.rel_dim = c->cfg.rel_dim;
     a.Gr = c->Grel; a.GM = c->Grel + (int64_t)c->cfg.max_batch * D;
     a.lr = lr; a.eps = c->eps;
-    KGE_LAUNCH(c, k_transr_update, dim3(ids.b, D / rows + 1), dim3(RT), 0, st, a);
+    a.rest = c->neg_partial;
+    const int rest_blocks = partial_rows_blocks(a.rest, a.share);
+    KGE_LAUNCH(c, k_transr_update, dim3(ids.b * a.slabs + rest_blocks), dim3(RT), 0, st, a);
+}
+
+// bytes of the workspace that the items of a mini-batch take (base null: only counted)
+size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* q) {
+    const size_t B = cfg.max_batch, C = cfg.max_chunks, PBS = B + B / PB + C;
+    size_t off = 0;
+    auto take = [&](size_t bytes) { char* p = base + off; off += (bytes + 255) / 256 * 256; return p; };
+    q->items = (TransrItem*)take(B * sizeof(TransrItem)); q->pblocks = (TransrBlock*)take(PBS * sizeof(TransrBlock));
+    q->first = (int*)take(B * 4); q->rank = (int*)take(B * 4); q->count = (int*)take(B * 4); q->slot_of = (int*)take(B * 4);
+    q->members = (int*)take(B * 4); q->ent = (uint32_t*)take(2 * B * 4);
+    q->n_items = (int*)take(C * 4); q->n_pblocks = (int*)take(C * 4);
+    return off;
+}
+// floats of partial rows: of the back-projection (its workgroups write a tile each), of dL/do
+size_t kge_transr_back_floats(const kge_config& cfg) {
+    const size_t D = cfg.ent_dim, NR = (size_t)cfg.max_chunks * (cfg.max_neg_per_chunk > 0 ? cfg.max_neg_per_chunk : 1);
+    return (NR + (size_t)cfg.max_chunks * BM + (size_t)KGE_TRANSR_BACK_WGS * BM) * D;
+}
+size_t kge_transr_go_floats(const kge_config& cfg) {
+    return (size_t)cfg.max_batch * cfg.ent_dim * ((size_t)cfg.max_neg_per_chunk / BM + 1);
 }

@@ -101,12 +101,11 @@ void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids,
         return;
     }
     if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_phi(c, ent, rel, ids, st);
-    if (c->cfg.model == KGE_TRANSR) kge_transr_phi(c, ent, rel, ids, gamma, pos_out, st);
-    kge_launch_gather(c, ent, rel, ids, gamma, pos_out, false, st);
+    kge_launch_gather(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
+    if (c->cfg.model == KGE_TRANSR) kge_transr_phi(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
     if (neg_out && k > 0) {
         if (c->cfg.model == KGE_TRANSR) {
-            kge_gemm_transr_project(c, rel, ids, k, chunk, kge_transr_projections(c), st);
-            kge_transr_score(c, ids, k, gamma, neg_out, ld_out, st);
+            kge_transr_project(c, rel, ids, k, chunk, gamma, neg_out, ld_out, false, false, st);
         } else if (is_gemm_model(c->cfg.model)) {
             kge_gemm_neg_score(c, ids.b, k, chunk, gamma, neg_out, ld_out, dist_mode, st);
         } else {
@@ -126,31 +125,33 @@ struct ProfScope {
     ~ProfScope() { c->launch_ev0 = nullptr; c->launch_ev1 = nullptr; }
 };
 
-// TransR after its phi and gather launches: the three batched products with the elementwise steps between them.
-// Profile slots: neg_score = the projection product, loss, neg_backward = the back-projection product, chain,
-// rel_update, update; the small kernels between them are not timed separately.
+// TransR after its gather launch.  Profile slots: phi, neg_score = projections and scores, loss, chain = dL/dP,
+// neg_backward = the back-projection, rel_update, update; dL/dM is not timed.
 int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids,
                         int K, int G, float gamma, float lr, bool long_lists, hipStream_t st) {
-    float* P = kge_transr_projections(c);
+    const bool form_w = kge_gemm_backward_forms_w(c);
+    int n_loss_parts;
+    {
+        ProfScope p(c, KGE_PROF_PHI);
+        kge_transr_phi(c, ent, rel, ids, G, gamma, nullptr, true, st);
+    }
     {
         ProfScope p(c, KGE_PROF_SCORE);
-        kge_gemm_transr_project(c, rel, ids, K, G, P, st);
+        n_loss_parts = kge_transr_project(c, rel, ids, K, G, gamma, c->S, c->ld_s, true, form_w, st);
     }
-    kge_transr_score(c, ids, K, gamma, c->S, c->ld_s, st);
-    {
+    if (!form_w) {
         ProfScope p(c, KGE_PROF_LOSS);
         kge_launch_loss(c, ids.b, K, gamma, st);
     }
-    kge_transr_dp(c, ids, K, st);
-    {
-        ProfScope p(c, KGE_PROF_BACKWARD);
-        kge_gemm_transr_back_project_sum(c, rel, ids, K, G, P, c->Gent + (int64_t)2 * ids.b * c->cfg.ent_dim, st);
-    }
-    kge_gemm_transr_matrix_grad(c, ids, K, G, P, kge_transr_matrix_grads(c), st);
     {
         ProfScope p(c, KGE_PROF_CHAIN);
-        kge_transr_chain(c, ent, rel, ids, st);
+        kge_transr_dp(c, ids, K, G, st);
     }
+    {
+        ProfScope p(c, KGE_PROF_BACKWARD);
+        kge_transr_back(c, rel, ids, K, G, st);
+    }
+    kge_transr_mgrad(c, ent, ids, K, G, st);
     if (long_lists) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     {
         ProfScope p(c, KGE_PROF_REL_UPDATE);
@@ -158,14 +159,14 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
     }
     {
         ProfScope p(c, KGE_PROF_UPDATE);
-        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, 0, true, st);
+        kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, n_loss_parts, true, st);
     }
     KGE_HIP(c, hipGetLastError());
     if (c->prof_on) {
         KGE_HIP(c, hipStreamSynchronize(st));
         for (int s = 0; s < KGE_PROF_SLOTS; ++s) {
             float ms = 0.f;
-            if (s == KGE_PROF_SORT && !long_lists) continue;
+            if ((s == KGE_PROF_SORT && !long_lists) || (s == KGE_PROF_LOSS && form_w)) continue;
             if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
         }
         c->prof_steps += 1;
@@ -228,13 +229,9 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         ProfScope p(c, KGE_PROF_PHI);
         kge_launch_rescal_phi(c, ent, rel, ids, st);
     }
-    if (c->cfg.model == KGE_TRANSR) {
-        ProfScope p(c, KGE_PROF_PHI);
-        kge_transr_phi(c, ent, rel, ids, gamma, nullptr, st);
-    }
     {
         ProfScope p(c, KGE_PROF_GATHER);
-        kge_launch_gather(c, ent, rel, ids, gamma, nullptr, !long_lists, st);
+        kge_launch_gather(c, ent, rel, ids, G, gamma, nullptr, !long_lists, st);
     }
     if (c->cfg.model == KGE_TRANSR) return enqueue_transr_rest(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, long_lists, st);
     {
@@ -402,7 +399,10 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const size_t o_rl = take(B * 4), o_idp = take(B * 4);
     const size_t nlp_gemm = (B / 32 + cfg->max_chunks + 1) * ((size_t)cfg->max_neg_per_chunk / 32 + 1);
     const size_t nlp_pair = (B / 8 + cfg->max_chunks + 1) * KGE_PAIR_MAX_PARTS;
-    const size_t o_nlp = take((nlp_gemm > nlp_pair ? nlp_gemm : nlp_pair) * 4);
+    const size_t nlp_transr = m == KGE_TRANSR ? (B + B / 32 + 16) * ((size_t)cfg->max_neg_per_chunk / 64 + 1) : 0;
+    size_t nlp = nlp_gemm > nlp_pair ? nlp_gemm : nlp_pair;
+    nlp = nlp > nlp_transr ? nlp : nlp_transr;
+    const size_t o_nlp = take(nlp * 4);
     const size_t o_ek0 = take(EK * 4), o_ek1 = take(EK * 4), o_ep0 = take(EK * 4), o_ep1 = take(EK * 4);
     const size_t o_rk0 = take(B * 4), o_rk1 = take(B * 4), o_rp0 = take(B * 4), o_rp1 = take(B * 4);
     const size_t o_flags = take(256), o_step = take(256), o_sides = take(sizeof(int32_t) * KGE_SIDES_CAP);
@@ -410,8 +410,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const bool bf = cfg->gemm_input == 1;
     const size_t o_Obf = take(bf ? B * c->ld_bf * 2 + 64 : 0), o_Nbf = take(bf ? NR * c->ld_bf * 2 + 64 : 0);
     const bool transr = m == KGE_TRANSR;
-    const size_t proj = transr ? B * (size_t)(cfg->max_neg_per_chunk > 0 ? cfg->max_neg_per_chunk : 1) * D * 4 : 0;
-    const size_t o_PP = take(transr ? B * D * 4 : 0), o_P3 = take(proj);
+    const size_t o_PP = take(transr ? B * D * 4 : 0), o_trg = take(transr ? kge_transr_carve_groups(*cfg, nullptr, &c->tr_groups) : 0);
     auto sort_digits = [](size_t keys) {  // counts of all slices: 8-bit digits, or 10-bit ones of few slices
         const size_t slices = (keys + KGE_SORT_SLICE - 1) / KGE_SORT_SLICE, few = (size_t)KGE_SORT_FEW_SLICES << KGE_SORT_MAX_BITS;
         return slices * 256 > few ? slices * 256 : few;
@@ -419,13 +418,16 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const size_t o_sc = take((sort_digits(EK) + sort_digits(B) + ((size_t)2 << KGE_SORT_MAX_BITS)) * 4);
     const bool pair_model = m == KGE_ROTATE || m == KGE_TRANSE_L1;
     const size_t o_rpw = take((EK / 4 + 4) * 4);
-    // partial rows, written before they are read (the fill below leaves them out).  A set of rows of the corrupting
+    // everything from here on is written before it is read (the fill below leaves it out).  Partial rows:  A set of rows of the corrupting
     // entities per 8 positives and per chunk at most; more than 256 MB only where 8 sets are already more
     const size_t zeroed = off;
     const size_t K1 = cfg->max_neg_per_chunk > 0 ? cfg->max_neg_per_chunk : 1;
     size_t sets_n = (B / 8 + cfg->max_chunks) * K1 * D;
     if (sets_n > (size_t)64 << 20) sets_n = 8 * NR * D > (size_t)64 << 20 ? 8 * NR * D : (size_t)64 << 20;
     const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? sets_n * 4 : 0);
+    const size_t o_P3 = take(transr ? 2 * B * K1 * D * 4 : 0);
+    const size_t o_tgo = take(transr ? kge_transr_go_floats(*cfg) * 4 : 0);
+    const size_t o_tbp = take(transr ? kge_transr_back_floats(*cfg) * 4 : 0);
     c->ws_bytes = (int64_t)off;
 
     hipError_t e = hipMalloc(&c->ws_base, off);
@@ -448,6 +450,9 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     c->Nbf = bf ? (uint16_t*)(base + o_Nbf) : nullptr;
     c->PP = transr ? (float*)(base + o_PP) : nullptr;
     c->P3 = transr ? (float*)(base + o_P3) : nullptr;
+    if (transr) kge_transr_carve_groups(*cfg, base + o_trg, &c->tr_groups);
+    c->tr_go_part = transr ? (float*)(base + o_tgo) : nullptr;
+    c->tr_back_part = transr ? (float*)(base + o_tbp) : nullptr;
     c->pair_part_o = pair_model ? (float*)(base + o_ppo) : nullptr;
     c->pair_part_n = pair_model ? (float*)(base + o_ppn) : nullptr;
     c->pair_part_n_floats = pair_model ? (int64_t)sets_n : 0;

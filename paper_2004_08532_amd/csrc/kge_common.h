@@ -27,6 +27,32 @@ struct PartialRows {
 // How the backward launch of RotatE / TransE-L1 is cut for batches of one shape (k_pair.hip).
 struct PairBwdPlan { int b, k, g, ti, n_i, i_parts, pj, tj, n_col, cpp, ng; };
 
+// TransR: the items of a mini-batch, i.e. the (chunk, relation) pairs that occur in it (k_transr.hip).  Item slots of chunk
+// c start at c * g; the positives of an item ("members") are numbered consecutively, item after item, chunk after chunk.
+struct alignas(16) TransrItem {
+    uint32_t rel;
+    int off, n;  // members off .. off + n - 1
+};
+struct alignas(32) TransrBlock {  // up to 32 members of one item
+    int slot;
+    uint32_t rel;
+    int off, n;  // members off .. off + n - 1
+    int first;   // number of the item's members before this block
+    int all;     // members of the item
+};
+struct TransrGroups {
+    TransrItem* items;     // [b] by slot
+    TransrBlock* pblocks;  // per chunk
+    int* members;          // [b] by member: position in the mini-batch
+    uint32_t* ent;         // [2 b] by member: rows of the kept and the replaced entity
+    int* count;            // [b] by member: members of its item
+    int* slot_of;          // [b] by position: the item slot if it is the first of its item, else -1
+    int* first;            // [b] by position, long chunks only: first position of the item in the chunk; its rank among those
+    int* rank;
+    int* n_items;          // [C]
+    int* n_pblocks;        // [C]
+};
+
 struct StepBlock;
 
 struct kge_ctx {
@@ -47,7 +73,10 @@ struct kge_ctx {
     int ld_bf;       // D rounded up to 64 (rows of whole 128-byte lines)
     float* S;        // [max_batch x ld_s]   negative scores, then backward coefficients W
     float* PP;       // TransR: [max_batch x D] p_i = M_i c_i
-    float* P3;       // TransR: [max_batch x max_neg_per_chunk x D] projections of the corrupting rows, then dL/dP
+    float* P3;       // TransR: [max_batch x max_neg_per_chunk x D] projections of the corrupting rows; the same of dL/dP
+    TransrGroups tr_groups;
+    float* tr_go_part;    // TransR: partial sums of dL/do
+    float* tr_back_part;  //         partial gradient rows of the corrupting entities
     float* GO;       // [max_batch x D]      dL/do_i
     float* pair_part_o;  // RotatE / TransE-L1: [KGE_PAIR_MAX_PARTS][max_batch x D] partial dL/do rows
     PartialRows go_partial, neg_partial;  // what the last backward launch left for the chain launch to add up
@@ -147,6 +176,15 @@ struct KeyList {
     uint32_t* key[2];        // sorted ids (ping-pong halves; the rank path writes half 0)
     uint32_t* pos[2];        // position in the key list of each sorted entry
 };
+// Workgroups of 256 threads for sum_partial_rows and the threads that share a piece: 16 bytes of 8 partial rows or more per
+// thread; a thread per piece where that already makes 2048 workgroups, which then take up to four rounds each.
+inline int partial_rows_blocks(const PartialRows& r, int& share) {
+    share = 1;
+    if (r.parts <= 1) return 0;
+    while (share < 16 && r.parts > 8 * share && r.n4 * share < 2048 * 256) share *= 2;
+    const int64_t blocks = (r.n4 * share + 255) / 256;
+    return (int)(blocks <= 2048 ? blocks : (blocks + 3) / 4 > 2048 ? (blocks + 3) / 4 : 2048);
+}
 void kge_make_key_lists(kge_ctx* c, const StepIds& ids, KeyList* ent, KeyList* rel);
 
 // ---------------------------------------------------------------------------------------------------------
@@ -155,7 +193,8 @@ void kge_make_key_lists(kge_ctx* c, const StepIds& ids, KeyList* ent, KeyList* r
 // a1/a2: gather rows, o_i, positive scores, norms
 // with_keys: the same launch also brings the key lists into (id, position) order (lists of up to
 // KGE_RANK_MAX_KEYS keys; longer lists go through kge_launch_sort)
-void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds& ids, float gamma, float* pos_out,
+// (TransR: and the items of the chunks of g positives)
+void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int g, float gamma, float* pos_out,
                        bool with_keys, hipStream_t st);
 void kge_launch_key_order(kge_ctx* c, const StepIds& ids, hipStream_t st);  // the key lists alone
 // chunks of one positive: everything between the ids and the gradient rows of the positives in one launch, and the
@@ -194,20 +233,20 @@ void kge_launch_rescal_phi(kge_ctx* c, const float* E, const float* R, const Ste
 void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
 // RESCAL, a7 for the relation matrices: gradient of a distinct relation formed from the factor rows, then Adagrad
 void kge_launch_rescal_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
-// TransR: the steps around its batched products (k_transr.hip) and the products (k_gemm.hip)
-void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, float gamma, float* pos_out,
-                    hipStream_t st);
-void kge_transr_score(kge_ctx* c, const StepIds& ids, int k, float gamma, float* out, int ld_out, hipStream_t st);
-void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, hipStream_t st);
-void kge_transr_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
+// TransR (k_transr.hip)
+constexpr int KGE_TRANSR_BACK_WGS = 768;
+size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* q);
+size_t kge_transr_back_floats(const kge_config& cfg);
+size_t kge_transr_go_floats(const kge_config& cfg);
+void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int g, float gamma, float* pos_out,
+                    bool train, hipStream_t st);
+// train: keep the projections, rows in the order of the members; form_w: store W = dL/df- instead of the scores, returns the number of loss sums left
+int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, float gamma, float* out, int ld_out,
+                       bool train, bool form_w, hipStream_t st);
+void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int g, hipStream_t st);
+void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, hipStream_t st);
+void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int g, hipStream_t st);
 void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
-float* kge_transr_projections(kge_ctx* c);
-float* kge_transr_matrix_grads(kge_ctx* c);
-void kge_gemm_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, float* P, hipStream_t st);
-void kge_gemm_transr_back_project_sum(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, const float* U,
-                                      float* out, hipStream_t st);
-void kge_gemm_transr_matrix_grad(kge_ctx* c, const StepIds& ids, int k, int g, const float* U, float* GM,
-                                 hipStream_t st);
 // a6: sort (id, position) of the entity and relation key lists
 void kge_launch_sort(kge_ctx* c, const StepIds& ids, hipStream_t st);
 // a7: per distinct row, sum its gradient rows and apply Adagrad; also reduces the loss terms
@@ -301,6 +340,52 @@ __device__ __forceinline__ float wave_max(float v) {
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 __device__ __forceinline__ float4 f4(float x) { return make_float4(x, x, x, x); }
+
+// sum of `parts` 16-byte pieces `stride` floats apart, in order; eight of them are asked for before the first is added (a
+// part that does not exist is read from part 0 and left out of the sum)
+__device__ __forceinline__ float4 sum_parts(const float* p, int parts, int64_t stride) {
+    if (parts <= 1) return ld4(p);  // (the same for every thread)
+    float4 s = f4(0.f);
+    for (int q0 = 0; q0 < parts; q0 += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = ld4(p + (q0 + q < parts ? q0 + q : 0) * stride);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (q0 + q < parts) { s.x += v[q].x; s.y += v[q].y; s.z += v[q].z; s.w += v[q].w; }
+        }
+    }
+    return s;
+}
+
+// Partial gradient rows -> their sums, by workgroup `block` of `blocks`: `share` threads per 16 bytes, each a contiguous
+// range of the partial rows; their sums meet in LDS in order.
+template <int THREADS>
+__device__ __forceinline__ void sum_partial_rows(const PartialRows& r, int share, int block, int blocks) {
+    __shared__ __attribute__((aligned(16))) float4 sums[THREADS];
+    const int cols = THREADS / share, per = (r.parts + share - 1) / share;
+    const int grp = threadIdx.x / cols, ln = threadIdx.x % cols;
+    const int q0 = grp * per, n = min(per, r.parts - q0);
+    for (int64_t e0 = (int64_t)block * cols; e0 < r.n4; e0 += (int64_t)blocks * cols) {
+        const int64_t e = e0 + ln;
+        float4 s = f4(0.f);
+        if (e < r.n4 && n > 0) s = sum_parts(r.src + q0 * r.stride + 4 * e, n, r.stride);
+        if (share == 1) {
+            if (e < r.n4) st4(r.out + 4 * e, s);
+            continue;
+        }
+        __syncthreads();
+        sums[threadIdx.x] = s;
+        __syncthreads();
+        if (grp == 0 && e < r.n4) {
+            for (int g2 = 1; g2 < share; ++g2) {
+                const float4 v = sums[g2 * cols + ln];
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            }
+            st4(r.out + 4 * e, s);
+        }
+    }
+}
 
 // Adagrad: S += g^2 ; x -= lr * g / (sqrt(S) + eps), with the hardware square root and reciprocal (1 ulp each): the
 // update is a step of size <= lr, so their 1e-7 relative error is far below the accuracy of g itself.

@@ -262,6 +262,30 @@ def test_cuts_of_the_elementwise_backward(kge, model, shape):
         p.close()
 
 
+TRANSR_ITEMS = {
+    # rows longer than a tile's columns; items of more positives than a block and than the two forms of dL/dP change over at;
+    # relation tables that do not fit the LDS counters; chunks longer than what an item workgroup keeps in LDS
+    "long-rows": dict(batch=36, chunk=18, neg_per_chunk=70, ent_dim=136),
+    "large-items": dict(batch=180, chunk=90, neg_per_chunk=65, ent_dim=128, n_relations=2),
+    "many-relations": dict(batch=64, chunk=32, neg_per_chunk=17, ent_dim=8, n_relations=5000, n_entities=301),
+    "long-chunk": dict(batch=2100, chunk=2100, neg_per_chunk=5, ent_dim=4, n_relations=7, n_triples=9000),
+    "long-chunk-many-relations": dict(batch=2100, chunk=2100, neg_per_chunk=5, ent_dim=8, n_relations=4200, n_triples=9000,
+                                      adv_temperature=1.0),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(TRANSR_ITEMS))
+def test_transr_items(kge, shape):
+    kw = dict(dict(steps=2), **TRANSR_ITEMS[shape])
+    kw["rel_dim"] = kw["ent_dim"] + kw["ent_dim"] ** 2
+    w = ragged("transr", **kw)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps, check_dedup_at=(0,))
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("b,g,k", [(1, 1, 1), (3, 1, 2), (2, 2, 1)])
 @pytest.mark.parametrize("model", MODELS)
 def test_smallest_batches(kge, model, b, g, k):
