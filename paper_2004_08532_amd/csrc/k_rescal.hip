@@ -154,58 +154,128 @@ struct RescalUpdArgs {
     const uint32_t* key;  // sorted relation ids of the step
     const uint32_t* pos;  // position in the mini-batch of each sorted entry
     int n, D, rows_per_slab;
+    int long_y;           // grid rows for the runs of LONG_RUN positives and more
     const float* GU;
     const float* GW;
     float lr, eps;
 };
 
-// Workgroup (p, slab): if sorted position p is the last of its run of equal relation ids, it owns that relation in
-// this step and updates `rows_per_slab` consecutive rows of its matrix (at most 1024 floats, a thread per 16 bytes):
-// the matrix and state slices are asked for first; the run's start is found by a parallel look-back over the keys;
-// then the outer products of the run's positives are summed in sorted order and Adagrad is applied.
-__global__ __launch_bounds__(RT) void k_rescal_update(RescalUpdArgs a) {
-    const int p = blockIdx.x, slab = blockIdx.y, tid = threadIdx.x;
-    const uint32_t key = a.key[p];
-    if (p + 1 < a.n && a.key[p + 1] == key) return;  // the run goes on (same decision in every thread)
-    __shared__ int first_other;  // distance from p back to the nearest entry with another key
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+constexpr int LONG_RUN = 16;  // runs of at least this many positives are summed on the matrix cores
+constexpr int LT = 32;        // ... in tiles of LT x LT elements of the matrix
+
+// Runs of LONG_RUN positives and more.  dL/dM = U^T W over the run is a matrix product whose inner length is the run:
+// a workgroup owns one 32 x 32 tile of the matrix, its four waves take blocks of 16 positives in turn (16 loads in
+// flight per lane, straight into fragments: a half-wave's load is 128 consecutive bytes of one factor row), their
+// sums meet in LDS in wave order, and Adagrad is applied to the tile.  What this avoids is the serial chain of the
+// slabs below, one round of loads per 4 positives (a relation with a quarter of the batch: 64 rounds and more).  From 16
+// on because that is the block of positives one wave takes; a shorter run would leave matrix instructions empty and is
+// at most four rounds of the slabs.  FB15k-sized, b = 1024, D = 200: 141 -> 132 us per training step; what is left is
+// bound by the matrices and their state (192 MB per step).
+// Workgroup q looks at sorted position q * LONG_RUN; every long run holds such a position, and the first one in it
+// owns the run.
+__device__ __forceinline__ void rescal_long_run(const RescalUpdArgs& a, int q, int tile, int tiles, float* red,
+                                                uint32_t* lpos, int* first_other) {
+    const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, D = a.D;
+    const int m0 = q * LONG_RUN;
+    const uint32_t key = a.key[m0];
+    if (q > 0 && a.key[m0 - LONG_RUN] == key) return;  // an earlier workgroup's run
+    // start: less than LONG_RUN entries back (the entry LONG_RUN back differs or is not there)
+    const int back = m0 - 1 - lane;
+    const bool other = back < 0 || lane >= LONG_RUN - 1 || a.key[back < 0 ? 0 : back] != key;
+    const int start = m0 - __builtin_ctzll(__ballot(other));
+    if (start + LONG_RUN > a.n || a.key[start + LONG_RUN - 1] != key) return;  // a short run: the slabs' work
+    const int r0 = (tile / tiles) * LT, c0 = (tile % tiles) * LT;
+    const int er = r0 + (tid >> 3), ec = c0 + 4 * (tid & 7);  // the elements that this thread updates
+    const bool act = er < D && ec < D;
+    const int64_t off = (int64_t)key * D * D + (act ? (int64_t)er * D + ec : 0);
+    const float4 xin = ld4(a.T + off), sin = ld4(a.St + off);
+    const int l = lane & 31, half = lane >> 5;
+    const float* gu = a.GU + (r0 + l < D ? r0 + l : D - 1);
+    const float* gw = a.GW + (c0 + l < D ? c0 + l : D - 1);
+    floatx16 acc = {};
+    for (int b0 = start;; b0 += RT) {
+        if (tid == 0) *first_other = RT;
+        __syncthreads();  // ... and lpos is free again
+        const int e = b0 + tid;
+        const bool in = e < a.n && a.key[e < a.n ? e : a.n - 1] == key;  // sorted: the run is a prefix of these
+        lpos[tid] = in ? a.pos[e] : 0;
+        const unsigned long long bal = __ballot(!in);
+        if (lane == 0 && bal) atomicMin(first_other, tid + __builtin_ctzll(bal));
+        __syncthreads();
+        const int m = *first_other;  // positives of the run among these RT
+        for (int kb = 16 * w; kb < m; kb += 64) {
+            float u[8], v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int64_t row = (int64_t)lpos[kb + 2 * j + half] * D;  // past the end: position 0, dropped below
+                u[j] = gu[row];
+                v[j] = gw[row];
+            }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const bool live = kb + 2 * j + half < m;
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(live ? u[j] : 0.f, live ? v[j] : 0.f, acc, 0, 0, 0);
+            }
+        }
+        __syncthreads();  // everyone has read m
+        if (m < RT) break;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) red[w * LT * LT + (8 * (i >> 2) + 4 * half + (i & 3)) * LT + l] = acc[i];
+    __syncthreads();
+    if (!act) return;
+    float4 g = ld4(red + 4 * tid);
+#pragma unroll
+    for (int k = 1; k < RT / 64; ++k) {
+        const float4 t = ld4(red + k * LT * LT + 4 * tid);
+        g.x += t.x; g.y += t.y; g.z += t.z; g.w += t.w;
+    }
+    float4 x = xin, s = sin;
+    adagrad4(g, x, s, a.lr, a.eps);
+    st4(a.St + off, s);
+    st4(a.T + off, x);
+}
+
+// Grid: b x (long_y + slabs).  The first long_y rows are (q, tile) of the long runs, which take the longest.  The others
+// are (p, slab): if sorted position p is the last of its run of equal relation ids, and the run is shorter than LONG_RUN,
+// it owns that relation in this step and updates `rows_per_slab` consecutive rows of its matrix (at most 1024 floats, a
+// thread per 16 bytes): the matrix and state slices are asked for first; then the outer products of the run's positives
+// are summed in sorted order and Adagrad is applied.  Held to 64 registers: both parts run at full occupancy.
+__global__ __launch_bounds__(RT, 8) void k_rescal_update(RescalUpdArgs a) {
+    __shared__ __attribute__((aligned(16))) float red[(RT / 64) * LT * LT];
     __shared__ uint32_t lpos[RT];
-    const int D = a.D, width = a.rows_per_slab * D, lanes = width / 4;
+    __shared__ int first_other;
+    const int tid = threadIdx.x, D = a.D;
+    if ((int)blockIdx.y < a.long_y) {
+        const int tiles = (D + LT - 1) / LT, wg = blockIdx.y * a.n + blockIdx.x, q = wg / (tiles * tiles);
+        if (q * LONG_RUN < a.n) rescal_long_run(a, q, wg - q * tiles * tiles, tiles, red, lpos, &first_other);
+        return;
+    }
+    const int p = blockIdx.x, slab = blockIdx.y - a.long_y;
+    const uint32_t key = a.key[p];
+    if (p + 1 < a.n && a.key[p + 1] == key) return;                    // the run goes on (same decision in every thread)
+    if (p + 1 >= LONG_RUN && a.key[p + 1 - LONG_RUN] == key) return;  // a long run
+    const int width = a.rows_per_slab * D, lanes = width / 4;
     const bool act = tid < lanes;
     const int e = act ? 4 * tid : 0, lrow = e / D, col = e - lrow * D;
     const int mrow = slab * a.rows_per_slab + lrow;
     const int64_t off = (int64_t)key * D * D + (int64_t)slab * width + e;
     float4 x = f4(0.f), s = f4(0.f);
     if (act) { x = ld4(a.T + off); s = ld4(a.St + off); }
-    if (tid == 0) first_other = 1 << 30;
-    __syncthreads();
-    for (int base = 1;; base += RT) {
-        const int q = p - (base + tid);
-        const bool differs = q < 0 || a.key[q < 0 ? 0 : q] != key;
-        const unsigned long long bal = __ballot(differs);
-        if ((tid & 63) == 0 && bal) atomicMin(&first_other, base + tid + __builtin_ctzll(bal));
-        __syncthreads();
-        const bool found = first_other < (1 << 30);
-        __syncthreads();  // everyone has read it before the next round may lower it
-        if (found) break;
-    }
-    const int start = p - first_other + 1;
+    // lane t of every wave looks at the t-th entry of the run from its end
+    const int lane = tid & 63, q = p - lane;
+    const bool other = q < 0 || lane >= LONG_RUN || a.key[q < 0 ? 0 : q] != key;
+    const int m = __builtin_ctzll(__ballot(other));
+    const uint32_t mine = a.pos[q < 0 ? 0 : q];
     float4 g = f4(0.f);
-    for (int c0 = start; c0 <= p; c0 += RT) {
-        __syncthreads();  // lpos is free again
-        lpos[tid] = a.pos[c0 + tid <= p ? c0 + tid : p];
-        __syncthreads();
-        const int m = p - c0 + 1 < RT ? p - c0 + 1 : RT;
-        if (act) {
-            // (16 positives in flight per thread instead of 4 was measured slower: the registers cost more in
-            // resident workgroups than the deeper queue gains on the few long runs)
 #pragma unroll 4
-            for (int j = 0; j < m; ++j) {
-                const int64_t row = (int64_t)lpos[j] * D;
-                const float u = a.GU[row + mrow];
-                const float4 w = ld4(a.GW + row + col);
-                g.x += u * w.x; g.y += u * w.y; g.z += u * w.z; g.w += u * w.w;
-            }
-        }
+    for (int j = m - 1; j >= 0; --j) {
+        const int64_t row = (int64_t)__builtin_amdgcn_readlane(mine, j) * D;
+        const float u = a.GU[row + mrow];
+        const float4 w = ld4(a.GW + row + col);
+        g.x += u * w.x; g.y += u * w.y; g.z += u * w.z; g.w += u * w.w;
     }
     if (act) {
         adagrad4(g, x, s, a.lr, a.eps);
@@ -244,5 +314,7 @@ void kge_launch_rescal_update(kge_ctx* c, float* R, float* SR, const StepIds& id
     a.n = ids.b; a.D = D; a.rows_per_slab = rows;
     a.GU = c->Grel; a.GW = c->Grel + (int64_t)ids.b * D;
     a.lr = lr; a.eps = c->eps;
-    KGE_LAUNCH(c, k_rescal_update, dim3(ids.b, D / rows), dim3(RT), 0, st, a);
+    const int tiles = (D + LT - 1) / LT;
+    a.long_y = ids.b < LONG_RUN ? 0 : (int)(((int64_t)((ids.b + LONG_RUN - 1) / LONG_RUN) * tiles * tiles + ids.b - 1) / ids.b);
+    KGE_LAUNCH(c, k_rescal_update, dim3(ids.b, a.long_y + D / rows), dim3(RT), 0, st, a);
 }

@@ -149,6 +149,37 @@ def test_matrix_relations_that_fill_half_of_the_batch(kge, model):
         p.close()
 
 
+RESCAL_RUNS = {
+    # positives per relation, around the length (16) from which a run is a matrix product and around one staging round
+    # (256) and a multiple of it; row lengths below, at and past a tile of 32, and several slabs per matrix
+    "around-16": dict(runs=[15, 16, 17, 1, 31, 32, 33, 14, 16, 15], ent_dim=36),
+    "no-long-run": dict(runs=[15, 15, 1, 15], ent_dim=64),
+    "fewer-than-16": dict(runs=[9, 6], ent_dim=4),
+    "one-run": dict(runs=[16], ent_dim=32),
+    "around-256": dict(runs=[255, 1, 256, 257, 511, 2, 512, 64, 65], ent_dim=100),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(RESCAL_RUNS))
+def test_rescal_matrix_update_of_runs(kge, shape):
+    """The matrix update of RESCAL takes long runs of equal relation ids as products on tiles and short ones in slabs."""
+    runs, D = RESCAL_RUNS[shape]["runs"], RESCAL_RUNS[shape]["ent_dim"]
+    w = ragged("rescal", ent_dim=D, rel_dim=D * D, batch=sum(runs), chunk=sum(runs), neg_per_chunk=17, n_relations=len(runs) + 3,
+               steps=2)
+
+    class Runs(configs.BatchStream):
+        def step(self, s):
+            h, r, t, neg, side = super().step(s)
+            r = np.random.default_rng(s).permutation(np.repeat(np.arange(len(runs)) + s, runs)).astype(r.dtype)
+            return h, r, t, neg, side
+
+    p = Pair(w, kge)
+    try:
+        run_steps(p, Runs(w), w.steps, check_dedup_at=(0, 1))
+    finally:
+        p.close()
+
+
 def test_training_shapes_with_thousands_of_tiles(kge):
     """A score matrix of 1035 x 1219 per step (three chunks): thousands of 32 x 32 tiles, four waves per tile, ragged
     edges in every dimension."""
