@@ -154,12 +154,21 @@ struct PairBwdArgs {
     float* loss_part;          // a sum per workgroup of the first range of coordinates
 };
 
-// What a wave needs to know of all scores of a positive: the maximum mx and the factor sc = 1 / (b z) of the softmax weights
-// exp(alpha f - mx) / z (uniform weights: sc = 1 / (b k)), and, for the ranking loss, dL/df+ (only where `pos` is set).
-__device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float* s, int k, float gamma, bool pos, int64_t row, float& mx, float& sc) {
+// exp of the softmax weights (argument <= 0): the operations that k_loss uses, so that W has the same bits whichever kernel
+// forms it.  Rows of up to 1024 scores take the hardware exp2, longer ones the library's exp.  (Library functions for all
+// rows, with 1 / (b z) as one factor, left the free-running trajectories of the medium RotatE configuration no closer to
+// the 64-bit ones: share of relation elements off by 1e-4 after ten steps 1.4e-4 and 2.9e-4 with two seeds, 0.7e-4 and
+// 2.3e-4 like this.)
+__device__ __forceinline__ float softmax_exp(float x, int k) {
+    return k <= 1024 ? __builtin_amdgcn_exp2f(x * 1.4426950408889634f) : expf(x);
+}
+
+// What a wave needs to know of all scores of a positive: the maximum mx and the sum z of the softmax weights
+// exp(alpha f - mx) / z (uniform weights: z = k), and, for the ranking loss, dL/df+ (only where `pos` is set).
+__device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float* s, int k, float gamma, bool pos, int64_t row, float& mx, float& z) {
     const int lane = threadIdx.x & 63;
     mx = 0.f;
-    sc = t.invb / (float)k;
+    z = (float)k;
     if (!(t.alpha > 0.f) && !(t.ranking && pos)) return;  // (the same for every thread)
     if (t.alpha > 0.f) {
         mx = -INFINITY;
@@ -172,7 +181,8 @@ __device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float
         mx = wave_max(mx);
     }
     const float fp = t.fpos[row];
-    float z = 0.f, on = 0.f;
+    z = 0.f;
+    float on = 0.f;
     for (int j0 = 0; j0 < k; j0 += 256) {
         float v[4];
 #pragma unroll
@@ -180,17 +190,17 @@ __device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (j0 + 64 * u + lane < k) {
-                const float e = t.alpha > 0.f ? expf(t.alpha * v[u] - mx) : 1.f;
+                const float e = t.alpha > 0.f ? softmax_exp(t.alpha * v[u] - mx, k) : 1.f;
                 z += e;
                 on += gamma - fp + v[u] > 0.f ? e : 0.f;
             }
         }
     }
-    sc = t.invb / wave_sum(z);
+    z = wave_sum(z);
     if (t.ranking && pos) {
         on = wave_sum(on);
         if (lane == 0) {
-            t.cpos[row] = -on * sc;
+            t.cpos[row] = -(on / z) * t.invb;
             t.row_loss[row] = 0.f;  // (the gather launch left the logistic loss of the positive there)
         }
     }
@@ -212,7 +222,7 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
     // to [-w, w] is w sign(difference), 0 for 0: one v_med3 where two compares and two selects stood
     constexpr float SCALE = CPLX ? 1.f : 18446744073709551616.f;
     extern __shared__ __attribute__((aligned(16))) float lds[];  // W^T of the block [negative][WPITCH]; later group sums
-    __shared__ float row_mx[TI], row_sc[TI], row_li[16];
+    __shared__ float row_mx[TI], row_z[TI], row_li[16];
     const int tid = threadIdx.x, cpp = t.cpp, wave = tid >> 6, lane = tid & 63, n_waves = blockDim.x >> 6;
     const int grp = tid / cpp, lc = tid - grp * cpp;
     const int c = blockIdx.y;
@@ -242,9 +252,9 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
         }
         for (int s = wave; s < gi; s += n_waves) {
             const int64_t row = (int64_t)c * a.g + i0 + s;
-            float mx, sc;
-            pair_row_stats(t, Sc + (int64_t)(i0 + s) * a.ld_s, a.k, a.gamma, jt == 0 && col == 0, row, mx, sc);
-            if (lane == 0) { row_mx[s] = mx; row_sc[s] = sc; }
+            float mx, z;
+            pair_row_stats(t, Sc + (int64_t)(i0 + s) * a.ld_s, a.k, a.gamma, jt == 0 && col == 0, row, mx, z);
+            if (lane == 0) { row_mx[s] = mx; row_z[s] = z; }
         }
         for (int j0 = jb0; j0 < jb1; j0 += t.tjb) {
             const int jn = min(t.tjb, jb1 - j0);  // negatives in this block
@@ -253,7 +263,7 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
             // so that such pairs add nothing
             for (int s = wave; s < TI; s += n_waves) {
                 const bool ok = s < gi;
-                const float mx = ok ? row_mx[s] : 0.f, sc = ok ? row_sc[s] : 0.f;
+                const float mx = ok ? row_mx[s] : 0.f, z = ok ? row_z[s] : 1.f;
                 const float fp = ok && t.ranking ? t.fpos[(int64_t)c * a.g + i0 + s] : 0.f;
                 const float* S = Sc + (int64_t)(i0 + (ok ? s : 0)) * a.ld_s + j0;
                 for (int jb = lane; jb < jn; jb += 256) {
@@ -262,16 +272,16 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
                     for (int u = 0; u < 4; ++u) f[u] = S[min(jb + 64 * u, jn - 1)];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        float w = t.alpha > 0.f ? sc * expf(t.alpha * f[u] - mx) : sc;
+                        float w = (t.alpha > 0.f ? softmax_exp(t.alpha * f[u] - mx, a.k) : 1.f) / z;
                         const bool on = ok && jb + 64 * u < jn;
                         if (t.ranking) {
                             const float m = a.gamma - fp + f[u];
                             li += on ? w * fmaxf(m, 0.f) : 0.f;
-                            w = m > 0.f ? w : 0.f;
+                            w = m > 0.f ? w * t.invb : 0.f;
                         } else {
-                            const float e = expf(-fabsf(f[u]));  // (library accuracy: cpp pair terms use every W)
+                            const float e = __builtin_amdgcn_exp2f(-fabsf(f[u]) * 1.4426950408889634f);  // exp(-|f|) in (0, 1]
                             li += on ? w * (fmaxf(f[u], 0.f) + __builtin_amdgcn_logf(1.f + e) * 0.6931471805599453f) : 0.f;
-                            w *= (f[u] >= 0.f ? 1.f : e) / (1.f + e);
+                            w = w * ((f[u] >= 0.f ? 1.f : e) * __builtin_amdgcn_rcpf(1.f + e)) * t.invb;
                         }
                         if (jb + 64 * u < jn) lds[(jb + 64 * u) * WPITCH + s] = ok ? w : 0.f;
                     }
@@ -368,7 +378,7 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
     __syncthreads();
     if (tid == 0) {
         for (int w = 1; w < n_waves; ++w) li += row_li[w];
-        t.loss_part[((int64_t)c * t.n_j + jt) * t.i_parts + ip] = li;
+        t.loss_part[((int64_t)c * t.n_j + jt) * t.i_parts + ip] = li * t.invb;
     }
 }
 
