@@ -155,10 +155,11 @@ struct PairBwdArgs {
 };
 
 // exp of the softmax weights (argument <= 0): the operations that k_loss uses, so that W has the same bits whichever kernel
-// forms it.  Rows of up to 1024 scores take the hardware exp2, longer ones the library's exp.  (Library functions for all
-// rows, with 1 / (b z) as one factor, left the free-running trajectories of the medium RotatE configuration no closer to
-// the 64-bit ones: share of relation elements off by 1e-4 after ten steps 1.4e-4 and 2.9e-4 with two seeds, 0.7e-4 and
-// 2.3e-4 like this.)
+// forms it.  Rows of up to 1024 scores take the hardware exp2, longer ones the library's exp.  The
+// reason is these bits, not a better result: ten free-running steps of the medium RotatE configuration, share of relation
+// elements off by 1e-4 from the 64-bit run, four seeds: 0.7 / 1.4 / 2.3 / 2.4e-4; with the separate loss kernel that this
+// launch replaced 0.7 / 1.5 / 1.9 / 2.5e-4.  Library functions times 1 / (b z) gave 1.4 and 2.9e-4 on the first and third.
+// The spread over seeds is larger than the differences between forms.
 __device__ __forceinline__ float softmax_exp(float x, int k) {
     return k <= 1024 ? __builtin_amdgcn_exp2f(x * 1.4426950408889634f) : expf(x);
 }
