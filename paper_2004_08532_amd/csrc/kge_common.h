@@ -6,6 +6,8 @@
 #include "kge.h"
 #include <hip/hip_ext.h>
 
+#include "k_pair_plan.h"
+
 // ---------------------------------------------------------------------------------------------------------
 // Context.  All device buffers are carved out of one allocation made in kge_create.
 //
@@ -23,9 +25,6 @@ struct PartialRows {
     int64_t stride;
     int64_t n4;      // 16-byte pieces per partial
 };
-
-// How the backward launch of RotatE / TransE-L1 is cut for batches of one shape (k_pair.hip).
-struct PairBwdPlan { int b, k, g, ti, n_i, i_parts, pj, tj, n_col, cpp, ng; };
 
 // TransR: the items of a mini-batch, i.e. the (chunk, relation) pairs that occur in it (k_transr.hip).  Item slots of chunk
 // c start at c * g; the positives of an item ("members") are numbered consecutively, item after item, chunk after chunk.
@@ -209,7 +208,6 @@ constexpr int KGE_SIDES_CAP = 65536;  // steps whose sides fit the workspace: lo
 constexpr int KGE_SORT_SLICE = 2048;     // keys per workgroup of the radix sort of long key lists
 constexpr int KGE_SORT_MAX_BITS = 10;    // bits per digit where a list has at most KGE_SORT_FEW_SLICES slices (else 8)
 constexpr int KGE_SORT_FEW_SLICES = 32;
-constexpr int KGE_PAIR_MAX_PARTS = 16;  // most partial rows of dL/do in the backward of RotatE / TransE-L1
 constexpr int KGE_RANK_MAX_KEYS = 14336;  // 14 * 1024: positions fit 14 bits, the list and its tables fit 64 KB of LDS
 // a3: negative scores of every chunk into out[b x ld_out]: matrix-product models / elementwise-reduce models
 void kge_gemm_neg_score(kge_ctx* c, int b, int k, int g, float gamma, float* out, int ld_out, int dist_mode,

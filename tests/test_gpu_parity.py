@@ -293,6 +293,20 @@ def test_cuts_of_the_elementwise_backward(kge, model, shape):
         p.close()
 
 
+@pytest.mark.parametrize("length", [1, 2])
+@pytest.mark.parametrize("model", ["transe_l2", "transe_l1", "distmult", "complex", "rotate"])
+def test_shortest_rows(kge, model, length):
+    """The shortest and the next row length that kge_create accepts (4 floats, 8 for rows of complex numbers), in chunks of
+    several positives."""
+    D = length * (8 if model in ("complex", "rotate") else 4)
+    w = ragged(model, ent_dim=D, rel_dim=D // 2 if model == "rotate" else D, batch=51, chunk=17, neg_per_chunk=70, steps=2)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps)
+    finally:
+        p.close()
+
+
 TRANSR_ITEMS = {
     # rows longer than a tile's columns; items of more positives than a block and than the two forms of dL/dP change over at;
     # relation tables that do not fit the LDS counters; chunks longer than what an item workgroup keeps in LDS
