@@ -254,7 +254,17 @@ __global__ __launch_bounds__(UPD_THREADS) void k_update(UpdateArgs a) {
     }
 }
 
+// Fills the step block of a kge_train_steps call (replay mode): one thread, the values travel as kernel arguments.
+// It stands in this file because every training step has loaded this file's code by the time graphs are replayed: in
+// kge_api.hip its first launch loaded that file's code with the 8 MiB scratch array, 3.5 ms in the middle of a program's first
+// long call (first 20-step call of a Freebase-shaped run 4488 -> 777 us).
+__global__ void k_set_step_block(StepBlock* blk, StepBlock value) { *blk = value; }
+
 }  // namespace
+
+void kge_launch_set_step_block(StepBlock* blk, const StepBlock& value, hipStream_t st) {
+    hipLaunchKernelGGL(k_set_step_block, dim3(1), dim3(1), 0, st, blk, value);
+}
 
 void kge_launch_update(kge_ctx* c, float* E, float* SE, float* R, float* SR, const StepIds& ids, float lr,
                        int n_loss_parts, bool with_entities, hipStream_t st) {

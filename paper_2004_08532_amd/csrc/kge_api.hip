@@ -76,9 +76,6 @@ StepIds direct_ids(const int64_t* h, const int64_t* r, const int64_t* t, int b, 
     return ids;
 }
 
-// Fills the step block of a kge_train_steps call (replay mode): one thread, the values travel as kernel arguments.
-__global__ void k_set_step_block(StepBlock* blk, StepBlock value) { *blk = value; }
-
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 int check_batch(kge_ctx* c, const void* ent, const void* rel, const int64_t* h, const int64_t* r, const int64_t* t,
@@ -589,7 +586,7 @@ int kge_train_steps(kge_ctx* c, float* ent, float* ent_state, float* rel, float*
             blk.sides = c->sides_dev;
         }
         blk.loss_out = loss_out ? loss_out + first : nullptr;
-        hipLaunchKernelGGL(k_set_step_block, dim3(1), dim3(1), 0, st, c->step_block, blk);
+        kge_launch_set_step_block(c->step_block, blk, st);
         hipError_t herr = hipSuccess;
         for (int64_t q = n / unit; q > 0 && herr == hipSuccess; --q) herr = hipGraphLaunch(cache->exec[which], st);
         KGE_HIP(c, herr);

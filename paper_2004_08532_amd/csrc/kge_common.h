@@ -251,6 +251,8 @@ void kge_launch_sort(kge_ctx* c, const StepIds& ids, hipStream_t st);
 // (with_entities: false leaves the entity rows to kge_launch_update_runs)
 void kge_launch_update(kge_ctx* c, float* E, float* SE, float* R, float* SR, const StepIds& ids, float lr,
                        int n_loss_parts, bool with_entities, hipStream_t st);
+// fills the step block that replayed steps read
+void kge_launch_set_step_block(StepBlock* blk, const StepBlock& value, hipStream_t st);
 // evaluation: ranks of the positives among their negatives (from fpos and the scores in S), and the metrics
 void kge_launch_rank(kge_ctx* c, int b, int k, int32_t* rank_out, hipStream_t st);
 void kge_launch_rank_metrics(const int32_t* ranks, int64_t n, double* out, hipStream_t st);
