@@ -129,12 +129,14 @@ int kge_train_step(kge_ctx* ctx, float* ent, float* ent_state, float* rel, float
  * kge_train_step; exists so that a whole pass over pre-sampled mini-batches (Sec. 3.1 step 1 done ahead of time)
  * costs one call.  Shorter calls (fewer than 16 steps) and the first steps of every call are launched kernel by
  * kernel; the last 16 or 32 steps of a call, and from 256 steps on all but its first, are replayed from HIP graphs that
- * the context builds on the first call that needs them with a given combination of tables, b, k, chunk, gamma and lr
- * (that call creates graph objects) and keeps: the kernels find the id arrays, the sides and the loss array of the
- * running call through a block in the workspace, so later calls with other arrays replay the same graphs and allocate
- * nothing.  On the legacy default stream, which cannot be captured, and while the caller is capturing the stream
- * itself, every step is launched kernel by kernel.  The sides of a long replay are copied into a fixed part of the
- * workspace; more than 65,536 replayed steps with sides run in segments of that length.
+ * the context builds and keeps, one set at a time, for a combination of tables, b, k, chunk, gamma and lr: the kernels
+ * find the id arrays, the sides and the loss array of the running call through a block in the workspace, so later calls
+ * with other arrays replay the same graphs and allocate nothing.  The graphs (of 16 steps for calls of 16 to 63, of 32 for
+ * longer ones) are built in the first call that could use them: a call of fewer than 256 steps launches all of its steps
+ * first, a longer one its first steps.  Steps whose graph cannot be built or started are launched kernel by kernel, so a
+ * graph is never the reason for an error.  On the legacy default stream, which cannot be captured, and while the caller
+ * is capturing the stream itself, every step is launched kernel by kernel.  The sides of a long replay are copied into a
+ * fixed part of the workspace; more than 65,536 replayed steps with sides run in segments of that length.
  */
 int kge_train_steps(kge_ctx* ctx, float* ent, float* ent_state, float* rel, float* rel_state,
                     const int64_t* h, const int64_t* r, const int64_t* t, int64_t b,

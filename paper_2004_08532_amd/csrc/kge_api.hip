@@ -288,7 +288,8 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
 // stays ahead (it does: 15 us of launching per four-kernel step against 20 us and more on the device; and a plain
 // launch carries its id pointers in its arguments, one dependent load less per kernel).  So:
 //   fewer than 16 steps       plain launches
-//   up to REPLAY_LONG steps   plain launches, and one graph for the last 16 or 32 steps (the call returns while they run)
+//   up to REPLAY_LONG steps   plain launches, and one graph for the last 16 or 32 steps (the call returns while they run);
+//                             the first such call plain launches only
 //   longer calls              plain launches for at least 32 steps, graphs of 32 for the rest
 // Measured per pass (all graphs, growing from one step -> this): 4 TransE-L1 steps 223 -> 201 us, 50 RotatE steps 3940 ->
 // 3890, 100 FB15k-sized DistMult steps 3976 -> 3895.
@@ -306,8 +307,8 @@ struct ReplayKey {
 };
 
 struct ReplayCache {
-    bool valid = false;
-    ReplayKey key;
+    bool counted = false;  // kge_graph_captures has counted the key
+    ReplayKey key = {};
     hipGraphExec_t exec[REPLAY_SIZES] = {};  // exec[i] runs REPLAY_STEPS[i] steps; captured when first needed
 };
 
@@ -316,27 +317,78 @@ void replay_drop(ReplayCache* rc) {
         if (rc->exec[i]) (void)hipGraphExecDestroy(rc->exec[i]);
         rc->exec[i] = nullptr;
     }
-    rc->valid = false;
+    rc->counted = false;
 }
 
-int capture_steps(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids, int K,
-                  int G, float gamma, float lr, hipStream_t st, int n, hipGraphExec_t* out) {
-    hipGraph_t graph = nullptr;
-    KGE_HIP(c, hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-    int rc = KGE_OK;
-    for (int s = 0; s < n && rc == KGE_OK; ++s) rc = enqueue_step(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, st);
-    hipError_t e = hipStreamEndCapture(st, &graph);
-    if (rc != KGE_OK) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return rc;
+// The cache, emptied if it holds graphs of another key; null without host memory.
+ReplayCache* replay_cache(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, int64_t b, int64_t k,
+                          int64_t chunk, float gamma, float lr) {
+    ReplayKey key;
+    memset(&key, 0, sizeof(key));
+    key.ent = ent; key.ent_state = ent_state; key.rel = rel; key.rel_state = rel_state;
+    key.b = b; key.k = k; key.chunk = chunk; key.gamma = gamma; key.lr = lr;
+    if (!c->replay) c->replay = new (std::nothrow) ReplayCache();
+    ReplayCache* cache = (ReplayCache*)c->replay;
+    if (cache && !(cache->key == key)) {
+        replay_drop(cache);
+        cache->key = key;
     }
-    if (e != hipSuccess) return fail(c, KGE_ERR_DEVICE, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    e = hipGraphInstantiate(out, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (e != hipSuccess) return fail(c, KGE_ERR_DEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
-    (void)hipGraphUpload(*out, st);  // so that the first launch does not pay for it; a failure here is not one
+    return cache;
+}
+
+// A graph of n steps into *out, which stays null if it cannot be built (that is no error: the steps can be launched
+// kernel by kernel).
+void capture_steps(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids, int K,
+                   int G, float gamma, float lr, hipStream_t st, int n, hipGraphExec_t* out) {
+    hipGraph_t graph = nullptr;
+    if (hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal) == hipSuccess) {
+        int rc = KGE_OK;
+        for (int s = 0; s < n && rc == KGE_OK; ++s) rc = enqueue_step(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, st);
+        const bool ok = hipStreamEndCapture(st, &graph) == hipSuccess && rc == KGE_OK;
+        if (ok && hipGraphInstantiate(out, graph, nullptr, nullptr, 0) != hipSuccess) *out = nullptr;
+        if (graph) (void)hipGraphDestroy(graph);
+        if (*out) {
+            ReplayCache* cache = (ReplayCache*)c->replay;
+            if (!cache->counted) c->graph_captures += 1;
+            cache->counted = true;
+            (void)hipGraphUpload(*out, st);  // so that the first launch does not pay for it; a failure here is not one
+        }
+    }
+    c->err[0] = 0;
     (void)hipGetLastError();
-    return KGE_OK;
+}
+
+// Replays the steps of a call from *done on, at most KGE_SIDES_CAP of them, and moves *done past those that were enqueued;
+// true if that was all of them.  (n_steps - *done is a multiple of the graph's `unit` steps, and so is KGE_SIDES_CAP.)
+bool replay_segment(kge_ctx* c, const int64_t* h, const int64_t* r, const int64_t* t, int64_t b, const int64_t* neg, int64_t n_neg,
+                    const int32_t* neg_sides, int64_t n_steps, float* loss_out, hipGraphExec_t exec, int64_t unit, hipStream_t st,
+                    int64_t* done) {
+    const int64_t first = *done, n = n_steps - first < KGE_SIDES_CAP ? n_steps - first : KGE_SIDES_CAP;
+    StepBlock blk;
+    blk.step = 0;
+    blk.h = h + first * b; blk.r = r + first * b; blk.t = t + first * b; blk.neg = neg + first * n_neg;
+    blk.sides = nullptr;
+    blk.side_bits = 0;
+    // the sides of a single graph travel as bits of the step block; those of a longer replay live in a fixed part of the
+    // workspace
+    if (neg_sides && n <= 64) {
+        for (int64_t s = 0; s < n; ++s) blk.side_bits |= (uint64_t)(neg_sides[first + s] == KGE_NEG_HEAD) << s;
+    } else if (neg_sides) {
+        if (hipMemcpyAsync(c->sides_dev, neg_sides + first, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        blk.sides = c->sides_dev;
+    }
+    blk.loss_out = loss_out ? loss_out + first : nullptr;
+    kge_launch_set_step_block(c->step_block, blk, st);
+    bool ok = hipGetLastError() == hipSuccess;
+    for (int64_t q = n / unit; ok && q > 0; --q) {
+        ok = hipGraphLaunch(exec, st) == hipSuccess;
+        if (ok) *done += unit;
+    }
+    (void)hipGetLastError();
+    return ok;
 }
 
 }  // namespace
@@ -533,66 +585,39 @@ int kge_train_steps(kge_ctx* c, float* ent, float* ent_state, float* rel, float*
     }();
     const bool may_replay = replay_enabled && !c->prof_on && cap == hipStreamCaptureStatusNone && st != nullptr &&
                             st != hipStreamLegacy;  // (the legacy default stream cannot be captured)
-    // the first n_plain steps are launched kernel by kernel, the rest is replayed
+    // kernel by kernel: the steps first .. last - 1
+    auto plain = [&](int64_t first, int64_t last) {
+        for (int64_t s = first; s < last; ++s) {
+            const StepIds ids = direct_ids(h + s * b, r + s * b, t + s * b, (int)b, neg + s * n_neg, (int)n_neg,
+                                           neg_sides ? neg_sides[s] : KGE_NEG_TAIL, loss_out ? loss_out + s : nullptr);
+            const int e = enqueue_step(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st);
+            if (e != KGE_OK) return e;
+        }
+        return (int)KGE_OK;
+    };
+    if (!may_replay || n_steps < REPLAY_STEPS[0]) return plain(0, n_steps);
+
     const int which = n_steps < 64 ? 0 : 1;
     const int64_t unit = REPLAY_STEPS[which];
-    int64_t n_plain = n_steps;
-    if (may_replay && n_steps >= REPLAY_STEPS[0]) n_plain = n_steps < REPLAY_LONG ? n_steps - unit : unit + n_steps % unit;
-    for (int64_t s = 0; s < n_plain; ++s) {
-        const StepIds ids = direct_ids(h + s * b, r + s * b, t + s * b, (int)b, neg + s * n_neg, (int)n_neg,
-                                       neg_sides ? neg_sides[s] : KGE_NEG_TAIL, loss_out ? loss_out + s : nullptr);
-        rc = enqueue_step(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st);
-        if (rc != KGE_OK) return rc;
-    }
-    if (n_plain == n_steps) return KGE_OK;
-
-    // replay: nothing here allocates once the graph exists
-    ReplayKey key;
-    memset(&key, 0, sizeof(key));
-    key.ent = ent; key.ent_state = ent_state; key.rel = rel; key.rel_state = rel_state;
-    key.b = b; key.k = k; key.chunk = chunk; key.gamma = gamma; key.lr = lr;
-    if (!c->replay) c->replay = new (std::nothrow) ReplayCache();
-    ReplayCache* cache = (ReplayCache*)c->replay;
-    if (!cache) return fail(c, KGE_ERR_DEVICE, "out of host memory%s");
-    if (!cache->valid || !(cache->key == key)) {
-        replay_drop(cache);
-        cache->key = key;
-        cache->valid = true;
-        c->graph_captures += 1;
-    }
+    ReplayCache* cache = replay_cache(c, ent, ent_state, rel, rel_state, b, k, chunk, gamma, lr);
+    // A call that is shorter than REPLAY_LONG and finds no graph runs without one and builds it when all of its steps are
+    // enqueued: 0.2 ms of host work that the GPU does not wait for (first 20-step call of a Freebase-shaped run 947 us with the
+    // capture before the last 16 steps, 787 us of plain steps).  A longer one builds it behind its plain start.
+    int64_t n_plain = n_steps < REPLAY_LONG ? n_steps - unit : unit + n_steps % unit;
+    if (!cache || (!cache->exec[which] && n_steps < REPLAY_LONG)) n_plain = n_steps;
+    rc = plain(0, n_plain);
+    if (rc != KGE_OK || !cache) return rc;
     if (!cache->exec[which]) {
         StepIds ids = direct_ids(nullptr, nullptr, nullptr, (int)b, nullptr, (int)n_neg, KGE_NEG_TAIL, nullptr);
         ids.blk = c->step_block;
-        rc = capture_steps(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st, (int)unit,
-                           &cache->exec[which]);
-        if (rc != KGE_OK) {
-            replay_drop(cache);
-            return rc;
-        }
+        capture_steps(c, ent, ent_state, rel, rel_state, ids, (int)k, (int)chunk, gamma, lr, st, (int)unit, &cache->exec[which]);
     }
-    // the sides of a single graph travel as bits of the step block; those of a longer replay live in a fixed part of
-    // the workspace, and one of more than KGE_SIDES_CAP steps runs in segments of that many (a multiple of the unit)
-    for (int64_t first = n_plain; first < n_steps; first += KGE_SIDES_CAP) {
-        const int64_t n = n_steps - first < KGE_SIDES_CAP ? n_steps - first : KGE_SIDES_CAP;
-        StepBlock blk;
-        blk.step = 0;
-        blk.h = h + first * b; blk.r = r + first * b; blk.t = t + first * b; blk.neg = neg + first * n_neg;
-        blk.sides = nullptr;
-        blk.side_bits = 0;
-        if (neg_sides && n <= 64) {
-            for (int64_t s = 0; s < n; ++s) blk.side_bits |= (uint64_t)(neg_sides[first + s] == KGE_NEG_HEAD) << s;
-        } else if (neg_sides) {
-            KGE_HIP(c, hipMemcpyAsync(c->sides_dev, neg_sides + first, sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, st));
-            blk.sides = c->sides_dev;
-        }
-        blk.loss_out = loss_out ? loss_out + first : nullptr;
-        kge_launch_set_step_block(c->step_block, blk, st);
-        hipError_t herr = hipSuccess;
-        for (int64_t q = n / unit; q > 0 && herr == hipSuccess; --q) herr = hipGraphLaunch(cache->exec[which], st);
-        KGE_HIP(c, herr);
-    }
-    KGE_HIP(c, hipGetLastError());
-    return KGE_OK;
+    // Replay what is left; steps whose graph could not be built or started are launched kernel by kernel, so that a call
+    // never ends with an error between two of its steps because of a graph.
+    int64_t done = n_plain;
+    while (done < n_steps && cache->exec[which] && replay_segment(c, h, r, t, b, neg, n_neg, neg_sides, n_steps, loss_out,
+                                                                   cache->exec[which], unit, st, &done)) {}
+    return plain(done, n_steps);
 }
 
 int kge_score(kge_ctx* c, const float* ent, const float* rel,

@@ -983,11 +983,13 @@ def test_train_steps_graph_replay_equals_step_by_step(kge, variant):
 @pytest.mark.parametrize("n_steps", [1, 15, 16, 17, 63, 64, 255, 256, 289])
 def test_train_steps_at_the_lengths_where_the_launch_schedule_changes(kge, n_steps):
     """Plain launches, one graph of 16 or 32 steps at the end, graphs of 32 after a plain start: the same bits and losses as
-    the steps run on the default stream, where every step is launched kernel by kernel."""
+    the steps run on the default stream, where every step is launched kernel by kernel.  Twice, with other ids: a call that
+    finds no graph runs another schedule than one that does."""
     w = configs.TINY.scaled(name="tiny-schedule", batch=64, chunk=16, neg_per_chunk=24, lr=0.01)
     gen = torch.Generator(device="cuda").manual_seed(n_steps)
     ids = lambda hi, n: torch.randint(0, hi, (n_steps, n), dtype=torch.int64, device="cuda", generator=gen)
     H, Rr, T, N = ids(w.n_entities, 64), ids(w.n_relations, 64), ids(w.n_entities, 64), ids(w.n_entities, 4 * 24)
+    N2 = ids(w.n_entities, 4 * 24)
     sides = [(s % 3 == 1) * 1 for s in range(n_steps)]
     E0, R0 = configs.init_tables(w)
     results = []
@@ -996,9 +998,10 @@ def test_train_steps_at_the_lengths_where_the_launch_schedule_changes(kge, n_ste
                              max_chunks=4)
         E, R = dev(E0), dev(R0)
         SE, SR = torch.zeros_like(E), torch.zeros_like(R)
-        loss = torch.zeros(n_steps, device="cuda")
+        loss = torch.zeros(2, n_steps, device="cuda")
         torch.cuda.synchronize()
-        ctx.train_steps(E, SE, R, SR, H, Rr, T, N, 24, 16, sides, w.gamma, w.lr, loss_out=loss, stream=stream)
+        ctx.train_steps(E, SE, R, SR, H, Rr, T, N, 24, 16, sides, w.gamma, w.lr, loss_out=loss[0], stream=stream)
+        ctx.train_steps(E, SE, R, SR, H, Rr, T, N2, 24, 16, sides[::-1], w.gamma, w.lr, loss_out=loss[1], stream=stream)
         torch.cuda.synchronize()
         ctx.close()
         results.append((E, SE, R, SR, loss))

@@ -77,13 +77,55 @@ def drive(recorder, body):
 def test_a_longer_call_needs_no_code_that_a_short_one_has_not_loaded(recorder, model, chunk):
     """The runtime loads the code of a source file when a kernel of it is first launched, which takes milliseconds for a large
     one.  A program that warms up with a few steps must not meet that in its first long call."""
-    first, second = drive(recorder, f'''
-lib_ = Library({model!r}, g={chunk})
-first, second = lib_.steps(5), lib_.steps(20)
-assert first[0] == 0 and second[0] == 0
-print(json.dumps([first[1], second[1]]))
+    first, later = drive(recorder, f'''
+x = Library({model!r}, g={chunk})
+calls = [x.steps(n) for n in (5, 20, 20, 300)]
+assert all(rc == 0 for rc, _ in calls)
+print(json.dumps([calls[0][1], sum((e for _, e in calls[1:]), [])]))
 ''')
     loaded = {e.split()[1] for e in first if e.startswith("kernel")}
-    new = [e for e in second if e.startswith("kernel") and e.split()[1] not in loaded]
-    assert any(e.startswith("graph") for e in second)
+    new = [e for e in later if e.startswith("kernel") and e.split()[1] not in loaded]
+    assert any(e.startswith("graph") for e in later)
     assert loaded and not new, new
+
+
+@pytest.mark.parametrize("model,k", [("transe_l2", 24), ("transr", 24), ("rotate", 5000)])  # (the last: sorted on a second stream)
+def test_a_graph_is_built_when_the_steps_of_a_short_call_are_enqueued(recorder, model, k):
+    """First call of 20 steps: launched kernel by kernel, the graph only built.  The next replays it, and both run every step."""
+    one, first, second, captures = drive(recorder, f'''
+x = Library({model!r}, k={k})
+print(json.dumps([x.steps(1), x.steps(20), x.steps(20), lib.kge_graph_captures(x.ctx)]))
+''')
+    assert one[0] == first[0] == second[0] == 0 and captures == 1
+    assert all(e.startswith("kernel") for e in first[1]) and len(first[1]) == 20 * len(one[1])
+    assert run_kernels(second[1]) == 20 * len(one[1]) and second[1][-1] == f"graph {16 * len(one[1])}"
+
+
+def run_kernels(events):
+    """Kernels of training steps in what a call enqueued, graphs counted by the kernels they hold."""
+    return sum(int(e.split()[1]) if e.startswith("graph") else 1 for e in events
+               if e != "copy" and "k_set_step_block" not in e)
+
+
+@pytest.mark.parametrize("nth", [1, 2])
+@pytest.mark.parametrize("n_steps", [16, 20, 64, 300, 65_536 + 97])
+@pytest.mark.parametrize("call", ["hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate", "hipGraphUpload",
+                                  "hipGraphLaunch", "hipMemcpyAsync", "capture: hipLaunchKernel"])
+def test_a_graph_that_fails_leaves_no_step_out(recorder, call, n_steps, nth):
+    """When building or starting a graph fails, the call still runs each of its steps once."""
+    launch = call.startswith("capture")
+    name = call.split()[-1]
+    one, got = drive(recorder, f'''
+x = Library("distmult")
+one = x.steps(1)
+unit = 16 if {n_steps} < 64 else 32
+plain = {n_steps} if {n_steps} < 256 else unit + {n_steps} % unit
+got = []
+for _ in range(3):
+    # a launch inside of the capture: the kernels before it are those of the plain start
+    rec.recorder_fail({name!r}.encode(), len(one[1]) * plain + 3 if {launch} else {nth})
+    got.append(x.steps({n_steps}))
+print(json.dumps([one, got]))
+''')
+    for rc, events in got if not launch else got[:1]:
+        assert rc == 0 and run_kernels(events) == n_steps * len(one[1])
