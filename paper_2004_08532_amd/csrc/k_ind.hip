@@ -273,7 +273,8 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
                     for (int x = 0; x < 4 * NP; ++x) go[x] *= r;
                     m = mx;
                 }
-                e = real ? __builtin_amdgcn_exp2f((a.alpha * f - m) * 1.4426950408889634f) : 0.f;
+                // (m is still -inf where every score so far was, i.e. distances beyond the floats: weight 0)
+                e = real && m > -INFINITY ? __builtin_amdgcn_exp2f((a.alpha * f - m) * 1.4426950408889634f) : 0.f;
             }
             if (a.ranking) {
                 const float t = a.gamma - fp + f;

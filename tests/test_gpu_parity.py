@@ -242,6 +242,28 @@ def test_chunks_of_one_positive(kge, model, option, shape):
         p.close()
 
 
+@pytest.mark.parametrize("loss", ["logistic", "ranking"])
+@pytest.mark.parametrize("model", ["transe_l2", "transe_l1", "rotate"])
+def test_chunks_of_one_positive_with_scores_beyond_the_floats(kge, model, loss):
+    """Self-adversarial weights where the first scores that every lane group sees are -inf in fp32 (16 corrupting entities so
+    far away that the distance overflows): their weight is 0, as in the oracle's 64 bits, and everything else is finite."""
+    w = ragged(model, batch=12, chunk=1, neg_per_chunk=40, adv_temperature=1.0, loss=loss, steps=1)
+    E, R = configs.init_tables(w)
+    far = w.n_entities - 1
+    E[far] = 3e37
+    p = Pair(w, kge, E=E, R=R)
+    try:
+        rng = np.random.default_rng(2)
+        h, t, neg = (rng.integers(0, far, n) for n in (12, 12, (12, 40)))
+        neg[:, :16] = far
+        p.step_checked(h, rng.integers(0, w.n_relations, 12), t, neg, 0)
+        assert torch.isfinite(p.dE).all() and torch.isfinite(p.dR).all() and torch.isfinite(p.dSE).all()
+        assert (p.dE[far] == 3e37).all()
+        p.assert_allowance_share("ranking-transe_l1" if (model, loss) == ("transe_l1", "ranking") else "default")
+    finally:
+        p.close()
+
+
 PAIR_BACKWARD_SHAPES = {
     # chunks of up to 128 positives take the backward in which a workgroup owns 16 positives x a range of negatives
     # and writes partial rows; here with 8 i-tiles of which the last is ragged, and 8 ranges of 22 negatives
