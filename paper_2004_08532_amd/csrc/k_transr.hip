@@ -30,6 +30,8 @@
 // positive on 32x32 tiles, projections written and read four times; b 798, g 266, k 52, D 56, 21 relations: 192 -> 74.
 // The three large products take 63-71 us each: 29 us of matrix instructions (a quarter of them padding, 100 -> 112 rows and
 // columns), the rest the start of a workgroup (four dependent loads) and an uneven number of workgroups per CU.
+#include <type_traits>
+
 #include "k_gemm_shared.h"
 #include "k_transr_items.h"
 
@@ -43,6 +45,7 @@ constexpr int A_FLOATS = BM * KP > BK * AP ? BM * KP : BK * AP, B_FLOATS = BN * 
 constexpr int PB = TRANSR_PB;              // positives per block of an item's positives
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 struct TransrArgs {
     const float* E;
@@ -82,33 +85,38 @@ struct TransrArgs {
 // block later, when they go to LDS (a select right behind the load would wait for it).  Rows outside only reach outputs
 // that are not stored, and read something valid.  No branch stands between the loads of a block, and none between the LDS
 // reads and matrix instructions of one (the number of column tiles NT is a template argument).
-template <int NT>
+// F64: operands in 32 bits, products and sums in 64.
+template <int NT, bool F64 = false>
 struct Tile {
+    typedef typename std::conditional<F64, double, float>::type Sum;
+    typedef typename std::conditional<F64, doublex4, floatx4>::type Acc;
     float* As;
     float* Bs;
-    floatx4 acc[NT];
-    float a_sum;  // ASUM: sum over K of the A values of row lane % 16 of the wave's sixteen (complete in every lane)
+    Acc acc[NT];
+    Sum a_sum;  // ASUM: sum over K of the A values of row lane % 16 of the wave's sixteen (complete in every lane)
     int wave, lane;
     bool active;  // the wave has rows
-    __device__ __forceinline__ int row(int v) const { return 16 * wave + 4 * (lane >> 4) + v; }  // of accumulator v
+    __device__ __forceinline__ int row16(int v) const { return F64 ? (lane >> 4) + 4 * v : 4 * (lane >> 4) + v; }
+    __device__ __forceinline__ int row(int v) const { return 16 * wave + row16(v); }  // of accumulator v
+    __device__ __forceinline__ Sum a_sum_of(int v) const { return __shfl(a_sum, row16(v), 64); }
 };
 
 // Waves take the groups of 16 rows in an order that changes from workgroup to workgroup, so that the SIMDs of a CU get about
 // the same number where there are fewer than four.
 __device__ __forceinline__ int row_wave() { return __builtin_amdgcn_readfirstlane(((threadIdx.x >> 6) + blockIdx.x) & 3); }
-template <int NT>
-__device__ __forceinline__ void tile_init(Tile<NT>& t, float* As, float* Bs, int rows) {
+template <int NT, bool F64>
+__device__ __forceinline__ void tile_init(Tile<NT, F64>& t, float* As, float* Bs, int rows) {
     t.As = As; t.Bs = Bs;
     t.wave = row_wave(); t.lane = threadIdx.x & 63;
     t.active = __builtin_amdgcn_readfirstlane(16 * t.wave < rows);
     t.a_sum = 0.f;
 #pragma unroll
-    for (int ct = 0; ct < NT; ++ct) t.acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < NT; ++ct) t.acc[ct] = typename Tile<NT, F64>::Acc{0, 0, 0, 0};
 }
 
 // 16 values of K (from s16 on) of a staged block
-template <bool A_KC, bool B_KC, bool ASUM, int NT>
-__device__ __forceinline__ void tile_mma(Tile<NT>& t, int s16) {
+template <bool A_KC, bool B_KC, bool ASUM, int NT, bool F64>
+__device__ __forceinline__ void tile_mma(Tile<NT, F64>& t, int s16) {
     const int r16 = t.lane & 15, kk = s16 + 4 * (t.lane >> 4), row = 16 * t.wave + r16;
     float fa[4];
     if (A_KC) {
@@ -118,7 +126,8 @@ __device__ __forceinline__ void tile_mma(Tile<NT>& t, int s16) {
 #pragma unroll
         for (int x = 0; x < 4; ++x) fa[x] = t.As[(kk + x) * AP + row];
     }
-    if (ASUM) t.a_sum += (fa[0] + fa[1]) + (fa[2] + fa[3]);
+    typedef typename Tile<NT, F64>::Sum Sum;
+    if (ASUM) t.a_sum += ((Sum)fa[0] + fa[1]) + ((Sum)fa[2] + fa[3]);
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) {
         float fb[4];
@@ -130,13 +139,16 @@ __device__ __forceinline__ void tile_mma(Tile<NT>& t, int s16) {
             for (int x = 0; x < 4; ++x) fb[x] = t.Bs[(kk + x) * BP + 16 * ct + r16];
         }
 #pragma unroll
-        for (int x = 0; x < 4; ++x) t.acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[x], fb[x], t.acc[ct], 0, 0, 0);
+        for (int x = 0; x < 4; ++x) {
+            if constexpr (F64) t.acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[x], fb[x], t.acc[ct], 0, 0, 0);
+            else t.acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[x], fb[x], t.acc[ct], 0, 0, 0);
+        }
     }
 }
 
 // The product over `runs` consecutive ranges of K values each; masks apply to the last block of a run.
-template <bool A_KC, bool B_KC, bool ASUM, int NT, class LoadA, class MaskA, class LoadB, class MaskB>
-__device__ __forceinline__ void tile_run(Tile<NT>& t, int K, int runs, LoadA load_a, MaskA mask_a, LoadB load_b, MaskB mask_b) {
+template <bool A_KC, bool B_KC, bool ASUM, int NT, bool F64, class LoadA, class MaskA, class LoadB, class MaskB>
+__device__ __forceinline__ void tile_run(Tile<NT, F64>& t, int K, int runs, LoadA load_a, MaskA mask_a, LoadB load_b, MaskB mask_b) {
     constexpr int NB = B_KC ? (NT + 1) / 2 : 4;  // pieces of B that hold columns of the tile
     const int tid = threadIdx.x;
     const int bpr = (K + BK - 1) / BK, nblk = bpr * runs;
@@ -421,6 +433,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a) {
 // both while a row of P is in registers (32 us for the FB15k-sized step, 130 MB of rows; two products took 67, their
 // tiles of sixteen rows nearly empty); others: two products.
 constexpr int DP_FEW = 16, MB = 4, DR = 8;
+constexpr int DN = 64;  // columns of a tile of those products
 
 // 64 corrupting rows of an item.  Thread (group, 16 bytes of the row), DR rows at a time in registers with their sums over
 // the item's positives, which come in batches of MB: the sums for dL/do stay in registers too and meet in LDS in group order.
@@ -490,58 +503,65 @@ __device__ void dp_few(const TransrArgs& a, int slot, int tile, const TransrItem
     }
 }
 
-// The first workgroups: the gradients of a block of the positives of an item of many x 128 columns, K over the corrupting
-// rows; the others: V of 64 corrupting rows of an item (of many: x 128 columns, K over the item's positives).
+// The first workgroups: the gradients of a block of the positives of an item of many x 64 columns, K over the corrupting
+// rows; the others: V of 64 corrupting rows of an item (of many: K over the item's positives, 64 columns at a time).
 //     V = 2 (W^T O - colsum(W) P) ,   dL/do = 2 (W P - rowsum(W) o)
+// These differences cancel where o is close to P, so both products are formed in 64 bits (v_mfma_f64_16x16x4_f64, half the
+// rate) and what is left is the rounding of the result.  Items of 17 to 97 positives, rows a hundredth of their length
+// apart, error of the entities' gradients: products in 32 bits 0.7 to 2.0e-4, in 64 bits 1.8 to 2.4e-7 (sums of 2 W (o - P),
+// positive by positive, 1.8 to 2.9e-7).  64 columns, so that the accumulators take the registers that 128 take in 32 bits:
+// dp_few needs its three waves per SIMD.  Per step, 32 -> 64 bits: FB15k-sized 279 -> 281 us, b 1024, g 1024, k 1024, D 128,
+// 2 relations 347 -> 360, b 1024, g 128, k 256, D 100, 2 relations 134.7 both.
 template <int NT>
 __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
     __shared__ __attribute__((aligned(16))) float lds[A_FLOATS + B_FLOATS];
     float* As = lds;
     float* Bs = lds + A_FLOATS;
     static_assert(sizeof(float4) * MB * RT + sizeof(float) * MB * BM <= sizeof(lds), "");
-    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15, quad = (tid & 63) >> 4;
+    const int D = a.D, tid = threadIdx.x, l16 = tid & 15;
     int c;
     if ((int)blockIdx.x >= go_blocks) {
         int slot, tile;
         TransrItem item;
-        const int tiles = (a.k + BM - 1) / BM * cols;
+        const int tiles = (a.k + BM - 1) / BM;
         if (!item_of(a, unit_of_block(blockIdx.x - go_blocks, tiles, tile), c, slot, item)) return;
-        const int n0 = tile % cols * BN, j0 = tile / cols * BM, rows = min(BM, a.k - j0), n = item.n;
+        const int j0 = tile * BM, rows = min(BM, a.k - j0), n = item.n;
         if (n <= DP_FEW) {
-            if (n0 == 0) dp_few(a, slot, tile / cols, item, reinterpret_cast<float4(*)[RT]>(lds), reinterpret_cast<float(*)[BM]>(lds + 4 * MB * RT));
+            dp_few(a, slot, tile, item, reinterpret_cast<float4(*)[RT]>(lds), reinterpret_cast<float(*)[BM]>(lds + 4 * MB * RT));
             return;
         }
-        const int ja = 4 * (tid % 16), db = n0 + 4 * (tid % 32);
+        const int ja = 4 * (tid % 16);
         const float* W = a.S + (int64_t)item.off * a.ld_s + j0 + (ja < rows ? ja : 0);
-        const float* O = a.O + (int64_t)item.off * D + (db < D ? db : n0);
-        Tile<NT> t;
-        tile_init(t, As, Bs, rows);
-        tile_run<false, false, true>(t, n, 1, [&](int, int kb, float4* r) { load_mc<2>(W, a.ld_s, n, kb, tid / 16, 16, r); },
-                                     [&](int kb, float4* r) { mask_mc<2>(n, kb, tid / 16, 16, r); },
-                                     [&](int, int kb, float4* r) { load_mc<4>(O, D, n, kb, tid / 32, 8, r); },
-                                     [&](int kb, float4* r) { mask_mc<4>(n, kb, tid / 32, 8, r); });
-        const int64_t base = ((int64_t)slot * a.k + j0) * D + n0 + (n0 + l16 < D ? l16 : 0);
-        float w[4], p[NT][4];  // all of P asked for before the first store
+        for (int n0 = 0; n0 < D; n0 += DN) {
+            const int db = n0 + 4 * (tid % 32);
+            const float* O = a.O + (int64_t)item.off * D + (db < D ? db : n0);
+            Tile<NT, true> t;
+            tile_init(t, As, Bs, rows);
+            tile_run<false, false, true>(t, n, 1, [&](int, int kb, float4* r) { load_mc<2>(W, a.ld_s, n, kb, tid / 16, 16, r); },
+                                         [&](int kb, float4* r) { mask_mc<2>(n, kb, tid / 16, 16, r); },
+                                         [&](int, int kb, float4* r) { load_mc<4>(O, D, n, kb, tid / 32, 8, r); },
+                                         [&](int kb, float4* r) { mask_mc<4>(n, kb, tid / 32, 8, r); });
+            const int64_t base = ((int64_t)slot * a.k + j0) * D + n0 + (n0 + l16 < D ? l16 : 0);
+            float p[NT][4];  // all of P asked for before the first store
 #pragma unroll
-        for (int v = 0; v < 4; ++v) w[v] = __shfl(t.a_sum, 4 * quad + v, 64);
+            for (int ct = 0; ct < NT; ++ct) {
+                const int d = n0 + 16 * ct + l16 < D ? 16 * ct : 0;
 #pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-            const int d = n0 + 16 * ct + l16 < D ? 16 * ct : 0;
+                for (int v = 0; v < 4; ++v) p[ct][v] = a.P[base + (int64_t)min(t.row(v), rows - 1) * D + d];
+            }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) p[ct][v] = a.P[base + (int64_t)min(t.row(v), rows - 1) * D + d];
-        }
+            for (int v = 0; v < 4; ++v) {
+                const double w = t.a_sum_of(v);
 #pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-            if (n0 + 16 * ct + l16 < D) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (t.row(v) < rows) a.V[base + (int64_t)t.row(v) * D + 16 * ct] = 2.f * (t.acc[ct][v] - w[v] * p[ct][v]);
+                for (int ct = 0; ct < NT; ++ct) {
+                    if (n0 + 16 * ct + l16 < D && t.row(v) < rows)
+                        a.V[base + (int64_t)t.row(v) * D + 16 * ct] = (float)(2. * (t.acc[ct][v] - w * p[ct][v]));
                 }
             }
         }
         return;
     }
-    const int n0 = blockIdx.x % cols * BN;
+    const int cols = (D + DN - 1) / DN, n0 = blockIdx.x % cols * DN;
     TransrBlock blk;
     if (!pblock_of(a, blockIdx.x / cols, c, blk) || blk.all <= DP_FEW) return;
     const int db = n0 + 4 * (tid % 32), n = blk.n;
@@ -549,7 +569,7 @@ __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
     const float* W[2];
 #pragma unroll
     for (int it = 0; it < 2; ++it) W[it] = a.S + (int64_t)(blk.off + min(tid / 8 + 32 * it, n - 1)) * a.ld_s;
-    Tile<NT> t;
+    Tile<NT, true> t;
     tile_init(t, As, Bs, n);
     tile_run<true, false, true>(t, a.k, 1, [&](int, int kb, float4* r) { load_kc<2>(W, a.k, kb, r); },
         [&](int kb, float4* r) {
@@ -577,7 +597,7 @@ __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        const float w = __shfl(t.a_sum, 4 * quad + v, 64);
+        const double w = t.a_sum_of(v);
         const int m = blk.off + t.row(v);
         if (t.row(v) >= n) continue;
         const int64_t at = (int64_t)m * D + n0 + l16, at_r = (int64_t)a.q.members[m] * D + n0 + l16;
@@ -586,7 +606,7 @@ __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
         for (int ct = 0; ct < NT; ++ct) {
             if (n0 + 16 * ct + l16 < D) {
                 const float gp = cp2 * (o[v][ct] - p[v][ct]);  // df+/do = -2 (o - p)
-                const float go = 2.f * (t.acc[ct][v] - w * o[v][ct]) - gp;
+                const float go = (float)(2. * (t.acc[ct][v] - w * o[v][ct])) - gp;
                 a.GO[at + 16 * ct] = go;
                 a.PP[at + 16 * ct] = gp;
                 a.Gr[at_r + 16 * ct] = sigma * go;
@@ -915,11 +935,11 @@ int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, in
 
 void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, hipStream_t st) {
     const TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
-    const int cols = (a.D + BN - 1) / BN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
-    const dim3 grid(go_blocks + item_grid(a, (k + BM - 1) / BM * cols).x);
-#define L(NT) KGE_LAUNCH(c, k_transr_dp<NT>, grid, dim3(RT), 0, st, a, go_blocks)
-    KGE_BY_COLUMNS(a.D, L);
-#undef L
+    const int cols = (a.D + DN - 1) / DN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
+    const dim3 grid(go_blocks + item_grid(a, (k + BM - 1) / BM).x);
+    if (a.D <= 32) KGE_LAUNCH(c, k_transr_dp<2>, grid, dim3(RT), 0, st, a, go_blocks);
+    else if (a.D <= 48) KGE_LAUNCH(c, k_transr_dp<3>, grid, dim3(RT), 0, st, a, go_blocks);
+    else KGE_LAUNCH(c, k_transr_dp<4>, grid, dim3(RT), 0, st, a, go_blocks);
     hipLaunchKernelGGL(k_transr_go, dim3((ids.b * (a.D / 4) + RT - 1) / RT), dim3(RT), 0, st, a);
 }
 

@@ -1,0 +1,91 @@
+"""Gradients of one training step against 64-bit autograd, on tables whose coordinates are multiples of a power of two, few
+enough bits that rows o, differences and scores are exact in 32 bits.  What is left is the error of the coefficients, of the
+sums and of the directions, and the limits below are the roundings on that way.  With an accumulator that starts at zero
+Adagrad leaves S = g^2, so |g| can be read back for every element of the tables."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+ULP = 2.0 ** -24  # largest relative error of one rounding to 32 bits
+
+
+@pytest.fixture(scope="module")
+def kge():
+    import paper_2004_08532_amd as k
+    return k
+
+
+def score64(model, E, R, h, r, x):
+    """Scores of (h, r, x) over the last dimension, without the margin: minus the distance.  (Tail corrupted.)"""
+    if model == "transr":
+        D = E.shape[1]
+        M = R[r][..., D:].reshape(*r.shape, D, D)
+        q = torch.matmul(M, (E[h] - E[x]).unsqueeze(-1)).squeeze(-1) + R[r][..., :D]
+        return -(q * q).sum(-1)
+    q = E[h] + R[r] - E[x]
+    if model == "transe_l1":
+        return -q.abs().sum(-1)
+    return -(q * q).sum(-1).sqrt()
+
+
+def gradients64(model, E, R, h, r, t, neg, chunk, gamma, alpha, loss):
+    E, R = (torch.from_numpy(x).double().requires_grad_() for x in (E, R))
+    h, r, t, neg = (torch.from_numpy(x) for x in (h, r, t, neg))
+    k = neg.shape[1]
+    fp = gamma + score64(model, E, R, h, r, t)
+    rows = neg.repeat_interleave(chunk, 0)
+    f = gamma + score64(model, E, R, h[:, None].expand(-1, k), r[:, None].expand(-1, k), rows)
+    w = torch.softmax(alpha * f.detach(), 1) if alpha > 0 else torch.full_like(f, 1.0 / k)
+    if loss == "ranking":
+        total = (w * torch.relu(gamma - fp[:, None] + f)).sum()
+    else:
+        total = torch.nn.functional.softplus(-fp).sum() + (w * torch.nn.functional.softplus(f)).sum()
+    (total / h.shape[0]).backward()
+    return E.grad.abs().numpy(), R.grad.abs().numpy()
+
+
+def gradients(kge, model, E, R, h, r, t, neg, chunk, gamma, alpha, loss):
+    b, k = h.shape[0], neg.shape[1]
+    ctx = kge.KgeContext(model, E.shape[0], R.shape[0], E.shape[1], R.shape[1], max_batch=b, max_neg_per_chunk=k,
+                         max_chunks=b // chunk, adv_temperature=alpha, loss=loss)
+    dE, dR = (torch.from_numpy(x.copy()).cuda() for x in (E, R))
+    sE, sR = torch.zeros_like(dE), torch.zeros_like(dR)
+    h, r, t, neg = (torch.from_numpy(x).cuda() for x in (h, r, t, neg.reshape(-1)))
+    try:
+        ctx.train_step(dE, sE, dR, sR, h, r, t, neg, k, chunk, 0, gamma, 0.1)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    return sE.double().sqrt().cpu().numpy(), sR.double().sqrt().cpu().numpy()
+
+
+def worst_row(got, want):
+    """Largest relative error (2-norms) of a row."""
+    size = np.linalg.norm(want, axis=1)
+    err = np.linalg.norm(got - want, axis=1)
+    assert not err[size == 0].any()
+    return float((err[size > 0] / size[size > 0]).max())
+
+
+@pytest.mark.parametrize("D,k", [(100, 70), (32, 256), (136, 33)])
+def test_transr_rows_close_to_each_other(kge, D, k):
+    """Every o is within a hundredth of its length of every projection, as in a trained table; items of 17, 32, 33 and 97
+    positives (products) and of 5 (sums).  No term o - P may lose digits to the length of o and P."""
+    rng = np.random.default_rng(3)
+    runs = [97, 33, 5, 32, 17]
+    g = sum(runs)
+    r = rng.permutation(np.repeat(np.arange(len(runs)), runs))
+    E = (1 + rng.integers(-16, 17, (2 * g + k, D)) / 4096).astype(np.float32)
+    R = np.zeros((len(runs), D + D * D), np.float32)
+    R[:, :D] = rng.integers(-4, 5, (len(runs), D)) / 4096
+    R[:, D:] = np.eye(D).reshape(-1)
+    ids = rng.permutation(2 * g + k)
+    args = (E, R, ids[:g], r, ids[g:2 * g], ids[2 * g:].reshape(1, k), g, 0.5, 0.0, "logistic")
+    (gE, gR), (wE, wR) = gradients(kge, "transr", *args), gradients64("transr", *args)
+    err = worst_row(gE, wE), worst_row(gR[:, :D], wR[:, :D])
+    print("\n[precision] transr", D, k, "entities %.1e translations %.1e" % err)
+    # coefficients: hardware exp2 and reciprocal of an argument below 1, four roundings; terms and their sum (errors of
+    # either sign, so that the norm of a row has that of its largest terms), Adagrad's square and its root
+    assert max(err) <= 16 * ULP, err
