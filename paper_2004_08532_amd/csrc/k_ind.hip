@@ -13,6 +13,7 @@
 // are formed on line: running maximum, rescaled sums.  b = 1024, k = 256, D = 400, TransE-L2 on the FB15k-sized graph: 60 us
 // = 420 MB of rows at 7 TB/s, where gather, forward and backward products took 128 + 111 + 604 us.
 #include "k_gemm_shared.h"
+#include "k_weights.h"
 
 namespace {
 
@@ -66,7 +67,8 @@ template <int SUB> __device__ __forceinline__ float sub_pick(float v, int q, int
 
 // MODE: IND_SCORE forward only; IND_UNIFORM logistic loss with weights 1/k; IND_GENERAL softmax weights and / or the
 // ranking loss.  A row is NV 16-byte pieces per lane (complex models: NV pairs of a real and an imaginary piece).
-template <int MODEL, int SUB, int NV, int MODE, bool BF>
+// LONG: more than KGE_SHORT_SCORES corrupting rows per positive.
+template <int MODEL, int SUB, int NV, int MODE, bool BF, bool LONG>
 __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
     constexpr bool CPLX = MODEL == KGE_COMPLEX || MODEL == KGE_ROTATE;
     constexpr bool DOT = MODEL == KGE_DISTMULT || MODEL == KGE_COMPLEX;
@@ -251,7 +253,13 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
         float w;
         if (MODE == IND_UNIFORM) {
             float l = 0.f;
-            w = w_and_loss<!BF>(f, a.wk, l);
+            if (DOT || MODEL == KGE_TRANSE_L2) {  // as the products of larger chunks do for rows of any length
+                w = w_and_loss<!BF>(f, a.wk, l);
+            } else {
+                float sg;
+                softplus_sigmoid_of<LONG>(f, l, sg);
+                w = a.wk * sg;
+            }
             if (MODEL == KGE_TRANSE_L2) w = d > 0.f ? w * (BF ? rcp_refined(d) : __builtin_amdgcn_rcpf(d)) : 0.f;
             if (BF) w = round_bf16(w);
             if (!real) w = 0.f;
@@ -267,22 +275,23 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
                 mx = fmaxf(mx, __shfl_xor(mx, SUB / 2, 64));
                 mx = fmaxf(mx, __shfl_xor(mx, SUB / 4, 64));
                 if (mx > m) {  // (the same in all lanes of the group)
-                    const float r = __builtin_amdgcn_exp2f((m - mx) * 1.4426950408889634f);
+                    const float r = softmax_exp<LONG>(m - mx);
                     z *= r; li *= r; active *= r;
 #pragma unroll
                     for (int x = 0; x < 4 * NP; ++x) go[x] *= r;
                     m = mx;
                 }
                 // (m is still -inf where every score so far was, i.e. distances beyond the floats: weight 0)
-                e = real && m > -INFINITY ? __builtin_amdgcn_exp2f((a.alpha * f - m) * 1.4426950408889634f) : 0.f;
+                e = real && m > -INFINITY ? softmax_exp<LONG>(a.alpha * f - m) : 0.f;
             }
             if (a.ranking) {
                 const float t = a.gamma - fp + f;
                 w = t > 0.f ? e : 0.f;
                 if (owner) { li += e * fmaxf(t, 0.f); active += w; z += e; }
             } else {
-                float sp = 0.f;
-                w = w_and_loss<true>(f, e, sp);
+                float sp, sg;
+                softplus_sigmoid_of<LONG>(f, sp, sg);
+                w = e * sg;
                 if (owner) { li += e * sp; z += e; }
             }
             if (MODEL == KGE_TRANSE_L2) w = d > 0.f ? w * __builtin_amdgcn_rcpf(d) : 0.f;
@@ -321,7 +330,7 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
         for (int q = 0; q < NS; ++q) gm = fmaxf(gm, s_m[q]);
     }
     for (int q = 0; q < NS; ++q) {
-        const float r = soft ? __builtin_amdgcn_exp2f((s_m[q] - gm) * 1.4426950408889634f) : 1.f;
+        const float r = soft ? softmax_exp<LONG>(s_m[q] - gm) : 1.f;
         gz += r * s_z[q]; gl += r * s_l[q]; ga += r * s_act[q];
     }
     const float invb = 1.f / (float)a.b;
@@ -330,10 +339,14 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
         for (int j = tid; j < k; j += IT) {
             const float raw = Srow[j];
             const float f = MODEL == KGE_TRANSE_L2 ? a.gamma - raw : raw;
-            const float e = soft ? __builtin_amdgcn_exp2f((a.alpha * f - gm) * 1.4426950408889634f) : 1.f;
-            float sp = 0.f, w;
-            if (a.ranking) w = a.gamma - fp + f > 0.f ? e * wz : 0.f;
-            else w = w_and_loss<true>(f, e * wz, sp);
+            const float e = soft ? softmax_exp<LONG>(a.alpha * f - gm) : 1.f;
+            float sp, sg, w;
+            if (a.ranking) {
+                w = a.gamma - fp + f > 0.f ? e * wz : 0.f;
+            } else {
+                softplus_sigmoid_of<LONG>(f, sp, sg);
+                w = e * wz * sg;
+            }
             if (MODEL == KGE_TRANSE_L2) w = raw > 0.f ? w * __builtin_amdgcn_rcpf(raw) : 0.f;
             Srow[j] = w;
         }
@@ -341,12 +354,12 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
     if (sub > 0) return;
     const float scale = MODE == IND_GENERAL ? invb / gz : 1.f;
     if (soft) {
-        const float r = __builtin_amdgcn_exp2f((m - gm) * 1.4426950408889634f);
+        const float r = softmax_exp<LONG>(m - gm);
 #pragma unroll
         for (int e = 0; e < 4 * NP; ++e) go[e] *= r;
     }
     for (int q = 1; q < NS; ++q) {
-        const float r = soft ? __builtin_amdgcn_exp2f((s_m[q] - gm) * 1.4426950408889634f) : 1.f;
+        const float r = soft ? softmax_exp<LONG>(s_m[q] - gm) : 1.f;
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const float4 v = part[q - 1][p * SUB + ln];
@@ -468,10 +481,14 @@ template <int MODEL, int SUB, int NV>
 void launch_mode(kge_ctx* c, const IndArgs& a, int mode, hipStream_t st) {
     constexpr bool HAS_BF = MODEL == KGE_TRANSE_L2 || MODEL == KGE_DISTMULT || MODEL == KGE_COMPLEX;
     const dim3 grid(a.b), block(IT);
-    if (mode == IND_SCORE) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_SCORE, false>), grid, block, 0, st, a);
-    else if (mode == IND_GENERAL) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_GENERAL, false>), grid, block, 0, st, a);
-    else if (HAS_BF && c->cfg.gemm_input == 1) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_UNIFORM, HAS_BF>), grid, block, 0, st, a);
-    else KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_UNIFORM, false>), grid, block, 0, st, a);
+    constexpr bool PAIR = !HAS_BF;
+    const bool lng = a.k > KGE_SHORT_SCORES;
+    if (mode == IND_SCORE) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_SCORE, false, false>), grid, block, 0, st, a);
+    else if (mode == IND_GENERAL && lng) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_GENERAL, false, true>), grid, block, 0, st, a);
+    else if (mode == IND_GENERAL) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_GENERAL, false, false>), grid, block, 0, st, a);
+    else if (HAS_BF && c->cfg.gemm_input == 1) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_UNIFORM, HAS_BF, false>), grid, block, 0, st, a);
+    else if (PAIR && lng) KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_UNIFORM, false, PAIR>), grid, block, 0, st, a);
+    else KGE_LAUNCH(c, (k_ind<MODEL, SUB, NV, IND_UNIFORM, false, false>), grid, block, 0, st, a);
 }
 
 template <int MODEL>

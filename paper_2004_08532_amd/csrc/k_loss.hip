@@ -10,23 +10,9 @@
 // and dL/df+_i = -sum_j w_ij [term > 0] / b comes out of the same pass over the row.
 // k_chain: one wavefront per positive.  Adds the positive pair's own term to dL/do, pushes it through
 // o = phi(a, r) and writes the three gradient rows of the positive (kept entity, replaced entity, relation).
-#include "kge_common.h"
+#include "k_weights.h"
 
 namespace {
-
-__device__ __forceinline__ float sigmoidf_(float x) {
-    if (x >= 0.f) return 1.f / (1.f + expf(-x));
-    const float e = expf(x);
-    return e / (1.f + e);
-}
-__device__ __forceinline__ float softplusf_(float x) { return fmaxf(x, 0.f) + log1pf(expf(-fabsf(x))); }
-// Both at once for a negative score, from one exponential, with the hardware exp2 / log2 / reciprocal (1 ulp each,
-// about 1e-6 relative: the size of the rounding of the fp32 products that the results go into)
-__device__ __forceinline__ void softplus_sigmoid(float f, float& sp, float& sg) {
-    const float e = __builtin_amdgcn_exp2f(-fabsf(f) * 1.4426950408889634f);  // exp(-|f|) in (0, 1]
-    sp = fmaxf(f, 0.f) + __builtin_amdgcn_logf(1.f + e) * 0.6931471805599453f;
-    sg = (f >= 0.f ? 1.f : e) * __builtin_amdgcn_rcpf(1.f + e);
-}
 
 struct LossArgs {
     float* S;  // in: negative scores (distances when is_dist); out: W
@@ -107,7 +93,7 @@ __global__ __launch_bounds__(256) void k_loss(LossArgs a) {
     }
 }
 
-// rows longer than 1024 scores: the same with three passes over memory
+// rows of more than KGE_SHORT_SCORES scores: the same with three passes over memory
 __global__ __launch_bounds__(256) void k_loss_long(LossArgs a) {
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);

@@ -18,6 +18,7 @@
 // them (softmax weights, logistic or ranking loss), and one workgroup per tile of positives sums the loss: there is no loss
 // kernel between the two launches.
 // Nothing is accumulated with atomics.
+#include "k_weights.h"
 #include "kge_common.h"
 
 namespace {
@@ -154,18 +155,9 @@ struct PairBwdArgs {
     float* loss_part;          // a sum per workgroup of the first range of coordinates
 };
 
-// exp of the softmax weights (argument <= 0): the operations that k_loss uses, so that W has the same bits whichever kernel
-// forms it.  Rows of up to 1024 scores take the hardware exp2, longer ones the library's exp.  The
-// reason is these bits, not a better result: ten free-running steps of the medium RotatE configuration, share of relation
-// elements off by 1e-4 from the 64-bit run, four seeds: 0.7 / 1.4 / 2.3 / 2.4e-4; with the separate loss kernel that this
-// launch replaced 0.7 / 1.5 / 1.9 / 2.5e-4.  Library functions times 1 / (b z) gave 1.4 and 2.9e-4 on the first and third.
-// The spread over seeds is larger than the differences between forms.
-__device__ __forceinline__ float softmax_exp(float x, int k) {
-    return k <= 1024 ? __builtin_amdgcn_exp2f(x * 1.4426950408889634f) : expf(x);
-}
-
 // What a wave needs to know of all scores of a positive: the maximum mx and the sum z of the softmax weights
 // exp(alpha f - mx) / z (uniform weights: z = k), and, for the ranking loss, dL/df+ (only where `pos` is set).
+template <bool LONG>
 __device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float* s, int k, float gamma, bool pos, int64_t row, float& mx, float& z) {
     const int lane = threadIdx.x & 63;
     mx = 0.f;
@@ -191,7 +183,7 @@ __device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             if (j0 + 64 * u + lane < k) {
-                const float e = t.alpha > 0.f ? softmax_exp(t.alpha * v[u] - mx, k) : 1.f;
+                const float e = t.alpha > 0.f ? softmax_exp<LONG>(t.alpha * v[u] - mx) : 1.f;
                 z += e;
                 on += gamma - fp + v[u] > 0.f ? e : 0.f;
             }
@@ -215,7 +207,8 @@ __device__ __forceinline__ void pair_row_stats(const PairBwdArgs& t, const float
 // k = 256, D = 400 78 -> 76 us, TransE-L1 b = 1440, g = 96, k = 138, D = 468 149 -> 80 us.
 // Held to 128 registers: 16 wavefronts per CU, four on every SIMD.
 // WALKS: a workgroup has several tiles of positives (where a set of partial rows for each would not fit the workspace).
-template <bool CPLX, int TI, bool WALKS>
+// LONG: rows of more than KGE_SHORT_SCORES scores.
+template <bool CPLX, int TI, bool WALKS, bool LONG>
 __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
     constexpr int WPITCH = TI + 4;                 // floats per staged row of W^T
     constexpr int PART = CPLX ? 2 : 1;
@@ -254,7 +247,7 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
         for (int s = wave; s < gi; s += n_waves) {
             const int64_t row = (int64_t)c * a.g + i0 + s;
             float mx, z;
-            pair_row_stats(t, Sc + (int64_t)(i0 + s) * a.ld_s, a.k, a.gamma, jt == 0 && col == 0, row, mx, z);
+            pair_row_stats<LONG>(t, Sc + (int64_t)(i0 + s) * a.ld_s, a.k, a.gamma, jt == 0 && col == 0, row, mx, z);
             if (lane == 0) { row_mx[s] = mx; row_z[s] = z; }
         }
         for (int j0 = jb0; j0 < jb1; j0 += t.tjb) {
@@ -273,16 +266,17 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
                     for (int u = 0; u < 4; ++u) f[u] = S[min(jb + 64 * u, jn - 1)];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
-                        float w = (t.alpha > 0.f ? softmax_exp(t.alpha * f[u] - mx, a.k) : 1.f) / z;
+                        float w = (t.alpha > 0.f ? softmax_exp<LONG>(t.alpha * f[u] - mx) : 1.f) / z;
                         const bool on = ok && jb + 64 * u < jn;
                         if (t.ranking) {
                             const float m = a.gamma - fp + f[u];
                             li += on ? w * fmaxf(m, 0.f) : 0.f;
                             w = m > 0.f ? w * t.invb : 0.f;
                         } else {
-                            const float e = __builtin_amdgcn_exp2f(-fabsf(f[u]) * 1.4426950408889634f);  // exp(-|f|) in (0, 1]
-                            li += on ? w * (fmaxf(f[u], 0.f) + __builtin_amdgcn_logf(1.f + e) * 0.6931471805599453f) : 0.f;
-                            w = w * ((f[u] >= 0.f ? 1.f : e) * __builtin_amdgcn_rcpf(1.f + e)) * t.invb;
+                            float sp, sg;
+                            softplus_sigmoid_of<LONG>(f[u], sp, sg);
+                            li += on ? w * sp : 0.f;
+                            w = w * sg * t.invb;
                         }
                         if (jb + 64 * u < jn) lds[(jb + 64 * u) * WPITCH + s] = ok ? w : 0.f;
                     }
@@ -414,16 +408,22 @@ int kge_pair_neg_backward(kge_ctx* c, int b, int k, int gsz, float gamma, hipStr
     const int lds = pair_bwd_lds(cplx, p.ti, p.ng, p.cpp, t.tjb);
     const dim3 grid(p.i_parts * p.pj * p.n_col, chunks), block((p.ng * p.cpp + 63) / 64 * 64);
     const bool walks = p.i_parts < p.n_i;
+#define KGE_BWD(CPLX, TI, WALKS)                                                                              \
+    do {                                                                                                      \
+        if (k > KGE_SHORT_SCORES) KGE_LAUNCH(c, (k_pair_bwd<CPLX, TI, WALKS, true>), grid, block, lds, st, a, t); \
+        else KGE_LAUNCH(c, (k_pair_bwd<CPLX, TI, WALKS, false>), grid, block, lds, st, a, t);                 \
+    } while (0)
     if (cplx) {
-        if (walks) KGE_LAUNCH(c, (k_pair_bwd<true, 16, true>), grid, block, lds, st, a, t);
-        else if (p.ti == 8) KGE_LAUNCH(c, (k_pair_bwd<true, 8, false>), grid, block, lds, st, a, t);
-        else KGE_LAUNCH(c, (k_pair_bwd<true, 16, false>), grid, block, lds, st, a, t);
+        if (walks) KGE_BWD(true, 16, true);
+        else if (p.ti == 8) KGE_BWD(true, 8, false);
+        else KGE_BWD(true, 16, false);
     } else {
-        if (walks) KGE_LAUNCH(c, (k_pair_bwd<false, 16, true>), grid, block, lds, st, a, t);
-        else if (p.ti == 8) KGE_LAUNCH(c, (k_pair_bwd<false, 8, false>), grid, block, lds, st, a, t);
-        else if (p.ti == 16) KGE_LAUNCH(c, (k_pair_bwd<false, 16, false>), grid, block, lds, st, a, t);
-        else KGE_LAUNCH(c, (k_pair_bwd<false, 32, false>), grid, block, lds, st, a, t);
+        if (walks) KGE_BWD(false, 16, true);
+        else if (p.ti == 8) KGE_BWD(false, 8, false);
+        else if (p.ti == 16) KGE_BWD(false, 16, false);
+        else KGE_BWD(false, 32, false);
     }
+#undef KGE_BWD
     // the chain launch that follows adds up the partial rows
     c->go_partial = {c->pair_part_o, c->GO, p.pj, rows_o, rows_o / 4};
     c->neg_partial = {c->pair_part_n, Gneg, p.i_parts, rows_n, rows_n / 4};

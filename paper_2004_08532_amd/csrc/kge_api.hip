@@ -8,6 +8,7 @@
 #include <new>
 
 #include "kge_common.h"
+#include "k_weights.h"
 
 // Scratch memory of kge_score_noalloc, the one entry point that allocates nothing: a fixed array in the library's
 // device image (every GPU that runs the library holds its own copy until the process ends).  In host code the name
@@ -126,7 +127,8 @@ struct ProfScope {
 // neg_backward = the back-projection, rel_update, update; dL/dM is not timed.
 int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids,
                         int K, int G, float gamma, float lr, bool long_lists, hipStream_t st) {
-    const bool form_w = kge_gemm_backward_forms_w(c);
+    // (rows of more than KGE_SHORT_SCORES scores: the loss kernel, with the functions it has for them)
+    const bool form_w = kge_gemm_backward_forms_w(c) && K <= KGE_SHORT_SCORES;
     int n_loss_parts;
     {
         ProfScope p(c, KGE_PROF_PHI);

@@ -89,3 +89,34 @@ def test_transr_rows_close_to_each_other(kge, D, k):
     # coefficients: hardware exp2 and reciprocal of an argument below 1, four roundings; terms and their sum (errors of
     # either sign, so that the norm of a row has that of its largest terms), Adagrad's square and its root
     assert max(err) <= 16 * ULP, err
+
+
+def far_negatives(model, b, g, k, D=8):
+    """Positives of small scores, negatives (no two of them the same row) of scores between -36 and -24 at a margin of 12."""
+    rng = np.random.default_rng(4)
+    n = b // g * k
+    if model == "transe_l2":  # one coordinate apart, so that distances are exact
+        far = np.zeros((n, D))
+        far[np.arange(n), rng.integers(0, D, n)] = rng.integers(38 * 4, 46 * 4, n) / 4
+    else:
+        step = {"transe_l1": [4.75, 5.0, 5.25, 5.5], "transr": [2.0, 2.25, 2.5]}[model]
+        far = rng.choice(step, (n, D)) * rng.choice([-1.0, 1.0], (n, D))
+    E = np.concatenate([np.zeros((b, D)), np.zeros((b, D)), far]).astype(np.float32)
+    E[np.arange(b, 2 * b), rng.integers(0, D, b)] = 0.25
+    R = np.zeros((3, D + D * D if model == "transr" else D), np.float32)
+    if model == "transr":
+        R[:, D:] = np.eye(D).reshape(-1)
+    return E, R, np.arange(b), rng.integers(0, 3, b), np.arange(b, 2 * b), np.arange(2 * b, 2 * b + n).reshape(b // g, k), g, 12.0
+
+
+@pytest.mark.parametrize("k", [1024, 1056])
+@pytest.mark.parametrize("model,g,alpha", [("transe_l1", 2, 0.0), ("transe_l1", 2, 0.5), ("transe_l1", 1, 0.0),
+                                           ("transe_l1", 1, 0.5), ("transe_l2", 1, 0.5), ("transr", 2, 0.0)])
+def test_coefficients_of_far_negatives(kge, model, g, alpha, k):
+    """W = w sigmoid(f) / b of scores around -30, where the argument of the hardware exp2 has lost four bits."""
+    args = far_negatives(model, 4, g, k) + (alpha, "logistic")
+    err = worst_row(gradients(kge, model, *args)[0], gradients64(model, *args)[0])
+    print("\n[precision] far negatives", model, g, alpha, k, "%.1f roundings" % (err / ULP))
+    # rows of more than 1024 scores: library exp (2), division, weight, product with it (3), their sum over positives and
+    # its square (2); softmax: exp (2), sum (3), division (1).  Others: and half an ulp of 36 log2(e) (27), reciprocal (2)
+    assert err <= (14 if k > 1024 else 43) * ULP, err / ULP
