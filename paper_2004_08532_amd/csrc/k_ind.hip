@@ -294,7 +294,7 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
                 w = e * sg;
                 if (owner) { li += e * sp; z += e; }
             }
-            if (MODEL == KGE_TRANSE_L2) w = d > 0.f ? w * __builtin_amdgcn_rcpf(d) : 0.f;
+            if (MODEL == KGE_TRANSE_L2) w = d > 0.f ? w / d : 0.f;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(IT) void k_ind(IndArgs a) {
                 softplus_sigmoid_of<LONG>(f, sp, sg);
                 w = e * wz * sg;
             }
-            if (MODEL == KGE_TRANSE_L2) w = raw > 0.f ? w * __builtin_amdgcn_rcpf(raw) : 0.f;
+            if (MODEL == KGE_TRANSE_L2) w = raw > 0.f ? w / raw : 0.f;
             Srow[j] = w;
         }
     }

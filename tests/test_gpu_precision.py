@@ -120,3 +120,20 @@ def test_coefficients_of_far_negatives(kge, model, g, alpha, k):
     # rows of more than 1024 scores: library exp (2), division, weight, product with it (3), their sum over positives and
     # its square (2); softmax: exp (2), sum (3), division (1).  Others: and half an ulp of 36 log2(e) (27), reciprocal (2)
     assert err <= (14 if k > 1024 else 43) * ULP, err / ULP
+
+
+@pytest.mark.parametrize("g", [1, 4])
+def test_coefficients_are_divided_by_the_distance(kge, g):
+    """TransE-L2 with the ranking loss, weights 1 / 256, distances 3, 5, 7 ...: the gradient of a corrupting row is the weight
+    divided by the distance, rounded once, times the distance."""
+    D, b, k = 8, 4, 64
+    n = b // g * k
+    d = (2 * np.arange(n) + 3).astype(np.float32)
+    E = np.zeros((2 * b + n, D), np.float32)
+    E[2 * b + np.arange(n), np.arange(n) % D] = d
+    h, t = np.arange(b), np.arange(b, 2 * b)
+    E[t, 0] = 1.0
+    got = gradients(kge, "transe_l2", E, np.zeros((1, D), np.float32), h, np.zeros(b, np.int64), t,
+                    np.arange(2 * b, 2 * b + n).reshape(b // g, k), g, 1024.0, 0.0, "ranking")[0]
+    want = (np.float32(1 / (b * k)) / d * np.float32(g) * d) ** 2  # the state, in 32 bits
+    assert np.array_equal(got[2 * b + np.arange(n), np.arange(n) % D], np.sqrt(want.astype(np.float64)))
