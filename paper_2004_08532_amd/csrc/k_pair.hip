@@ -212,9 +212,11 @@ template <bool CPLX, int TI, bool WALKS, bool LONG>
 __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
     constexpr int WPITCH = TI + 4;                 // floats per staged row of W^T
     constexpr int PART = CPLX ? 2 : 1;
-    // TransE-L1: coordinates are held times 2^64 (exactly, for anything below 2^63), so that the clamp of a difference
-    // to [-w, w] is w sign(difference), 0 for 0: one v_med3 where two compares and two selects stood
-    constexpr float SCALE = CPLX ? 1.f : 18446744073709551616.f;
+    // TransE-L1: coordinates are held times 2^64, so that the clamp of a difference to [-w, w], w <= 1, is w sign(difference), 0
+    // for 0: one v_med3 where two compares and two selects stood.  That holds if one of the two coordinates is 2^-40 or more
+    // (they differ by 2^-64 then, or not at all); a thread compares where both may be smaller, and, unscaled, where one of
+    // its o rows has a coordinate from 2^63 on.
+    constexpr float SMALL = 0x1p24f;  // (2^-40, scaled)
     extern __shared__ __attribute__((aligned(16))) float lds[];  // W^T of the block [negative][WPITCH]; later group sums
     __shared__ float row_mx[TI], row_z[TI], row_li[16];
     const int tid = threadIdx.x, cpp = t.cpp, wave = tid >> 6, lane = tid & 63, n_waves = blockDim.x >> 6;
@@ -240,9 +242,22 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
 #pragma unroll
         for (int s = 0; s < TI; ++s) {
             const float* po = Oc + (int64_t)(i0 + (s < gi ? s : 0)) * a.D + ccs;
-            x_re[s] = po[0] * SCALE;
+            x_re[s] = po[0];
             g_re[s] = 0.f;
             if (CPLX) { x_im[s] = po[NC]; g_im[s] = 0.f; }
+        }
+        float scale = 1.f, y_least = 0.f;  // smallest |y| that all of x can be clamped against
+        if (!CPLX) {
+            bool large = false, small = false;
+#pragma unroll
+            for (int s = 0; s < TI; ++s) large |= !(fabsf(x_re[s]) < 0x1p63f);
+            scale = large ? 1.f : 0x1p64f;
+#pragma unroll
+            for (int s = 0; s < TI; ++s) {
+                x_re[s] *= scale;
+                small |= fabsf(x_re[s]) < SMALL;
+            }
+            y_least = large ? INFINITY : small ? SMALL : 0.f;
         }
         for (int s = wave; s < gi; s += n_waves) {
             const int64_t row = (int64_t)c * a.g + i0 + s;
@@ -291,7 +306,7 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
             // and its use, and waiting for that store would cost more than the round's arithmetic
             uint32_t off = 4u * (grp * a.D + cc);
             uint32_t nxt = min(off + step, last);
-            float y_re = *(const float*)(nb + off) * SCALE, y_im = CPLX ? *(const float*)(nb + im + off) : 0.f;
+            float y_re = *(const float*)(nb + off) * scale, y_im = CPLX ? *(const float*)(nb + im + off) : 0.f;
             float y1_re = *(const float*)(nb + nxt), y1_im = CPLX ? *(const float*)(nb + im + nxt) : 0.f;
             for (int jj = grp; jj < jn; jj += t.ng) {
                 float n_re = 0.f, n_im = 0.f;
@@ -301,33 +316,42 @@ __global__ __launch_bounds__(1024) void k_pair_bwd(PairArgs a, PairBwdArgs t) {
                 }
                 nxt = min(nxt + step, last);
                 const float z_re = *(const float*)(nb + nxt), z_im = CPLX ? *(const float*)(nb + im + nxt) : 0.f;
+                if (!CPLX && !(fabsf(y_re) >= y_least)) {
 #pragma unroll
-                for (int s4 = 0; s4 < TI; s4 += 4) {
-                    const float4 w4 = ld4(&lds[jj * WPITCH + s4]);
-                    const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
+                    for (int s = 0; s < TI; ++s) {
+                        const float w = lds[jj * WPITCH + s], v = x_re[s] > y_re ? w : (x_re[s] < y_re ? -w : 0.f);
+                        g_re[s] -= v;
+                        n_re += v;
+                    }
+                } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int s = s4 + e;
-                        const float q_re = x_re[s] - y_re;  // o - n
-                        if (CPLX) {
-                            const float q_im = x_im[s] - y_im;
-                            // w / |q|; q = 0 gives a finite factor times 0
-                            const float f = wv[e] * __builtin_amdgcn_rsqf(fmaf(q_im, q_im, fmaf(q_re, q_re, 1.2e-38f)));
-                            g_re[s] = fmaf(-f, q_re, g_re[s]);
-                            g_im[s] = fmaf(-f, q_im, g_im[s]);
-                            n_re = fmaf(f, q_re, n_re);
-                            n_im = fmaf(f, q_im, n_im);
-                        } else {
-                            const float v = __builtin_amdgcn_fmed3f(q_re, -wv[e], wv[e]);
-                            g_re[s] -= v;
-                            n_re += v;
+                    for (int s4 = 0; s4 < TI; s4 += 4) {
+                        const float4 w4 = ld4(&lds[jj * WPITCH + s4]);
+                        const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int s = s4 + e;
+                            const float q_re = x_re[s] - y_re;  // o - n
+                            if (CPLX) {
+                                const float q_im = x_im[s] - y_im;
+                                // w / |q|; q = 0 gives a finite factor times 0
+                                const float f = wv[e] * __builtin_amdgcn_rsqf(fmaf(q_im, q_im, fmaf(q_re, q_re, 1.2e-38f)));
+                                g_re[s] = fmaf(-f, q_re, g_re[s]);
+                                g_im[s] = fmaf(-f, q_im, g_im[s]);
+                                n_re = fmaf(f, q_re, n_re);
+                                n_im = fmaf(f, q_im, n_im);
+                            } else {
+                                const float v = __builtin_amdgcn_fmed3f(q_re, -wv[e], wv[e]);
+                                g_re[s] -= v;
+                                n_re += v;
+                            }
                         }
                     }
                 }
                 *(float*)(db + off) = n_re;
                 if (CPLX) *(float*)(db + im + off) = n_im;
                 off += step;
-                y_re = y1_re * SCALE; y_im = y1_im;
+                y_re = y1_re * scale; y_im = y1_im;
                 y1_re = z_re; y1_im = z_im;
             }
         }

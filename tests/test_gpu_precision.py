@@ -137,3 +137,20 @@ def test_coefficients_are_divided_by_the_distance(kge, g):
                     np.arange(2 * b, 2 * b + n).reshape(b // g, k), g, 1024.0, 0.0, "ranking")[0]
     want = (np.float32(1 / (b * k)) / d * np.float32(g) * d) ** 2  # the state, in 32 bits
     assert np.array_equal(got[2 * b + np.arange(n), np.arange(n) % D], np.sqrt(want.astype(np.float64)))
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -140, 2.0 ** -100, 2.0 ** -70, 1.0, 2.0 ** 66])
+@pytest.mark.parametrize("g", [1, 24])
+def test_signs_of_small_and_large_differences(kge, g, scale):
+    """TransE-L1: the gradient depends on the sign of o - n alone, however small or large the coordinates are (the smallest
+    scale: differences below the normal numbers), 0 where they are equal."""
+    D, b, k = 24, 48, 40
+    rng = np.random.default_rng(6)
+    E = (rng.integers(-8, 9, (2 * b + b // g * k, D)) * scale).astype(np.float32)
+    R = (rng.integers(-2, 3, (3, D)) * scale).astype(np.float32)
+    ids = rng.permutation(E.shape[0])
+    args = (E, R, ids[:b], rng.integers(0, 3, b), ids[b:2 * b], ids[2 * b:].reshape(b // g, k), g, 64.0 * max(scale, 1.0), 0.0, "ranking")
+    (gE, gR), (wE, wR) = gradients(kge, "transe_l1", *args), gradients64("transe_l1", *args)
+    # sums of terms +-w and 0, w = 1 / (b k): one rounding per term of a sum that never passes 1 / b in a row of o
+    for got, want in ((gE, wE), (gR, wR)):
+        np.testing.assert_allclose(got, want, rtol=1e-5, atol=64 * ULP / b)
