@@ -36,7 +36,10 @@ struct SortArgs {
     uint32_t* bases[2];    // with k_sort_offsets: [digits] number of keys with a smaller digit; slice_tot then holds the
                            // keys with the digit in the earlier slices
     int pass;
-    bool offsets[2];       // k_sort_offsets has walked the list's slices (8-bit digits)
+    // k_sort_offsets has walked the list's slices (8-bit digits).  Not bool: from a byte index that is the same in all lanes
+    // the compiler formed a scalar load of bases[which] whose base was off by the index and whose offset made up for it; the
+    // hardware drops the low two bits of each, so for list 1 it loaded a pointer from halves of two
+    int offsets[2];
 };
 
 // the lanes of the wave that hold the same digit as this lane (valid lanes only)

@@ -205,6 +205,19 @@ def test_independent_negatives(kge, model):
         p.close()
 
 
+@pytest.mark.parametrize("batch", [327_680, 329_729])
+def test_key_lists_of_very_many_slices(kge, batch):
+    """The relation list is 160 slices of 2048 keys (the most that the scatter of the radix sort walks by itself) and 161 and a
+    bit, the entity list more: their offsets come from a launch of their own."""
+    w = ragged("transe_l2", ent_dim=4, rel_dim=4, batch=batch, chunk=batch, neg_per_chunk=8, n_entities=20_000, n_relations=2000,
+               n_triples=400_000, steps=1)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps)
+    finally:
+        p.close()
+
+
 INDEPENDENT_SHAPES = {
     # rows of each lane-group width (16, 32, 64 lanes, two and four pieces per lane), key lists below and above the
     # radix sort's limit, counts of negatives around the four rows a lane group takes per round
