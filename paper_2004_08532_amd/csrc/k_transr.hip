@@ -238,9 +238,9 @@ __device__ __forceinline__ int unit_of_block(int block, int tiles, int& tile) {
     tile = n % tiles;
     return n / tiles * 8 + xcd;
 }
-dim3 unit_grid(int units, int tiles) { return dim3((units + 7) / 8 * 8 * tiles); }
-dim3 item_grid(const TransrArgs& a, int tiles) { return unit_grid(a.b / a.g * a.max_items, tiles); }
-dim3 block_grid(const TransrArgs& a, int tiles) { return unit_grid(a.b / a.g * a.max_pblocks, tiles); }
+int unit_blocks(int units, int tiles) { return (units + 7) / 8 * 8 * tiles; }
+int item_blocks(const TransrArgs& a, int tiles) { return unit_blocks(a.b / a.g * a.max_items, tiles); }
+int pblock_blocks(const TransrArgs& a, int tiles) { return unit_blocks(a.b / a.g * a.max_pblocks, tiles); }
 // The record of the unit and the number of units in its chunk are asked for together.
 __device__ __forceinline__ bool item_of(const TransrArgs& a, int unit, int& c, int& slot, TransrItem& item) {
     c = unit / a.max_items;
@@ -336,13 +336,15 @@ __global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
 // 64 corrupting rows x a block of an item's positives: projections, then the scores of the positives against them.  (An
 // item of more than 32 positives is projected once per block: at that size the scores are the larger part of the work.)
 template <int NT>
-__global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a) {
+__global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int blocks) {
     __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
     const int tiles = (a.k + BM - 1) / BM, D = a.D, tid = threadIdx.x;
     int c, tile;
     TransrBlock blk;
     float loss = 0.f;
-    const int unit = unit_of_block(blockIdx.x, tiles, tile);
+    const int block = flat_block();
+    if (block >= blocks) return;
+    const int unit = unit_of_block(block, tiles, tile);
     if (pblock_of(a, unit, c, blk)) {
         const int j0 = tile * BM, rows = min(BM, a.k - j0), n = blk.n;
         const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D;
@@ -426,7 +428,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a) {
     loss = wave_sum(loss);
     if ((tid & 63) == 0) part[tid >> 6] = loss;
     __syncthreads();
-    if (tid == 0) a.loss_part[blockIdx.x] = (part[0] + part[1] + part[2] + part[3]) * a.wk;
+    if (tid == 0) a.loss_part[block] = (part[0] + part[1] + part[2] + part[3]) * a.wk;
 }
 
 // Items of at most DP_FEW positives: the sums over an item's positives and over the corrupting rows on the vector ALUs,
@@ -513,18 +515,19 @@ __device__ void dp_few(const TransrArgs& a, int slot, int tile, const TransrItem
 // dp_few needs its three waves per SIMD.  Per step, 32 -> 64 bits: FB15k-sized 279 -> 281 us, b 1024, g 1024, k 1024, D 128,
 // 2 relations 347 -> 360, b 1024, g 128, k 256, D 100, 2 relations 134.7 both.
 template <int NT>
-__global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
+__global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks, int blocks) {
     __shared__ __attribute__((aligned(16))) float lds[A_FLOATS + B_FLOATS];
     float* As = lds;
     float* Bs = lds + A_FLOATS;
     static_assert(sizeof(float4) * MB * RT + sizeof(float) * MB * BM <= sizeof(lds), "");
-    const int D = a.D, tid = threadIdx.x, l16 = tid & 15;
+    const int D = a.D, tid = threadIdx.x, l16 = tid & 15, block = flat_block();
     int c;
-    if ((int)blockIdx.x >= go_blocks) {
+    if (block >= blocks) return;
+    if (block >= go_blocks) {
         int slot, tile;
         TransrItem item;
         const int tiles = (a.k + BM - 1) / BM;
-        if (!item_of(a, unit_of_block(blockIdx.x - go_blocks, tiles, tile), c, slot, item)) return;
+        if (!item_of(a, unit_of_block(block - go_blocks, tiles, tile), c, slot, item)) return;
         const int j0 = tile * BM, rows = min(BM, a.k - j0), n = item.n;
         if (n <= DP_FEW) {
             dp_few(a, slot, tile, item, reinterpret_cast<float4(*)[RT]>(lds), reinterpret_cast<float(*)[BM]>(lds + 4 * MB * RT));
@@ -561,9 +564,9 @@ __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks) {
         }
         return;
     }
-    const int cols = (D + DN - 1) / DN, n0 = blockIdx.x % cols * DN;
+    const int cols = (D + DN - 1) / DN, n0 = block % cols * DN;
     TransrBlock blk;
-    if (!pblock_of(a, blockIdx.x / cols, c, blk) || blk.all <= DP_FEW) return;
+    if (!pblock_of(a, block / cols, c, blk) || blk.all <= DP_FEW) return;
     const int db = n0 + 4 * (tid % 32), n = blk.n;
     const float* P = a.P + (int64_t)blk.slot * a.k * D + (db < D ? db : n0);
     const float* W[2];
@@ -787,19 +790,19 @@ struct TransrUpdArgs {
     const float* GM;
     float lr, eps;
     PartialRows rest;     // gradient rows of the corrupting entities, still in parts
-    int share;
+    int share, rest_blocks;
 };
 
 // Workgroup (p, slab): slab 0 is the translation, slab s > 0 rows (s - 1) * rows_per_slab .. of the matrix.  If sorted
 // position p is the last of its run of equal relation ids, the workgroup sums the run's gradient rows for its slab in
 // sorted order (translation: a row per positive; matrix: one per item) and applies Adagrad.
 __global__ __launch_bounds__(RT) void k_transr_update(TransrUpdArgs a) {
-    const int tid = threadIdx.x;
-    if ((int)blockIdx.x >= a.n * a.slabs) {
-        sum_partial_rows<RT>(a.rest, a.share, blockIdx.x - a.n * a.slabs, gridDim.x - a.n * a.slabs);
+    const int tid = threadIdx.x, block = flat_block(), rows_blocks = a.n * a.slabs;
+    if (block >= rows_blocks) {
+        if (block < rows_blocks + a.rest_blocks) sum_partial_rows<RT>(a.rest, a.share, block - rows_blocks, a.rest_blocks);
         return;
     }
-    const int p = blockIdx.x / a.slabs, slab = blockIdx.x % a.slabs;
+    const int p = block / a.slabs, slab = block % a.slabs;
     const uint32_t key = a.key[p];
     if (p + 1 < a.n && a.key[p + 1] == key) return;  // the run goes on (same decision in every thread)
     __shared__ int first_other, n_rows;
@@ -926,20 +929,21 @@ int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, in
                        bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, gamma);
     a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train;
-    const dim3 grid = block_grid(a, (k + BM - 1) / BM);
-#define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, grid, dim3(RT), 0, st, a)
+    const int blocks = pblock_blocks(a, (k + BM - 1) / BM);
+#define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, flat_grid(blocks), dim3(RT), 0, st, a, blocks)
     KGE_BY_COLUMNS(a.D, L);
 #undef L
-    return form_w ? (int)grid.x : 0;
+    return form_w ? blocks : 0;
 }
 
 void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, hipStream_t st) {
     const TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
     const int cols = (a.D + DN - 1) / DN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
-    const dim3 grid(go_blocks + item_grid(a, (k + BM - 1) / BM).x);
-    if (a.D <= 32) KGE_LAUNCH(c, k_transr_dp<2>, grid, dim3(RT), 0, st, a, go_blocks);
-    else if (a.D <= 48) KGE_LAUNCH(c, k_transr_dp<3>, grid, dim3(RT), 0, st, a, go_blocks);
-    else KGE_LAUNCH(c, k_transr_dp<4>, grid, dim3(RT), 0, st, a, go_blocks);
+    const int blocks = go_blocks + item_blocks(a, (k + BM - 1) / BM);
+    const dim3 grid = flat_grid(blocks);
+    if (a.D <= 32) KGE_LAUNCH(c, k_transr_dp<2>, grid, dim3(RT), 0, st, a, go_blocks, blocks);
+    else if (a.D <= 48) KGE_LAUNCH(c, k_transr_dp<3>, grid, dim3(RT), 0, st, a, go_blocks, blocks);
+    else KGE_LAUNCH(c, k_transr_dp<4>, grid, dim3(RT), 0, st, a, go_blocks, blocks);
     hipLaunchKernelGGL(k_transr_go, dim3((ids.b * (a.D / 4) + RT - 1) / RT), dim3(RT), 0, st, a);
 }
 
@@ -960,7 +964,7 @@ void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int 
 
 void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int gsz, hipStream_t st) {
     const TransrArgs a = make_args(c, E, nullptr, ids, k, gsz, 0.f);
-    const dim3 grid = item_grid(a, ((a.D + BM - 1) / BM) * ((a.D + BN - 1) / BN));
+    const dim3 grid(item_blocks(a, ((a.D + BM - 1) / BM) * ((a.D + BN - 1) / BN)));
 #define L(NT) KGE_LAUNCH(c, k_transr_mgrad<NT>, grid, dim3(RT), 0, st, a)
     KGE_BY_COLUMNS(a.D, L);
 #undef L
@@ -976,8 +980,8 @@ void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, floa
     a.Gr = c->Grel; a.GM = c->Grel + (int64_t)c->cfg.max_batch * D;
     a.lr = lr; a.eps = c->eps;
     a.rest = c->neg_partial;
-    const int rest_blocks = partial_rows_blocks(a.rest, a.share);
-    KGE_LAUNCH(c, k_transr_update, dim3(ids.b * a.slabs + rest_blocks), dim3(RT), 0, st, a);
+    a.rest_blocks = partial_rows_blocks(a.rest, a.share);
+    KGE_LAUNCH(c, k_transr_update, flat_grid(ids.b * a.slabs + a.rest_blocks), dim3(RT), 0, st, a);
 }
 
 // bytes of the workspace that the items of a mini-batch take (base null: only counted)

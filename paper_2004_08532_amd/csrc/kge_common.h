@@ -186,6 +186,13 @@ inline int partial_rows_blocks(const PartialRows& r, int& share) {
 }
 void kge_make_key_lists(kge_ctx* c, const StepIds& ids, KeyList* ent, KeyList* rel);
 
+// Grids of more workgroups than one dimension takes (less than 2^32 threads): rows of 2^20, in the order of flat_block().
+// What comes behind the last workgroup in the last row has to end at once.
+inline dim3 flat_grid(int64_t blocks) {
+    const int64_t row = (int64_t)1 << 20;
+    return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
+}
+
 // ---------------------------------------------------------------------------------------------------------
 // Host-side launchers (each in the source file named after its kernel group)
 // ---------------------------------------------------------------------------------------------------------
@@ -340,6 +347,7 @@ __device__ __forceinline__ float wave_max(float v) {
 __device__ __forceinline__ float4 ld4(const float* p) { return *reinterpret_cast<const float4*>(p); }
 __device__ __forceinline__ void st4(float* p, float4 v) { *reinterpret_cast<float4*>(p) = v; }
 __device__ __forceinline__ float4 f4(float x) { return make_float4(x, x, x, x); }
+__device__ __forceinline__ int flat_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
 // sum of `parts` 16-byte pieces `stride` floats apart, in order; eight of them are asked for before the first is added (a
 // part that does not exist is read from part 0 and left out of the sum)

@@ -1,10 +1,11 @@
-// A stand-in for the HIP runtime that runs nothing on any device: it hands out host memory, counts and names what is
-// launched, and fails calls on request.  Loaded into the global scope before libkge.so, it lets a test on the CPU see what
+// A stand-in for the HIP runtime that runs nothing on any device: it hands out addresses, counts and names what is launched,
+// refuses grids that the runtime refuses, and fails calls on request.  Loaded into the global scope before libkge.so, it lets a test on the CPU see what
 // the library's host code enqueues, in which order, and what it does when a call of the runtime fails.
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/mman.h>
 
 #include <map>
 #include <string>
@@ -17,6 +18,7 @@ struct Kernel { int module; std::string name; };
 struct Graph { int kernels; };
 
 std::map<const void*, Kernel>& kernels() { static std::map<const void*, Kernel> m; return m; }
+std::map<void*, size_t>& sizes() { static std::map<void*, size_t> m; return m; }
 std::string& events() { static std::string s; return s; }
 std::map<std::string, int>& failing() { static std::map<std::string, int> m; return m; }  // calls until the one that fails
 void* capturing = nullptr;
@@ -29,9 +31,14 @@ int outcome(const char* call) {
     return pending = 2;  // (out of memory)
 }
 
-int launch(const void* f, void*) {
+int launch(const void* f, Dim3 grid, Dim3 block) {
     const Kernel& k = kernels()[f];
     if (const int e = outcome("hipLaunchKernel")) return e;
+    const uint64_t most = UINT32_MAX;  // threads per dimension
+    if (!grid.x || !grid.y || !grid.z || (uint64_t)grid.x * block.x > most || (uint64_t)grid.y * block.y > most || grid.y > 65535) {
+        events() += "refused " + k.name + "\n";
+        return pending = 9;  // (invalid configuration)
+    }
     if (capturing) { ++captured; return 0; }
     char line[64];
     snprintf(line, sizeof(line), "kernel %d ", k.module);
@@ -66,8 +73,8 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** strea
     *grid = cfg_grid; *block = cfg_block; *lds = cfg_lds; *stream = cfg_stream;
     return 0;
 }
-int hipLaunchKernel(const void* f, Dim3, Dim3, void**, size_t, void* stream) { return launch(f, stream); }
-int hipExtLaunchKernel(const void* f, Dim3, Dim3, void**, size_t, void* stream, void*, void*, int) { return launch(f, stream); }
+int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, size_t, void*) { return launch(f, grid, block); }
+int hipExtLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, size_t, void*, void*, void*, int) { return launch(f, grid, block); }
 int hipGetDeviceCount(int* n) { *n = 1; return 0; }
 int hipSetDevice(int) { return 0; }
 int hipDeviceSynchronize() { return 0; }
@@ -76,10 +83,15 @@ int hipGetLastError() { const int e = pending; pending = 0; return e; }
 int hipGetSymbolAddress(void** p, const void*) { static char area[1 << 23]; *p = area; return 0; }
 int hipMalloc(void** p, size_t n) {
     if (const int e = outcome("hipMalloc")) return e;
-    *p = malloc(n);  // (untouched pages cost nothing)
-    return *p ? 0 : 2;
+    *p = mmap(nullptr, n, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);  // (addresses that nothing may touch)
+    if (*p == MAP_FAILED) return pending = 2;
+    sizes()[*p] = n;
+    return 0;
 }
-int hipFree(void* p) { free(p); return 0; }
+int hipFree(void* p) {
+    if (p) munmap(p, sizes()[p]);
+    return 0;
+}
 int hipMemset(void*, int, size_t) { return 0; }
 int hipMemsetAsync(void*, int, size_t, void*) { return 0; }
 int hipMemcpyAsync(void*, const void*, size_t, int, void*) {

@@ -349,6 +349,9 @@ TRANSR_ITEMS = {
     "large-items": dict(batch=180, chunk=90, neg_per_chunk=65, ent_dim=128, n_relations=2),
     "many-relations": dict(batch=64, chunk=32, neg_per_chunk=17, ent_dim=8, n_relations=5000, n_entities=301),
     "long-chunk": dict(batch=2100, chunk=2100, neg_per_chunk=5, ent_dim=4, n_relations=7, n_triples=9000),
+    # projections, dL/dP and relation update of more than 2^20 workgroups each: grids of two dimensions
+    "many-workgroups": dict(batch=540_000, chunk=600, neg_per_chunk=65, ent_dim=4, n_entities=60_000, n_relations=3000,
+                            n_triples=600_000, steps=1),
     "long-chunk-many-relations": dict(batch=2100, chunk=2100, neg_per_chunk=5, ent_dim=8, n_relations=4200, n_triples=9000,
                                       adv_temperature=1.0),
 }

@@ -34,11 +34,11 @@ lib.kge_train_steps.argtypes = [vp] * 5 + [vp] * 3 + [i64, vp, i64, i64, vp, i64
 
 class Library:
     """One context of `model` with b positives in chunks of g, k corrupting entities each, rows of D floats."""
-    def __init__(self, model, b=64, g=16, k=24, D=64, **kw):
+    def __init__(self, model, b=64, g=16, k=24, D=64, relations=20, **kw):
         m = MODELS.index(model)
         rel = {"rotate": D // 2, "rescal": D * D, "transr": D + D * D}.get(model, D)
         self.b, self.g, self.k = b, g, k
-        cfg = Config(model=m, num_entities=1000, num_relations=20, ent_dim=D, rel_dim=rel, max_batch=b, max_neg_per_chunk=k,
+        cfg = Config(model=m, num_entities=1000, num_relations=relations, ent_dim=D, rel_dim=rel, max_batch=b, max_neg_per_chunk=k,
                      max_chunks=b // g, **kw)
         self.ctx = vp()
         assert lib.kge_create(ctypes.byref(cfg), ctypes.byref(self.ctx)) == 0
@@ -129,3 +129,13 @@ print(json.dumps([one, got]))
 ''')
     for rc, events in got if not launch else got[:1]:
         assert rc == 0 and run_kernels(events) == n_steps * len(one[1])
+
+
+@pytest.mark.parametrize("shape", ["b=20_000, g=100, k=4, D=1024", "b=1 << 20, g=1 << 10, k=1024, D=4, relations=1_000_000"])
+def test_transr_steps_of_very_many_workgroups(recorder, shape):
+    """Workspaces of 80 and 60 GB: more workgroups of the relation update, or of the projections, than one dimension of a grid
+    takes."""
+    rc, events = drive(recorder, f'''
+print(json.dumps(Library("transr", {shape}).steps(1)))
+''')
+    assert not [e for e in events if e.startswith("refused")] and rc == 0
