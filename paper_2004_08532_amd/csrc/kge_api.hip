@@ -469,12 +469,14 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const size_t o_sc = take((sort_digits(EK) + sort_digits(B) + ((size_t)2 << KGE_SORT_MAX_BITS)) * 4);
     const bool pair_model = m == KGE_ROTATE || m == KGE_TRANSE_L1;
     const size_t o_rpw = take((EK / 4 + 4) * 4);
-    // everything from here on is written before it is read (the fill below leaves it out).  Partial rows:  A set of rows of the corrupting
-    // entities per 8 positives and per chunk at most; more than 256 MB only where 8 sets are already more
+    // everything from here on is written before it is read (the fill below leaves it out).  Partial rows: a set of rows of the
+    // corrupting entities per 8 positives of a chunk is the most that a launch writes; no more than 256 MB of them, or 8 sets
+    // per chunk where those are more (a launch that would need more walks several tiles of positives per workgroup)
     const size_t zeroed = off;
     const size_t K1 = cfg->max_neg_per_chunk > 0 ? cfg->max_neg_per_chunk : 1;
     size_t sets_n = (B / 8 + cfg->max_chunks) * K1 * D;
-    if (sets_n > (size_t)64 << 20) sets_n = 8 * NR * D > (size_t)64 << 20 ? 8 * NR * D : (size_t)64 << 20;
+    const size_t sets_cap = 8 * NR * D > (size_t)64 << 20 ? 8 * NR * D : (size_t)64 << 20;
+    sets_n = sets_n < sets_cap ? sets_n : sets_cap;
     const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? sets_n * 4 : 0);
     const size_t o_P3 = take(transr ? 2 * B * K1 * D * 4 : 0);
     const size_t o_tgo = take(transr ? kge_transr_go_floats(*cfg) * 4 : 0);

@@ -139,3 +139,13 @@ def test_transr_steps_of_very_many_workgroups(recorder, shape):
 print(json.dumps(Library("transr", {shape}).steps(1)))
 ''')
     assert not [e for e in events if e.startswith("refused")] and rc == 0
+
+
+@pytest.mark.parametrize("model,b,g,k,D,most", [("rotate", 1024, 1, 256, 400, 1.4e9),      # 118 M floats of partial rows
+                                                ("transe_l1", 1024, 8, 256, 400, 0.4e9),   # 26 M floats
+                                                ("rotate", 1024, 1024, 1024, 1024, 0.5e9)])  # 256 MB of them, not 0.5 GB
+def test_workspace_holds_the_partial_rows_that_a_step_can_write(recorder, model, b, g, k, D, most):
+    size = drive(recorder, f'''
+print(json.dumps(lib.kge_workspace_bytes(Library({model!r}, b={b}, g={g}, k={k}, D={D}).ctx)))
+''')
+    assert size < most
