@@ -1,10 +1,11 @@
 // Logistic or pairwise ranking loss (paper Sec. 2) on the positive and negative scores, its derivatives, and the chain rule from
 // dL/do back to the head / tail / relation rows (the back-propagation half of Sec. 3.1 step 3).
 //
-// k_loss: one wavefront per positive.  The k negative scores of the row are read by the 64 lanes, the optional
-// softmax weights use shuffle reductions for the maximum and the sum, and the row leaves behind the
-// coefficient matrix W that the backward products consume:
-//     W_ij = w_ij * sigmoid(f-_ij) / b               (DistMult, ComplEx, RotatE, TransE-L1)
+// k_loss: one wavefront per positive, for the models whose backward is a matrix product where the forward launch does not form W
+// itself (softmax weights, the ranking loss; TransR: also rows of more than 1024 scores).  The k negative scores of the
+// row are read by the 64 lanes, the optional softmax weights use shuffle reductions for the maximum and the sum, and the row
+// leaves behind the coefficient matrix W that the backward products consume:
+//     W_ij = w_ij * sigmoid(f-_ij) / b               (DistMult, ComplEx, RESCAL, TransR)
 //     W_ij = w_ij * sigmoid(f-_ij) / (b * dist_ij)    (TransE-L2, so that dO = W N - rowsum(W) o)
 // Ranking loss max(0, gamma - f+_i + f-_ij): sigmoid(f-_ij) is replaced by the indicator of a positive margin term,
 // and dL/df+_i = -sum_j w_ij [term > 0] / b comes out of the same pass over the row.

@@ -19,7 +19,6 @@
 // kernel between the two launches.
 // Nothing is accumulated with atomics.
 #include "k_weights.h"
-#include "kge_common.h"
 
 namespace {
 
@@ -30,11 +29,9 @@ constexpr int PPITCH = 36;   // floats per staged row: 16-byte aligned rows
 struct PairArgs {
     const float* O;    // [b x D]
     const float* Nst;  // [C*k x D]
-    float* S;          // forward: out [b x ld_s]; backward: W in
+    float* S;          // [b x ld_s] scores: out of the forward, into the backward
     int ld_s, g, k, D;
     float gamma;
-    float* GO;         // [b x D]
-    float* Gneg;       // [C*k x D] gradient rows of the corrupting entities
 };
 
 template <bool CPLX>

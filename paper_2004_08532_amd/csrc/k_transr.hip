@@ -12,7 +12,7 @@
 //   (k_gather)        the items of every chunk (k_transr_items.h), beside the corrupting rows and the order of the keys
 //   k_transr_phi      o_i, p_i = M_i c_i: an item's a and c rows times M^T; the positive's score and logistic-loss terms
 //   k_transr_project  P_t = N_c M_t^T, and in its epilogue S_ij = gamma - |o_i - P_tj|^2 for the item's positives
-//                     (logistic loss with uniform weights: W = dL/df-, no loss kernel)
+//                     (logistic loss with uniform weights, up to 1024 scores per row: W = dL/df-, no loss kernel)
 //   (k_loss)          W otherwise
 //   k_transr_dp       V_tj = sum over the item's positives of 2 W_ij (o_i - P_tj); dL/do_i = - sum_j of the same terms
 //                     - 2 cpos (o - p), dL/dp_i = 2 cpos (o - p), gradient of the translation (k_transr_go ends these for

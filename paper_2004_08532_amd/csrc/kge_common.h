@@ -331,9 +331,6 @@ __device__ __forceinline__ uint32_t clamp_key(const KeyList& l, int64_t id) {
     id = id < 0 ? 0 : (id >= l.n_ids ? l.n_ids - 1 : id);
     return (uint32_t)id;
 }
-__device__ __forceinline__ uint32_t fetch_key(const KeyList& l, int idx) {
-    return clamp_key(l, *key_address(l, key_sources(l), idx));
-}
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -72,7 +72,10 @@ TRAJECTORY_OUTLIERS = {
     "tiny": (1e-4, 1e-5),                  # measured 4.7e-5 / 0
     "small-distmult": (1e-2, 5e-3),        # measured 4.7e-3 / 2.5e-3
     "small-complex": (5.4e-2, 2.8e-2),     # measured 2.7e-2 / 1.4e-2
-    "medium": (2.6e-5, 1.3e-4),            # measured 1.3e-5 / 6.3e-5   (50,000 entities)
+    # medium (50,000 entities): median over eight seeds.  One seed says nothing about a form of the kernels: their shares spread
+    # from 1.1e-5 to 5.1e-4 / 6.9e-5 to 3.0e-3, and which seed is worse changes with every form.  Medians measured 2.7e-5 /
+    # 2.1e-4 with a loss kernel of its own before the backward, 2.7e-5 / 2.3e-4 with W formed in the backward.
+    "medium": (5.5e-5, 4.2e-4),
     "freebase-transe_l2": (1e-5, 1e-5),    # measured 1.5e-6 / 6.7e-7   (200,003 entities)
     "freebase-complex": (7.3e-5, 4.6e-4),  # measured 3.6e-5 / 2.3e-4   (200,003 entities)
 }
@@ -278,19 +281,18 @@ def test_chunks_of_one_positive_with_scores_beyond_the_floats(kge, model, loss):
 
 
 PAIR_BACKWARD_SHAPES = {
-    # chunks of up to 128 positives take the backward in which a workgroup owns 16 positives x a range of negatives
-    # and writes partial rows; here with 8 i-tiles of which the last is ragged, and 8 ranges of 22 negatives
-    "tiled": dict(batch=250, chunk=125, neg_per_chunk=173),
-    # rows of 840 floats: the tiled backward walks the coordinates in several passes
-    "tiled-long-rows": dict(batch=80, chunk=40, neg_per_chunk=23, ent_dim=840),
-    # longer chunks would need too many partial rows: workgroups that own rows of one side only
-    "per-side": dict(batch=300, chunk=150, neg_per_chunk=70),
+    # two chunks whose last tile of positives is ragged whatever the tile, several ranges of negatives
+    "ragged-tiles": dict(batch=250, chunk=125, neg_per_chunk=173),
+    # rows of 840 floats: the coordinates are cut into ranges
+    "long-rows": dict(batch=80, chunk=40, neg_per_chunk=23, ent_dim=840),
+    # more positives than negatives in a chunk
+    "long-chunks": dict(batch=300, chunk=150, neg_per_chunk=70),
 }
 
 
 @pytest.mark.parametrize("shape", sorted(PAIR_BACKWARD_SHAPES))
 @pytest.mark.parametrize("model", ["rotate", "transe_l1"])
-def test_both_forms_of_the_elementwise_backward(kge, model, shape):
+def test_elementwise_backward(kge, model, shape):
     kw = dict(PAIR_BACKWARD_SHAPES[shape])
     if "ent_dim" in kw:
         kw["rel_dim"] = kw["ent_dim"] // 2 if model == "rotate" else kw["ent_dim"]
@@ -310,14 +312,22 @@ PAIR_BACKWARD_CUTS = {
     "many-ranges": dict(batch=65, chunk=65, neg_per_chunk=449, ent_dim=200, loss="ranking", gamma=0.3, adv_temperature=1.0),
     # a set of partial rows for each of the 65 tiles of positives does not fit the workspace: workgroups walk several tiles
     "walks": dict(batch=1040, chunk=1040, neg_per_chunk=1024, ent_dim=1024, steps=1),
+    # ... nor does one for each tile of 32, the largest of TransE-L1 (65 tiles, room for 64 sets)
+    "walks-larger-tiles": dict(batch=2080, chunk=2080, neg_per_chunk=1024, ent_dim=1024, steps=1),
+    # more than 1024 scores per row: the library's exponential functions, without and with walking
+    "long-scores": dict(batch=50, chunk=25, neg_per_chunk=1100, adv_temperature=1.0),
+    "walks-long-scores": dict(batch=1040, chunk=1040, neg_per_chunk=1040, ent_dim=1024, steps=1),
+    "walks-larger-tiles-long-scores": dict(batch=2080, chunk=2080, neg_per_chunk=1040, ent_dim=1024, steps=1),
 }
 
 
 @pytest.mark.parametrize("shape", sorted(PAIR_BACKWARD_CUTS))
 @pytest.mark.parametrize("model", ["rotate", "transe_l1"])
 def test_cuts_of_the_elementwise_backward(kge, model, shape):
-    if shape == "walks" and model == "transe_l1":
+    if shape in ("walks", "walks-long-scores") and model == "transe_l1":
         pytest.skip("tiles of 32 positives: their partial rows fit")
+    if shape.startswith("walks-larger-tiles") and model == "rotate":
+        pytest.skip("has no tiles of 32 positives")
     kw = dict(dict(steps=2, ent_dim=72), **PAIR_BACKWARD_CUTS[shape])
     kw["rel_dim"] = kw["ent_dim"] // 2 if model == "rotate" else kw["ent_dim"]
     w = ragged(model, **kw)
@@ -426,11 +436,16 @@ def test_medium_shape_reduced_entities(kge):
         run_steps(p, bs, 3)
     finally:
         p.close()
-    p = Pair(w, kge)
-    try:
-        assert_trajectory(free_run(p, bs, 10), "medium")
-    finally:
-        p.close()
+    profs = []
+    for seed in range(8):
+        ws = w.scaled(seed=seed)
+        p = Pair(ws, kge)
+        try:
+            profs.append(free_run(p, configs.BatchStream(ws), 10))
+        finally:
+            p.close()
+    assert_trajectory({table: {key: float(np.median([prof[table][key] for prof in profs])) for key in profs[0][table]}
+                       for table in ("E", "R")}, "medium")
 
 
 @pytest.mark.parametrize("alpha", [0.0, 1.0])
