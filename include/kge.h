@@ -86,8 +86,11 @@ typedef struct {
 
 /* Create a context and its workspace on cfg->device.  (host) cfg, (host) out.  The workspace is sized from
  * max_batch, max_neg_per_chunk, max_chunks and ent_dim and stays allocated until kge_destroy; it holds what Sec. 3.1
- * step 2 fetches for one mini-batch (the rows, their gradients) and never the tables.  (Library lifecycle: the
- * paper has no passage for it.) */
+ * step 2 fetches for one mini-batch (the rows, their gradients) and never the tables.  The largest parts: TransR keeps every
+ * corrupting row projected for every positive, and the gradients of these rows, 8 * max_batch * max_neg_per_chunk * ent_dim
+ * bytes (2.1 GB at 2048, 1024, 128), and a matrix gradient per positive, 4 * max_batch * rel_dim; RotatE and TransE-L1 keep
+ * partial sums, at most 256 MB or 32 * max_chunks * max_neg_per_chunk * ent_dim bytes.  (Library lifecycle: the paper has no
+ * passage for it.) */
 int kge_create(const kge_config* cfg, kge_ctx** out);
 
 /* Free the workspace and the context.  kge_destroy(NULL) does nothing.  The caller must have synchronised
