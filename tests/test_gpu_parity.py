@@ -209,11 +209,11 @@ def test_independent_negatives(kge, model):
         p.close()
 
 
-@pytest.mark.parametrize("batch", [327_680, 329_729])
-def test_key_lists_of_very_many_slices(kge, batch):
-    """The relation list is 160 slices of 2048 keys (the most that the scatter of the radix sort walks by itself) and 161 and a
-    bit, the entity list more: their offsets come from a launch of their own."""
-    w = ragged("transe_l2", ent_dim=4, rel_dim=4, batch=batch, chunk=batch, neg_per_chunk=8, n_entities=20_000, n_relations=2000,
+@pytest.mark.parametrize("batch,chunk,k", [(327_680, 327_680, 8), (329_729, 329_729, 8), (1100, 1, 300)])
+def test_key_lists_of_very_many_slices(kge, batch, chunk, k):
+    """The relation list is 160 slices of 2048 keys (the most that the scatter of the radix sort walks by itself), 161 and a bit
+    (the entity list more: their offsets come from a launch of their own), or one slice beside an entity list of 163."""
+    w = ragged("transe_l2", ent_dim=4, rel_dim=4, batch=batch, chunk=chunk, neg_per_chunk=k, n_entities=20_000, n_relations=2000,
                n_triples=400_000, steps=1)
     p = Pair(w, kge)
     try:
