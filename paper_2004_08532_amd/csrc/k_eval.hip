@@ -6,7 +6,8 @@
 
 namespace {
 
-// one wave per positive: count the negatives of its row that score strictly higher
+// One wave per positive: count the negatives of its row that score strictly higher.  Bound by the round trip of the loads: eight
+// of them in flight (kge_rank of 1000 positives, 500 candidates, D 64: 13.3 us with one after the other).
 __global__ __launch_bounds__(256) void k_rank(const float* fpos, const float* S, int ld_s, int b, int k, int32_t* rank_out) {
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -14,7 +15,13 @@ __global__ __launch_bounds__(256) void k_rank(const float* fpos, const float* S,
     const float fp = fpos[i];
     const float* s = S + (int64_t)i * ld_s;
     int cnt = 0;
-    for (int j = lane; j < k; j += 64) cnt += s[j] > fp ? 1 : 0;
+    for (int j0 = lane; j0 < k; j0 += 512) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = s[j0 + 64 * u < k ? j0 + 64 * u : j0];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) cnt += j0 + 64 * u < k && v[u] > fp ? 1 : 0;
+    }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
     if (lane == 0) rank_out[i] = 1 + cnt;

@@ -1,0 +1,258 @@
+// Gather and forward product in one launch, for steps of few output tiles.
+//
+// The forward product needs o_i = phi(a_i, r_i) and the corrupting rows; the gather launch forms and stages them, and a
+// second launch reads them back.  Where the output has no more tiles than the chip holds workgroups, the tiles can read
+// the table rows themselves: a workgroup of eight waves owns a 32 x 32 output tile, every wave asks for whole rows (of four
+// positives and four corrupting entities) in one round, forms o, and lays both operands out in LDS in slices of 256 floats
+// of K, which the waves then split between them.  The tiles stage the corrupting rows for the backward
+// product; o rows, the scores of the positives and the key order come from other workgroups of the launch
+// (k_gather_rows.h), which need nothing from the tiles.  What it saves is the ramp and the drain of a launch and a round
+// trip through memory: gather + forward 8.0 + 7.2 -> 13.4 us at Freebase scale, 8.3 + 6.7 -> 11.1 FB15k-sized (D 400),
+// 5.1 + 5.3 -> 6.9 in a step of 256 positives (D 64).
+#include "k_gather_rows.h"
+#include "k_gemm_shared.h"
+
+namespace {
+
+constexpr int FT = 512, FW = FT / 64, TILE = 32;
+constexpr int RPW = TILE / FW;   // rows of either operand per wave
+constexpr int SLICE = 256;       // floats of K in LDS at a time
+constexpr int PITCH = SLICE + 4;  // floats; 16-byte reads of 16 consecutive rows fall into different banks
+constexpr int FRONT_MAX_KEYS = 8192;  // (they lie in the LDS of the tiles)
+static_assert(FRONT_MAX_KEYS <= 2 * TILE * PITCH && FW * TILE * TILE + FW * 2 * TILE + FW <= 2 * TILE * PITCH, "LDS");
+
+struct FrontArgs {
+    GatherArgs ga;
+    float* C;
+    int ldc, g, k;
+    int gx, gy, tiles, per_xcd;
+    int rank_wgs;  // rank blocks, rounded up to a multiple of 8
+    int out_mode;
+    bool stage;    // training: stage the corrupting rows
+    float wk;
+    float* neg_loss_part;
+};
+
+// One 32 x 32 tile.  Bound by the round trips kernel arguments -> ids -> rows (2.1 us of a tile's 9 at Freebase scale: 224 tiles,
+// D 400) and by the matrix cores (1.5 us: a CU holds one tile, whose products take 3,200 cycles on its four SIMDs).  Every wave
+// reads whole rows, all of them in flight together: tiles that read their K ranges of the rows piece by piece took twice as
+// long.  Two slices of K, so that two workgroups share a CU's LDS and the second slice arrives while the first is multiplied.
+template <int MODEL, int NV>
+__device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* lds) {
+    constexpr bool CPLX = MODEL == KGE_COMPLEX;
+    constexpr int P = CPLX ? 2 * NV : NV;  // slices of K (ComplEx: real and imaginary parts of 256 coordinates)
+    static_assert(!CPLX || NV == 1, "the two halves of a row are a slice each");
+    const GatherArgs& a = f.ga;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, D = a.D;
+    const int n0 = (tile % f.gx) * TILE, m0 = (tile / f.gx) % f.gy * TILE, c = tile / (f.gx * f.gy);
+    const StepView sv = step_view(a.ids);
+    const bool head = sv.side == KGE_NEG_HEAD;
+    float* As = lds;
+    float* Bs = lds + TILE * PITCH;
+    const int half = D / 2;
+    auto width = [&](int p) { return CPLX ? half : min(SLICE, D - SLICE * p); };
+    auto piece = [&](int p) { return (CPLX ? half : SLICE) * p + (4 * lane < width(p) ? 4 * lane : 0); };
+
+    // rows past the end of the matrix: the last row again, dropped in the epilogue
+    float4 A[RPW][P], R[RPW][P], N[RPW][P];
+    const float *pa[RPW], *pr[RPW], *pn[RPW];
+#pragma unroll
+    for (int q = 0; q < RPW; ++q) {
+        const int i = c * f.g + min(m0 + w + FW * q, f.g - 1), j = c * f.k + min(n0 + w + FW * q, f.k - 1);
+        pn[q] = a.E + clamp_id(sv.neg[j], a.n_ent) * (int64_t)D;
+        if (MODEL == KGE_RESCAL) {
+            pa[q] = a.O + (int64_t)i * D;
+        } else {
+            pa[q] = a.E + clamp_id(head ? sv.t[i] : sv.h[i], a.n_ent) * (int64_t)D;
+            pr[q] = a.R + clamp_id(sv.r[i], a.n_rel) * (int64_t)a.Dr;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+            A[q][p] = ld4(pa[q] + piece(p));
+            if (MODEL != KGE_RESCAL) R[q][p] = ld4(pr[q] + piece(p));
+            N[q][p] = ld4(pn[q] + piece(p));
+        }
+    }
+    if constexpr (CPLX) {
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+            const float4 x = A[q][0], y = A[q][1], u = R[q][0];
+            float4 v = R[q][1];
+            if (head) v = make_float4(-v.x, -v.y, -v.z, -v.w);  // o = t conj(r)
+            A[q][0] = make_float4(x.x * u.x - y.x * v.x, x.y * u.y - y.y * v.y, x.z * u.z - y.z * v.z, x.w * u.w - y.w * v.w);
+            A[q][1] = make_float4(x.x * v.x + y.x * u.x, x.y * v.y + y.y * u.y, x.z * v.z + y.z * u.z, x.w * v.w + y.w * u.w);
+        }
+    }
+    // the corrupting rows for the backward product: the (up to four) rows of tiles share the work of staging them
+    const int by = m0 / TILE, sharers = min(f.gy, RPW);
+    auto stages = [&](int q) { return f.stage && q % sharers == by && n0 + w + FW * q < f.k; };
+    floatx16 acc = {};
+    float on = 0.f, nn = 0.f;  // TransE-L2: |o|^2 and |n|^2 of row lane % 32 over this lane's part of K
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const bool in = 4 * lane < width(p);
+        if (p > 0) __syncthreads();
+#pragma unroll
+        for (int q = 0; q < RPW; ++q) {
+            float4 o = A[q][p], n = N[q][p];
+            const float4 r = R[q][p];
+            if (MODEL == KGE_DISTMULT) o = make_float4(o.x * r.x, o.y * r.y, o.z * r.z, o.w * r.w);
+            if (MODEL == KGE_TRANSE_L2) {
+                o = head ? make_float4(o.x - r.x, o.y - r.y, o.z - r.z, o.w - r.w)
+                         : make_float4(o.x + r.x, o.y + r.y, o.z + r.z, o.w + r.w);
+            }
+            o = in ? o : f4(0.f);
+            if (stages(q) && in) st4(a.Nst + (int64_t)(c * f.k + n0 + w + FW * q) * D + piece(p), n);
+            n = in ? n : f4(0.f);
+            st4(As + (w + FW * q) * PITCH + 4 * lane, o);
+            st4(Bs + (w + FW * q) * PITCH + 4 * lane, n);
+        }
+        __syncthreads();
+        const int octets = (width(p) + 7) / 8;
+        const float* ra = As + (lane & 31) * PITCH + 4 * (lane >> 5);
+        const float* rb = Bs + (lane & 31) * PITCH + 4 * (lane >> 5);
+        for (int q = w; q < octets; q += FW) {
+            const float4 x = ld4(ra + 8 * q), y = ld4(rb + 8 * q);
+            if (MODEL == KGE_TRANSE_L2) {
+                on += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+                nn += y.x * y.x + y.y * y.y + y.z * y.z + y.w * y.w;
+            }
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc, 0, 0, 0);
+        }
+    }
+    __syncthreads();
+    // sums of the waves (in wave order) and the norms
+    float* norms = lds + FW * TILE * TILE;
+    if (MODEL == KGE_TRANSE_L2) {
+        on += __shfl_xor(on, 32, 64);
+        nn += __shfl_xor(nn, 32, 64);
+        norms[w * 2 * TILE + lane] = lane < 32 ? on : nn;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) lds[w * TILE * TILE + (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * TILE + (lane & 31)] = acc[v];
+    __syncthreads();
+    float loss = 0.f;
+    float* C = f.C + (int64_t)c * f.g * f.ldc;
+#pragma unroll
+    for (int it = 0; it < TILE * TILE / FT; ++it) {
+        const int e = threadIdx.x + it * FT, gm = m0 + (e >> 5), gn = n0 + (e & 31);
+        if (gm >= f.g || gn >= f.k) continue;
+        float s = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < FW; ++ww) s += lds[ww * TILE * TILE + e];
+        float out;
+        if (MODEL == KGE_TRANSE_L2) {
+            float o2 = 0.f, n2 = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < FW; ++ww) {
+                o2 += norms[ww * 2 * TILE + (e >> 5)];
+                n2 += norms[ww * 2 * TILE + TILE + (e & 31)];
+            }
+            const float d = sqrtf(fmaxf(o2 + n2 - 2.f * s, 0.f));
+            out = f.out_mode == OUT_DIST ? d : a.gamma - d;
+            if (f.out_mode == OUT_W) {
+                const float coef = w_and_loss<true>(a.gamma - d, f.wk, loss);
+                out = d > 0.f ? coef * __builtin_amdgcn_rcpf(d) : 0.f;
+            }
+        } else {
+            out = f.out_mode == OUT_W ? w_and_loss<true>(s, f.wk, loss) : s;
+        }
+        C[(int64_t)gm * f.ldc + gn] = out;
+    }
+    if (f.out_mode == OUT_W) {
+        loss = wave_sum(loss);
+        float* part = norms + FW * 2 * TILE;
+        if (lane == 0) part[w] = loss;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float t = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < FW; ++ww) t += part[ww];
+            f.neg_loss_part[tile] = t * f.wk;
+        }
+    }
+}
+
+template <int MODEL, int NV>
+__global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_front(FrontArgs f) {
+    __shared__ __attribute__((aligned(16))) uint32_t front_lds[2 * TILE * PITCH];
+    int block = blockIdx.x;
+    if (block < f.rank_wgs) {
+        const GatherArgs& a = f.ga;
+        if (block < a.ent_rank_blocks) rank_block<FT>(a.ent, block, front_lds);
+        else if (block < a.rank_blocks) rank_block<FT>(a.rel, block - a.ent_rank_blocks, front_lds);
+        return;
+    }
+    block -= f.rank_wgs;
+    if (block < 8 * f.per_xcd) {
+        const int tile = xcd_tile(block >> 3, f.per_xcd);
+        if (tile < f.tiles) front_tile<MODEL, NV>(f, tile, reinterpret_cast<float*>(front_lds));
+        return;
+    }
+    const int row = (block - 8 * f.per_xcd) * FW + (threadIdx.x >> 6);
+    if (row < f.ga.b) gather_row<MODEL, NV>(f.ga, row);
+}
+
+}  // namespace
+
+// Forward of chunks of gsz positives and k corrupting rows in the gather launch?
+// Tiles read a table row once per tile that needs it, the gather launch once, so the line lies where that costs more than a
+// launch (us per training step, separate -> one launch; TransE-L2):
+//   tiles   rows of 400: 256 41.7 -> 37.9, 640 65.9 -> 60.4, 768 68.9 -> 64.6, 1024 66.9 -> 67.1
+//           rows of 160: 640 46.3 -> 44.5, 768 47.6 -> 47.4;  of 128: 624 40.3 -> 39.1, 640 43.4 -> 43.6, 768 44.6 -> 46.7
+//   keys    ordered by brute force here, in buckets of the id range in the gather launch of long lists (512 tiles and
+//           fewer, rows of 64): 6144 39.1 -> 35.4, 8192 40.6 -> 34.7, 12288 45.0 -> 47.9.  Lists that are sorted in other
+//           launches don't matter: 20480 keys 67.8 -> 67.3
+// Rows of more than two slices of K would not fit the registers of a wave.
+bool kge_front_fits(const kge_ctx* c, int b, int k, int gsz, bool with_keys) {
+    const int m = c->cfg.model, D = c->cfg.ent_dim;
+    if (c->cfg.gemm_input != 0 || D > 2 * SLICE) return false;
+    if (m != KGE_TRANSE_L2 && m != KGE_DISTMULT && m != KGE_COMPLEX && m != KGE_RESCAL) return false;
+    const int64_t chunks = b / gsz, tiles = chunks * ((gsz + TILE - 1) / TILE) * ((k + TILE - 1) / TILE);
+    return tiles <= (D > 128 ? 768 : 512) && !(with_keys && 2 * (int64_t)b + chunks * k > FRONT_MAX_KEYS);
+}
+
+void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* pos_out,
+                      bool with_keys, float* out, int ld_out, int out_mode, hipStream_t st) {
+    FrontArgs f = {};
+    kge_fill_gather_args(c, E, R, ids, gsz, gamma, pos_out, &f.ga);
+    f.C = out; f.ldc = ld_out; f.g = gsz; f.k = k;
+    f.gx = (k + TILE - 1) / TILE; f.gy = (gsz + TILE - 1) / TILE; f.tiles = f.gx * f.gy * (ids.b / gsz);
+    f.per_xcd = (f.tiles + 7) / 8;
+    f.out_mode = out_mode;
+    f.wk = 1.f / ((float)k * (float)ids.b);
+    f.neg_loss_part = c->neg_loss_part;
+    f.stage = out_mode != OUT_SCORE;
+    if (with_keys) {
+        constexpr int ITEMS = RankShape<FT>::ITEMS;
+        kge_make_key_lists(c, ids, &f.ga.ent, &f.ga.rel);
+        f.ga.ent_rank_blocks = (f.ga.ent.n + ITEMS - 1) / ITEMS;
+        f.ga.rank_blocks = f.ga.ent_rank_blocks + (f.ga.rel.n + ITEMS - 1) / ITEMS;
+        f.rank_wgs = (f.ga.rank_blocks + 7) / 8 * 8;
+        c->ebuf = 0;
+        c->rbuf = 0;
+    }
+    const dim3 grid(f.rank_wgs + 8 * f.per_xcd + (ids.b + FW - 1) / FW);
+    const int nv = (c->cfg.ent_dim + SLICE - 1) / SLICE;
+    switch (c->cfg.model) {
+    case KGE_TRANSE_L2:
+        if (nv == 1) KGE_LAUNCH(c, (k_front<KGE_TRANSE_L2, 1>), grid, dim3(FT), 0, st, f);
+        else KGE_LAUNCH(c, (k_front<KGE_TRANSE_L2, 2>), grid, dim3(FT), 0, st, f);
+        break;
+    case KGE_DISTMULT:
+        if (nv == 1) KGE_LAUNCH(c, (k_front<KGE_DISTMULT, 1>), grid, dim3(FT), 0, st, f);
+        else KGE_LAUNCH(c, (k_front<KGE_DISTMULT, 2>), grid, dim3(FT), 0, st, f);
+        break;
+    case KGE_RESCAL:
+        if (nv == 1) KGE_LAUNCH(c, (k_front<KGE_RESCAL, 1>), grid, dim3(FT), 0, st, f);
+        else KGE_LAUNCH(c, (k_front<KGE_RESCAL, 2>), grid, dim3(FT), 0, st, f);
+        break;
+    default: KGE_LAUNCH(c, (k_front<KGE_COMPLEX, 1>), grid, dim3(FT), 0, st, f); break;
+    }
+}

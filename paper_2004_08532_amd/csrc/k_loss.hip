@@ -165,8 +165,6 @@ struct ChainArgs {
     int rest_share;  // threads that share the partial rows of one 16-byte piece
 };
 
-__device__ __forceinline__ int64_t clamp_id(int64_t id, int64_t n) { return id < 0 ? 0 : (id >= n ? n - 1 : id); }
-
 template <int MODEL, int NV>
 __global__ __launch_bounds__(256) void k_chain(ChainArgs a) {
     if ((int)blockIdx.x >= a.chain_blocks) {  // partial rows of the corrupting entities -> their gradient rows

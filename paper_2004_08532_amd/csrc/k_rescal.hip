@@ -39,8 +39,6 @@ struct RescalArgs {
     float* GW;          // [b x D]  chain: right factor
 };
 
-__device__ __forceinline__ int64_t clamp_id(int64_t id, int64_t n) { return id < 0 ? 0 : (id >= n ? n - 1 : id); }
-
 template <bool CHAIN>
 __global__ __launch_bounds__(RT) void k_rescal(RescalArgs a) {
     __shared__ __attribute__((aligned(16))) float vec[MAX_D];  // the vector that multiplies M

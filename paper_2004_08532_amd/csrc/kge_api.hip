@@ -99,6 +99,10 @@ void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids,
         return;
     }
     if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_phi(c, ent, rel, ids, st);
+    if (neg_out && k > 0 && dist_mode == 0 && kge_front_fits(c, ids.b, k, chunk, false)) {
+        kge_launch_front(c, ent, rel, ids, k, chunk, gamma, pos_out, false, neg_out, ld_out, dist_mode, st);
+        return;
+    }
     kge_launch_gather(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
     if (c->cfg.model == KGE_TRANSR) kge_transr_phi(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
     if (neg_out && k > 0) {
@@ -228,12 +232,16 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         ProfScope p(c, KGE_PROF_PHI);
         kge_launch_rescal_phi(c, ent, rel, ids, st);
     }
-    {
+    const bool front = kge_front_fits(c, B, K, G, !long_lists);
+    if (front) {
+        ProfScope p(c, KGE_PROF_GATHER);
+        kge_launch_front(c, ent, rel, ids, K, G, gamma, nullptr, !long_lists, c->S, c->ld_s, kge_gemm_backward_forms_w(c) ? 2 : 1, st);
+    } else {
         ProfScope p(c, KGE_PROF_GATHER);
         kge_launch_gather(c, ent, rel, ids, G, gamma, nullptr, !long_lists, st);
     }
     if (c->cfg.model == KGE_TRANSR) return enqueue_transr_rest(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, long_lists, st);
-    {
+    if (!front) {
         ProfScope p(c, KGE_PROF_SCORE);
         if (is_gemm_model(c->cfg.model))
             kge_gemm_neg_score(c, B, K, G, gamma, c->S, c->ld_s, kge_gemm_backward_forms_w(c) ? 2 : 1, st);
@@ -273,7 +281,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         KGE_HIP(c, hipStreamSynchronize(st));
         for (int s = 0; s < KGE_PROF_SLOTS; ++s) {
             float ms = 0.f;
-            if ((s == KGE_PROF_SORT && !long_lists) || (s == KGE_PROF_LOSS && !run_loss) ||
+            if ((s == KGE_PROF_SORT && !long_lists) || (s == KGE_PROF_SCORE && front) || (s == KGE_PROF_LOSS && !run_loss) ||
                 (s == KGE_PROF_CHAIN && !run_chain) || ((s == KGE_PROF_PHI || s == KGE_PROF_REL_UPDATE) && c->cfg.model != KGE_RESCAL))
                 continue;  // that kernel did not run in this configuration
             if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
@@ -712,7 +720,10 @@ int kge_rank(kge_ctx* c, const float* ent, const float* rel,
     KGE_HIP(c, hipSetDevice(c->cfg.device));
     const StepIds ids = direct_ids(h, r, t, (int)b, neg, (int)((b / chunk) * k), neg_side, nullptr);
     hipStream_t st = (hipStream_t)hip_stream;
-    if (is_gemm_model(c->cfg.model) && kge_gemm_forward_can_rank(c) && !kge_ind_score_fits(c, (int)chunk)) {
+    // (the scores that ranks are counted from are those of kge_score bit for bit, so where kge_score forms them in the gather
+    // launch, so does this)
+    if (is_gemm_model(c->cfg.model) && kge_gemm_forward_can_rank(c) && !kge_ind_score_fits(c, (int)chunk) &&
+        !kge_front_fits(c, (int)b, (int)k, (int)chunk, false)) {
         // the gather launch sets every rank to 1, the forward launch adds the candidates that score higher
         c->rank_out = rank_out;
         forward(c, ent, rel, ids, (int)k, (int)chunk, gamma, nullptr, c->S, c->ld_s, 3, st);

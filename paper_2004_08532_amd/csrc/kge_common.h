@@ -202,6 +202,10 @@ inline dim3 flat_grid(int64_t blocks) {
 // (TransR: and the items of the chunks of g positives)
 void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int g, float gamma, float* pos_out,
                        bool with_keys, hipStream_t st);
+// ... and a3 in the same launch, where the output has few tiles
+bool kge_front_fits(const kge_ctx* c, int b, int k, int g, bool with_keys);
+void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int g, float gamma, float* pos_out,
+                      bool with_keys, float* out, int ld_out, int out_mode, hipStream_t st);
 void kge_launch_key_order(kge_ctx* c, const StepIds& ids, hipStream_t st);  // the key lists alone
 // chunks of one positive: everything between the ids and the gradient rows of the positives in one launch, and the
 // update of the entity rows that forms the corrupting rows' gradients itself
@@ -327,6 +331,7 @@ __device__ __forceinline__ const int64_t* key_address(const KeyList& l, const Ke
     const int64_t* p2 = s.p[2] + (idx - ab);
     return idx < a ? p0 : (idx < ab ? p1 : p2);
 }
+__device__ __forceinline__ int64_t clamp_id(int64_t id, int64_t n) { return id < 0 ? 0 : (id >= n ? n - 1 : id); }
 __device__ __forceinline__ uint32_t clamp_key(const KeyList& l, int64_t id) {
     id = id < 0 ? 0 : (id >= l.n_ids ? l.n_ids - 1 : id);
     return (uint32_t)id;

@@ -196,6 +196,34 @@ def test_training_shapes_with_thousands_of_tiles(kge):
             p.close()
 
 
+# forward product in the gather launch and, past the last of each pair of limits, in a launch of its own: rows (one and two
+# slices of 256 floats, ragged octets of K), tiles (32 x 32, full and ragged; 512 of them, with rows of more than 128 floats
+# 768), keys that the launch orders (8192)
+FORWARD_SHAPES = {
+    "row-4": (64, 32, 33, 8), "row-252": (66, 33, 31, 256), "row-256": (64, 32, 32, 264), "row-260": (30, 15, 65, 248),
+    "row-512": (96, 96, 100, 512), "row-516": (66, 33, 40, 520),
+    "tiles-512": (512, 32, 1024, 8), "tiles-513": (1026, 342, 510, 16), "tiles-768": (768, 32, 1024, 136),
+    "tiles-800": (800, 32, 1024, 136), "keys-8192": (2048, 64, 128, 16), "keys-8194": (2049, 683, 1365, 16),
+    "keys-sorted": (2048, 8, 64, 16),
+}
+
+
+@pytest.mark.parametrize("shape", sorted(FORWARD_SHAPES))
+@pytest.mark.parametrize("model", ["transe_l2", "distmult", "complex", "rescal"])
+def test_forward_product_beside_the_gather(kge, model, shape):
+    b, g, k, dim = FORWARD_SHAPES[shape]
+    if model == "rescal" and b * k * dim * dim > 3e8:
+        pytest.skip("dim * dim products per negative in the oracle")
+    if model != "complex" and shape in ("row-4", "row-252", "row-260", "row-516"):
+        dim = int(shape[4:])  # (rows of ComplEx are multiples of 8)
+    w = ragged(model, batch=b, chunk=g, neg_per_chunk=k, ent_dim=dim, rel_dim=dim * dim if model == "rescal" else dim, steps=2)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps, check_dedup_at=(0, 1), family="few positives")
+    finally:
+        p.close()
+
+
 @pytest.mark.parametrize("model", ["transe_l2", "complex", "rotate", "transe_l1"])
 def test_independent_negatives(kge, model):
     """Every positive with corrupting entities of its own (chunks of one positive, the sampling that Sec. 3.3 of the
