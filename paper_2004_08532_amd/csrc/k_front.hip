@@ -33,6 +33,14 @@ struct FrontArgs {
     float* neg_loss_part;
 };
 
+// sum of the eight waves' values `stride` floats apart, in pairs
+__device__ __forceinline__ float sum_of_waves(const float* p, int stride) {
+    float v[FW];
+#pragma unroll
+    for (int w = 0; w < FW; ++w) v[w] = p[w * stride];
+    return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+
 // One 32 x 32 tile.  Bound by the round trips kernel arguments -> ids -> rows (2.1 us of a tile's 9 at Freebase scale: 224 tiles,
 // D 400) and by the matrix cores (1.5 us: a CU holds one tile, whose products take 3,200 cycles on its four SIMDs).  Every wave
 // reads whole rows, all of them in flight together: tiles that read their K ranges of the rows piece by piece took twice as
@@ -89,7 +97,7 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
     // the corrupting rows for the backward product: the (up to four) rows of tiles share the work of staging them
     const int by = m0 / TILE, sharers = min(f.gy, RPW);
     auto stages = [&](int q) { return f.stage && q % sharers == by && n0 + w + FW * q < f.k; };
-    floatx16 acc = {};
+    floatx16 acc = {}, acc2 = {};  // (two, so that a sum is a chain of half the length)
     float on = 0.f, nn = 0.f;  // TransE-L2: |o|^2 and |n|^2 of row lane % 32 over this lane's part of K
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -121,9 +129,9 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
                 nn += y.x * y.x + y.y * y.y + y.z * y.z + y.w * y.w;
             }
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, y.x, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, y.y, acc2, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, y.z, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, y.w, acc2, 0, 0, 0);
         }
     }
     __syncthreads();
@@ -135,7 +143,7 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
         norms[w * 2 * TILE + lane] = lane < 32 ? on : nn;
     }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) lds[w * TILE * TILE + (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * TILE + (lane & 31)] = acc[v];
+    for (int v = 0; v < 16; ++v) lds[w * TILE * TILE + (8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * TILE + (lane & 31)] = acc[v] + acc2[v];
     __syncthreads();
     float loss = 0.f;
     float* C = f.C + (int64_t)c * f.g * f.ldc;
@@ -143,17 +151,10 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
     for (int it = 0; it < TILE * TILE / FT; ++it) {
         const int e = threadIdx.x + it * FT, gm = m0 + (e >> 5), gn = n0 + (e & 31);
         if (gm >= f.g || gn >= f.k) continue;
-        float s = 0.f;
-#pragma unroll
-        for (int ww = 0; ww < FW; ++ww) s += lds[ww * TILE * TILE + e];
+        const float s = sum_of_waves(lds + e, TILE * TILE);
         float out;
         if (MODEL == KGE_TRANSE_L2) {
-            float o2 = 0.f, n2 = 0.f;
-#pragma unroll
-            for (int ww = 0; ww < FW; ++ww) {
-                o2 += norms[ww * 2 * TILE + (e >> 5)];
-                n2 += norms[ww * 2 * TILE + TILE + (e & 31)];
-            }
+            const float o2 = sum_of_waves(norms + (e >> 5), 2 * TILE), n2 = sum_of_waves(norms + TILE + (e & 31), 2 * TILE);
             const float d = sqrtf(fmaxf(o2 + n2 - 2.f * s, 0.f));
             out = f.out_mode == OUT_DIST ? d : a.gamma - d;
             if (f.out_mode == OUT_W) {
