@@ -1,12 +1,9 @@
 // Shared by the two matrix-product sources (k_gemm.hip: fp32 operands, small tiles split over K; k_gemm_bf.hip:
 // bf16 operands, 64x64 tiles): the argument block, the epilogue kinds and the helpers both use.
 #pragma once
-#include "kge_common.h"
+#include "k_split.h"
 
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 enum { EPI_PLAIN = 0, EPI_L2_FWD = 1, EPI_L2_DO = 2, EPI_L2_DN = 3, EPI_CHAIN_L2 = 4, EPI_CHAIN_DM = 5, EPI_CHAIN_CX = 6 };
 // what the forward launch leaves behind (see kge_gemm_neg_score); OUT_RANK: nothing but the ranks of the positives
@@ -80,6 +77,8 @@ __device__ __forceinline__ int xcd_tile(int q, int per_xcd) { return (blockIdx.x
 
 }  // namespace
 
+// fp32 operands, many tiles (k_gemm_split.hip)
+void kge_gemm_split_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);
 // bf16 operands (k_gemm_bf.hip): the same two launches on 64x64 tiles
 void kge_gemm_bf_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);
 void kge_gemm_bf_backward(kge_ctx* c, const void* args_o, const void* args_n, int epi_o, int epi_n, int chunks,

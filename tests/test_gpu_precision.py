@@ -154,3 +154,46 @@ def test_signs_of_small_and_large_differences(kge, g, scale):
     # sums of terms +-w and 0, w = 1 / (b k): one rounding per term of a sum that never passes 1 / b in a row of o
     for got, want in ((gE, wE), (gR, wR)):
         np.testing.assert_allclose(got, want, rtol=1e-5, atol=64 * ULP / b)
+
+
+@pytest.mark.parametrize("b,g,k,D", [(1024, 1024, 1536, 36), (1000, 500, 1600, 104), (1056, 33, 1500, 64), (1024, 32, 1505, 100)])
+def test_forward_product_of_many_tiles(kge, b, g, k, D):
+    """Scores of more than 1504 tiles of 32 x 32 (sums of products of parts of the operands), rows of ordinary numbers against 64
+    bits, and rows of infinities, NaN and numbers at the end of the floats against the same sums in the float's arithmetic."""
+    gen = np.random.default_rng(9)
+    n = b // g * k
+    E = gen.uniform(-1, 1, (2 * b + n, D)).astype(np.float32)
+    E[2 * b:, 0] = np.abs(E[2 * b:, 0]) / 4 + 0.25
+    big = np.float32(3.4e38)  # rounds to infinity in 8 bits
+    E[0, 0], E[1, 0], E[2, 0], E[3, 0], E[4, 1], E[5, :] = np.inf, -np.inf, np.nan, big, big, 0
+    E[b - 1, D - 1] = np.float32(1e-40)
+    E[2 * b + k // 2, 0] = np.inf  # a corrupting row of the first chunk
+    ids = np.arange(2 * b + n)
+    c = kge.KgeContext("distmult", E.shape[0], 1, D, D, max_batch=b, max_neg_per_chunk=k, max_chunks=b // g)
+    dev = lambda x: torch.from_numpy(x).cuda()
+    pos, neg, ranks = torch.empty(b, device="cuda"), torch.empty((b, k), device="cuda"), torch.empty(b, dtype=torch.int32, device="cuda")
+    dE, dR = dev(E), torch.ones((1, D), device="cuda")
+    h, r, t, m = dev(ids[:b]), dev(np.zeros(b, np.int64)), dev(ids[b:2 * b]), dev(ids[2 * b:])
+    try:
+        c.score(dE, dR, h, r, t, m, k, g, 0, 12.0, pos, neg)
+        c.rank(dE, dR, h, r, t, m, k, g, 0, 12.0, ranks)
+        torch.cuda.synchronize()
+    finally:
+        c.close()
+    pos, neg = pos.cpu().numpy(), neg.cpu().numpy()
+    with np.errstate(all="ignore"):
+        x, y = E[:b].astype(np.float64), E[2 * b:].astype(np.float64)
+        want = np.concatenate([(x[i:i + g] @ y[i // g * k:(i // g + 1) * k].T) for i in range(0, b, g)])
+    ordinary = np.isfinite(want) & (np.abs(want) < 1e30)
+    assert np.array_equal(np.isnan(neg), np.isnan(want))
+    assert np.array_equal(np.isinf(neg), np.isinf(want.astype(np.float32)))
+    sure = np.isinf(want)
+    assert np.array_equal(neg[sure], want[sure])
+    huge = np.isfinite(want) & ~ordinary & (np.abs(want) < 3e38)
+    assert huge.any() and np.max(np.abs(neg[huge] / want[huge] - 1)) < 1e-6
+    err = np.linalg.norm(neg[ordinary] - want[ordinary]) / np.linalg.norm(want[ordinary])
+    # half an ulp of the result and of the sum of the small parts, one rounding per 16 products of a sum that grows like the root
+    # of their number; the fp32 instructions' error is D roundings of such a sum
+    print("\n[precision] forward product", b, g, k, D, "%.2f roundings" % (err / ULP))
+    assert err < 2 * ULP
+    assert np.array_equal(ranks.cpu().numpy(), 1 + (neg > pos[:, None]).sum(1))
