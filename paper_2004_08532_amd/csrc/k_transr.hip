@@ -43,6 +43,8 @@ constexpr int KP = 36;                     // pitch of a staged [row][k] block: 
 constexpr int AP = BM + 4, BP = BN + 4;    // pitches of staged [k][row] blocks: 4 * pitch = 16 mod 64 banks
 constexpr int A_FLOATS = BM * KP > BK * AP ? BM * KP : BK * AP, B_FLOATS = BN * KP > BK * BP ? BN * KP : BK * BP;
 constexpr int PB = TRANSR_PB;              // positives per block of an item's positives
+constexpr int DP_FEW = 16;                 // items of at most so many positives: V and dL/do positive by positive
+static_assert(DP_FEW <= PB, "such an item is one block");
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -56,6 +58,7 @@ struct TransrArgs {
     float gamma, wk;
     int out_w;       // project: store W = dL/df- instead of the score
     int train;       // project: keep the projections, scores in the order of the members; phi: likewise
+    int form_v;      // project: form V and dL/do of items of few positives, whose P is then not stored (dp leaves them alone)
     int segments;    // back: ranges of a chunk's items
     TransrGroups q;
     float* O;        // [b x D]      o
@@ -350,7 +353,6 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
         const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D;
         const float* N = a.N + ((int64_t)c * a.k + j0) * D;
         float* P = a.P + ((int64_t)blk.slot * a.k + j0) * D;
-        const bool store_p = a.train && blk.first == 0;
         const float* pa[2];
 #pragma unroll
         for (int it = 0; it < 2; ++it) pa[it] = N + (int64_t)min(tid / 8 + 32 * it, rows - 1) * D;
@@ -376,7 +378,9 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
 #pragma unroll
             for (int it = 0; it < 4; ++it) st4(Bs + (tid / 32 + 8 * it) * BN + 4 * (tid % 32), ro[it]);
             __syncthreads();
-            if (!t.active) continue;
+            const bool form_v = a.form_v && blk.all <= DP_FEW;  // (the same for every thread; one pass over the columns)
+            if (!t.active && !form_v) continue;
+            const bool store_p = a.train && blk.first == 0 && !form_v;
 #pragma unroll
             for (int ct = 0; ct < NT; ++ct) {
                 const int d = n0 + 16 * ct + l16;
@@ -388,7 +392,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
             }
             // four positives per round, so that every lane has a score to finish: positive m0 + lane % 4, row q
             const int x = tid & 3, j = t.row(q);
-            for (int m0 = 0; m0 < n; m0 += 4) {
+            auto scores = [&](int m0) {  // positive m0 + x, row q; what is stored of it (0: there is none)
                 float r[4];
 #pragma unroll
                 for (int y = 0; y < 4; ++y) {
@@ -409,16 +413,80 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
                     }
                     r[y] = sum16x4(ss);
                 }
-                if (m0 + x < n && j < rows) {
-                    float s = x == 0 ? r[0] : x == 1 ? r[1] : x == 2 ? r[2] : r[3];
-                    const int m = blk.off + m0 + x;
-                    float* ps = a.S + (int64_t)(a.train ? m : a.q.members[m]) * a.ld_s + j0 + j;
-                    if (n0 > 0) s += *ps;  // what the columns before contributed
-                    if (n0 + BN >= D) {
-                        s = a.gamma - s;
-                        if (a.out_w) s = w_and_loss<true>(s, a.wk, loss);
+                if (m0 + x >= n || j >= rows) return 0.f;
+                float s = x == 0 ? r[0] : x == 1 ? r[1] : x == 2 ? r[2] : r[3];
+                const int m = blk.off + m0 + x;
+                float* ps = a.S + (int64_t)(a.train ? m : a.q.members[m]) * a.ld_s + j0 + j;
+                if (n0 > 0) s += *ps;  // what the columns before contributed
+                if (n0 + BN >= D) {
+                    s = a.gamma - s;
+                    if (a.out_w) s = w_and_loss<true>(s, a.wk, loss);
+                }
+                *ps = s;
+                return s;
+            };
+            if (!form_v) {
+                for (int m0 = 0; m0 < n; m0 += 4) scores(m0);
+                continue;
+            }
+            // V_tj and dL/do (partial: over these 64 rows) while P is here: positive by positive, as dp_few forms them.  W of a
+            // round goes through LDS from the lane that has formed it to the lanes that hold the row; the sums for dL/do of two
+            // positives meet there too, one row per wave and quarter of a wave, and are added up in that order.
+            floatx4 vsum[NT];
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) vsum[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+            constexpr int GROUPS = RT / 16;
+            float* w2 = As + 64 * t.wave;                         // [4 positives][16 rows] of this wave
+            auto go = [&](int y) { return y == 0 ? As + 256 : Bs + DP_FEW * BN; };  // [group of 16 lanes][BN]; behind w2, behind the o rows
+            static_assert(256 + GROUPS * BN <= A_FLOATS && (DP_FEW + GROUPS) * BN <= B_FLOATS, "");
+            const int quad = t.lane >> 4;
+            for (int m0 = 0; m0 < n; m0 += 4) {
+                w2[16 * x + t.row16(q)] = t.active ? 2.f * scores(m0) : 0.f;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                for (int y0 = 0; y0 < min(4, n - m0); y0 += 2) {
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        if (m0 + y0 + y >= n) break;
+                        const float4 w = ld4(w2 + 16 * (y0 + y) + 4 * quad);
+                        const float* po = Bs + (m0 + y0 + y) * BN + l16;
+                        float* pg = go(y) + (4 * t.wave + quad) * BN + l16;
+#pragma unroll
+                        for (int ct = 0; ct < NT; ++ct) {
+                            const float o = po[16 * ct];
+                            float g = 0.f;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const float e = (v == 0 ? w.x : v == 1 ? w.y : v == 2 ? w.z : w.w) * (o - t.acc[ct][v]);
+                                vsum[ct][v] += e;
+                                g -= e;
+                            }
+                            pg[16 * ct] = g;
+                        }
                     }
-                    *ps = s;
+                    __syncthreads();
+                    const int lanes = D / 4, y = tid >> 7, d = 4 * (tid & 127);  // half of the threads per positive
+                    if ((tid & 127) < lanes && m0 + y0 + y < n) {
+                        const float* pg = go(y) + d;
+                        float4 s = ld4(pg);
+#pragma unroll
+                        for (int e = 1; e < GROUPS; ++e) {
+                            const float4 u = ld4(pg + e * BN);
+                            s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
+                        }
+                        st4(a.GOp + ((int64_t)tile * a.b + blk.off + m0 + y0 + y) * D + d, s);
+                    }
+                    __syncthreads();
+                }
+            }
+            float* V = a.V + ((int64_t)blk.slot * a.k + j0) * D;
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) {
+                const int d = 16 * ct + l16;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (d < D && t.row(v) < rows) V[(int64_t)t.row(v) * D + d] = vsum[ct][v];
                 }
             }
         }
@@ -434,7 +502,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
 // Items of at most DP_FEW positives: the sums over an item's positives and over the corrupting rows on the vector ALUs,
 // both while a row of P is in registers (32 us for the FB15k-sized step, 130 MB of rows; two products took 67, their
 // tiles of sixteen rows nearly empty); others: two products.
-constexpr int DP_FEW = 16, MB = 4, DR = 8;
+constexpr int MB = 4, DR = 8;
 constexpr int DN = 64;  // columns of a tile of those products
 
 // 64 corrupting rows of an item.  Thread (group, 16 bytes of the row), DR rows at a time in registers with their sums over
@@ -530,6 +598,7 @@ __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks, i
         if (!item_of(a, unit_of_block(block - go_blocks, tiles, tile), c, slot, item)) return;
         const int j0 = tile * BM, rows = min(BM, a.k - j0), n = item.n;
         if (n <= DP_FEW) {
+            if (a.form_v) return;
             dp_few(a, slot, tile, item, reinterpret_cast<float4(*)[RT]>(lds), reinterpret_cast<float(*)[BM]>(lds + 4 * MB * RT));
             return;
         }
@@ -882,7 +951,7 @@ TransrArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& 
     a.max_items = transr_max_items(gsz, a.n_rel);
     a.max_pblocks = transr_max_pblocks(gsz, a.n_rel);
     a.gamma = gamma; a.wk = 1.f / ((float)(k > 0 ? k : 1) * (float)ids.b);
-    a.out_w = 0; a.train = 1; a.segments = 1;
+    a.out_w = 0; a.train = 1; a.form_v = 0; a.segments = 1;
     a.q = c->tr_groups;
     a.O = c->O; a.PP = c->PP; a.P = c->P3; a.V = c->P3 + (int64_t)c->cfg.max_batch * c->cfg.max_neg_per_chunk * D;
     a.N = c->Nst; a.S = c->S; a.GO = c->GO; a.GOp = c->tr_go_part;
@@ -898,6 +967,9 @@ int back_segments(const TransrArgs& a) {
     int s = (KGE_TRANSR_BACK_WGS + base - 1) / base;
     return s > a.max_items ? a.max_items : s;
 }
+
+// Where the projection holds W (no loss kernel) and whole rows of P (one pass over the columns), it forms V itself.
+bool forms_v(const kge_ctx* c) { return c->cfg.ent_dim <= BN; }
 
 // column tiles of 16 per workgroup
 #define KGE_BY_COLUMNS(D, LAUNCH)                                                                     \
@@ -928,7 +1000,7 @@ void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& i
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* out, int ld_out, bool train,
                        bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, gamma);
-    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train;
+    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train; a.form_v = train && form_w && forms_v(c);
     const int blocks = pblock_blocks(a, (k + BM - 1) / BM);
 #define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, flat_grid(blocks), dim3(RT), 0, st, a, blocks)
     KGE_BY_COLUMNS(a.D, L);
@@ -936,8 +1008,9 @@ int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, in
     return form_w ? blocks : 0;
 }
 
-void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, hipStream_t st) {
-    const TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
+void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, bool form_w, hipStream_t st) {
+    TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
+    a.form_v = form_w && forms_v(c);
     const int cols = (a.D + DN - 1) / DN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
     const int blocks = go_blocks + item_blocks(a, (k + BM - 1) / BM);
     const dim3 grid = flat_grid(blocks);

@@ -148,7 +148,7 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
     }
     {
         ProfScope p(c, KGE_PROF_CHAIN);
-        kge_transr_dp(c, ids, K, G, st);
+        kge_transr_dp(c, ids, K, G, form_w, st);
     }
     {
         ProfScope p(c, KGE_PROF_BACKWARD);

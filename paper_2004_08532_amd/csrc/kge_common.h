@@ -252,7 +252,7 @@ void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& i
 // train: keep the projections, rows in the order of the members; form_w: store W = dL/df- instead of the scores, returns the number of loss sums left
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, float gamma, float* out, int ld_out,
                        bool train, bool form_w, hipStream_t st);
-void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int g, hipStream_t st);
+void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int g, bool form_w, hipStream_t st);  // (form_w as in kge_transr_project)
 void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, hipStream_t st);
 void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int g, hipStream_t st);
 void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
