@@ -22,14 +22,16 @@
 //                     K range is the corrupting rows and the positives
 //   k_transr_update   duplicate reduction and Adagrad for the relation rows [r | M] (Sec. 3.1 step 4); the partial sums
 //                     of k_transr_back
-// The products run on v_mfma_f32_16x16x4_f32: a workgroup owns 64 rows x up to 128 columns (whole matrices at D <= 128),
+// The products run on v_mfma_f32_16x16x4_f32, those of k_transr_back and k_transr_mgrad of longer rows on the bf16 matrix
+// cores: a workgroup owns 64 rows x up to 128 columns (whole matrices at D <= 128),
 // K in blocks of 32 staged in LDS for its four waves (16 rows each), the next block's global loads in flight while one is
 // multiplied.  (128 rows per workgroup were measured: equal or slower, half as many waves fit a SIMD.)  All sums have a
 // fixed order.
-// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 292 us per step, 450 with three products per
-// positive on 32x32 tiles, projections written and read four times; b 798, g 266, k 52, D 56, 21 relations: 192 -> 74.
-// The three large products take 63-71 us each: 29 us of matrix instructions (a quarter of them padding, 100 -> 112 rows and
-// columns), the rest the start of a workgroup (four dependent loads) and an uneven number of workgroups per CU.
+// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 292 us per step with all products in fp32 and V
+// in a launch of its own (450 with three products per positive on 32x32 tiles, projections written and read four times; b 798,
+// g 266, k 52, D 56, 21 relations: 192 -> 74).  The three large products took 63-71 us each: 29 us of matrix instructions (a
+// quarter of them padding, 100 -> 112 rows and columns), the rest the start of a workgroup (four dependent loads) and an uneven
+// number of workgroups per CU.
 #include <type_traits>
 
 #include "k_gemm_shared.h"
@@ -46,7 +48,6 @@ constexpr int PB = TRANSR_PB;              // positives per block of an item's p
 constexpr int DP_FEW = 16;                 // items of at most so many positives: V and dL/do positive by positive
 static_assert(DP_FEW <= PB, "such an item is one block");
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 struct TransrArgs {
@@ -207,6 +208,112 @@ template <int N>
 __device__ __forceinline__ void mask_mc(int K, int blk, int k0, int step, float4* r) {
 #pragma unroll
     for (int it = 0; it < N; ++it) r[it] = BK * blk + k0 + step * it >= K ? f4(0.f) : r[it];
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Products whose B is stored with K along its rows, on the bf16 matrix cores, operands in three parts (k_split.h): 96 matrix
+// cycles per 16 x 16 x 32 instead of 256.  A wave's sixteen rows of A are its own, so they go from memory to registers as the
+// instruction wants them (lane: row lane % 16, eight values of K from 8 (lane / 16) on) and are split there; B is split once
+// on its way to LDS, [column][k], 80 bytes per column with the 16-byte groups permuted by column / 16, so that neither the
+// reads of 16 columns nor the transposing writes (columns four apart) pile up on a few banks.
+// From SPLIT_FROM column tiles on, where the matrix instructions outweigh what splitting adds to the chain of a K block
+// (k_transr_back, k_transr_mgrad; us per step, fp32 -> split): D 100 FB15k-sized 290 -> 270, D 124 k 500 340 -> 287, D 400 401 ->
+// 370, D 96 97.3 -> 93.0; D 64 62.5 -> 70.3, D 48 153.5 -> 158.5.  The projections (B with K along its columns) measured the
+// same at D 100 and slower elsewhere (D 400: 123 -> 147).  Three workgroups per CU: held to four they spill, two are slower
+// (FB15k-sized 239 against 268).  Error against 64 bits of the entities' gradients 1.9e-7 -> 0.7e-7, matrices 0.9e-7 -> 0.6e-7.
+constexpr int SPLIT_FROM = 5;
+constexpr int SP = 40;  // bf16 per column
+__device__ __forceinline__ int split_at(int col, int group) { return col * SP + 8 * (group ^ ((col >> 4) & 3)); }
+
+template <int NT>
+struct SplitTile {
+    floatx4 big[NT], acc[NT];  // (acc: the small products, after split_run the sum)
+    int wave, lane;
+    bool active;  // the wave has rows
+    __device__ __forceinline__ int row16(int v) const { return 4 * (lane >> 4) + v; }
+    __device__ __forceinline__ int row(int v) const { return 16 * wave + row16(v); }  // of accumulator v
+    __device__ __forceinline__ int a_row() const { return 16 * wave + (lane & 15); }  // of A
+    __device__ __forceinline__ int a_k() const { return 8 * (lane >> 4); }
+};
+template <int NT>
+__device__ __forceinline__ void split_init(SplitTile<NT>& t, int rows) {
+    t.wave = row_wave(); t.lane = threadIdx.x & 63;
+    t.active = __builtin_amdgcn_readfirstlane(16 * t.wave < rows);
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) t.big[ct] = t.acc[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
+}
+
+// A thread's piece of B, K values 4 (tid / 32) .. of columns 4 (tid % 32) .., transposed on the way to LDS
+template <bool LARGE>
+__device__ __forceinline__ void split_store(uint16_t* Bs, int stride, int cols, const float4 (&r)[4]) {
+    const int tid = threadIdx.x, k = 4 * (tid / 32);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+        const int col = 4 * (tid % 32) + it;
+        if (col >= cols) continue;
+        auto at_col = [&](const float4& v) { return it == 0 ? v.x : it == 1 ? v.y : it == 2 ? v.z : v.w; };
+        const Split2 lo = split2<LARGE>(at_col(r[0]), at_col(r[1])), hi = split2<LARGE>(at_col(r[2]), at_col(r[3]));
+        uint16_t* at = Bs + split_at(col, k >> 3) + (k & 4);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(at + q * stride) = make_uint2(lo.p[q], hi.p[q]);
+    }
+}
+template <bool LARGE>
+__device__ __forceinline__ Split8 split_row(const float4& x, const float4& y) {
+    const Split2 s[4] = {split2<LARGE>(x.x, x.y), split2<LARGE>(x.z, x.w), split2<LARGE>(y.x, y.y), split2<LARGE>(y.z, y.w)};
+    Split8 r;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) r.p[q] = __builtin_bit_cast(bf16x8, make_uint4(s[0].p[q], s[1].p[q], s[2].p[q], s[3].p[q]));
+    return r;
+}
+
+// Bs: uint16_t [3][16 NT][SP].  load_a(run, block, two pieces): A's row a_row(), K values a_k() .. a_k() + 7 of the block.
+template <int NT, class LoadA, class MaskA, class LoadB, class MaskB>
+__device__ __forceinline__ void split_run(SplitTile<NT>& t, uint16_t* Bs, int K, int runs, LoadA load_a, MaskA mask_a, LoadB load_b, MaskB mask_b) {
+    constexpr int STRIDE = 16 * NT * SP;
+    const int bpr = (K + BK - 1) / BK, nblk = bpr * runs;
+    float4 ra[2], rb[4];
+    int run = 0, kb = 0;  // of the block that is loaded
+    if (nblk > 0) { load_a(0, 0, ra); load_b(0, 0, rb); }
+    for (int blk = 0; blk < nblk; ++blk) {
+        if (kb == bpr - 1) { mask_a(kb, ra); mask_b(kb, rb); }
+        float m = 0.f, ma = fmaxf(magnitude(ra[0]), magnitude(ra[1]));
+#pragma unroll
+        for (int it = 0; it < 4; ++it) m = fmaxf(m, magnitude(rb[it]));
+        Split8 a;
+        if (__any(is_large(ma))) a = split_row<true>(ra[0], ra[1]);
+        else a = split_row<false>(ra[0], ra[1]);
+        __syncthreads();  // the block before has been read
+        if (__any(is_large(m))) split_store<true>(Bs, STRIDE, 16 * NT, rb);
+        else split_store<false>(Bs, STRIDE, 16 * NT, rb);
+        __syncthreads();
+        if (kb == bpr - 1) { kb = 0; ++run; } else { ++kb; }
+        if (blk + 1 < nblk) { load_a(run, kb, ra); load_b(run, kb, rb); }
+        if (t.active) {
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) {
+                const uint16_t* p = Bs + split_at(16 * ct + (t.lane & 15), t.lane >> 4);
+                Split8 b;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) b.p[q] = *reinterpret_cast<const bf16x8*>(p + q * STRIDE);
+                mfma_split(a, b, t.big[ct], t.acc[ct]);
+            }
+        }
+    }
+}
+template <int NT>
+__device__ __forceinline__ void split_sum(SplitTile<NT>& t) {
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) t.acc[ct] += t.big[ct];
+}
+// a row of A whose K floats start at p
+__device__ __forceinline__ void load_row(const float* p, int k, int K, float4 (&r)[2]) {
+    r[0] = ld4(p + (k < K ? k : 0));
+    r[1] = ld4(p + (k + 4 < K ? k + 4 : 0));
+}
+__device__ __forceinline__ void mask_row(int k, int K, float4 (&r)[2]) {
+    r[0] = k < K ? r[0] : f4(0.f);
+    r[1] = k + 4 < K ? r[1] : f4(0.f);
 }
 
 // x of the lane that control word CTRL names (within a row of 16 lanes: vector ALU moves, no LDS)
@@ -708,7 +815,7 @@ __global__ __launch_bounds__(RT) void k_transr_go(TransrArgs a) {
 // V_t M_t.  The first workgroups: 64 corrupting rows of a chunk x 128 columns x a range of the chunk's items; the others:
 // dL/do and dL/dp of a block of an item's positives (rows 2 m, 2 m + 1) x 128 columns, straight into their gradient rows.
 template <int NT>
-__global__ __launch_bounds__(RT, 4) void k_transr_back(TransrArgs a, int neg_blocks) {
+__global__ __launch_bounds__(RT, 4) void k_transr_back_f32(TransrArgs a, int neg_blocks) {
     __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
     const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15;
     Tile<NT> t;
@@ -794,7 +901,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_back(TransrArgs a, int neg_blo
 
 // 64 rows x 128 columns of dL/dM of an item.  K: the chunk's corrupting rows, then two rows per positive.
 template <int NT>
-__global__ __launch_bounds__(RT, 4) void k_transr_mgrad(TransrArgs a) {
+__global__ __launch_bounds__(RT, 4) void k_transr_mgrad_f32(TransrArgs a) {
     __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
     const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, tiles = (D + BM - 1) / BM * cols;
     int c, slot, tile;
@@ -843,6 +950,153 @@ __global__ __launch_bounds__(RT, 4) void k_transr_mgrad(TransrArgs a) {
         for (int ct = 0; ct < NT; ++ct) {
             const int d = n0 + 16 * ct + l16;
             if (d < D) out[(int64_t)e * D + d] = t.acc[ct][v];
+        }
+    }
+}
+
+// The same on the bf16 matrix cores.
+template <int NT>
+__global__ __launch_bounds__(RT, 3) void k_transr_back(TransrArgs a, int neg_blocks) {
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[3 * 16 * NT * SP];
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15;
+    SplitTile<NT> t;
+    const bool neg = (int)blockIdx.x < neg_blocks;
+    const int x = neg ? blockIdx.x : blockIdx.x - neg_blocks;
+    const int n0 = x % cols * BN, col = n0 + 4 * (tid % 32), colc = col < D ? col : n0;  // D is a multiple of 4
+    if (neg) {
+        const int tiles = (a.k + BM - 1) / BM, seg = x / cols % a.segments, y = x / cols / a.segments;
+        const int tile = y % tiles, c = y / tiles, j0 = tile * BM, rows = min(BM, a.k - j0);
+        const int items = a.q.n_items[c], s0 = (int)((int64_t)items * seg / a.segments), s1 = (int)((int64_t)items * (seg + 1) / a.segments);
+        split_init(t, rows);
+        const float* V = a.V + (((int64_t)c * a.g + s0) * a.k + j0 + min(t.a_row(), rows - 1)) * D;
+        // the matrix of the item at hand and of the next one (its relation id is asked for an item ahead)
+        const TransrItem* item = a.q.items + c * a.g + s0;
+        const int last = s1 - s0 - 1;
+        int cur = 0;
+        const float* here = a.R + D + (last >= 0 ? item[0].rel : 0) * a.rel_dim + colc;
+        uint32_t next = last >= 0 ? item[last > 0].rel : 0;
+        split_run(t, Bs, D, s1 - s0,
+            [&](int run, int kb, float4 (&r)[2]) { load_row(V + (int64_t)run * a.k * D, BK * kb + t.a_k(), D, r); },
+            [&](int kb, float4 (&r)[2]) { mask_row(BK * kb + t.a_k(), D, r); },
+            [&](int run, int kb, float4* r) {
+                if (run != cur) {
+                    cur = run;
+                    here = a.R + D + next * a.rel_dim + colc;
+                    next = item[min(run + 1, last)].rel;
+                }
+                load_mc<4>(here, D, D, kb, 4 * (tid / 32), 1, r);
+            },
+            [&](int kb, float4* r) { mask_mc<4>(D, kb, 4 * (tid / 32), 1, r); });
+        split_sum(t);
+        float* out = a.back_part + (((int64_t)seg * (a.b / a.g) + c) * a.k + j0) * D;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (t.row(v) < rows) out[(int64_t)t.row(v) * D + d] = t.acc[ct][v];
+                }
+            }
+        }
+        return;
+    }
+    int c;
+    TransrBlock blk;
+    if (!pblock_of(a, x / cols, c, blk)) return;
+    const int n = blk.n;
+    const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D + colc;
+    const bool head = step_view(a.ids).side == KGE_NEG_HEAD;
+    split_init(t, 2 * n);
+    const int row = min(t.a_row(), 2 * n - 1);
+    const float* pa = ((row & 1) ? a.PP : a.GO) + (int64_t)(blk.off + row / 2) * D;
+    int i[2];  // rows 2 h, 2 h + 1 of the lane's four
+#pragma unroll
+    for (int h = 0; h < 2; ++h) i[h] = a.q.members[blk.off + min(t.row(2 * h) / 2, n - 1)];
+    split_run(t, Bs, D, 1, [&](int, int kb, float4 (&r)[2]) { load_row(pa, BK * kb + t.a_k(), D, r); },
+                     [&](int kb, float4 (&r)[2]) { mask_row(BK * kb + t.a_k(), D, r); },
+                     [&](int, int kb, float4* r) { load_mc<4>(M, D, D, kb, 4 * (tid / 32), 1, r); },
+                     [&](int kb, float4* r) { mask_mc<4>(D, kb, 4 * (tid / 32), 1, r); });
+    split_sum(t);
+    if (!t.active) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (t.row(v) >= 2 * n) continue;
+        // key positions: heads 0 .. b-1, tails b .. 2b-1; even rows belong to the kept entity
+        const bool to_head = head == (bool)(v & 1);
+        float* out = a.Gent + ((int64_t)(to_head ? 0 : a.b) + i[v / 2]) * D;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) out[d] = t.acc[ct][v];
+        }
+    }
+}
+
+template <int NT>
+__global__ __launch_bounds__(RT, 3) void k_transr_mgrad(TransrArgs a) {
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[3 * 16 * NT * SP];
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, tiles = (D + BM - 1) / BM * cols;
+    int c, slot, tile;
+    TransrItem item;
+    if (!item_of(a, unit_of_block(blockIdx.x, tiles, tile), c, slot, item)) return;
+    const int n0 = tile % cols * BN, e0 = tile / cols * BM, n2 = 2 * item.n;
+    const int cb = n0 + 4 * (tid % 32), kb0 = 4 * (tid / 32), cbc = cb < D ? cb : n0;
+    SplitTile<NT> t;
+    split_init(t, min(BM, D - e0));
+    const int e = min(e0 + t.a_row(), D - 1);
+    const float* V = a.V + (int64_t)slot * a.k * D + e;
+    const float* N = a.N + (int64_t)c * a.k * D + cbc;
+    const uint32_t* ent = a.q.ent + 2 * item.off;
+    uint32_t id[4];  // of the first block of positives: there when the corrupting rows are done
+#pragma unroll
+    for (int it = 0; it < 4; ++it) id[it] = ent[min(kb0 + it, n2 - 1)];
+    // A is stored with K along its rows: a lane's eight values are eight rows of 16 consecutive lanes' floats
+    auto eight = [&](float4 (&r)[2], auto at) {
+        r[0] = make_float4(at(0), at(1), at(2), at(3));
+        r[1] = make_float4(at(4), at(5), at(6), at(7));
+    };
+    auto mask_eight = [&](int k, int K, float4 (&r)[2]) {
+        r[0] = make_float4(k < K ? r[0].x : 0.f, k + 1 < K ? r[0].y : 0.f, k + 2 < K ? r[0].z : 0.f, k + 3 < K ? r[0].w : 0.f);
+        r[1] = make_float4(k + 4 < K ? r[1].x : 0.f, k + 5 < K ? r[1].y : 0.f, k + 6 < K ? r[1].z : 0.f, k + 7 < K ? r[1].w : 0.f);
+    };
+    split_run(t, Bs, a.k, 1,
+        [&](int, int kb, float4 (&r)[2]) {
+            const int k = BK * kb + t.a_k();
+            eight(r, [&](int j) { return V[(int64_t)min(k + j, a.k - 1) * D]; });
+        },
+        [&](int kb, float4 (&r)[2]) { mask_eight(BK * kb + t.a_k(), a.k, r); },
+        [&](int, int kb, float4* r) { load_mc<4>(N, D, a.k, kb, kb0, 1, r); },
+        [&](int kb, float4* r) { mask_mc<4>(a.k, kb, kb0, 1, r); });
+    split_run(t, Bs, n2, 1,
+        [&](int, int kb, float4 (&r)[2]) {
+            const int k = BK * kb + t.a_k();
+            eight(r, [&](int j) {
+                const int kk = min(k + j, n2 - 1);
+                return ((kk & 1) ? a.PP : a.GO)[(int64_t)(item.off + kk / 2) * D + e];
+            });
+        },
+        [&](int kb, float4 (&r)[2]) { mask_eight(BK * kb + t.a_k(), n2, r); },
+        [&](int, int kb, float4* r) {
+            if (kb > 0) {
+#pragma unroll
+                for (int it = 0; it < 4; ++it) id[it] = ent[min(BK * kb + kb0 + it, n2 - 1)];
+            }
+#pragma unroll
+            for (int it = 0; it < 4; ++it) r[it] = ld4(a.E + (int64_t)id[it] * D + cbc);
+        },
+        [&](int kb, float4* r) { mask_mc<4>(n2, kb, kb0, 1, r); });
+    split_sum(t);
+    float* out = a.GM + (int64_t)slot * D * D;
+    const int l16 = tid & 15;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int er = e0 + t.row(v);
+        if (er >= D) continue;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) out[(int64_t)er * D + d] = t.acc[ct][v];
         }
     }
 }
@@ -968,8 +1222,26 @@ int back_segments(const TransrArgs& a) {
     return s > a.max_items ? a.max_items : s;
 }
 
-// Where the projection holds W (no loss kernel) and whole rows of P (one pass over the columns), it forms V itself.
-bool forms_v(const kge_ctx* c) { return c->cfg.ent_dim <= BN; }
+// Does the projection form V of items of few positives?  It has to hold W (no loss kernel) and whole rows of P (one pass over the
+// columns), and it pays where most of k_transr_dp's work goes away: chunks that have hardly an item of more than DP_FEW
+// positives, and rows worth more than the launch that stays for the others.  (us per step, k_transr_dp -> projection: chunks of
+// 16 to 64, k 128, D 64 102 -> 96, k 500, D 36 143 -> 134, k 64, D 100 164 -> 160, k 32, D 64 66.7 -> 67.4; FB15k-sized 287 -> 274;
+// chunks of 256, 60 relations 143 -> 149, chunks of 1000, 1000 relations 200 -> 206.)
+bool forms_v(const kge_ctx* c, int k, int gsz) {
+    const int D = c->cfg.ent_dim;
+    return D <= BN && (int64_t)k * D >= 4096 && (gsz <= 64 || c->cfg.num_relations >= 8 * (int64_t)gsz);
+}
+
+template <int NT>
+auto back_kernel() {
+    if constexpr (NT < SPLIT_FROM) return k_transr_back_f32<NT>;
+    else return k_transr_back<NT>;
+}
+template <int NT>
+auto mgrad_kernel() {
+    if constexpr (NT < SPLIT_FROM) return k_transr_mgrad_f32<NT>;
+    else return k_transr_mgrad<NT>;
+}
 
 // column tiles of 16 per workgroup
 #define KGE_BY_COLUMNS(D, LAUNCH)                                                                     \
@@ -1000,7 +1272,7 @@ void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& i
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* out, int ld_out, bool train,
                        bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, gamma);
-    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train; a.form_v = train && form_w && forms_v(c);
+    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train; a.form_v = train && form_w && forms_v(c, k, gsz);
     const int blocks = pblock_blocks(a, (k + BM - 1) / BM);
 #define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, flat_grid(blocks), dim3(RT), 0, st, a, blocks)
     KGE_BY_COLUMNS(a.D, L);
@@ -1010,7 +1282,7 @@ int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, in
 
 void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
-    a.form_v = form_w && forms_v(c);
+    a.form_v = form_w && forms_v(c, k, gsz);
     const int cols = (a.D + DN - 1) / DN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
     const int blocks = go_blocks + item_blocks(a, (k + BM - 1) / BM);
     const dim3 grid = flat_grid(blocks);
@@ -1030,7 +1302,7 @@ void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int 
     if (a.segments == 1) a.back_part = out;
     const int neg_blocks = chunks * ((k + BM - 1) / BM) * a.segments * cols;
     const dim3 grid(neg_blocks + chunks * a.max_pblocks * cols);
-#define L(NT) KGE_LAUNCH(c, k_transr_back<NT>, grid, dim3(RT), 0, st, a, neg_blocks)
+#define L(NT) KGE_LAUNCH(c, back_kernel<NT>(), grid, dim3(RT), 0, st, a, neg_blocks)
     KGE_BY_COLUMNS(a.D, L);
 #undef L
 }
@@ -1038,7 +1310,7 @@ void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int 
 void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int gsz, hipStream_t st) {
     const TransrArgs a = make_args(c, E, nullptr, ids, k, gsz, 0.f);
     const dim3 grid(item_blocks(a, ((a.D + BM - 1) / BM) * ((a.D + BN - 1) / BN)));
-#define L(NT) KGE_LAUNCH(c, k_transr_mgrad<NT>, grid, dim3(RT), 0, st, a)
+#define L(NT) KGE_LAUNCH(c, mgrad_kernel<NT>(), grid, dim3(RT), 0, st, a)
     KGE_BY_COLUMNS(a.D, L);
 #undef L
 }

@@ -391,6 +391,12 @@ TRANSR_ITEMS = {
     # projections, dL/dP and relation update of more than 2^20 workgroups each: grids of two dimensions
     "many-workgroups": dict(batch=540_000, chunk=600, neg_per_chunk=65, ent_dim=4, n_entities=60_000, n_relations=3000,
                             n_triples=600_000, steps=1),
+    # dL/dP in the projection (items up to and beyond 16 positives, a ragged tile of corrupting rows), products in parts
+    # (five column tiles and more, a ragged last one)
+    "projection-16": dict(batch=120, chunk=60, neg_per_chunk=130, ent_dim=36, n_relations=4),
+    "projection-few": dict(batch=48, chunk=16, neg_per_chunk=66, ent_dim=68, n_relations=9),
+    "projection-128": dict(batch=128, chunk=64, neg_per_chunk=33, ent_dim=128, n_relations=40),
+    "projection-100": dict(batch=64, chunk=32, neg_per_chunk=64, ent_dim=100, n_relations=300, loss="ranking", gamma=0.02),
     "long-chunk-many-relations": dict(batch=2100, chunk=2100, neg_per_chunk=5, ent_dim=8, n_relations=4200, n_triples=9000,
                                       adv_temperature=1.0),
 }
