@@ -130,7 +130,7 @@ struct ProfScope {
 // TransR after its gather launch.  Profile slots: phi, neg_score = projections and scores, loss, chain = dL/dP,
 // neg_backward = the back-projection, rel_update, update; dL/dM is not timed.
 int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids,
-                        int K, int G, float gamma, float lr, bool long_lists, hipStream_t st) {
+                        int K, int G, float gamma, float lr, bool long_lists, bool beside, hipStream_t st) {
     // (rows of more than KGE_SHORT_SCORES scores: the loss kernel, with the functions it has for them)
     const bool form_w = kge_gemm_backward_forms_w(c) && K <= KGE_SHORT_SCORES;
     int n_loss_parts;
@@ -155,7 +155,7 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
         kge_transr_back(c, rel, ids, K, G, st);
     }
     kge_transr_mgrad(c, ent, ids, K, G, st);
-    if (long_lists) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    if (beside) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     {
         ProfScope p(c, KGE_PROF_REL_UPDATE);
         kge_transr_update(c, rel, rel_state, ids, lr, st);
@@ -180,7 +180,7 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
 // Chunks of one positive.  Profile slots: gather = the key order, neg_backward = k_ind, update = the entity rows (without
 // the join of runs that cross tiles), rel_update = relation rows and loss.
 int enqueue_ind_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids, int K,
-                     float gamma, float lr, bool long_lists, hipStream_t st) {
+                     float gamma, float lr, bool long_lists, bool beside, hipStream_t st) {
     if (!long_lists) {
         ProfScope p(c, KGE_PROF_GATHER);
         kge_launch_key_order(c, ids, st);
@@ -189,7 +189,7 @@ int enqueue_ind_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float
         ProfScope p(c, KGE_PROF_BACKWARD);
         kge_ind_step(c, ent, rel, ids, K, gamma, st);
     }
-    if (long_lists) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    if (beside) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     {
         ProfScope p(c, KGE_PROF_UPDATE);
         kge_launch_update_runs(c, ent, ent_state, ids, K, lr, st);
@@ -214,10 +214,20 @@ int enqueue_ind_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float
 int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids, int K,
                  int G, float gamma, float lr, hipStream_t st) {
     const int B = ids.b;
-    // Ordering the key lists needs only the ids.  Short lists are ordered by extra blocks of the gather launch;
-    // long ones by a radix sort on a second stream that joins before the update.
-    const bool long_lists = 2 * B + ids.n_neg > KGE_RANK_MAX_KEYS;
-    if (long_lists) {
+    // Ordering the key lists needs only the ids.  Short lists are ordered by extra blocks of the gather launch; long ones by a
+    // radix sort, on a second stream that joins before the update.  A fork and a join cost about 10 us each outside of a graph,
+    // and k_ind slows down what runs beside it, so the steps of chunks of one positive that are launched one by one sort on
+    // the main stream, where that takes less (us per step, beside -> before: TransE-L2 b 1024 k 256 D 400 156 -> 149, b 512
+    // k 64 D 128 75 -> 59; replayed 147.5 -> 148, 62 -> 59; RotatE b 1024 k 256 D 400 198 -> 205, k 128 D 200 111 -> 105;
+    // chunks of more positives, TransE-L2 b 2048 g 8 k 64 D 200 87 -> 92).
+    const bool long_lists = 2 * B + ids.n_neg > KGE_RANK_MAX_KEYS, ind = kge_ind_step_fits(c, G);
+    const bool long_ind = c->cfg.model == KGE_ROTATE && (int64_t)ids.n_neg * c->cfg.ent_dim >= (int64_t)1 << 26;
+    const bool beside = long_lists && (!ind || ids.blk || long_ind);
+    if (long_lists && !beside) {
+        ProfScope p(c, KGE_PROF_SORT);
+        kge_launch_sort(c, ids, st);
+    }
+    if (beside) {
         KGE_HIP(c, hipEventRecord(c->ev_fork, st));
         KGE_HIP(c, hipStreamWaitEvent(c->side_stream, c->ev_fork, 0));
         {
@@ -227,7 +237,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         KGE_HIP(c, hipEventRecord(c->ev_join, c->side_stream));
     }
     if (c->cfg.validate_indices) launch_validate(c, ids, st);
-    if (kge_ind_step_fits(c, G)) return enqueue_ind_rest(c, ent, ent_state, rel, rel_state, ids, K, gamma, lr, long_lists, st);
+    if (ind) return enqueue_ind_rest(c, ent, ent_state, rel, rel_state, ids, K, gamma, lr, long_lists, beside, st);
     if (c->cfg.model == KGE_RESCAL) {
         ProfScope p(c, KGE_PROF_PHI);
         kge_launch_rescal_phi(c, ent, rel, ids, st);
@@ -240,7 +250,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         ProfScope p(c, KGE_PROF_GATHER);
         kge_launch_gather(c, ent, rel, ids, G, gamma, nullptr, !long_lists, st);
     }
-    if (c->cfg.model == KGE_TRANSR) return enqueue_transr_rest(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, long_lists, st);
+    if (c->cfg.model == KGE_TRANSR) return enqueue_transr_rest(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, long_lists, beside, st);
     if (!front) {
         ProfScope p(c, KGE_PROF_SCORE);
         if (is_gemm_model(c->cfg.model))
@@ -267,7 +277,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_chain(c, ent, rel, ids, st);
         else kge_launch_chain(c, ent, rel, ids, st);
     }
-    if (long_lists) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    if (beside) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (c->cfg.model == KGE_RESCAL) {
         ProfScope p(c, KGE_PROF_REL_UPDATE);
         kge_launch_rescal_update(c, rel, rel_state, ids, lr, st);
