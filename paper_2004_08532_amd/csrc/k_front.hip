@@ -9,6 +9,8 @@
 // (k_gather_rows.h), which need nothing from the tiles.  What it saves is the ramp and the drain of a launch and a round
 // trip through memory: gather + forward 8.0 + 7.2 -> 13.4 us at Freebase scale, 8.3 + 6.7 -> 11.1 FB15k-sized (D 400),
 // 5.1 + 5.3 -> 6.9 in a step of 256 positives (D 64).
+// TransE-L1 forms its sums of absolute differences from the same staged rows.  (RotatE does not: every tile would form the
+// sines and cosines of its 32 relation rows again.)
 #include "k_gather_rows.h"
 #include "k_gemm_shared.h"
 
@@ -98,6 +100,7 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
     const int by = m0 / TILE, sharers = min(f.gy, RPW);
     auto stages = [&](int q) { return f.stage && q % sharers == by && n0 + w + FW * q < f.k; };
     floatx16 acc = {}, acc2 = {};  // (two, so that a sum is a chain of half the length)
+    float sums[2][2] = {{0.f, 0.f}, {0.f, 0.f}};  // TransE-L1
     float on = 0.f, nn = 0.f;  // TransE-L2: |o|^2 and |n|^2 of row lane % 32 over this lane's part of K
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -108,7 +111,7 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
             float4 o = A[q][p], n = N[q][p];
             const float4 r = R[q][p];
             if (MODEL == KGE_DISTMULT) o = make_float4(o.x * r.x, o.y * r.y, o.z * r.z, o.w * r.w);
-            if (MODEL == KGE_TRANSE_L2) {
+            if (MODEL == KGE_TRANSE_L2 || MODEL == KGE_TRANSE_L1) {
                 o = head ? make_float4(o.x - r.x, o.y - r.y, o.z - r.z, o.w - r.w)
                          : make_float4(o.x + r.x, o.y + r.y, o.z + r.z, o.w + r.w);
             }
@@ -119,6 +122,37 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
             st4(Bs + (w + FW * q) * PITCH + 4 * lane, n);
         }
         __syncthreads();
+        if constexpr (MODEL == KGE_TRANSE_L1) {
+            // pairs (ti + {0,16}, tj + {0,16}); the two halves of the workgroup take groups of four coordinates in turn.  32
+            // coordinates are summed on their own, then added to the total: the order of k_pair_fwd, bit for bit
+            for (int c0 = 0; c0 < width(p); c0 += 32) {
+                float part[2][2] = {{0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll
+                for (int cq = 0; cq < 32; cq += 8) {
+                    const int cc = c0 + cq + 4 * (threadIdx.x >> 8);
+                    if (cc >= width(p)) break;
+                    float4 o[2], n[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        o[u] = ld4(As + ((threadIdx.x >> 4 & 15) + 16 * u) * PITCH + cc);
+                        n[u] = ld4(Bs + ((threadIdx.x & 15) + 16 * u) * PITCH + cc);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            part[u][q] += fabsf(o[u].x - n[q].x);
+                            part[u][q] += fabsf(o[u].y - n[q].y);
+                            part[u][q] += fabsf(o[u].z - n[q].z);
+                            part[u][q] += fabsf(o[u].w - n[q].w);
+                        }
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) { sums[u][0] += part[u][0]; sums[u][1] += part[u][1]; }
+            }
+            continue;
+        }
         const int octets = (width(p) + 7) / 8;
         const float* ra = As + (lane & 31) * PITCH + 4 * (lane >> 5);
         const float* rb = Bs + (lane & 31) * PITCH + 4 * (lane >> 5);
@@ -135,6 +169,22 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
         }
     }
     __syncthreads();
+    if constexpr (MODEL == KGE_TRANSE_L1) {
+        float* C = f.C + (int64_t)c * f.g * f.ldc;
+        float* other = lds + 4 * (threadIdx.x & 255);
+        if (threadIdx.x >= 256) st4(other, make_float4(sums[0][0], sums[0][1], sums[1][0], sums[1][1]));
+        __syncthreads();
+        if (threadIdx.x >= 256) return;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int i = m0 + (threadIdx.x >> 4) + 16 * u, j = n0 + (threadIdx.x & 15) + 16 * q;
+                if (i < f.g && j < f.k) C[(int64_t)i * f.ldc + j] = a.gamma - (sums[u][q] + other[2 * u + q]);
+            }
+        }
+        return;
+    }
     // sums of the waves (in wave order) and the norms
     float* norms = lds + FW * TILE * TILE;
     if (MODEL == KGE_TRANSE_L2) {
@@ -205,6 +255,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 // Forward of chunks of gsz positives and k corrupting rows in the gather launch?
 // Tiles read a table row once per tile that needs it, the gather launch once, so the line lies where that costs more than a
 // launch (us per training step, separate -> one launch; TransE-L2):
+//   (TransE-L1, rows of 400: 256 61.4 -> 57.2, 768 107.5 -> 103.4; of 64: 416 41.1 -> 41.6, 512 54.9 -> 52.3)
 //   tiles   rows of 400: 256 41.7 -> 37.9, 640 65.9 -> 60.4, 768 68.9 -> 64.6, 1024 66.9 -> 67.1
 //           rows of 160: 640 46.3 -> 44.5, 768 47.6 -> 47.4;  of 128: 624 40.3 -> 39.1, 640 43.4 -> 43.6, 768 44.6 -> 46.7
 //   keys    ordered by brute force here, in buckets of the id range in the gather launch of long lists (512 tiles and
@@ -214,13 +265,13 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 bool kge_front_fits(const kge_ctx* c, int b, int k, int gsz, bool with_keys) {
     const int m = c->cfg.model, D = c->cfg.ent_dim;
     if (c->cfg.gemm_input != 0 || D > 2 * SLICE) return false;
-    if (m != KGE_TRANSE_L2 && m != KGE_DISTMULT && m != KGE_COMPLEX && m != KGE_RESCAL) return false;
+    if (m != KGE_TRANSE_L2 && m != KGE_TRANSE_L1 && m != KGE_DISTMULT && m != KGE_COMPLEX && m != KGE_RESCAL) return false;
     const int64_t chunks = b / gsz, tiles = chunks * ((gsz + TILE - 1) / TILE) * ((k + TILE - 1) / TILE);
     return tiles <= (D > 128 ? 768 : 512) && !(with_keys && 2 * (int64_t)b + chunks * k > FRONT_MAX_KEYS);
 }
 
 void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* pos_out,
-                      bool with_keys, float* out, int ld_out, int out_mode, hipStream_t st) {
+                      bool train, bool with_keys, float* out, int ld_out, int out_mode, hipStream_t st) {
     FrontArgs f = {};
     kge_fill_gather_args(c, E, R, ids, gsz, gamma, pos_out, &f.ga);
     f.C = out; f.ldc = ld_out; f.g = gsz; f.k = k;
@@ -229,7 +280,7 @@ void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds&
     f.out_mode = out_mode;
     f.wk = 1.f / ((float)k * (float)ids.b);
     f.neg_loss_part = c->neg_loss_part;
-    f.stage = out_mode != OUT_SCORE;
+    f.stage = train;
     if (with_keys) {
         constexpr int ITEMS = RankShape<FT>::ITEMS;
         kge_make_key_lists(c, ids, &f.ga.ent, &f.ga.rel);
@@ -245,6 +296,10 @@ void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds&
     case KGE_TRANSE_L2:
         if (nv == 1) KGE_LAUNCH(c, (k_front<KGE_TRANSE_L2, 1>), grid, dim3(FT), 0, st, f);
         else KGE_LAUNCH(c, (k_front<KGE_TRANSE_L2, 2>), grid, dim3(FT), 0, st, f);
+        break;
+    case KGE_TRANSE_L1:
+        if (nv == 1) KGE_LAUNCH(c, (k_front<KGE_TRANSE_L1, 1>), grid, dim3(FT), 0, st, f);
+        else KGE_LAUNCH(c, (k_front<KGE_TRANSE_L1, 2>), grid, dim3(FT), 0, st, f);
         break;
     case KGE_DISTMULT:
         if (nv == 1) KGE_LAUNCH(c, (k_front<KGE_DISTMULT, 1>), grid, dim3(FT), 0, st, f);

@@ -100,7 +100,7 @@ void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids,
     }
     if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_phi(c, ent, rel, ids, st);
     if (neg_out && k > 0 && dist_mode == 0 && kge_front_fits(c, ids.b, k, chunk, false)) {
-        kge_launch_front(c, ent, rel, ids, k, chunk, gamma, pos_out, false, neg_out, ld_out, dist_mode, st);
+        kge_launch_front(c, ent, rel, ids, k, chunk, gamma, pos_out, false, false, neg_out, ld_out, dist_mode, st);
         return;
     }
     kge_launch_gather(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
@@ -245,7 +245,8 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     const bool front = kge_front_fits(c, B, K, G, !long_lists);
     if (front) {
         ProfScope p(c, KGE_PROF_GATHER);
-        kge_launch_front(c, ent, rel, ids, K, G, gamma, nullptr, !long_lists, c->S, c->ld_s, kge_gemm_backward_forms_w(c) ? 2 : 1, st);
+        kge_launch_front(c, ent, rel, ids, K, G, gamma, nullptr, true, !long_lists, c->S, c->ld_s,
+                         !is_gemm_model(c->cfg.model) ? 0 : kge_gemm_backward_forms_w(c) ? 2 : 1, st);
     } else {
         ProfScope p(c, KGE_PROF_GATHER);
         kge_launch_gather(c, ent, rel, ids, G, gamma, nullptr, !long_lists, st);

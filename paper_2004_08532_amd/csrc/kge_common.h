@@ -205,7 +205,7 @@ void kge_launch_gather(kge_ctx* c, const float* E, const float* R, const StepIds
 // ... and a3 in the same launch, where the output has few tiles
 bool kge_front_fits(const kge_ctx* c, int b, int k, int g, bool with_keys);
 void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int g, float gamma, float* pos_out,
-                      bool with_keys, float* out, int ld_out, int out_mode, hipStream_t st);
+                      bool train, bool with_keys, float* out, int ld_out, int out_mode, hipStream_t st);
 void kge_launch_key_order(kge_ctx* c, const StepIds& ids, hipStream_t st);  // the key lists alone
 // chunks of one positive: everything between the ids and the gradient rows of the positives in one launch, and the
 // update of the entity rows that forms the corrupting rows' gradients itself
