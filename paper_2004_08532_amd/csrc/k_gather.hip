@@ -35,7 +35,9 @@ __global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
         }
         return;
     }
-    gather_row<MODEL, NV>(a, (block - a.rank_blocks) * ROWS_PER_BLOCK + (threadIdx.x >> 6));
+    const int lane = threadIdx.x & 63;
+    const int row = (block - a.rank_blocks) * ROWS_PER_BLOCK + (threadIdx.x >> 6);
+#include "k_gather_row_body.h"
 }
 
 template <int MODEL, int THREADS>

@@ -407,11 +407,14 @@ void launch_bwd(kge_ctx* c, GemmArgs gO, GemmArgs gN, int chunks, hipStream_t st
 
 }  // namespace
 
-// Forward products of many tiles: on the bf16 matrix cores (k_gemm_split.hip).  Score calls, us, here -> there: 2016 tiles, D 400
+// Forward products of many tiles: on the bf16 matrix cores (k_gemm_split.hip).  Whole calls, us, here -> there: 2016 tiles, D 400
 // 38.4 -> 28.5, D 64 16.5 -> 13.8; 2048 tiles in chunks of 128 43.6 -> 33.3; 1672 tiles, D 600 49.2 -> 38.8; 3008 tiles in chunks
 // of 16 52.3 -> 52.9; 1504 tiles in chunks of 32 54.5 -> 51.8; 1024 tiles, D 400 23.0 -> 23.6, D 100 13.0 -> 15.2.
-static bool split_forward(int chunks, int gsz, int k) {
-    return (int64_t)chunks * ((gsz + TILE - 1) / TILE) * ((k + TILE - 1) / TILE) >= 1504;
+// Training only.  A candidate that is the replaced entity itself has the positive's score but for rounding, which then decides its
+// rank: of 1000 positives against 1000 uniform and 1000 degree-proportional candidates 33 changed ranks with the sums taken
+// in this other order, and a rank is a whole number that stays what it is.
+static bool split_forward(int out_mode, int chunks, int gsz, int k) {
+    return (out_mode == OUT_DIST || out_mode == OUT_W) && (int64_t)chunks * ((gsz + TILE - 1) / TILE) * ((k + TILE - 1) / TILE) >= 1504;
 }
 
 // S_c = O_c N_c^T with the model's epilogue.  out_mode: 0 the scores (kge_score path); 1 what the loss kernel wants
@@ -439,7 +442,7 @@ void kge_gemm_neg_score(kge_ctx* c, int b, int k, int gsz, float gamma, float* o
         g.sA = (int64_t)gsz * c->ld_bf; g.sB = (int64_t)k * c->ld_bf;
         kge_gemm_bf_forward(c, &g, epi, chunks, st);
     }
-    else if (split_forward(chunks, gsz, k)) kge_gemm_split_forward(c, &g, epi, chunks, st);
+    else if (split_forward(out_mode, chunks, gsz, k)) kge_gemm_split_forward(c, &g, epi, chunks, st);
     else if (epi == EPI_L2_FWD) launch_fwd<EPI_L2_FWD>(c, g, chunks, st);
     else launch_fwd<EPI_PLAIN>(c, g, chunks, st);
 }

@@ -1,13 +1,11 @@
-// The forward product S_c = O_c N_c^T of steps with many output tiles: fp32 operands on the bf16 matrix cores (k_split.h).
+// The forward product S_c = O_c N_c^T of training steps with many output tiles: fp32 operands on the bf16 matrix cores (k_split.h).
 //
 // A workgroup of eight (four) waves owns a 64 x 128 (32 x 128) output tile over the whole of K, a wave a 32 x 32 block of it.
 // Per K block of 32 the threads load the fp32 rows of both operands (whole cache lines, two blocks ahead), split them once and
 // lay the three parts out in LDS; a wave reads six 16-byte operands per six matrix instructions.  LDS is double-buffered, one
 // workgroup barrier per K block.
 // 1000 x 2000 x 400, one tile per CU: 20.3 us, of which 4.7 are matrix instructions, about as much are the vector
-// instructions of the split, and the rest the phases between two barriers; the small fp32 tiles of k_gemm.hip took 38.9 with
-// the count of the ranks in the epilogue (their atomics, one per row and 32 columns, meet on the same cache lines) and 31
-// without.
+// instructions of the split, and the rest the phases between two barriers; the small fp32 tiles of k_gemm.hip take 31.
 #include <type_traits>
 
 #include "k_gemm_shared.h"
@@ -51,13 +49,11 @@ template <int EPI, typename S>
 __global__ __launch_bounds__(S::THREADS) void k_gemm_split_fwd(GemmArgs g) {
     constexpr int BM = S::BM, BN = S::BN, PLANE_A = S::PLANE_A, PLANE_B = S::PLANE_B, STEP = S::STEP, RA = S::RA, RB = S::RB;
     __shared__ __attribute__((aligned(16))) __bf16 lds[2][S::BUFFER];
-    __shared__ int above[BM];
     const int tile = xcd_tile(blockIdx.x >> 3, gridDim.x >> 3);
     if (tile >= g.tiles) return;
     const int t = threadIdx.x, w = t >> 6, lane = t & 63;
     const int n0 = (tile % g.gx) * BN, m0 = (tile / g.gx) % g.gy * BM, c = tile / (g.gx * g.gy);
     const int wm = 32 * (w / (BN / 32)), wn = 32 * (w % (BN / 32));  // this wave's block of the tile
-    if (t < BM) above[t] = 0;
 
     // rows past the end of the matrix: the last row again, dropped in the epilogue.  K values past the end become zeros.
     const int row = t >> 3, piece = t & 7;
@@ -130,15 +126,12 @@ __global__ __launch_bounds__(S::THREADS) void k_gemm_split_fwd(GemmArgs g) {
     // fetched before its first store.
     auto row_of = [&](int v) { return wm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); };
     const int gn = n0 + wn + (lane & 31);
-    const bool rank = g.out_mode == OUT_RANK;
-    float norm[16], fp[16];
+    float norm[16];
     if (EPI == EPI_L2_FWD) {
         const float cv = g.colv[c * g.s_colv + min(gn, g.N - 1)];
 #pragma unroll
         for (int v = 0; v < 16; ++v) norm[v] = g.rowv[c * g.s_rowv + min(m0 + row_of(v), g.M - 1)] + cv;
     }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) fp[v] = rank ? g.fpos[c * g.M + min(m0 + row_of(v), g.M - 1)] : 0.f;
     float* C = g.C + c * g.sC;
     float loss = 0.f;
 #pragma unroll
@@ -150,12 +143,6 @@ __global__ __launch_bounds__(S::THREADS) void k_gemm_split_fwd(GemmArgs g) {
             d = sqrtf(fmaxf(norm[v] - 2.f * s, 0.f));
             s = g.gamma - d;
         }
-        if (rank) {
-            const unsigned long long m = __ballot(in && s > fp[v]);
-            const int cnt = __popcll(lane < 32 ? (m & 0xffffffffull) : (m >> 32));
-            if ((lane & 31) == 0 && cnt > 0) atomicAdd(&above[row_of(v)], cnt);
-            continue;
-        }
         if (!in) continue;
         if (g.out_mode == OUT_W) {  // W = w sigmoid(f) [/ |o - n|, 0 where the distance is 0]
             s = w_and_loss<true>(s, g.wk, loss);
@@ -164,11 +151,6 @@ __global__ __launch_bounds__(S::THREADS) void k_gemm_split_fwd(GemmArgs g) {
             s = d;
         }
         C[(int64_t)gm * g.ldc + gn] = s;
-    }
-    if (rank) {
-        // rank_i = 1 + #{j : f-_ij > f+_i}: this tile's count onto the row's rank (integer atomics, any order)
-        __syncthreads();
-        if (t < BM && m0 + t < g.M && above[t] > 0) atomicAdd(&g.rank[c * g.M + m0 + t], above[t]);
     }
     if (g.out_mode == OUT_W) {
         // negative part of the loss, one sum per 32 x 32 block that lies inside the matrix, indexed as 32 x 32 tiles are

@@ -99,7 +99,9 @@ void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids,
         return;
     }
     if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_phi(c, ent, rel, ids, st);
-    if (neg_out && k > 0 && dist_mode == 0 && kge_front_fits(c, ids.b, k, chunk, false)) {
+    // (TransE-L1's sums have the same order there.  The others' have not, and ranks of candidates that tie with the positive hang
+    // on the last bit: see split_forward in k_gemm.hip)
+    if (c->cfg.model == KGE_TRANSE_L1 && neg_out && k > 0 && dist_mode == 0 && kge_front_fits(c, ids.b, k, chunk, false)) {
         kge_launch_front(c, ent, rel, ids, k, chunk, gamma, pos_out, false, false, neg_out, ld_out, dist_mode, st);
         return;
     }
@@ -731,10 +733,7 @@ int kge_rank(kge_ctx* c, const float* ent, const float* rel,
     KGE_HIP(c, hipSetDevice(c->cfg.device));
     const StepIds ids = direct_ids(h, r, t, (int)b, neg, (int)((b / chunk) * k), neg_side, nullptr);
     hipStream_t st = (hipStream_t)hip_stream;
-    // (the scores that ranks are counted from are those of kge_score bit for bit, so where kge_score forms them in the gather
-    // launch, so does this)
-    if (is_gemm_model(c->cfg.model) && kge_gemm_forward_can_rank(c) && !kge_ind_score_fits(c, (int)chunk) &&
-        !kge_front_fits(c, (int)b, (int)k, (int)chunk, false)) {
+    if (is_gemm_model(c->cfg.model) && kge_gemm_forward_can_rank(c) && !kge_ind_score_fits(c, (int)chunk)) {
         // the gather launch sets every rank to 1, the forward launch adds the candidates that score higher
         c->rank_out = rank_out;
         forward(c, ent, rel, ids, (int)k, (int)chunk, gamma, nullptr, c->S, c->ld_s, 3, st);
