@@ -24,6 +24,7 @@ namespace {
 
 constexpr int RT = 256;       // threads per workgroup
 constexpr int MAX_D = 1024;   // entity rows are at most this long
+constexpr int ROWS = 4;       // rows of M per thread and round
 
 struct RescalArgs {
     const float* E;
@@ -37,52 +38,79 @@ struct RescalArgs {
     float* Gent;        // gradient rows in key order: heads | tails | corrupting rows
     float* GU;          // [b x D]  chain: left factor of the positive's matrix gradient
     float* GW;          // [b x D]  chain: right factor
+    const uint32_t* key;  // sorted relation ids of the step and their positions in the mini-batch, where they are there
+    const uint32_t* pos;  // already (else null)
 };
 
-template <bool CHAIN>
+// Bound by the round trips of the matrix rows: b D^2 floats (164 MB at b 1024, D 200) out of the L2s and the Infinity Cache.  The
+// first round is asked for before the vector that it multiplies is there, every further one while the one before is multiplied.
+// Where the relation list has been ordered already (the chain rule), an XCD takes a contiguous range of it, so that positives of a
+// relation read its matrix from one L2.  50 FB15k-sized steps, us: 6386 -> 6003 (without the order 8 rows per round take 200
+// more, 8 rows with it 6266, 16 rows 7312: fewer waves; ordering the list in a launch of its own before phi costs what it gives).
+// WIDE: rows of more than 256 floats, whose row dots take several pieces per lane.
+template <bool CHAIN, bool WIDE>
 __global__ __launch_bounds__(RT) void k_rescal(RescalArgs a) {
     __shared__ __attribute__((aligned(16))) float vec[MAX_D];  // the vector that multiplies M
     __shared__ __attribute__((aligned(16))) float res[MAX_D];  // the product
     __shared__ __attribute__((aligned(16))) float4 part[RT];   // column sums of the thread groups
-    const int i = blockIdx.x, tid = threadIdx.x, D = a.D, lanes = D / 4;
+    const int tid = threadIdx.x, D = a.D, lanes = D / 4;
     const StepView sv = step_view(a.ids);
+    int i = blockIdx.x;
+    int64_t rid;
+    if (a.pos) {  // workgroups go to the XCDs in turn
+        const int per_xcd = (a.b + 7) / 8, p = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+        if (p >= a.b) return;
+        i = a.pos[p];
+        rid = a.key[p];
+    } else {
+        rid = clamp_id(sv.r[i], a.n_rel);
+    }
     const bool head = sv.side == KGE_NEG_HEAD;
     const int64_t hid = clamp_id(sv.h[i], a.n_ent), tl = clamp_id(sv.t[i], a.n_ent);
-    const int64_t rid = clamp_id(sv.r[i], a.n_rel);
     const float* pa = a.E + (head ? tl : hid) * (int64_t)D;  // the kept entity
     const float* pc = a.E + (head ? hid : tl) * (int64_t)D;  // the entity that the negatives replace
     const float* M = a.R + rid * (int64_t)D * D;
     const float cp = CHAIN ? a.cpos[i] : 0.f;
 
+    // phi: o = M^T a (tail corrupted: column sums) or M a (head: row dots); the chain rule needs the transposed one
+    const bool rowdot = CHAIN ? !head : head;
+    const int w = tid >> 6, lane = tid & 63;
+    const int groups = RT / lanes, grp = tid / lanes;  // column-slice ownership (lanes <= 256)
+    // this thread's piece of a row, its first row and the step to its next (lanes past the row's end read its first piece and
+    // add nothing, threads past the last group have no row)
+    const int piece = rowdot ? (lane < lanes ? lane : 0) : tid % lanes;
+    const int first = rowdot ? w : (grp < groups ? grp : D), step = rowdot ? RT / 64 : groups;
+    struct Rows { float4 m[ROWS]; };
+    auto load = [&](int r0) {
+        Rows x;
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) x.m[u] = ld4(M + (int64_t)(r0 + u * step < D ? r0 + u * step : 0) * D + 4 * piece);
+        return x;
+    };
+    Rows x = {};
+    if (!WIDE || !rowdot) x = load(first);
+
     for (int d = tid; d < D; d += RT) vec[d] = CHAIN ? a.GO[(int64_t)i * D + d] + cp * pc[d] : pa[d];
     __syncthreads();
 
-    // phi: o = M^T a (tail corrupted: column sums) or M a (head: row dots); the chain rule needs the transposed one
-    const bool rowdot = CHAIN ? !head : head;
-    const int groups = RT / lanes, grp = tid / lanes, v = tid % lanes;  // column-slice ownership (lanes <= 256)
     if (rowdot) {
-        const int w = tid >> 6, lane = tid & 63;
-        float4 vv[4];
+        float4 vv[WIDE ? 4 : 1];
 #pragma unroll
-        for (int it = 0; it < 4; ++it) {
+        for (int it = 0; it < (WIDE ? 4 : 1); ++it) {
             const int q = lane + 64 * it;
             vv[it] = q < lanes ? ld4(vec + 4 * q) : f4(0.f);
         }
-        if (lanes <= 64) {
-            // one piece per lane: four rows per round, so that four loads are in flight (lanes past the row's end
-            // read its first piece and add nothing)
-            const float* Mc = M + (lane < lanes ? 4 * lane : 0);
-            for (int r0 = w; r0 < D; r0 += 4 * (RT / 64)) {
-                float4 m[4];
+        if constexpr (!WIDE) {  // one piece per lane
+            for (int r0 = first; r0 < D; r0 += ROWS * step) {
+                const Rows next = load(r0 + ROWS * step);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) m[u] = ld4(Mc + (int64_t)(r0 + u * (RT / 64) < D ? r0 + u * (RT / 64) : r0) * D);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    float s = lane < lanes ? m[u].x * vv[0].x + m[u].y * vv[0].y + m[u].z * vv[0].z + m[u].w * vv[0].w : 0.f;
+                for (int u = 0; u < ROWS; ++u) {
+                    float s = lane < lanes ? x.m[u].x * vv[0].x + x.m[u].y * vv[0].y + x.m[u].z * vv[0].z + x.m[u].w * vv[0].w : 0.f;
                     s = wave_sum(s);
-                    const int r = r0 + u * (RT / 64);
+                    const int r = r0 + u * step;
                     if (lane == 0 && r < D) res[r] = s;
                 }
+                x = next;
             }
         } else {
             for (int r = w; r < D; r += RT / 64) {
@@ -102,18 +130,16 @@ __global__ __launch_bounds__(RT) void k_rescal(RescalArgs a) {
         }
     } else {
         float4 y = f4(0.f);
-        if (grp < groups) {
-            for (int r0 = grp; r0 < D; r0 += 4 * groups) {  // four rows per round, their loads in flight together
-                float4 m[4];
+        for (int r0 = first; r0 < D; r0 += ROWS * step) {
+            const Rows next = load(r0 + ROWS * step);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) m[u] = ld4(M + (int64_t)(r0 + u * groups < D ? r0 + u * groups : r0) * D + 4 * v);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int r = r0 + u * groups;
-                    const float s = r < D ? vec[r] : 0.f;
-                    y.x += s * m[u].x; y.y += s * m[u].y; y.z += s * m[u].z; y.w += s * m[u].w;
-                }
+            for (int u = 0; u < ROWS; ++u) {
+                const int r = r0 + u * step;
+                const float s = r < D ? vec[r] : 0.f;
+                const float4 m = r < D ? x.m[u] : f4(0.f);
+                y.x += s * m.x; y.y += s * m.y; y.z += s * m.z; y.w += s * m.w;
             }
+            x = next;
         }
         part[tid] = y;
         __syncthreads();
@@ -283,7 +309,7 @@ __global__ __launch_bounds__(RT, 8) void k_rescal_update(RescalUpdArgs a) {
 }
 
 RescalArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& ids) {
-    RescalArgs a;
+    RescalArgs a = {};
     a.E = E; a.R = R; a.ids = ids; a.b = ids.b; a.D = c->cfg.ent_dim;
     a.n_ent = c->cfg.num_entities; a.n_rel = c->cfg.num_relations;
     a.O = c->O; a.GO = c->GO; a.cpos = c->cpos; a.Gent = c->Gent;
@@ -291,16 +317,23 @@ RescalArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& 
     return a;
 }
 
+template <bool CHAIN>
+void launch_rescal(kge_ctx* c, const RescalArgs& a, hipStream_t st) {
+    const dim3 grid(a.pos ? (a.b + 7) / 8 * 8 : a.b);
+    if (a.D > 256) KGE_LAUNCH(c, (k_rescal<CHAIN, true>), grid, dim3(RT), 0, st, a);
+    else KGE_LAUNCH(c, (k_rescal<CHAIN, false>), grid, dim3(RT), 0, st, a);
+}
+
 }  // namespace
 
 void kge_launch_rescal_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st) {
-    const RescalArgs a = make_args(c, E, R, ids);
-    KGE_LAUNCH(c, k_rescal<false>, dim3(ids.b), dim3(RT), 0, st, a);
+    launch_rescal<false>(c, make_args(c, E, R, ids), st);
 }
 
-void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st) {
-    const RescalArgs a = make_args(c, E, R, ids);
-    KGE_LAUNCH(c, k_rescal<true>, dim3(ids.b), dim3(RT), 0, st, a);
+void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, bool ordered, hipStream_t st) {
+    RescalArgs a = make_args(c, E, R, ids);
+    if (ordered) { a.key = c->rkey[c->rbuf]; a.pos = c->rpos[c->rbuf]; }
+    launch_rescal<true>(c, a, st);
 }
 
 void kge_launch_rescal_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st) {

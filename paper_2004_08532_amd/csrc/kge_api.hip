@@ -277,7 +277,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     }
     if (run_chain) {
         ProfScope p(c, KGE_PROF_CHAIN);
-        if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_chain(c, ent, rel, ids, st);
+        if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_chain(c, ent, rel, ids, !beside, st);
         else kge_launch_chain(c, ent, rel, ids, st);
     }
     if (beside) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));

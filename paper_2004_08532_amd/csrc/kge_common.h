@@ -239,7 +239,8 @@ int kge_pair_neg_backward(kge_ctx* c, int b, int k, int g, float gamma, hipStrea
 void kge_launch_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
 // RESCAL: o_i from the kept entity and the relation's matrix (before the gather launch); chain rule through it
 void kge_launch_rescal_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
-void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
+// ordered: the key lists have been ordered on this stream
+void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, bool ordered, hipStream_t st);
 // RESCAL, a7 for the relation matrices: gradient of a distinct relation formed from the factor rows, then Adagrad
 void kge_launch_rescal_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
 // TransR (k_transr.hip)

@@ -184,6 +184,23 @@ def test_rescal_matrix_update_of_runs(kge, shape):
         p.close()
 
 
+# rows of the matrix (one to many rounds, one and several pieces per lane), positives (a ragged share per XCD), keys ordered by
+# the gather launch and sorted on a stream of their own
+RESCAL_ROWS = {"4": (9, 9, 5, 4), "20": (33, 11, 7, 20), "68": (24, 8, 9, 68), "252": (17, 17, 5, 252), "256": (16, 8, 5, 256),
+               "260": (10, 5, 5, 260), "sorted": (512, 8, 256, 8)}
+
+
+@pytest.mark.parametrize("shape", sorted(RESCAL_ROWS))
+def test_rescal_matrix_rows(kge, shape):
+    b, g, k, dim = RESCAL_ROWS[shape]
+    w = ragged("rescal", batch=b, chunk=g, neg_per_chunk=k, ent_dim=dim, rel_dim=dim * dim, n_relations=6, side_mode="alternate", steps=4)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), w.steps, check_dedup_at=(0, 3))
+    finally:
+        p.close()
+
+
 def test_training_shapes_with_thousands_of_tiles(kge):
     """A score matrix of 1035 x 1219 per step (three chunks): thousands of 32 x 32 tiles, four waves per tile, ragged
     edges in every dimension."""
