@@ -171,7 +171,8 @@ def test_forward_product_of_many_tiles(kge, b, g, k, D):
     f = np.concatenate([x[i:i + g] @ y[i // g * k:(i // g + 1) * k].T for i in range(0, b, g)])
     fp = (x * c).sum(1)
     loss = np.logaddexp(0, -fp).mean() + np.logaddexp(0, f).mean()
-    w = 1 / (1 + np.exp(-f)) / (b * k)
+    with np.errstate(over="ignore"):
+        w = 1 / (1 + np.exp(-f)) / (b * k)
     dy = np.concatenate([w[i:i + g].T @ x[i:i + g] for i in range(0, b, g)])[:, 1:]
     ctx = kge.KgeContext("distmult", E.shape[0], 1, D, D, max_batch=b, max_neg_per_chunk=k, max_chunks=b // g)
     dev = lambda v: torch.from_numpy(v).cuda()
