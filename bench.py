@@ -56,7 +56,8 @@ def parse():
 def algorithmic_work(w, h, r, t, neg, rowwise=False):
     """Per-step algorithmic bytes / flops of every kernel, averaged over the given steps (ids on the host).
 
-    gather : every gathered row read once and every staged row (o_i, corrupting rows) written once
+    gather : every gathered row read once and every staged row (o_i, corrupting rows) written once; in steps of few tiles
+             this launch forms the negative scores too, and there is no neg_score entry with a time
     update : per distinct row, table and state read and written (4 rows) plus every gradient row read once
     GEMMs  : 2 b k D flops forward, 4 b k D backward; pair kernels: b k D_c pair-coordinates
     """

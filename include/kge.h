@@ -205,7 +205,7 @@ int kge_check_indices(kge_ctx* ctx, void* hip_stream);
  * (host) *steps_out the number of steps they cover.  kge_profile_slot_name: (host) static name of a slot.
  */
 enum {
-    KGE_PROF_GATHER = 0,   /* row gather + positive scores             */
+    KGE_PROF_GATHER = 0,   /* row gather + positive scores (few tiles: and negative scores) */
     KGE_PROF_SCORE = 1,    /* chunked negative scoring                  */
     KGE_PROF_LOSS = 2,     /* loss and backward coefficients            */
     KGE_PROF_BACKWARD = 3, /* dL/do and gradient rows of the negatives  */
