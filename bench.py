@@ -56,8 +56,7 @@ def parse():
 def algorithmic_work(w, h, r, t, neg, rowwise=False):
     """Per-step algorithmic bytes / flops of every kernel, averaged over the given steps (ids on the host).
 
-    gather : every gathered row read once and every staged row (o_i, corrupting rows) written once; in steps of few tiles
-             this launch forms the negative scores too, and there is no neg_score entry with a time
+    gather : every gathered row read once and every staged row (o_i, corrupting rows) written once
     update : per distinct row, table and state read and written (4 rows) plus every gradient row read once
     GEMMs  : 2 b k D flops forward, 4 b k D backward; pair kernels: b k D_c pair-coordinates
     """
@@ -88,6 +87,40 @@ def algorithmic_work(w, h, r, t, neg, rowwise=False):
         "sort": {"bytes": 8.0 * (n_keys + b)},
         "unique_entity_rows": float(ue), "unique_relation_rows": float(ur),
     }
+
+
+def kernel_report(w, ms, nsteps, work):
+    """Average time of every kernel and what it achieves of the card's peaks.  In steps of few tiles the gather launch forms
+    the negative scores too: it is then rated by its bytes and by the flops of the scoring product, the closer of the two to
+    its peak first ("other" is the other one), and "neg_score", which has no launch of its own, carries the rate of the
+    product over that whole launch."""
+    gemm = w.model in ("transe_l2", "distmult", "complex", "rescal", "transr")
+    flop_peak = (BF16_MATRIX_PEAK_TFLOPS if w.bf16_inputs else FP32_MATRIX_PEAK_TFLOPS) if gemm else FP32_VECTOR_PEAK_TFLOPS
+
+    def rates(work_of, us):
+        found = []
+        if us > 0 and "bytes" in work_of:
+            found.append(dict(bound="hbm", achieved=work_of["bytes"] / (us * 1e-6) / 1e9, peak=HBM_PEAK_GBS, unit="GB/s"))
+        if us > 0 and "flops" in work_of:
+            found.append(dict(bound="mfma" if gemm else "alu", achieved=work_of["flops"] / (us * 1e-6) / 1e12, peak=flop_peak,
+                              unit="TFLOP/s"))
+        for r in found:
+            r["frac"] = r["achieved"] / r["peak"]
+        return sorted(found, key=lambda r: -r["frac"])
+
+    avg_us = {name: 1e3 * total / max(nsteps, 1) for name, total in ms.items()}
+    # (chunks of one positive have one kernel for scores and gradients, timed as neg_backward)
+    merged = avg_us.get("neg_score") == 0 and avg_us.get("gather", 0) > 0 and w.chunk > 1
+    kernels = {}
+    for name, us in avg_us.items():
+        work_of = work.get(name, {})
+        if merged and name == "gather":
+            work_of = {**work_of, **work["neg_score"]}
+        found = rates(work_of, us)
+        kernels[name] = {"avg_us": us, **(found[0] if found else {}), **({"other": found[1]} if len(found) > 1 else {})}
+    if merged:
+        kernels["neg_score"].update(rates(work["neg_score"], avg_us["gather"])[0], launch="gather")
+    return kernels
 
 
 def measured_traffic(workload):
@@ -262,21 +295,7 @@ def main():
         ms, nsteps = ctx.profile_read()
         ctx.profile(False)
         work = algorithmic_work(w, h[W + K:], r[W + K:], t[W + K:], neg[W + K:], args.rowwise_state)
-        gemm = w.model in ("transe_l2", "distmult", "complex", "rescal", "transr")
-        for name, total_ms in ms.items():
-            avg_us = 1e3 * total_ms / max(nsteps, 1)
-            ent = {"avg_us": avg_us}
-            wk = work.get(name, {})
-            if "bytes" in wk and avg_us > 0:
-                ent.update(bound="hbm", achieved=wk["bytes"] / (avg_us * 1e-6) / 1e9, peak=HBM_PEAK_GBS, unit="GB/s")
-            elif "flops" in wk and avg_us > 0:
-                peak = (BF16_MATRIX_PEAK_TFLOPS if w.bf16_inputs else FP32_MATRIX_PEAK_TFLOPS) if gemm \
-                    else FP32_VECTOR_PEAK_TFLOPS
-                ent.update(bound="mfma" if gemm else "alu", achieved=wk["flops"] / (avg_us * 1e-6) / 1e12, peak=peak,
-                           unit="TFLOP/s")
-            if "achieved" in ent:
-                ent["frac"] = ent["achieved"] / ent["peak"]
-            kernels[name] = ent
+        kernels = kernel_report(w, ms, nsteps, work)
         traffic = measured_traffic(w.name)
         for name, ent in kernels.items():
             ent["traffic"] = traffic.get(name)
@@ -285,6 +304,7 @@ def main():
         d = kernels[dom]
         roofline = {"kernel": dom, "bound": d.get("bound"), "achieved": d.get("achieved"), "peak": d.get("peak"),
                     "unit": d.get("unit"), "frac": d.get("frac"), "traffic": d.get("traffic"), "avg_us": d["avg_us"],
+                    "other": d.get("other"),
                     "unique_entity_rows_per_step": work["unique_entity_rows"],
                     "unique_relation_rows_per_step": work["unique_relation_rows"]}
 
