@@ -59,7 +59,7 @@ struct TransrArgs {
     float gamma, wk;
     int out_w;       // project: store W = dL/df- instead of the score
     int train;       // project: keep the projections, scores in the order of the members; phi: likewise
-    int form_v;      // project: form V and dL/do of items of few positives, whose P is then not stored (dp leaves them alone)
+    int form_v;      // dp: the projection has formed V and dL/do of items of few positives
     int segments;    // back: ranges of a chunk's items
     TransrGroups q;
     float* O;        // [b x D]      o
@@ -445,7 +445,11 @@ __global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
 
 // 64 corrupting rows x a block of an item's positives: projections, then the scores of the positives against them.  (An
 // item of more than 32 positives is projected once per block: at that size the scores are the larger part of the work.)
-template <int NT>
+// FORM_V: form V and dL/do of items of few positives too, whose P is then not stored.  Calls that don't (scoring, rows of more
+// than BN floats, steps with a loss kernel) get a kernel without that code, which takes 12 to 20 registers and at rows of 49 to
+// 64 floats a wave per SIMD (kge_score, b 1024, k 256, D 64: 38.0 us with it, 36.1 without, D 128 84.3 and 83.3; kge_rank of
+// 1000 positives in one chunk, k 1000, D 64: 77.4 and 72.9).
+template <int NT, bool FORM_V>
 __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int blocks) {
     __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
     const int tiles = (a.k + BM - 1) / BM, D = a.D, tid = threadIdx.x;
@@ -485,7 +489,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
 #pragma unroll
             for (int it = 0; it < 4; ++it) st4(Bs + (tid / 32 + 8 * it) * BN + 4 * (tid % 32), ro[it]);
             __syncthreads();
-            const bool form_v = a.form_v && blk.all <= DP_FEW;  // (the same for every thread; one pass over the columns)
+            const bool form_v = FORM_V && blk.all <= DP_FEW;  // (the same for every thread; one pass over the columns)
             if (!t.active && !form_v) continue;
             const bool store_p = a.train && blk.first == 0 && !form_v;
 #pragma unroll
@@ -1272,10 +1276,13 @@ void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& i
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* out, int ld_out, bool train,
                        bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, gamma);
-    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train; a.form_v = train && form_w && forms_v(c, k, gsz);
+    a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train;
     const int blocks = pblock_blocks(a, (k + BM - 1) / BM);
-#define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, flat_grid(blocks), dim3(RT), 0, st, a, blocks)
-    KGE_BY_COLUMNS(a.D, L);
+#define L(NT) KGE_LAUNCH(c, (k_transr_project<NT, true>), flat_grid(blocks), dim3(RT), 0, st, a, blocks)
+#define L0(NT) KGE_LAUNCH(c, (k_transr_project<NT, false>), flat_grid(blocks), dim3(RT), 0, st, a, blocks)
+    if (train && form_w && forms_v(c, k, gsz)) KGE_BY_COLUMNS(a.D, L);
+    else KGE_BY_COLUMNS(a.D, L0);
+#undef L0
 #undef L
     return form_w ? blocks : 0;
 }

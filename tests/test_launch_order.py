@@ -131,6 +131,31 @@ print(json.dumps([one, got]))
         assert rc == 0 and run_kernels(events) == n_steps * len(one[1])
 
 
+def test_transr_calls_that_form_no_v_launch_a_projection_without_it(recorder):
+    """The projection that forms V and dL/do too needs more registers: kge_score, kge_rank, steps with a loss kernel and steps of
+    rows of more than 128 floats have one without that code."""
+    forms, others = drive(recorder, '''
+lib.kge_score.argtypes = [vp] * 6 + [i64, vp, i64, i64, i32, f32, vp, vp, vp]
+lib.kge_rank.argtypes = [vp] * 6 + [i64, vp, i64, i64, i32, f32, vp, vp]
+
+def projections(events):
+    return sorted({e.split()[2] for e in events if "k_transr_project" in e})
+
+def forward(x, name, outputs):
+    p = 4096
+    rec.recorder_clear()
+    assert getattr(lib, name)(x.ctx, p, p, p, p, p, x.b, p, x.k, x.g, 0, 12.0, p, *[p] * outputs) == 0
+    return projections(rec.recorder_events().decode().splitlines())
+
+x = Library("transr", k=64)
+plain = [forward(x, "kge_score", 2), forward(x, "kge_rank", 1), projections(Library("transr", k=64, adv_temperature=1.0).steps(1)[1]),
+         projections(Library("transr", k=64, loss=1).steps(1)[1])]
+print(json.dumps([projections(x.steps(1)[1]), plain]))
+''')
+    assert len(forms) == 1 and len(others) == 4
+    assert all(len(k) == 1 and k == others[0] and k != forms for k in others), (forms, others)
+
+
 @pytest.mark.parametrize("shape", ["b=20_000, g=100, k=4, D=1024", "b=1 << 20, g=1 << 10, k=1024, D=4, relations=1_000_000"])
 def test_transr_steps_of_very_many_workgroups(recorder, shape):
     """Workspaces of 80 and 60 GB: more workgroups of the relation update, or of the projections, than one dimension of a grid
