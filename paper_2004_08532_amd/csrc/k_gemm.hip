@@ -407,14 +407,25 @@ void launch_bwd(kge_ctx* c, GemmArgs gO, GemmArgs gN, int chunks, hipStream_t st
 
 }  // namespace
 
-// Forward products of many tiles: on the bf16 matrix cores (k_gemm_split.hip).  Whole calls, us, here -> there: 2016 tiles, D 400
-// 38.4 -> 28.5, D 64 16.5 -> 13.8; 2048 tiles in chunks of 128 43.6 -> 33.3; 1672 tiles, D 600 49.2 -> 38.8; 3008 tiles in chunks
-// of 16 52.3 -> 52.9; 1504 tiles in chunks of 32 54.5 -> 51.8; 1024 tiles, D 400 23.0 -> 23.6, D 100 13.0 -> 15.2.
+// Forward products of many tiles: on the bf16 matrix cores (k_gemm_split.hip), in training steps.  us per step, here -> there
+// (TransE-L2, DistMult, ComplEx; b, g, k, D):
+//   chunks of more than 32   1000, 1000, 1504, 400 85.4 -> 76.8 (1504 tiles of 32 x 32);  1000, 1000, 2000, 64 46.7 -> 43.4;  2048, 256,
+//                            1024, 400 120 -> 109, D 32 54.4 -> 51.8;  2048, 64, 768, 400 164 -> 155;  2013, 33, 800, 100 137 -> 132
+//   1024 tiles               1000, 1000, 1024, 400 62.7 -> 63.0, D 64 33.0 -> 33.6;  1024, 128, 1024, 100 50.3 -> 51.3.  (From 1152
+//                            tiles on there are gains of 3 to 6 % already: 1024, 128, 1280, 200 64.2 -> 60.9)
+//   chunks of 17 to 32       1504, 32, 1024, 200 141.1 -> 139.5;  1024, 32, 1536, 400 244.5 -> 242.9;  1024, 32, 1504, 100 118.3 -> 118.6
+//   of 16 and fewer          1024, 16, 1504, 400 458 -> 462, D 200 247.1 -> 248.4;  2048, 16, 384, 400 253.2 -> 251.8;  2048, 4, 96,
+//                            100 127.1 -> 130.3
+//   tiles of k_gemm_split.hip that reach far past the matrix: a quarter of their 32 x 32 blocks inside 3072, 2, 32, 400 293 -> 326, half
+//                            2048, 2, 64, 100 154 -> 160, 0.64 3072, 96, 544, 400 141 -> 144;  0.67 2016, 96, 800, 200 100.5 -> 98.9,
+//                            three quarters 2030, 70, 512, 200 96.4 -> 89.9, 2016, 96, 768, 100 85.7 -> 86.8
 // Training only.  A candidate that is the replaced entity itself has the positive's score but for rounding, which then decides its
 // rank: of 1000 positives against 1000 uniform and 1000 degree-proportional candidates 33 changed ranks with the sums taken
 // in this other order, and a rank is a whole number that stays what it is.
 static bool split_forward(int out_mode, int chunks, int gsz, int k) {
-    return (out_mode == OUT_DIST || out_mode == OUT_W) && (int64_t)chunks * ((gsz + TILE - 1) / TILE) * ((k + TILE - 1) / TILE) >= 1504;
+    if ((out_mode != OUT_DIST && out_mode != OUT_W) || gsz <= 16) return false;
+    const int64_t rows = (gsz + TILE - 1) / TILE, cols = (k + TILE - 1) / TILE;
+    return chunks * rows * cols >= 1504 && 3 * rows * cols >= 2 * (int64_t)kge_gemm_split_blocks(gsz, k);
 }
 
 // S_c = O_c N_c^T with the model's epilogue.  out_mode: 0 the scores (kge_score path); 1 what the loss kernel wants

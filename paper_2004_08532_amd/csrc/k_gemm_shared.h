@@ -1,5 +1,6 @@
-// Shared by the two matrix-product sources (k_gemm.hip: fp32 operands, small tiles split over K; k_gemm_bf.hip:
-// bf16 operands, 64x64 tiles): the argument block, the epilogue kinds and the helpers both use.
+// Shared by the sources that form matrix products (k_gemm.hip: fp32 operands, small tiles split over K; k_gemm_split.hip: fp32
+// operands, larger tiles on the bf16 matrix cores; k_gemm_bf.hip: bf16 operands, 64x64 tiles; k_front.hip: small tiles in the gather
+// launch; k_transr.hip; k_ind.hip): the argument block, the epilogue kinds and the helpers that several of them use.
 #pragma once
 #include "k_split.h"
 
@@ -77,7 +78,8 @@ __device__ __forceinline__ int xcd_tile(int q, int per_xcd) { return (blockIdx.x
 
 }  // namespace
 
-// fp32 operands, many tiles (k_gemm_split.hip)
+// fp32 operands, many tiles (k_gemm_split.hip), and the 32 x 32 blocks that its tiles of a chunk of g positives and k negatives have
+int kge_gemm_split_blocks(int g, int k);
 void kge_gemm_split_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);
 // bf16 operands (k_gemm_bf.hip): the same two launches on 64x64 tiles
 void kge_gemm_bf_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);

@@ -169,13 +169,22 @@ void launch(kge_ctx* c, GemmArgs g, int chunks, hipStream_t st) {
 }
 
 // 32 rows per tile where a chunk has no more (1024 x 1500, D 400, chunks of 32: 51 us against 62 with 64 rows).
+using Short = Shape<32, 128>;
+using Tall = Shape<64, 128>;
+bool short_chunk(int g) { return g <= Short::BM; }
 template <int EPI>
 void pick(kge_ctx* c, const GemmArgs& g, int chunks, hipStream_t st) {
-    if (g.M <= 32) launch<EPI, Shape<32, 128>>(c, g, chunks, st);
-    else launch<EPI, Shape<64, 128>>(c, g, chunks, st);
+    if (short_chunk(g.M)) launch<EPI, Short>(c, g, chunks, st);
+    else launch<EPI, Tall>(c, g, chunks, st);
 }
 
 }  // namespace
+
+int kge_gemm_split_blocks(int g, int k) {
+    const int rows = short_chunk(g) ? Short::BM : Tall::BM, cols = Short::BN;
+    static_assert(Short::BN == Tall::BN, "");
+    return (g + rows - 1) / rows * ((k + cols - 1) / cols) * (rows / 32 * (cols / 32));
+}
 
 void kge_gemm_split_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st) {
     const GemmArgs& g = *static_cast<const GemmArgs*>(args);

@@ -156,6 +156,22 @@ print(json.dumps([projections(x.steps(1)[1]), plain]))
     assert all(len(k) == 1 and k == others[0] and k != forms for k in others), (forms, others)
 
 
+# (b, g, k) and whether the forward product is the one on larger tiles of the bf16 matrix cores: few tiles, chunks of few
+# positives, tiles that reach far past a chunk's rows or columns
+@pytest.mark.parametrize("loss", ["adv_temperature=0.0", "adv_temperature=1.0", "loss=1"])
+@pytest.mark.parametrize("b,g,k,split", [(1000, 1000, 1504, True), (1000, 1000, 1472, False), (2048, 256, 1024, True),
+                                         (1504, 32, 1024, True), (1513, 17, 528, True), (1504, 16, 1024, False), (2048, 4, 96, False),
+                                         (3072, 2, 32, False), (2048, 2, 64, False), (48_128, 32, 32, False), (48_128, 32, 64, False),
+                                         (48_128, 32, 86, True), (3072, 96, 544, False), (2016, 96, 800, True)])
+def test_split_forward_product_where_its_tiles_are_filled(recorder, b, g, k, split, loss):
+    rc, events = drive(recorder, f'''
+print(json.dumps(Library("transe_l2", b={b}, g={g}, k={k}, D=400, {loss}).steps(1)))
+''')
+    assert rc == 0
+    assert any("k_gemm_split_fwd" in e for e in events) == split
+    assert any("k_gemm_fwd" in e for e in events) != split
+
+
 @pytest.mark.parametrize("shape", ["b=20_000, g=100, k=4, D=1024", "b=1 << 20, g=1 << 10, k=1024, D=4, relations=1_000_000"])
 def test_transr_steps_of_very_many_workgroups(recorder, shape):
     """Workspaces of 80 and 60 GB: more workgroups of the relation update, or of the projections, than one dimension of a grid
