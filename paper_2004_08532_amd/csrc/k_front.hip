@@ -254,20 +254,33 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 
 // Forward of chunks of gsz positives and k corrupting rows in the gather launch?
 // Tiles read a table row once per tile that needs it, the gather launch once, so the line lies where that costs more than a
-// launch (us per training step, separate -> one launch; TransE-L2):
-//   (TransE-L1, rows of 400: 256 61.4 -> 57.2, 768 107.5 -> 103.4; of 64: 416 41.1 -> 41.6, 512 54.9 -> 52.3)
-//   tiles   rows of 400: 256 41.7 -> 37.9, 640 65.9 -> 60.4, 768 68.9 -> 64.6, 1024 66.9 -> 67.1
-//           rows of 160: 640 46.3 -> 44.5, 768 47.6 -> 47.4;  of 128: 624 40.3 -> 39.1, 640 43.4 -> 43.6, 768 44.6 -> 46.7
-//   keys    ordered by brute force here, in buckets of the id range in the gather launch of long lists (512 tiles and
-//           fewer, rows of 64): 6144 39.1 -> 35.4, 8192 40.6 -> 34.7, 12288 45.0 -> 47.9.  Lists that are sorted in other
-//           launches don't matter: 20480 keys 67.8 -> 67.3
+// launch (us per training step, separate -> one launch; chunks of 128 where nothing else is said):
+//   TransE-L2   rows of 400: 256 tiles 41.7 -> 37.9, 640 66.0 -> 61.0, 1024 66.9 -> 67.1;  of 160: 512 43.0 -> 41.3, 576 46.8 ->
+//               44.5;  of 128: 624 40.3 -> 39.1, 640 43.4 -> 43.6, 768 44.6 -> 46.7
+//   DistMult    rows of 400: 640 64.0 -> 62.8, 768 67.9 -> 67.5;  of 160: 768 51.2 -> 48.6;  of 128: 512 39.4 -> 36.4, 624 42.3 ->
+//               40.9;  of 64: 512 37.1 -> 33.6
+//   RESCAL      rows of 200: 256 87.9 -> 83.6, 768 (chunks of 256) 103.3 -> 97.9;  of 64: 512 57.2 -> 52.4
+//   TransE-L1   rows of 400: 256 61.4 -> 57.2, 704 103.6 -> 99.3;  of 160: 576 62.4 -> 60.5, 704 67.7 -> 70.2;  of 64: 416 47.6 ->
+//               46.3, 512 48.6 -> 46.3
+//   ComplEx     rows of 400: 256 39.9 -> 36.3, 576 62.2 -> 58.0, 768 (chunks of 256) 62.3 -> 57.4;  of 256: 384 42.1 -> 40.9, 512
+//               45.0 -> 46.9;  of 160: 384 37.7 -> 37.0, 512 41.6 -> 43.5, 640 47.1 -> 51.3;  of 64: 384 33.0 -> 32.4, 512 37.3 ->
+//               38.7 (its halves are a slice each, and these are at most half full there)
+//   keys        ordered by brute force here, in buckets of the id range in the gather launch of long lists (512 tiles and
+//               fewer, rows of 64): 6144 39.1 -> 35.4, 8192 40.6 -> 34.7, 12288 45.0 -> 47.9.  With more tiles than that they add to a
+//               launch that is several rounds long: TransE-L2 rows of 400 7168 keys 66.0 -> 61.0, 7680 68.4 -> 70.0, 8192 70.2 -> 72.1,
+//               rows of 160 7168 48.9 -> 49.1, 8192 51.3 -> 53.5, ComplEx rows of 400 6912 63.0 -> 61.5, 7168 63.8 -> 65.2, 7680
+//               66.4 -> 68.0;  not so with the others, whose tiles need fewer registers (DistMult 7680 66.3 -> 65.7, rows of 200 8192
+//               53.0 -> 49.8; TransE-L1 and RESCAL above).  Lists that are sorted in other launches don't matter: 20480 keys
+//               67.8 -> 67.3
 // Rows of more than two slices of K would not fit the registers of a wave.
 bool kge_front_fits(const kge_ctx* c, int b, int k, int gsz, bool with_keys) {
     const int m = c->cfg.model, D = c->cfg.ent_dim;
     if (c->cfg.gemm_input != 0 || D > 2 * SLICE) return false;
     if (m != KGE_TRANSE_L2 && m != KGE_TRANSE_L1 && m != KGE_DISTMULT && m != KGE_COMPLEX && m != KGE_RESCAL) return false;
     const int64_t chunks = b / gsz, tiles = chunks * ((gsz + TILE - 1) / TILE) * ((k + TILE - 1) / TILE);
-    return tiles <= (D > 128 ? 768 : 512) && !(with_keys && 2 * (int64_t)b + chunks * k > FRONT_MAX_KEYS);
+    const int64_t most_tiles = m == KGE_COMPLEX && D <= SLICE ? 384 : D > 128 ? 768 : 512;
+    const int64_t most_keys = (m == KGE_TRANSE_L2 || m == KGE_COMPLEX) && tiles > 512 ? 7168 : FRONT_MAX_KEYS;
+    return tiles <= most_tiles && !(with_keys && 2 * (int64_t)b + chunks * k > most_keys);
 }
 
 void kge_launch_front(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* pos_out,

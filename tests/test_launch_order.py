@@ -156,6 +156,33 @@ print(json.dumps([projections(x.steps(1)[1]), plain]))
     assert all(len(k) == 1 and k == others[0] and k != forms for k in others), (forms, others)
 
 
+# (b, g, k, D) and whether the tiles of the forward product are in the gather launch: the limits on tiles and on keys
+FRONT = {
+    "complex": [(1024, 128, 384, 64, True), (1024, 128, 416, 64, False), (1024, 128, 384, 256, True), (1024, 128, 416, 256, False),
+                (1024, 256, 768, 264, True), (1024, 256, 800, 264, False), (1024, 128, 640, 400, True), (1024, 128, 672, 400, False)],
+    "transe_l2": [(1024, 128, 512, 64, True), (1024, 128, 544, 64, False), (1024, 128, 640, 400, True), (1024, 128, 672, 400, False),
+                  (1024, 256, 768, 400, True), (2048, 128, 256, 400, True), (2048, 128, 288, 400, False)],
+    "distmult": [(1024, 128, 512, 128, True), (1024, 128, 544, 128, False), (1024, 128, 768, 400, True), (1024, 128, 800, 400, False),
+                 (16, 16, 8160, 8, True), (16, 16, 8161, 8, False), (1024, 128, 768, 512, True), (1024, 128, 768, 516, False)],
+    "transe_l1": [(1024, 128, 512, 64, True), (1024, 128, 768, 400, True)],
+    "rescal": [(1024, 128, 512, 64, True), (1024, 128, 768, 200, True)],
+}
+
+
+@pytest.mark.parametrize("model", sorted(FRONT))
+def test_forward_product_in_the_gather_launch_where_it_is_the_faster_one(recorder, model):
+    got = drive(recorder, f'''
+got = []
+for b, g, k, D, _ in {FRONT[model]!r}:
+    rc, events = Library({model!r}, b=b, g=g, k=k, D=D).steps(1)
+    assert rc == 0
+    got.append([any("k_front" in e for e in events), any("k_gather" in e for e in events)])
+print(json.dumps(got))
+''')
+    assert [f for f, _ in got] == [s[4] for s in FRONT[model]]
+    assert [g for _, g in got] == [not s[4] for s in FRONT[model]]
+
+
 # (b, g, k) and whether the forward product is the one on larger tiles of the bf16 matrix cores: few tiles, chunks of few
 # positives, tiles that reach far past a chunk's rows or columns
 @pytest.mark.parametrize("loss", ["adv_temperature=0.0", "adv_temperature=1.0", "loss=1"])
