@@ -218,12 +218,23 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
     const int B = ids.b;
     // Ordering the key lists needs only the ids.  Short lists are ordered by extra blocks of the gather launch; long ones by a
     // radix sort, on a second stream that joins before the update.  A fork and a join cost about 10 us each outside of a graph,
-    // and k_ind slows down what runs beside it, so the steps of chunks of one positive that are launched one by one sort on
-    // the main stream, where that takes less (us per step, beside -> before: TransE-L2 b 1024 k 256 D 400 156 -> 149, b 512
-    // k 64 D 128 75 -> 59; replayed 147.5 -> 148, 62 -> 59; RotatE b 1024 k 256 D 400 198 -> 205, k 128 D 200 111 -> 105;
-    // chunks of more positives, TransE-L2 b 2048 g 8 k 64 D 200 87 -> 92).
+    // and k_ind slows down what runs beside it, so steps of chunks of one positive that are launched one by one sort on the
+    // main stream, but where k_ind (a workgroup per positive) has more workgroups than the chip holds, whose second round
+    // leaves room for the sort, and work enough.  us per step, main stream / beside (b, k, D):
+    //   TransE-L2  1024, 256, 400 146 / 153;  512, 128, 400 81 / 88;  1536, 256, 400 215 / 210;  2048, 512, 200 328 / 316
+    //   DistMult   1024, 512, 400 262 / 269;  1280, 128, 400 117 / 121;  2048, 128, 400 148 / 156;  1280, 200, 400 152 / 150;  1280, 256,
+    //              400 190 / 187;  2048, 256, 400 268 / 259;  2048, 512, 400 476 / 454;  rows of more than 512 floats, of which the chip
+    //              holds half as many: 512, 256, 800 154 / 162;  1024, 128, 640 147 / 139;  1024, 256, 640 218 / 208
+    //   ComplEx    1024, 256, 400 145 / 153;  1280, 256, 400 197 / 187;  2048, 512, 400 482 / 449;  1024, 256, 640 218 / 208
+    //   TransE-L1  1024, 256, 400 185 / 191;  1280, 256, 400 244 / 237;  2048, 512, 400 614 / 576;  1024, 256, 640 298 / 286
+    //   RotatE     (three workgroups per CU instead of four)  700, 256, 400 146 / 151;  800, 256, 400 176 / 166;  1024, 192, 400 167 /
+    //              162;  1024, 256, 400 203 / 194;  1024, 200, 256 122 / 124;  2048, 128, 256 149 / 156
+    // Replayed steps (TransE-L2 1024, 256, 400 147.5 beside, 148) and chunks of more positives (TransE-L2 b 2048, g 8, k 64, D 200
+    // 87 beside, 92) sort beside.
     const bool long_lists = 2 * B + ids.n_neg > KGE_RANK_MAX_KEYS, ind = kge_ind_step_fits(c, G);
-    const bool long_ind = c->cfg.model == KGE_ROTATE && (int64_t)ids.n_neg * c->cfg.ent_dim >= (int64_t)1 << 26;
+    const bool rotate = c->cfg.model == KGE_ROTATE, long_rows = c->cfg.ent_dim > 512;
+    const bool long_ind = B > (long_rows ? 512 : rotate ? 768 : 1024) &&
+                          (int64_t)ids.n_neg * c->cfg.ent_dim >= (int64_t)(rotate || long_rows ? 72 : 120) << 20;
     const bool beside = long_lists && (!ind || ids.blk || long_ind);
     if (long_lists && !beside) {
         ProfScope p(c, KGE_PROF_SORT);

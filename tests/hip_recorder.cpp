@@ -22,7 +22,7 @@ std::map<void*, size_t>& sizes() { static std::map<void*, size_t> m; return m; }
 std::string& events() { static std::string s; return s; }
 std::map<std::string, int>& failing() { static std::map<std::string, int> m; return m; }  // calls until the one that fails
 void* capturing = nullptr;
-int captured = 0, modules = 0, pending = 0;
+int captured = 0, modules = 0, pending = 0, waits = 0;
 
 int outcome(const char* call) {
     auto it = failing().find(call);
@@ -52,7 +52,8 @@ extern "C" {
 
 // ---- for the test
 const char* recorder_events() { return events().c_str(); }
-void recorder_clear() { events().clear(); }
+void recorder_clear() { events().clear(); waits = 0; }
+int recorder_waits() { return waits; }  // waits of one stream for another
 void recorder_fail(const char* call, int nth) { failing()[call] = nth; }
 
 // ---- the runtime
@@ -107,7 +108,7 @@ int hipEventRecord(void*, void*) { return outcome("hipEventRecord"); }
 int hipStreamCreateWithFlags(void** s, unsigned) { *s = malloc(1); return 0; }
 int hipStreamDestroy(void* s) { free(s); return 0; }
 int hipStreamSynchronize(void*) { return 0; }
-int hipStreamWaitEvent(void*, void*, unsigned) { return outcome("hipStreamWaitEvent"); }
+int hipStreamWaitEvent(void*, void*, unsigned) { ++waits; return outcome("hipStreamWaitEvent"); }
 int hipStreamIsCapturing(void* s, int* status) { *status = s && s == capturing; return 0; }
 int hipStreamBeginCapture(void* s, int) {
     if (const int e = outcome("hipStreamBeginCapture")) return e;

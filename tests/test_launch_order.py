@@ -199,6 +199,22 @@ print(json.dumps(Library("transe_l2", b={b}, g={g}, k={k}, D=400, {loss}).steps(
     assert any("k_gemm_fwd" in e for e in events) != split
 
 
+# chunks of one positive, steps launched one by one: (model, b, k, D) and whether the keys are sorted beside k_ind, with a fork
+# and a join: more positives than the chip holds workgroups of k_ind, and enough work
+@pytest.mark.parametrize("model,b,k,D,beside", [
+    ("distmult", 1024, 1024, 400, False), ("distmult", 1280, 256, 400, True), ("distmult", 1280, 200, 400, False),
+    ("complex", 2048, 512, 400, True), ("transe_l1", 2048, 512, 400, True), ("transe_l2", 2048, 256, 400, True),
+    ("transe_l2", 2048, 128, 400, False), ("distmult", 512, 256, 800, False), ("complex", 1024, 256, 640, True),
+    ("distmult", 1024, 64, 800, False), ("rotate", 768, 256, 400, False), ("rotate", 800, 256, 400, True),
+    ("rotate", 1024, 192, 400, True), ("rotate", 2048, 128, 256, False)])
+def test_keys_of_chunks_of_one_positive_sorted_beside_where_that_is_shorter(recorder, model, b, k, D, beside):
+    waits = drive(recorder, f'''
+assert Library({model!r}, b={b}, g=1, k={k}, D={D}).steps(1)[0] == 0
+print(json.dumps(rec.recorder_waits()))
+''')
+    assert waits == (2 if beside else 0)
+
+
 @pytest.mark.parametrize("shape", ["b=20_000, g=100, k=4, D=1024", "b=1 << 20, g=1 << 10, k=1024, D=4, relations=1_000_000"])
 def test_transr_steps_of_very_many_workgroups(recorder, shape):
     """Workspaces of 80 and 60 GB: more workgroups of the relation update, or of the projections, than one dimension of a grid
