@@ -247,7 +247,7 @@ __global__ __launch_bounds__(FT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
         return;
     }
     const int row = (block - 8 * f.per_xcd) * FW + (threadIdx.x >> 6);
-    if (row < f.ga.b) gather_row<MODEL, NV>(f.ga, row);
+    if (row < f.ga.b) gather_row<MODEL, NV>(f.ga, row);  // (positives, fp32: the tiles stage the corrupting rows)
 }
 
 }  // namespace

@@ -7,7 +7,7 @@
 // dense staging array that the chunked negative scoring reads.  Waves past the positives copy the k
 // corrupting rows of every chunk into staging (the O(bkd/g) rows of Sec. 3.3) and compute |n|^2 for TransE-L2.
 // In a training step the same launch carries extra blocks that bring the step's key lists into (id, position)
-// order for the duplicate reduction (rank_block below): that work needs only the ids, so it rides along here.
+// order for the duplicate reduction (rank_block in k_gather_rows.h): that work needs only the ids, so it rides along here.
 #include "k_gather_rows.h"
 
 namespace {
@@ -35,9 +35,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(GatherArgs a) {
         }
         return;
     }
-    const int lane = threadIdx.x & 63;
-    const int row = (block - a.rank_blocks) * ROWS_PER_BLOCK + (threadIdx.x >> 6);
-#include "k_gather_row_body.h"
+    gather_row<MODEL, NV>(a, (block - a.rank_blocks) * ROWS_PER_BLOCK + (threadIdx.x >> 6));
 }
 
 template <int MODEL, int THREADS>
