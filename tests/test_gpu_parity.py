@@ -221,14 +221,17 @@ FORWARD_SHAPES = {
     "row-512": (96, 96, 100, 512), "row-516": (66, 33, 40, 520),
     "tiles-512": (512, 32, 1024, 8), "tiles-513": (1026, 342, 510, 16), "tiles-768": (768, 32, 1024, 136),
     "tiles-800": (800, 32, 1024, 136), "keys-8192": (2048, 64, 128, 16), "keys-8194": (2049, 683, 1365, 16),
-    "keys-sorted": (2048, 8, 64, 16),
+    "keys-sorted": (2048, 8, 64, 16), "keys-8320": (4096, 1024, 32, 16), "row-400": (512, 128, 96, 400), "slice-256": (64, 32, 32, 256),
 }
+# RESCAL, where the oracle forms dim * dim products per negative: the same limits with nearly empty tiles and few negatives
+RESCAL_FORWARD_SHAPES = {"row-512": (24, 24, 24, 512), "row-516": (24, 24, 24, 516), "row-400": (96, 48, 16, 400), "tiles-768": (1536, 2, 2, 136),
+                         "tiles-800": (1600, 2, 2, 136)}
 
 
 @pytest.mark.parametrize("shape", sorted(FORWARD_SHAPES))
 @pytest.mark.parametrize("model", ["transe_l2", "transe_l1", "distmult", "complex", "rescal"])
 def test_forward_product_beside_the_gather(kge, model, shape):
-    b, g, k, dim = FORWARD_SHAPES[shape]
+    b, g, k, dim = RESCAL_FORWARD_SHAPES.get(shape, FORWARD_SHAPES[shape]) if model == "rescal" else FORWARD_SHAPES[shape]
     if model == "rescal" and b * k * dim * dim > 3e8:
         pytest.skip("dim * dim products per negative in the oracle")
     if model != "complex" and shape in ("row-4", "row-252", "row-260", "row-516"):
