@@ -1,16 +1,16 @@
 // Gather and forward product in one launch, for steps of few output tiles.
 //
 // The forward product needs o_i = phi(a_i, r_i) and the corrupting rows; the gather launch forms and stages them, and a
-// second launch reads them back.  Where the output has no more tiles than the chip holds workgroups, the tiles can read
-// the table rows themselves: a workgroup of eight waves owns a 32 x 32 output tile, every wave asks for whole rows (of four
+// second launch reads them back.  Where the output has few tiles (the chip holds 512 of these workgroups, two per CU by their LDS;
+// the limits, 384 to 768 tiles, are measured: kge_front_fits) the tiles can read the table rows themselves: a workgroup of eight waves owns a 32 x 32 output tile, every wave asks for whole rows (of four
 // positives and four corrupting entities) in one round, forms o, and lays both operands out in LDS in slices of 256 floats
 // of K, which the waves then split between them.  The tiles stage the corrupting rows for the backward
 // product; o rows, the scores of the positives and the key order come from other workgroups of the launch
 // (k_gather_rows.h), which need nothing from the tiles.  What it saves is the ramp and the drain of a launch and a round
 // trip through memory: gather + forward 8.0 + 7.2 -> 13.4 us at Freebase scale, 8.3 + 6.7 -> 11.1 FB15k-sized (D 400),
 // 5.1 + 5.3 -> 6.9 in a step of 256 positives (D 64).
-// TransE-L1 forms its sums of absolute differences from the same staged rows.  (RotatE does not: every tile would form the
-// sines and cosines of its 32 relation rows again.)
+// TransE-L1 forms its sums of absolute differences from the same staged rows.  (RotatE has not been tried here: every tile would
+// form the sines and cosines of its 32 relation rows again.)
 #include "k_gather_rows.h"
 #include "k_gemm_shared.h"
 
@@ -29,7 +29,7 @@ struct FrontArgs {
     int ldc, g, k;
     int gx, gy, tiles, per_xcd;
     int rank_wgs;  // rank blocks, rounded up to a multiple of 8
-    int out_mode;
+    int out_mode;  // TransE-L1: OUT_SCORE; others (training steps only): OUT_DIST or OUT_W
     bool stage;    // training: stage the corrupting rows
     float wk;
     float* neg_loss_part;
@@ -206,7 +206,7 @@ __device__ __forceinline__ void front_tile(const FrontArgs& f, int tile, float* 
         if (MODEL == KGE_TRANSE_L2) {
             const float o2 = sum_of_waves(norms + (e >> 5), 2 * TILE), n2 = sum_of_waves(norms + TILE + (e & 31), 2 * TILE);
             const float d = sqrtf(fmaxf(o2 + n2 - 2.f * s, 0.f));
-            out = f.out_mode == OUT_DIST ? d : a.gamma - d;
+            out = d;
             if (f.out_mode == OUT_W) {
                 const float coef = w_and_loss<true>(a.gamma - d, f.wk, loss);
                 out = d > 0.f ? coef * __builtin_amdgcn_rcpf(d) : 0.f;

@@ -1,12 +1,13 @@
 // fp32 products on the bf16 matrix cores.
 //
 // A float is the sum of three bf16 numbers (24 bits of significand in three times 8): x0 = bf16(x), x1 = bf16(x - x0),
-// x2 = the rest, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|.  Of the nine products of two such sums the three smallest (2^-27 of the
-// product and less, an eighth of the rounding of one fp32 multiplication) are left out; the other six are exact in fp32 and
-// are added up in fp32 by the matrix cores, x0 y0 in one accumulator and the five small ones in another.  Six bf16
-// instructions take 3/8 of the time of the fp32 instructions they replace.  Error against 64 bits, sums of 400 products of
-// numbers in (-1, 1), relative 2-norm: 0.96e-7, with the fp32 instructions 3.7e-7 (there every product is a rounding of the
-// running sum, here sixteen or 32 are added at a time).
+// x2 = the rest, |x1| <= 2^-9 |x|, |x2| <= 2^-18 |x|.  That holds from 2^-110 on: the last bits of smaller numbers lie below the
+// smallest bf16, 2^-133, and up to 2^-134 is lost (at 1e-34 4.6e-7 of the number).  Of the nine products of two such sums the
+// three smallest (2^-27 of the product and less, an eighth of the rounding of one fp32 multiplication) are left out; the other
+// six are exact in fp32 and are added up in fp32 by the matrix cores, x0 y0 in one accumulator and the five small ones in
+// another.  Six bf16 instructions take 3/8 of the time of the fp32 instructions they replace.  Error against 64 bits, sums of 400
+// products of numbers in (-1, 1), relative 2-norm: 0.96e-7, with the fp32 instructions 3.7e-7 (there every product is a rounding
+// of the running sum, here sixteen or 32 are added at a time).
 #pragma once
 #include "kge_common.h"
 
