@@ -382,11 +382,25 @@ void set_tiling(GemmArgs& g, int chunks, bool coordinate_tiles = false) {
     g.tiles = g.gx * g.gy * chunks;
 }
 
+// Tiles of k_gemm_wide.hip, which give the same bits.  us per kge_score (DistMult, TransE-L2), here -> there (b, g, k, D):
+//   enough of them           1000, 1000, 1024, 400 24.1 -> 21.2 (1024 tiles of 32 x 32), D 200 17.7 -> 16.1, D 128 13.7 -> 13.9, D 32 12.6 -> 12.7; 1000,
+//                            1000, 1504, 64 14.6 -> 13.8, D 400 34.8 -> 29.8;  600, 600, 600, 100 11.8 -> 13.0 (361 tiles)
+//   filled ones              1024, 64, 1024, 400 29.4 -> 26.9;  2016, 63, 1000, 400 48.0 -> 42.6;  1008, 48, 1024, 200 25.2 -> 24.0; three quarters
+//                            of their 32 x 32 blocks inside the matrix 2016, 96, 1024, 400 42.4 -> 45.3, half 2048, 32, 1024, 400 64.9 ->
+//                            76.5; all, but half of the rows are not there 2013, 33, 800, 100 28.9 -> 31.3
+// kge_rank gains more (fewer atomics): 2040, 40, 1500, 64 54.9 -> 39.4, D 400 104 -> 95.6.
+bool wide_tiles(const GemmArgs& g, int chunks) {
+    if (g.tiles < (g.out_mode == OUT_RANK || g.K > 128 ? 1024 : 1280)) return false;
+    const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) * chunks;
+    return 8 * (int64_t)g.tiles >= 7 * 4 * tiles && 10 * (int64_t)g.M * g.N * chunks >= 6 * 64 * 64 * tiles;
+}
+
 template <int EPI>
 void launch_fwd(kge_ctx* c, GemmArgs g, int chunks, hipStream_t st) {
     set_tiling(g, chunks);
     const dim3 grid(8 * ((g.tiles + 7) / 8));
     const int nw = pick_nw(g.tiles, (g.K + TILE - 1) / TILE, 16);
+    if (nw == 4 && wide_tiles(g, chunks)) return kge_gemm_wide_forward(c, &g, EPI, chunks, st);
     if (nw == 4) KGE_LAUNCH(c, (k_gemm_fwd<4, EPI>), grid, dim3(256), 0, st, g);
     else if (nw == 8) KGE_LAUNCH(c, (k_gemm_fwd<8, EPI>), grid, dim3(512), 0, st, g);
     else KGE_LAUNCH(c, (k_gemm_fwd<16, EPI>), grid, dim3(1024), 0, st, g);

@@ -81,6 +81,8 @@ __device__ __forceinline__ int xcd_tile(int q, int per_xcd) { return (blockIdx.x
 // fp32 operands, many tiles (k_gemm_split.hip), and the 32 x 32 blocks that its tiles of a chunk of g positives and k negatives have
 int kge_gemm_split_blocks(int g, int k);
 void kge_gemm_split_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);
+// the bits of k_gemm_fwd with four waves, on larger tiles (k_gemm_wide.hip)
+void kge_gemm_wide_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);
 // bf16 operands (k_gemm_bf.hip): the same two launches on 64x64 tiles
 void kge_gemm_bf_forward(kge_ctx* c, const void* args, int epi, int chunks, hipStream_t st);
 void kge_gemm_bf_backward(kge_ctx* c, const void* args_o, const void* args_n, int epi_o, int epi_n, int chunks,

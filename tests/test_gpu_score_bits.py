@@ -126,3 +126,51 @@ def test_bits_of_the_scores_of_positives_rescal(kge, D):
         first = fma(x[1], y[1], x[0] * y[0]) if D <= 256 else fma(x[0], y[0], x[1] * y[1])
         acc = acc + fma(x[3], y[3], fma(x[2], y[2], first))
     assert np.array_equal(pos.cpu().numpy().view(np.int32), wave_sum(acc).view(np.int32))
+
+
+@pytest.mark.parametrize("b,k,D", [(1000, 1100, 400), (1025, 1057, 36), (1020, 1280, 132), (1060, 2049, 4)])
+@pytest.mark.parametrize("model", ["transe_l2", "distmult", "complex"])
+def test_negative_scores_hang_on_the_pair_alone(kge, model, b, k, D):
+    """One chunk is scored on tiles of 64 x 64, chunks of 20 (half of such tiles' rows would be missing) on tiles of 32 x 32: the
+    same bits, and ranks, with blocks of K past the end, short last ones and ragged edges.  Candidates that are the replaced entity tie."""
+    if model == "complex" and D % 8:
+        D += 4
+    gen = np.random.default_rng(3)
+    n, g = 3000, 20
+    b -= b % g
+    E = torch.from_numpy(gen.uniform(-1, 1, (n, D)).astype(F)).cuda()
+    R = torch.from_numpy(gen.uniform(-1, 1, (5, D)).astype(F)).cuda()
+    h, t, neg = (torch.from_numpy(gen.integers(0, n, m)).cuda() for m in (b, b, k))
+    neg[::7] = t[:neg[::7].numel()]
+    r = torch.from_numpy(gen.integers(0, 5, b)).cuda()
+    got = {}
+    for chunk, ids in ((b, neg), (g, neg.repeat(b // g))):
+        ctx = kge.KgeContext(model, n, 5, D, D, max_batch=b, max_neg_per_chunk=k, max_chunks=b // chunk)
+        pos, out = torch.empty(b, device="cuda"), torch.empty((b, k), device="cuda")
+        ranks = torch.empty(b, dtype=torch.int32, device="cuda")
+        try:
+            ctx.score(E, R, h, r, t, ids, k, chunk, 0, GAMMA, pos, out)
+            ctx.rank(E, R, h, r, t, ids, k, chunk, 0, GAMMA, ranks)
+            torch.cuda.synchronize()
+        finally:
+            ctx.close()
+        got[chunk] = out.cpu().numpy(), ranks.cpu().numpy(), pos.cpu().numpy()
+    np.testing.assert_array_equal(got[b][0], got[g][0])
+    np.testing.assert_array_equal(got[b][1], got[g][1])
+    np.testing.assert_array_equal(got[b][1], 1 + (got[b][0] > got[b][2][:, None]).sum(1))
+
+
+@pytest.mark.parametrize("adv", [0.0, 1.0])
+@pytest.mark.parametrize("model", ["transe_l2", "distmult"])
+def test_training_steps_on_the_tiles_of_the_scores(kge, model, adv):
+    """Coefficients with their loss, and scores and distances for the loss kernel, of 64 x 64 tiles in training steps."""
+    from harness import configs
+    from parity_util import Pair
+    from test_gpu_parity import ragged, run_steps
+    w = ragged(model, n_entities=60_001, n_triples=20_000, batch=1020, chunk=340, neg_per_chunk=1050, ent_dim=140, rel_dim=140, steps=1,
+               adv_temperature=adv)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), 1)
+    finally:
+        p.close()
