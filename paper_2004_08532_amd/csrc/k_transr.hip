@@ -11,27 +11,30 @@
 // that an item's rows are contiguous; what a caller sees is put back into the order of the mini-batch where it is stored.
 //   (k_gather)        the items of every chunk (k_transr_items.h), beside the corrupting rows and the order of the keys
 //   k_transr_phi      o_i, p_i = M_i c_i: an item's a and c rows times M^T; the positive's score and logistic-loss terms
-//   k_transr_project  P_t = N_c M_t^T, and in its epilogue S_ij = gamma - |o_i - P_tj|^2 for the item's positives
-//                     (logistic loss with uniform weights, up to 1024 scores per row: W = dL/df-, no loss kernel)
-//   (k_loss)          W otherwise
+// then, where W needs no loss kernel (logistic loss, uniform weights, up to 1024 scores per row) and rows have up to 128 floats:
+//   k_transr_project_units  (k_transr_unit.h) scores, W, V and the corrupting rows' gradients in one pass over the UNITS, the blocks
+//                     of up to 32 positives of an item
+//   k_transr_go       dL/do_i, dL/dp_i and the gradient of the translation from their parts
+//   k_transr_mgrad    dL/dM of a unit: V_t^T N_c + sum over its positives of dL/do a^T + dL/dp c^T, one product whose K range is
+//                     the corrupting rows and the positives; beside it M^T dL/do_i, M^T dL/dp_i
+// and otherwise
+//   k_transr_project  P_t = N_c M_t^T, and in its epilogue S_ij = gamma - |o_i - P_tj|^2 for the item's positives (or W = dL/df-)
+//   (k_loss)          W
 //   k_transr_dp       V_tj = sum over the item's positives of 2 W_ij (o_i - P_tj); dL/do_i = - sum_j of the same terms
 //                     - 2 cpos (o - p), dL/dp_i = 2 cpos (o - p), gradient of the translation (k_transr_go ends these for
 //                     items of few positives)
 //   k_transr_back     sum over a chunk's items of V_t M_t (partial over ranges of items); M^T dL/do_i, M^T dL/dp_i
-//   k_transr_mgrad    dL/dM of an item: V_t^T N_c + sum over its positives of dL/do a^T + dL/dp c^T, one product whose
-//                     K range is the corrupting rows and the positives
+//   k_transr_mgrad    dL/dM of an item
+// and in the end
 //   k_transr_update   duplicate reduction and Adagrad for the relation rows [r | M] (Sec. 3.1 step 4); the partial sums
-//                     of k_transr_back
-// The products run on v_mfma_f32_16x16x4_f32, those of k_transr_back and k_transr_mgrad of longer rows on the bf16 matrix
-// cores: a workgroup owns 64 rows x up to 128 columns (whole matrices at D <= 128),
+//                     of the corrupting rows' gradients
+// The products (but for k_transr_unit.h's) run on v_mfma_f32_16x16x4_f32, those of k_transr_back and k_transr_mgrad of longer rows on
+// the bf16 matrix cores: a workgroup owns 64 rows x up to 128 columns (whole matrices at D <= 128),
 // K in blocks of 32 staged in LDS for its four waves (16 rows each), the next block's global loads in flight while one is
 // multiplied.  (128 rows per workgroup were measured: equal or slower, half as many waves fit a SIMD.)  All sums have a
 // fixed order.
-// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 292 us per step with all products in fp32 and V
-// in a launch of its own (450 with three products per positive on 32x32 tiles, projections written and read four times; b 798,
-// g 266, k 52, D 56, 21 relations: 192 -> 74).  The three large products took 63-71 us each: 29 us of matrix instructions (a
-// quarter of them padding, 100 -> 112 rows and columns), the rest the start of a workgroup (four dependent loads) and an uneven
-// number of workgroups per CU.
+// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 191 us per step; 250 with projection, V M and M^T dL/do
+// in launches of their own, 292 with all products in fp32 and V in a launch too (450 with three products per positive on 32x32 tiles).
 #include <type_traits>
 
 #include "k_gemm_shared.h"
@@ -59,8 +62,8 @@ struct TransrArgs {
     float gamma, wk;
     int out_w;       // project: store W = dL/df- instead of the score
     int train;       // project: keep the projections, scores in the order of the members; phi: likewise
-    int form_v;      // dp: the projection has formed V and dL/do of items of few positives
-    int segments;    // back: ranges of a chunk's items
+    int segments;    // back, unit: ranges of a chunk's items (units)
+    int units;       // k_transr_project_units has run: gradients of the positives in parts of UROWS rows, V and matrix gradients by unit
     TransrGroups q;
     float* O;        // [b x D]      o
     float* PP;       // [b x D]      p, then dL/dp
@@ -368,6 +371,25 @@ __device__ __forceinline__ bool pblock_of(const TransrArgs& a, int unit, int& c,
     return e < a.q.n_pblocks[c];
 }
 
+// a unit as an item of its own
+__device__ __forceinline__ bool unit_item_of(const TransrArgs& a, int unit, int& c, int& slot, TransrItem& item) {
+    TransrBlock blk;
+    if (!pblock_of(a, unit, c, blk)) return false;
+    slot = c * a.g + unit - c * a.max_pblocks;
+    item = {blk.rel, blk.off, blk.n};
+    return true;
+}
+
+__device__ __forceinline__ void lds_barrier() {  // orders LDS traffic only: global loads stay in flight across it
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+}  // namespace
+#include "k_transr_unit.h"
+namespace {
+
 // Rows 2 m and 2 m + 1 of the product: a and c of the block's m-th positive.
 template <int NT>
 __global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
@@ -390,6 +412,7 @@ __global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
         pa[it] = a.E + id * D;
         if (tid % 8 == 0 && row == tid / 8 + 32 * it) a.q.ent[2 * blk.off + row] = (uint32_t)id;
     }
+    if (a.train && tid < n) a.q.unit_of[a.q.members[blk.off + tid]] = tid > 0 ? -1 : c * a.g + (int)blockIdx.x - c * a.max_pblocks;
     const float sigma = head ? -1.f : 1.f;
     const int l16 = tid & 15, quad = (tid & 63) >> 4;
     float ss[2] = {0.f, 0.f};
@@ -445,11 +468,7 @@ __global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
 
 // 64 corrupting rows x a block of an item's positives: projections, then the scores of the positives against them.  (An
 // item of more than 32 positives is projected once per block: at that size the scores are the larger part of the work.)
-// FORM_V: form V and dL/do of items of few positives too, whose P is then not stored.  Calls that don't (scoring, rows of more
-// than BN floats, steps with a loss kernel) get a kernel without that code, which takes 12 to 20 registers and at rows of 49 to
-// 64 floats a wave per SIMD (kge_score, b 1024, k 256, D 64: 38.0 us with it, 36.1 without, D 128 84.3 and 83.3; kge_rank of
-// 1000 positives in one chunk, k 1000, D 64: 77.4 and 72.9).
-template <int NT, bool FORM_V>
+template <int NT>
 __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int blocks) {
     __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
     const int tiles = (a.k + BM - 1) / BM, D = a.D, tid = threadIdx.x;
@@ -489,9 +508,8 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
 #pragma unroll
             for (int it = 0; it < 4; ++it) st4(Bs + (tid / 32 + 8 * it) * BN + 4 * (tid % 32), ro[it]);
             __syncthreads();
-            const bool form_v = FORM_V && blk.all <= DP_FEW;  // (the same for every thread; one pass over the columns)
-            if (!t.active && !form_v) continue;
-            const bool store_p = a.train && blk.first == 0 && !form_v;
+            if (!t.active) continue;
+            const bool store_p = a.train && blk.first == 0;
 #pragma unroll
             for (int ct = 0; ct < NT; ++ct) {
                 const int d = n0 + 16 * ct + l16;
@@ -503,7 +521,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
             }
             // four positives per round, so that every lane has a score to finish: positive m0 + lane % 4, row q
             const int x = tid & 3, j = t.row(q);
-            auto scores = [&](int m0) {  // positive m0 + x, row q; what is stored of it (0: there is none)
+            for (int m0 = 0; m0 < n; m0 += 4) {
                 float r[4];
 #pragma unroll
                 for (int y = 0; y < 4; ++y) {
@@ -524,7 +542,7 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
                     }
                     r[y] = sum16x4(ss);
                 }
-                if (m0 + x >= n || j >= rows) return 0.f;
+                if (m0 + x >= n || j >= rows) continue;
                 float s = x == 0 ? r[0] : x == 1 ? r[1] : x == 2 ? r[2] : r[3];
                 const int m = blk.off + m0 + x;
                 float* ps = a.S + (int64_t)(a.train ? m : a.q.members[m]) * a.ld_s + j0 + j;
@@ -534,71 +552,6 @@ __global__ __launch_bounds__(RT, 4) void k_transr_project(TransrArgs a, int bloc
                     if (a.out_w) s = w_and_loss<true>(s, a.wk, loss);
                 }
                 *ps = s;
-                return s;
-            };
-            if (!form_v) {
-                for (int m0 = 0; m0 < n; m0 += 4) scores(m0);
-                continue;
-            }
-            // V_tj and dL/do (partial: over these 64 rows) while P is here: positive by positive, as dp_few forms them.  W of a
-            // round goes through LDS from the lane that has formed it to the lanes that hold the row; the sums for dL/do of two
-            // positives meet there too, one row per wave and quarter of a wave, and are added up in that order.
-            floatx4 vsum[NT];
-#pragma unroll
-            for (int ct = 0; ct < NT; ++ct) vsum[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-            constexpr int GROUPS = RT / 16;
-            float* w2 = As + 64 * t.wave;                         // [4 positives][16 rows] of this wave
-            auto go = [&](int y) { return y == 0 ? As + 256 : Bs + DP_FEW * BN; };  // [group of 16 lanes][BN]; behind w2, behind the o rows
-            static_assert(256 + GROUPS * BN <= A_FLOATS && (DP_FEW + GROUPS) * BN <= B_FLOATS, "");
-            const int quad = t.lane >> 4;
-            for (int m0 = 0; m0 < n; m0 += 4) {
-                w2[16 * x + t.row16(q)] = t.active ? 2.f * scores(m0) : 0.f;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                for (int y0 = 0; y0 < min(4, n - m0); y0 += 2) {
-#pragma unroll
-                    for (int y = 0; y < 2; ++y) {
-                        if (m0 + y0 + y >= n) break;
-                        const float4 w = ld4(w2 + 16 * (y0 + y) + 4 * quad);
-                        const float* po = Bs + (m0 + y0 + y) * BN + l16;
-                        float* pg = go(y) + (4 * t.wave + quad) * BN + l16;
-#pragma unroll
-                        for (int ct = 0; ct < NT; ++ct) {
-                            const float o = po[16 * ct];
-                            float g = 0.f;
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) {
-                                const float e = (v == 0 ? w.x : v == 1 ? w.y : v == 2 ? w.z : w.w) * (o - t.acc[ct][v]);
-                                vsum[ct][v] += e;
-                                g -= e;
-                            }
-                            pg[16 * ct] = g;
-                        }
-                    }
-                    __syncthreads();
-                    const int lanes = D / 4, y = tid >> 7, d = 4 * (tid & 127);  // half of the threads per positive
-                    if ((tid & 127) < lanes && m0 + y0 + y < n) {
-                        const float* pg = go(y) + d;
-                        float4 s = ld4(pg);
-#pragma unroll
-                        for (int e = 1; e < GROUPS; ++e) {
-                            const float4 u = ld4(pg + e * BN);
-                            s.x += u.x; s.y += u.y; s.z += u.z; s.w += u.w;
-                        }
-                        st4(a.GOp + ((int64_t)tile * a.b + blk.off + m0 + y0 + y) * D + d, s);
-                    }
-                    __syncthreads();
-                }
-            }
-            float* V = a.V + ((int64_t)blk.slot * a.k + j0) * D;
-#pragma unroll
-            for (int ct = 0; ct < NT; ++ct) {
-                const int d = 16 * ct + l16;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (d < D && t.row(v) < rows) V[(int64_t)t.row(v) * D + d] = vsum[ct][v];
-                }
             }
         }
     }
@@ -709,7 +662,6 @@ __global__ __launch_bounds__(RT) void k_transr_dp(TransrArgs a, int go_blocks, i
         if (!item_of(a, unit_of_block(block - go_blocks, tiles, tile), c, slot, item)) return;
         const int j0 = tile * BM, rows = min(BM, a.k - j0), n = item.n;
         if (n <= DP_FEW) {
-            if (a.form_v) return;
             dp_few(a, slot, tile, item, reinterpret_cast<float4(*)[RT]>(lds), reinterpret_cast<float(*)[BM]>(lds + 4 * MB * RT));
             return;
         }
@@ -806,8 +758,19 @@ __global__ __launch_bounds__(RT) void k_transr_go(TransrArgs a) {
     const int i = a.q.members[m], all = a.q.count[m];
     const float cp2 = 2.f * a.cpos[m];
     const float4 o = ld4(a.O + at), p = ld4(a.PP + at);
-    if (all > DP_FEW) return;
-    const float4 s = sum_parts(a.GOp + at, (a.k + BM - 1) / BM, (int64_t)a.b * a.D);
+    if (all > DP_FEW && !a.units) return;
+    const int rows = a.units ? 16 : BM, parts = (a.k + rows - 1) / rows;
+    double sx = 0, sy = 0, sz = 0, sw = 0;  // (in 64 bits: up to 64 parts and more, one after the other)
+    for (int q0 = 0; q0 < parts; q0 += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = ld4(a.GOp + at + (q0 + q < parts ? q0 + q : 0) * (int64_t)a.b * a.D);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            if (q0 + q < parts) { sx += v[q].x; sy += v[q].y; sz += v[q].z; sw += v[q].w; }
+        }
+    }
+    const float4 s = make_float4((float)sx, (float)sy, (float)sz, (float)sw);
     const float4 gp = make_float4(cp2 * (o.x - p.x), cp2 * (o.y - p.y), cp2 * (o.z - p.z), cp2 * (o.w - p.w));  // df+/do = -2 (o - p)
     const float4 go = make_float4(s.x - gp.x, s.y - gp.y, s.z - gp.z, s.w - gp.w);
     st4(a.GO + at, go);
@@ -816,8 +779,48 @@ __global__ __launch_bounds__(RT) void k_transr_go(TransrArgs a) {
     st4(a.Gr + (int64_t)i * a.D + 4 * (e % lanes), make_float4(sigma * go.x, sigma * go.y, sigma * go.z, sigma * go.w));
 }
 
-// V_t M_t.  The first workgroups: 64 corrupting rows of a chunk x 128 columns x a range of the chunk's items; the others:
-// dL/do and dL/dp of a block of an item's positives (rows 2 m, 2 m + 1) x 128 columns, straight into their gradient rows.
+// dL/do and dL/dp of a block of an item's positives (rows 2 m, 2 m + 1) times M, 128 columns, straight into their gradient rows
+template <int NT>
+__device__ __forceinline__ void back_positives_f32(const TransrArgs& a, int x, float* As, float* Bs) {
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15;
+    const int n0 = x % cols * BN, col = n0 + 4 * (tid % 32), colc = col < D ? col : n0;
+    Tile<NT> t;
+    int c;
+    TransrBlock blk;
+    if (!pblock_of(a, x / cols, c, blk)) return;
+    const int n = blk.n;
+    const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D + colc;
+    const bool head = step_view(a.ids).side == KGE_NEG_HEAD;
+    tile_init(t, As, Bs, 2 * n);
+    const float* pa[2];
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const int row = min(tid / 8 + 32 * it, 2 * n - 1);
+        pa[it] = ((row & 1) ? a.PP : a.GO) + (int64_t)(blk.off + row / 2) * D;
+    }
+    int i[2];  // rows 2 h, 2 h + 1 of the lane's four
+#pragma unroll
+    for (int h = 0; h < 2; ++h) i[h] = a.q.members[blk.off + min(t.row(2 * h) / 2, n - 1)];
+    tile_run<true, false, false>(t, D, 1, [&](int, int kb, float4* r) { load_kc<2>(pa, D, kb, r); },
+                                 [&](int kb, float4* r) { mask_kc<2>(D, kb, r); },
+                                 [&](int, int kb, float4* r) { load_mc<4>(M, D, D, kb, tid / 32, 8, r); },
+                                 [&](int kb, float4* r) { mask_mc<4>(D, kb, tid / 32, 8, r); });
+    if (!t.active) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (t.row(v) >= 2 * n) continue;
+        // key positions: heads 0 .. b-1, tails b .. 2b-1; even rows belong to the kept entity
+        const bool to_head = head == (bool)(v & 1);
+        float* out = a.Gent + ((int64_t)(to_head ? 0 : a.b) + i[v / 2]) * D;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) out[d] = t.acc[ct][v];
+        }
+    }
+}
+
+// V_t M_t.  The first workgroups: 64 corrupting rows of a chunk x 128 columns x a range of the chunk's items; the others: the positives.
 template <int NT>
 __global__ __launch_bounds__(RT, 4) void k_transr_back_f32(TransrArgs a, int neg_blocks) {
     __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
@@ -868,49 +871,17 @@ __global__ __launch_bounds__(RT, 4) void k_transr_back_f32(TransrArgs a, int neg
         }
         return;
     }
-    int c;
-    TransrBlock blk;
-    if (!pblock_of(a, x / cols, c, blk)) return;
-    const int n = blk.n;
-    const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D + colc;
-    const bool head = step_view(a.ids).side == KGE_NEG_HEAD;
-    tile_init(t, As, Bs, 2 * n);
-    const float* pa[2];
-#pragma unroll
-    for (int it = 0; it < 2; ++it) {
-        const int row = min(tid / 8 + 32 * it, 2 * n - 1);
-        pa[it] = ((row & 1) ? a.PP : a.GO) + (int64_t)(blk.off + row / 2) * D;
-    }
-    int i[2];  // rows 2 h, 2 h + 1 of the lane's four
-#pragma unroll
-    for (int h = 0; h < 2; ++h) i[h] = a.q.members[blk.off + min(t.row(2 * h) / 2, n - 1)];
-    tile_run<true, false, false>(t, D, 1, [&](int, int kb, float4* r) { load_kc<2>(pa, D, kb, r); },
-                                 [&](int kb, float4* r) { mask_kc<2>(D, kb, r); },
-                                 [&](int, int kb, float4* r) { load_mc<4>(M, D, D, kb, tid / 32, 8, r); },
-                                 [&](int kb, float4* r) { mask_mc<4>(D, kb, tid / 32, 8, r); });
-    if (!t.active) return;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        if (t.row(v) >= 2 * n) continue;
-        // key positions: heads 0 .. b-1, tails b .. 2b-1; even rows belong to the kept entity
-        const bool to_head = head == (bool)(v & 1);
-        float* out = a.Gent + ((int64_t)(to_head ? 0 : a.b) + i[v / 2]) * D;
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-            const int d = n0 + 16 * ct + l16;
-            if (d < D) out[d] = t.acc[ct][v];
-        }
-    }
+    back_positives_f32<NT>(a, x, As, Bs);
 }
 
 // 64 rows x 128 columns of dL/dM of an item.  K: the chunk's corrupting rows, then two rows per positive.
 template <int NT>
-__global__ __launch_bounds__(RT, 4) void k_transr_mgrad_f32(TransrArgs a) {
-    __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
+__device__ __forceinline__ void mgrad_f32(const TransrArgs& a, int block, float* As, float* Bs) {
     const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, tiles = (D + BM - 1) / BM * cols;
     int c, slot, tile;
     TransrItem item;
-    if (!item_of(a, unit_of_block(blockIdx.x, tiles, tile), c, slot, item)) return;
+    const int unit = unit_of_block(block, tiles, tile);
+    if (a.units ? !unit_item_of(a, unit, c, slot, item) : !item_of(a, unit, c, slot, item)) return;
     const int n0 = tile % cols * BN, e0 = tile / cols * BM, n2 = 2 * item.n;
     const int ca = e0 + 4 * (tid % 16), cb = n0 + 4 * (tid % 32), ka = tid / 16, kb0 = tid / 32;
     const int cac = ca < D ? ca : e0, cbc = cb < D ? cb : n0;
@@ -958,7 +929,53 @@ __global__ __launch_bounds__(RT, 4) void k_transr_mgrad_f32(TransrArgs a) {
     }
 }
 
+// The first workgroups: matrix gradients; the others, where k_transr_project_units has done the corrupting rows: back_positives.
+template <int NT>
+__global__ __launch_bounds__(RT, 4) void k_transr_mgrad_f32(TransrArgs a, int blocks, int back) {
+    __shared__ __attribute__((aligned(16))) float As[A_FLOATS], Bs[B_FLOATS];
+    const int block = flat_block();
+    if (block < blocks) mgrad_f32<NT>(a, block, As, Bs);
+    else if (block - blocks < back) back_positives_f32<NT>(a, block - blocks, As, Bs);
+}
+
 // The same on the bf16 matrix cores.
+template <int NT>
+__device__ __forceinline__ void back_positives(const TransrArgs& a, int x, uint16_t* Bs) {
+    const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, l16 = tid & 15;
+    const int n0 = x % cols * BN, col = n0 + 4 * (tid % 32), colc = col < D ? col : n0;
+    SplitTile<NT> t;
+    int c;
+    TransrBlock blk;
+    if (!pblock_of(a, x / cols, c, blk)) return;
+    const int n = blk.n;
+    const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D + colc;
+    const bool head = step_view(a.ids).side == KGE_NEG_HEAD;
+    split_init(t, 2 * n);
+    const int row = min(t.a_row(), 2 * n - 1);
+    const float* pa = ((row & 1) ? a.PP : a.GO) + (int64_t)(blk.off + row / 2) * D;
+    int i[2];  // rows 2 h, 2 h + 1 of the lane's four
+#pragma unroll
+    for (int h = 0; h < 2; ++h) i[h] = a.q.members[blk.off + min(t.row(2 * h) / 2, n - 1)];
+    split_run(t, Bs, D, 1, [&](int, int kb, float4 (&r)[2]) { load_row(pa, BK * kb + t.a_k(), D, r); },
+                     [&](int kb, float4 (&r)[2]) { mask_row(BK * kb + t.a_k(), D, r); },
+                     [&](int, int kb, float4* r) { load_mc<4>(M, D, D, kb, 4 * (tid / 32), 1, r); },
+                     [&](int kb, float4* r) { mask_mc<4>(D, kb, 4 * (tid / 32), 1, r); });
+    split_sum(t);
+    if (!t.active) return;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (t.row(v) >= 2 * n) continue;
+        // key positions: heads 0 .. b-1, tails b .. 2b-1; even rows belong to the kept entity
+        const bool to_head = head == (bool)(v & 1);
+        float* out = a.Gent + ((int64_t)(to_head ? 0 : a.b) + i[v / 2]) * D;
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+            const int d = n0 + 16 * ct + l16;
+            if (d < D) out[d] = t.acc[ct][v];
+        }
+    }
+}
+
 template <int NT>
 __global__ __launch_bounds__(RT, 3) void k_transr_back(TransrArgs a, int neg_blocks) {
     __shared__ __attribute__((aligned(16))) uint16_t Bs[3 * 16 * NT * SP];
@@ -1005,45 +1022,16 @@ __global__ __launch_bounds__(RT, 3) void k_transr_back(TransrArgs a, int neg_blo
         }
         return;
     }
-    int c;
-    TransrBlock blk;
-    if (!pblock_of(a, x / cols, c, blk)) return;
-    const int n = blk.n;
-    const float* M = a.R + (int64_t)blk.rel * a.rel_dim + D + colc;
-    const bool head = step_view(a.ids).side == KGE_NEG_HEAD;
-    split_init(t, 2 * n);
-    const int row = min(t.a_row(), 2 * n - 1);
-    const float* pa = ((row & 1) ? a.PP : a.GO) + (int64_t)(blk.off + row / 2) * D;
-    int i[2];  // rows 2 h, 2 h + 1 of the lane's four
-#pragma unroll
-    for (int h = 0; h < 2; ++h) i[h] = a.q.members[blk.off + min(t.row(2 * h) / 2, n - 1)];
-    split_run(t, Bs, D, 1, [&](int, int kb, float4 (&r)[2]) { load_row(pa, BK * kb + t.a_k(), D, r); },
-                     [&](int kb, float4 (&r)[2]) { mask_row(BK * kb + t.a_k(), D, r); },
-                     [&](int, int kb, float4* r) { load_mc<4>(M, D, D, kb, 4 * (tid / 32), 1, r); },
-                     [&](int kb, float4* r) { mask_mc<4>(D, kb, 4 * (tid / 32), 1, r); });
-    split_sum(t);
-    if (!t.active) return;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        if (t.row(v) >= 2 * n) continue;
-        // key positions: heads 0 .. b-1, tails b .. 2b-1; even rows belong to the kept entity
-        const bool to_head = head == (bool)(v & 1);
-        float* out = a.Gent + ((int64_t)(to_head ? 0 : a.b) + i[v / 2]) * D;
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-            const int d = n0 + 16 * ct + l16;
-            if (d < D) out[d] = t.acc[ct][v];
-        }
-    }
+    back_positives<NT>(a, x, Bs);
 }
 
 template <int NT>
-__global__ __launch_bounds__(RT, 3) void k_transr_mgrad(TransrArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t Bs[3 * 16 * NT * SP];
+__device__ __forceinline__ void mgrad(const TransrArgs& a, int block, uint16_t* Bs) {
     const int D = a.D, tid = threadIdx.x, cols = (D + BN - 1) / BN, tiles = (D + BM - 1) / BM * cols;
     int c, slot, tile;
     TransrItem item;
-    if (!item_of(a, unit_of_block(blockIdx.x, tiles, tile), c, slot, item)) return;
+    const int unit = unit_of_block(block, tiles, tile);
+    if (a.units ? !unit_item_of(a, unit, c, slot, item) : !item_of(a, unit, c, slot, item)) return;
     const int n0 = tile % cols * BN, e0 = tile / cols * BM, n2 = 2 * item.n;
     const int cb = n0 + 4 * (tid % 32), kb0 = 4 * (tid / 32), cbc = cb < D ? cb : n0;
     SplitTile<NT> t;
@@ -1105,12 +1093,20 @@ __global__ __launch_bounds__(RT, 3) void k_transr_mgrad(TransrArgs a) {
     }
 }
 
+template <int NT>
+__global__ __launch_bounds__(RT, 3) void k_transr_mgrad(TransrArgs a, int blocks, int back) {
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[3 * 16 * NT * SP];
+    const int block = flat_block();
+    if (block < blocks) mgrad<NT>(a, block, Bs);
+    else if (block - blocks < back) back_positives<NT>(a, block - blocks, Bs);
+}
+
 struct TransrUpdArgs {
     float* T;             // relation table [n_rel x (D + D*D)]
     float* St;            // its Adagrad accumulator
     const uint32_t* key;  // sorted relation ids of the step
     const uint32_t* pos;  // position in the mini-batch of each sorted entry
-    const int* slot_of;   // item slot of the positives that are the first of their item, else -1
+    const int* slot_of;   // item (unit) slot of the positives that are the first of theirs, else -1
     int n, D, rows_per_slab, slabs;
     int64_t rel_dim;
     const float* Gr;
@@ -1209,7 +1205,7 @@ TransrArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& 
     a.max_items = transr_max_items(gsz, a.n_rel);
     a.max_pblocks = transr_max_pblocks(gsz, a.n_rel);
     a.gamma = gamma; a.wk = 1.f / ((float)(k > 0 ? k : 1) * (float)ids.b);
-    a.out_w = 0; a.train = 1; a.form_v = 0; a.segments = 1;
+    a.out_w = 0; a.train = 1; a.segments = 1; a.units = 0;
     a.q = c->tr_groups;
     a.O = c->O; a.PP = c->PP; a.P = c->P3; a.V = c->P3 + (int64_t)c->cfg.max_batch * c->cfg.max_neg_per_chunk * D;
     a.N = c->Nst; a.S = c->S; a.GO = c->GO; a.GOp = c->tr_go_part;
@@ -1226,14 +1222,15 @@ int back_segments(const TransrArgs& a) {
     return s > a.max_items ? a.max_items : s;
 }
 
-// Does the projection form V of items of few positives?  It has to hold W (no loss kernel) and whole rows of P (one pass over the
-// columns), and it pays where most of k_transr_dp's work goes away: chunks that have hardly an item of more than DP_FEW
-// positives, and rows worth more than the launch that stays for the others.  (us per step, k_transr_dp -> projection: chunks of
-// 16 to 64, k 128, D 64 102 -> 96, k 500, D 36 143 -> 134, k 64, D 100 164 -> 160, k 32, D 64 66.7 -> 67.4; FB15k-sized 287 -> 274;
-// chunks of 256, 60 relations 143 -> 149, chunks of 1000, 1000 relations 200 -> 206.)
-bool forms_v(const kge_ctx* c, int k, int gsz) {
-    const int D = c->cfg.ent_dim;
-    return D <= BN && (int64_t)k * D >= 4096 && (gsz <= 64 || c->cfg.num_relations >= 8 * (int64_t)gsz);
+// Everything between phi and the matrix gradients in k_transr_project_units?  Wherever it can be: us per step, launches of their own ->
+// units (b, g, k, D, relations)  1024, 128, 256, 100, 1345 250 -> 191;  D 128 281 -> 246;  D 64 152 -> 112;  k 500, D 32 151 -> 121;  20 relations
+// 145 -> 128;  800, 400, 300, 72, 100 135 -> 109;  700, 20, 77, 96, 1345 137 -> 128;  1800, 900, 40, 124, 1000 201 -> 202.
+bool in_units(const kge_ctx* c, bool form_w) { return form_w && c->cfg.ent_dim <= BN; }
+// Ranges of a chunk's units: a workgroup per CU, at least one unit each.
+int unit_segments(const TransrArgs& a) {
+    const int base = (a.b / a.g) * ((a.k + UROWS - 1) / UROWS);
+    const int s = (KGE_TRANSR_UNIT_WGS + base - 1) / base;
+    return s > a.max_pblocks ? a.max_pblocks : s;
 }
 
 template <int NT>
@@ -1276,20 +1273,34 @@ void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& i
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, float gamma, float* out, int ld_out, bool train,
                        bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, gamma);
+    if (train && in_units(c, form_w)) {
+        const int chunks = ids.b / gsz;
+        float* rows = a.Gent + (int64_t)2 * ids.b * a.D;
+        const int64_t stride = (int64_t)chunks * k * a.D;
+        a.segments = unit_segments(a);
+        c->neg_partial = {c->tr_back_part, rows, a.segments, stride, stride / 4};
+        if (a.segments == 1) a.back_part = rows;
+        const int wgs = chunks * ((k + UROWS - 1) / UROWS) * a.segments;
+#define L(NT) KGE_LAUNCH(c, k_transr_project_units<NT>, dim3(wgs), dim3(UT), 0, st, a)
+        KGE_BY_COLUMNS(a.D, L);
+#undef L
+        return wgs;
+    }
     a.S = out; a.ld_s = ld_out; a.out_w = form_w; a.train = train;
     const int blocks = pblock_blocks(a, (k + BM - 1) / BM);
-#define L(NT) KGE_LAUNCH(c, (k_transr_project<NT, true>), flat_grid(blocks), dim3(RT), 0, st, a, blocks)
-#define L0(NT) KGE_LAUNCH(c, (k_transr_project<NT, false>), flat_grid(blocks), dim3(RT), 0, st, a, blocks)
-    if (train && form_w && forms_v(c, k, gsz)) KGE_BY_COLUMNS(a.D, L);
-    else KGE_BY_COLUMNS(a.D, L0);
-#undef L0
+#define L(NT) KGE_LAUNCH(c, k_transr_project<NT>, flat_grid(blocks), dim3(RT), 0, st, a, blocks)
+    KGE_BY_COLUMNS(a.D, L);
 #undef L
     return form_w ? blocks : 0;
 }
 
 void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, nullptr, nullptr, ids, k, gsz, 0.f);
-    a.form_v = form_w && forms_v(c, k, gsz);
+    a.units = in_units(c, form_w);
+    if (a.units) {
+        KGE_LAUNCH(c, k_transr_go, dim3((ids.b * (a.D / 4) + RT - 1) / RT), dim3(RT), 0, st, a);
+        return;
+    }
     const int cols = (a.D + DN - 1) / DN, go_blocks = (ids.b / gsz * a.max_pblocks * cols + 7) / 8 * 8;
     const int blocks = go_blocks + item_blocks(a, (k + BM - 1) / BM);
     const dim3 grid = flat_grid(blocks);
@@ -1299,7 +1310,8 @@ void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int gsz, bool form_w, 
     hipLaunchKernelGGL(k_transr_go, dim3((ids.b * (a.D / 4) + RT - 1) / RT), dim3(RT), 0, st, a);
 }
 
-void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, hipStream_t st) {
+void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int gsz, bool form_w, hipStream_t st) {
+    if (in_units(c, form_w)) return;  // k_transr_project_units and k_transr_mgrad
     TransrArgs a = make_args(c, nullptr, R, ids, k, gsz, 0.f);
     const int chunks = ids.b / gsz, cols = (a.D + BN - 1) / BN;
     a.segments = back_segments(a);
@@ -1314,20 +1326,22 @@ void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int 
 #undef L
 }
 
-void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int gsz, hipStream_t st) {
-    const TransrArgs a = make_args(c, E, nullptr, ids, k, gsz, 0.f);
-    const dim3 grid(item_blocks(a, ((a.D + BM - 1) / BM) * ((a.D + BN - 1) / BN)));
-#define L(NT) KGE_LAUNCH(c, mgrad_kernel<NT>(), grid, dim3(RT), 0, st, a)
+void kge_transr_mgrad(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int gsz, bool form_w, hipStream_t st) {
+    TransrArgs a = make_args(c, E, R, ids, k, gsz, 0.f);
+    a.units = in_units(c, form_w);
+    const int tiles = ((a.D + BM - 1) / BM) * ((a.D + BN - 1) / BN), blocks = a.units ? pblock_blocks(a, tiles) : item_blocks(a, tiles);
+    const int back = a.units ? ids.b / gsz * a.max_pblocks : 0;  // (rows of one column tile)
+#define L(NT) KGE_LAUNCH(c, mgrad_kernel<NT>(), flat_grid((int64_t)blocks + back), dim3(RT), 0, st, a, blocks, back)
     KGE_BY_COLUMNS(a.D, L);
 #undef L
 }
 
-void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st) {
+void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, bool form_w, hipStream_t st) {
     TransrUpdArgs a;
     const int D = c->cfg.ent_dim;
     int rows = 1024 / D;  // matrix rows per workgroup: the largest divisor of D that keeps a slab within 1024 floats
     while (D % rows != 0) --rows;
-    a.T = R; a.St = SR; a.key = c->rkey[c->rbuf]; a.pos = c->rpos[c->rbuf]; a.slot_of = c->tr_groups.slot_of;
+    a.T = R; a.St = SR; a.key = c->rkey[c->rbuf]; a.pos = c->rpos[c->rbuf]; a.slot_of = in_units(c, form_w) ? c->tr_groups.unit_of : c->tr_groups.slot_of;
     a.n = ids.b; a.D = D; a.rows_per_slab = rows; a.slabs = D / rows + 1; a.rel_dim = c->cfg.rel_dim;
     a.Gr = c->Grel; a.GM = c->Grel + (int64_t)c->cfg.max_batch * D;
     a.lr = lr; a.eps = c->eps;
@@ -1342,7 +1356,7 @@ size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* 
     size_t off = 0;
     auto take = [&](size_t bytes) { char* p = base + off; off += (bytes + 255) / 256 * 256; return p; };
     q->items = (TransrItem*)take(B * sizeof(TransrItem)); q->pblocks = (TransrBlock*)take(PBS * sizeof(TransrBlock));
-    q->first = (int*)take(B * 4); q->rank = (int*)take(B * 4); q->count = (int*)take(B * 4); q->slot_of = (int*)take(B * 4);
+    q->first = (int*)take(B * 4); q->rank = (int*)take(B * 4); q->count = (int*)take(B * 4); q->slot_of = (int*)take(B * 4); q->unit_of = (int*)take(B * 4);
     q->members = (int*)take(B * 4); q->ent = (uint32_t*)take(2 * B * 4);
     q->n_items = (int*)take(C * 4); q->n_pblocks = (int*)take(C * 4);
     return off;
@@ -1353,5 +1367,5 @@ size_t kge_transr_back_floats(const kge_config& cfg) {
     return (NR + (size_t)cfg.max_chunks * BM + (size_t)KGE_TRANSR_BACK_WGS * BM) * D;
 }
 size_t kge_transr_go_floats(const kge_config& cfg) {
-    return (size_t)cfg.max_batch * cfg.ent_dim * ((size_t)cfg.max_neg_per_chunk / BM + 1);
+    return (size_t)cfg.max_batch * cfg.ent_dim * ((size_t)cfg.max_neg_per_chunk / (cfg.ent_dim <= BN ? 16 : BM) + 1);
 }

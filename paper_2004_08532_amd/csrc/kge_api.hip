@@ -154,13 +154,13 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
     }
     {
         ProfScope p(c, KGE_PROF_BACKWARD);
-        kge_transr_back(c, rel, ids, K, G, st);
+        kge_transr_back(c, rel, ids, K, G, form_w, st);
     }
-    kge_transr_mgrad(c, ent, ids, K, G, st);
+    kge_transr_mgrad(c, ent, rel, ids, K, G, form_w, st);
     if (beside) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     {
         ProfScope p(c, KGE_PROF_REL_UPDATE);
-        kge_transr_update(c, rel, rel_state, ids, lr, st);
+        kge_transr_update(c, rel, rel_state, ids, lr, form_w, st);
     }
     {
         ProfScope p(c, KGE_PROF_UPDATE);

@@ -46,6 +46,7 @@ struct TransrGroups {
     uint32_t* ent;         // [2 b] by member: rows of the kept and the replaced entity
     int* count;            // [b] by member: members of its item
     int* slot_of;          // [b] by position: the item slot if it is the first of its item, else -1
+    int* unit_of;          // [b] by position: c * g + e if it is the first of block e of its chunk's blocks, else -1
     int* first;            // [b] by position, long chunks only: first position of the item in the chunk; its rank among those
     int* rank;
     int* n_items;          // [C]
@@ -244,7 +245,7 @@ void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const S
 // RESCAL, a7 for the relation matrices: gradient of a distinct relation formed from the factor rows, then Adagrad
 void kge_launch_rescal_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
 // TransR (k_transr.hip)
-constexpr int KGE_TRANSR_BACK_WGS = 768;
+constexpr int KGE_TRANSR_BACK_WGS = 768, KGE_TRANSR_UNIT_WGS = 256;
 size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* q);
 size_t kge_transr_back_floats(const kge_config& cfg);
 size_t kge_transr_go_floats(const kge_config& cfg);
@@ -254,9 +255,9 @@ void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& i
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, float gamma, float* out, int ld_out,
                        bool train, bool form_w, hipStream_t st);
 void kge_transr_dp(kge_ctx* c, const StepIds& ids, int k, int g, bool form_w, hipStream_t st);  // (form_w as in kge_transr_project)
-void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, hipStream_t st);
-void kge_transr_mgrad(kge_ctx* c, const float* E, const StepIds& ids, int k, int g, hipStream_t st);
-void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
+void kge_transr_back(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, bool form_w, hipStream_t st);
+void kge_transr_mgrad(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int k, int g, bool form_w, hipStream_t st);
+void kge_transr_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, bool form_w, hipStream_t st);
 // a6: sort (id, position) of the entity and relation key lists
 void kge_launch_sort(kge_ctx* c, const StepIds& ids, hipStream_t st);
 // a7: per distinct row, sum its gradient rows and apply Adagrad; also reduces the loss terms

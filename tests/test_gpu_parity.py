@@ -1126,3 +1126,22 @@ def test_train_steps_at_the_lengths_where_the_launch_schedule_changes(kge, n_ste
         results.append((E, SE, R, SR, loss))
     for a, b_ in zip(*results):
         assert torch.isfinite(a).all() and torch.equal(a, b_)
+
+
+# TransR steps with W formed on the way: corrupting rows around the 16 of a wave and the 128 of a workgroup, blocks of more positives
+# than one, rows around the K steps of 32 and the column tiles of 16, more ranges than a chunk has blocks
+TRANSR_UNITS = {"rows-1": (64, 64, 1, 20, 3), "rows-15": (96, 32, 15, 68, 40), "rows-129": (140, 70, 129, 100, 5), "rows-257": (66, 33, 257, 128, 2),
+                "one-relation": (140, 140, 70, 36, 1), "wide-chunk": (400, 400, 130, 84, 300), "short-rows": (48, 24, 40, 4, 7)}
+
+
+@pytest.mark.parametrize("side", ["tail", "head"])
+@pytest.mark.parametrize("shape", sorted(TRANSR_UNITS))
+def test_transr_blocks_of_positives(kge, shape, side):
+    b, g, k, D, relations = TRANSR_UNITS[shape]
+    w = ragged("transr", n_entities=2_000, n_relations=relations, n_triples=3_000, batch=b, chunk=g, neg_per_chunk=k, ent_dim=D, rel_dim=D + D * D,
+               side_mode=side, steps=2)
+    p = Pair(w, kge)
+    try:
+        run_steps(p, configs.BatchStream(w), 2)
+    finally:
+        p.close()
