@@ -286,15 +286,17 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         if (gemm) kge_gemm_neg_backward(c, ent, rel, ids, K, G, gamma, st);
         else n_loss_parts = kge_pair_neg_backward(c, B, K, G, gamma, st);
     }
+    const bool by_runs = c->cfg.model == KGE_RESCAL && kge_rescal_chain_by_runs(c);  // the chain rule needs the relations' order
+    if (beside && by_runs) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (run_chain) {
         ProfScope p(c, KGE_PROF_CHAIN);
-        if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_chain(c, ent, rel, ids, !beside, st);
+        if (c->cfg.model == KGE_RESCAL) kge_launch_rescal_chain(c, ent, rel, ids, !beside || by_runs, st);
         else kge_launch_chain(c, ent, rel, ids, st);
     }
-    if (beside) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
+    if (beside && !by_runs) KGE_HIP(c, hipStreamWaitEvent(st, c->ev_join, 0));
     if (c->cfg.model == KGE_RESCAL) {
         ProfScope p(c, KGE_PROF_REL_UPDATE);
-        kge_launch_rescal_update(c, rel, rel_state, ids, lr, st);
+        kge_launch_rescal_update(c, ent, rel, rel_state, ids, lr, st);
     }
     {
         ProfScope p(c, KGE_PROF_UPDATE);
@@ -512,6 +514,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? sets_n * 4 : 0);
     const size_t o_P3 = take(transr ? 2 * B * K1 * D * 4 : 0);
     const size_t o_tgo = take(transr ? kge_transr_go_floats(*cfg) * 4 : 0);
+    const size_t o_rr = take(m == KGE_RESCAL ? kge_rescal_runs_bytes(*cfg) : 0);
     const size_t o_tbp = take(transr ? kge_transr_back_floats(*cfg) * 4 : 0);
     c->ws_bytes = (int64_t)off;
 
@@ -538,6 +541,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     if (transr) kge_transr_carve_groups(*cfg, base + o_trg, &c->tr_groups);
     c->tr_go_part = transr ? (float*)(base + o_tgo) : nullptr;
     c->tr_back_part = transr ? (float*)(base + o_tbp) : nullptr;
+    c->rescal_runs = m == KGE_RESCAL ? base + o_rr : nullptr;
     c->pair_part_o = pair_model ? (float*)(base + o_ppo) : nullptr;
     c->pair_part_n = pair_model ? (float*)(base + o_ppn) : nullptr;
     c->pair_part_n_floats = pair_model ? (int64_t)sets_n : 0;

@@ -78,6 +78,7 @@ struct kge_ctx {
     float* tr_go_part;    // TransR: partial sums of dL/do
     float* tr_back_part;  //         partial gradient rows of the corrupting entities
     float* GO;       // [max_batch x D]      dL/do_i
+    void* rescal_runs;   // RESCAL: the runs of equal relations of the running step
     float* pair_part_o;  // RotatE / TransE-L1: [KGE_PAIR_MAX_PARTS][max_batch x D] partial dL/do rows
     PartialRows go_partial, neg_partial;  // what the last backward launch left for the chain launch to add up
     float* pair_part_n;  //                     partial rows of the corrupting entities, a set per tile of positives
@@ -240,10 +241,13 @@ int kge_pair_neg_backward(kge_ctx* c, int b, int k, int g, float gamma, hipStrea
 void kge_launch_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
 // RESCAL: o_i from the kept entity and the relation's matrix (before the gather launch); chain rule through it
 void kge_launch_rescal_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, hipStream_t st);
-// ordered: the key lists have been ordered on this stream
-void kge_launch_rescal_chain(kge_ctx* c, const float* E, const float* R, const StepIds& ids, bool ordered, hipStream_t st);
+// ordered: the key lists have been ordered on this stream.  By runs (rows of 148 to 256 floats): they have to be, and
+// kge_launch_rescal_update does the chain rule of relations of few positives
+bool kge_rescal_chain_by_runs(const kge_ctx* c);
+size_t kge_rescal_runs_bytes(const kge_config& cfg);
+void kge_launch_rescal_chain(kge_ctx* c, const float* E, float* R, const StepIds& ids, bool ordered, hipStream_t st);
 // RESCAL, a7 for the relation matrices: gradient of a distinct relation formed from the factor rows, then Adagrad
-void kge_launch_rescal_update(kge_ctx* c, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
+void kge_launch_rescal_update(kge_ctx* c, const float* E, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
 // TransR (k_transr.hip)
 constexpr int KGE_TRANSR_BACK_WGS = 768, KGE_TRANSR_UNIT_WGS = 256;
 size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* q);

@@ -161,6 +161,12 @@ RESCAL_RUNS = {
     "fewer-than-16": dict(runs=[9, 6], ent_dim=4),
     "one-run": dict(runs=[16], ent_dim=32),
     "around-256": dict(runs=[255, 1, 256, 257, 511, 2, 512, 64, 65], ent_dim=100),
+    # rows of 148 to 256 floats: chain rule and update by runs (parts of 32 rows or columns, tiles of 16, waves without one; runs
+    # of one to four positives per wave, long runs that begin and end inside of a block of 16 positions and share one with others)
+    "144": dict(runs=[1, 3, 16], ent_dim=144), "148": dict(runs=[15, 16, 17, 1, 2, 3, 4, 5, 14, 31], ent_dim=148),
+    "180": dict(runs=[1, 20, 18, 2, 7, 16], ent_dim=180), "200-short": dict(runs=[8, 1, 1, 2], ent_dim=200),
+    "252": dict(runs=[33, 1, 15], ent_dim=252), "256": dict(runs=[16], ent_dim=256), "many": dict(runs=[520, 1, 600, 2], ent_dim=148),
+    "streamed": dict(runs=[1, 2, 17], ent_dim=256, n_relations=650),
 }
 
 
@@ -168,8 +174,8 @@ RESCAL_RUNS = {
 def test_rescal_matrix_update_of_runs(kge, shape):
     """The matrix update of RESCAL takes long runs of equal relation ids as products on tiles and short ones in slabs."""
     runs, D = RESCAL_RUNS[shape]["runs"], RESCAL_RUNS[shape]["ent_dim"]
-    w = ragged("rescal", ent_dim=D, rel_dim=D * D, batch=sum(runs), chunk=sum(runs), neg_per_chunk=17, n_relations=len(runs) + 3,
-               steps=2)
+    w = ragged("rescal", ent_dim=D, rel_dim=D * D, batch=sum(runs), chunk=sum(runs), neg_per_chunk=17 if D < 140 else 5,
+               n_relations=RESCAL_RUNS[shape].get("n_relations", len(runs) + 3), steps=2)
 
     class Runs(configs.BatchStream):
         def step(self, s):
