@@ -193,7 +193,7 @@ def test_rescal_matrix_update_of_runs(kge, shape):
 # rows of the matrix (one to many rounds, one and several pieces per lane), positives (a ragged share per XCD), keys ordered by
 # the gather launch and sorted on a stream of their own
 RESCAL_ROWS = {"4": (9, 9, 5, 4), "20": (33, 11, 7, 20), "68": (24, 8, 9, 68), "252": (17, 17, 5, 252), "256": (16, 8, 5, 256),
-               "260": (10, 5, 5, 260), "sorted": (512, 8, 256, 8)}
+               "260": (10, 5, 5, 260), "sorted": (512, 8, 256, 8), "sorted-148": (64, 1, 230, 148)}
 
 
 @pytest.mark.parametrize("shape", sorted(RESCAL_ROWS))
