@@ -73,6 +73,12 @@ def algorithmic_work(w, h, r, t, neg, rowwise=False):
     coords = D // 2 if w.model == "rotate" else D
     rescal = w.model in ("rescal", "transr")  # relation rows hold D x D matrices, read by their own kernels
     transr = w.model == "transr"  # three products batched over the positives, 2 b k D^2 flops each
+    # RESCAL: matrices that the chain rule reads for how many positives.  Rows of 148 to 256 floats: once for each relation of 16
+    # positives and more (the update does the others)
+    chain_b, chain_m = b, b
+    if w.model == "rescal" and 148 <= D <= 256:
+        runs = [np.unique(r[s], return_counts=True)[1] for s in range(n)]
+        chain_b, chain_m = (np.mean([f(c[c >= 16]) for c in runs]) for f in (np.sum, np.size))
     return {
         "gather": {"bytes": 4.0 * ((2 * b + C * k) * D + (0 if rescal else b * Dr)) + 4.0 * (b + C * k) * D},
         "phi": {"bytes": 4.0 * b * (Dr + 2 * D)},
@@ -82,7 +88,7 @@ def algorithmic_work(w, h, r, t, neg, rowwise=False):
         "neg_score": {"flops": pair_fwd * b * k * coords if pair_fwd else 2.0 * b * k * D * (D if transr else 1)},
         "neg_backward": {"flops": pair_bwd * b * k * coords if pair_bwd else
                          (2.0 * b * k * D * D if transr else 4.0 * b * k * D)},
-        "chain": {"bytes": 4.0 * (8 * b * D + b * Dr) if rescal else 4.0 * (6 * b * D + 2 * b * Dr)},
+        "chain": {"bytes": 4.0 * (8 * chain_b * D + chain_m * Dr) if rescal else 4.0 * (6 * b * D + 2 * b * Dr)},
         "loss": {"bytes": 8.0 * b * k},
         "sort": {"bytes": 8.0 * (n_keys + b)},
         "unique_entity_rows": float(ue), "unique_relation_rows": float(ur),

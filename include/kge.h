@@ -209,7 +209,8 @@ enum {
     KGE_PROF_SCORE = 1,    /* chunked negative scoring                  */
     KGE_PROF_LOSS = 2,     /* loss and backward coefficients            */
     KGE_PROF_BACKWARD = 3, /* dL/do and gradient rows of the negatives  */
-    KGE_PROF_CHAIN = 4,    /* chain rule to head / tail / relation rows */
+    KGE_PROF_CHAIN = 4,    /* chain rule to head / tail / relation rows (RESCAL with rows of 148 to 256 floats: of the relations of
+                              16 positives and more; KGE_PROF_REL_UPDATE holds that of the others) */
     KGE_PROF_SORT = 5,     /* (id, position) sort, on its own stream    */
     KGE_PROF_UPDATE = 6,   /* segment sum + sparse Adagrad              */
     KGE_PROF_PHI = 7,      /* RESCAL: o = M_r^T h or M_r t              */

@@ -337,12 +337,11 @@ static_assert(RUNS_LDS >= PT / 64 * LT * LT + PT, "long runs share the memory");
 //     G[n, x] = sum_j a_j[n] go_j[x]         (the matrix's)
 // so that a workgroup that holds this part in registers does both, and Adagrad, from one read of it (UPDATE: the m positives are
 // all that the relation has; without it y and the factor rows).  Bound by memory: matrices and state, 235 MB per step at b 1024,
-// D 200 on the FB15k-sized graph, in 58 us, where the chain rule positive by positive (17 us) and an update that formed the gradient
-// alone (55) took 72 with 1.5 times the launches' reads.  512 threads and 76 registers (three workgroups per CU): with 256 threads and
+// D 200 on the FB15k-sized graph, in 58 us (4.1 TB/s; a large copy reaches 5.2 to 6.0); with the longer runs' chain rule (7) in place of
+// the chain rule positive by positive (17) and an update of the matrices alone (55).  512 threads and 76 registers (three workgroups per CU): with 256 threads and
 // four tiles per wave 62 us, with 64 columns per workgroup 66, with 64 registers (spills) 72, as workgroups that stay 75.
-// A wave takes tiles of 16 x; lane (q, l) holds n = 2 l + c,
-// x = 4 q + i of each, which is the layout of a B operand of v_mfma_f32_16x16x4_f32 for the first product (k = q, instruction i)
-// and that of the result of the second (row 4 q + i, column l).
+// A wave takes tiles of 16 x; lane (q, l) holds n = 2 l + c, x = 4 q + i of each, which is the layout of a B operand of
+// v_mfma_f32_16x16x4_f32 for the first product (k = q, instruction i) and that of the result of the second (row 4 q + i, column l).
 template <bool HEAD, bool UPDATE, bool STREAM>
 __device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, const StepView& sv, uint32_t key, int p, int m, int slab, float* lds) {
     const RescalArgs& r = a.chain;
