@@ -200,21 +200,23 @@ int kge_check_indices(kge_ctx* ctx, void* hip_stream);
  * library's counterpart).  kge_profile(ctx, 1) makes every following kge_train_step / kge_train_steps launch
  * each of its kernels with a start and a stop event that receive the dispatch's own begin / end timestamps (the
  * duration a kernel trace reports), and synchronise the stream after every step; kge_profile(ctx, 0) restores
- * normal asynchronous operation.  Either call clears the accumulated times.
+ * normal asynchronous operation.  A slot whose kernel a step does not launch gets nothing from it.  Either call clears the accumulated times.
  * kge_profile_read: (host) ms_out[KGE_PROF_SLOTS] receives the summed kernel times in milliseconds per slot,
  * (host) *steps_out the number of steps they cover.  kge_profile_slot_name: (host) static name of a slot.
  */
 enum {
     KGE_PROF_GATHER = 0,   /* row gather + positive scores (few tiles: and negative scores) */
-    KGE_PROF_SCORE = 1,    /* chunked negative scoring                  */
+    KGE_PROF_SCORE = 1,    /* chunked negative scoring (TransR where one launch forms scores, W and the gradient rows of the
+                              negatives: that launch)                   */
     KGE_PROF_LOSS = 2,     /* loss and backward coefficients            */
-    KGE_PROF_BACKWARD = 3, /* dL/do and gradient rows of the negatives  */
+    KGE_PROF_BACKWARD = 3, /* dL/do and gradient rows of the negatives (TransR: nothing where KGE_PROF_SCORE holds these) */
     KGE_PROF_CHAIN = 4,    /* chain rule to head / tail / relation rows (RESCAL with rows of 148 to 256 floats: of the relations of
-                              16 positives and more; KGE_PROF_REL_UPDATE holds that of the others) */
+                              16 positives and more; KGE_PROF_REL_UPDATE holds that of the others; TransR: dL/dP and dL/do, the
+                              gradients of the matrices are not timed)  */
     KGE_PROF_SORT = 5,     /* (id, position) sort, on its own stream    */
     KGE_PROF_UPDATE = 6,   /* segment sum + sparse Adagrad              */
-    KGE_PROF_PHI = 7,      /* RESCAL: o = M_r^T h or M_r t              */
-    KGE_PROF_REL_UPDATE = 8, /* RESCAL: update of the relation matrices */
+    KGE_PROF_PHI = 7,      /* RESCAL: o = M_r^T h or M_r t; TransR: projections of the positives */
+    KGE_PROF_REL_UPDATE = 8, /* RESCAL, TransR: update of the relation rows; chunks of one positive: of the relation rows, and the loss */
     KGE_PROF_SLOTS = 9
 };
 int kge_profile(kge_ctx* ctx, int32_t enable);

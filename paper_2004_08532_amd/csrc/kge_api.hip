@@ -120,19 +120,39 @@ void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids,
 
 // ---- optional per-kernel timing (kge_profile): the one kernel launched inside a scope carries the scope's two
 // events as its start / stop events (KGE_LAUNCH), the stream is synchronised after the step, and the elapsed times
-// are accumulated per slot.
+// of the scopes that launched something are accumulated per slot.  (Events that no launch has carried cannot be read, those of an
+// earlier step's launch would be counted again.)
 struct ProfScope {
     kge_ctx* c;
-    ProfScope(kge_ctx* c_, int slot) : c(c_) {
+    int slot;
+    ProfScope(kge_ctx* c_, int slot_) : c(c_), slot(slot_) {
         if (c->prof_on) { c->launch_ev0 = c->prof_ev[slot][0]; c->launch_ev1 = c->prof_ev[slot][1]; }
     }
-    ~ProfScope() { c->launch_ev0 = nullptr; c->launch_ev1 = nullptr; }
+    ~ProfScope() {
+        if (c->prof_on && !c->launch_ev0) c->prof_launched |= 1u << slot;
+        c->launch_ev0 = nullptr; c->launch_ev1 = nullptr;
+    }
 };
 
-// TransR after its gather launch.  Profile slots: phi, neg_score = projections and scores, loss, chain = dL/dP,
-// neg_backward = the back-projection, rel_update, update; dL/dM is not timed.
+int end_of_step(kge_ctx* c, hipStream_t st) {
+    KGE_HIP(c, hipGetLastError());
+    if (c->prof_on) {
+        KGE_HIP(c, hipStreamSynchronize(st));
+        for (int s = 0; s < KGE_PROF_SLOTS; ++s) {
+            float ms = 0.f;
+            if (!(c->prof_launched >> s & 1)) continue;
+            if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
+        }
+        c->prof_steps += 1;
+    }
+    return KGE_OK;
+}
+
+// TransR after its gather launch.  Profile slots: phi, neg_score = projections and scores (in one pass with dL/dP and the
+// back-projection of the corrupting rows where k_transr_project_units runs), loss, chain = dL/dP and dL/do (or what is left of
+// dL/do), neg_backward = the back-projection (or nothing), rel_update, update; dL/dM is not timed.
 int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids,
-                        int K, int G, float gamma, float lr, bool long_lists, bool beside, hipStream_t st) {
+                        int K, int G, float gamma, float lr, bool beside, hipStream_t st) {
     // (rows of more than KGE_SHORT_SCORES scores: the loss kernel, with the functions it has for them)
     const bool form_w = kge_gemm_backward_forms_w(c) && K <= KGE_SHORT_SCORES;
     int n_loss_parts;
@@ -166,17 +186,7 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
         ProfScope p(c, KGE_PROF_UPDATE);
         kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, n_loss_parts, true, st);
     }
-    KGE_HIP(c, hipGetLastError());
-    if (c->prof_on) {
-        KGE_HIP(c, hipStreamSynchronize(st));
-        for (int s = 0; s < KGE_PROF_SLOTS; ++s) {
-            float ms = 0.f;
-            if ((s == KGE_PROF_SORT && !long_lists) || (s == KGE_PROF_LOSS && form_w)) continue;
-            if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
-        }
-        c->prof_steps += 1;
-    }
-    return KGE_OK;
+    return end_of_step(c, st);
 }
 
 // Chunks of one positive.  Profile slots: gather = the key order, neg_backward = k_ind, update = the entity rows (without
@@ -200,22 +210,13 @@ int enqueue_ind_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, float
         ProfScope p(c, KGE_PROF_REL_UPDATE);
         kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, 0, false, st);
     }
-    KGE_HIP(c, hipGetLastError());
-    if (c->prof_on) {
-        KGE_HIP(c, hipStreamSynchronize(st));
-        const int slots[] = {long_lists ? KGE_PROF_SORT : KGE_PROF_GATHER, KGE_PROF_BACKWARD, KGE_PROF_UPDATE, KGE_PROF_REL_UPDATE};
-        for (int s : slots) {
-            float ms = 0.f;
-            if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
-        }
-        c->prof_steps += 1;
-    }
-    return KGE_OK;
+    return end_of_step(c, st);
 }
 
 int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* rel_state, const StepIds& ids, int K,
                  int G, float gamma, float lr, hipStream_t st) {
     const int B = ids.b;
+    c->prof_launched = 0;
     // Ordering the key lists needs only the ids.  Short lists are ordered by extra blocks of the gather launch; long ones by a
     // radix sort, on a second stream that joins before the update.  A fork and a join cost about 10 us each outside of a graph,
     // and k_ind slows down what runs beside it, so steps of chunks of one positive that are launched one by one sort on the
@@ -264,7 +265,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         ProfScope p(c, KGE_PROF_GATHER);
         kge_launch_gather(c, ent, rel, ids, G, gamma, nullptr, !long_lists, st);
     }
-    if (c->cfg.model == KGE_TRANSR) return enqueue_transr_rest(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, long_lists, beside, st);
+    if (c->cfg.model == KGE_TRANSR) return enqueue_transr_rest(c, ent, ent_state, rel, rel_state, ids, K, G, gamma, lr, beside, st);
     if (!front) {
         ProfScope p(c, KGE_PROF_SCORE);
         if (is_gemm_model(c->cfg.model))
@@ -302,19 +303,7 @@ int enqueue_step(kge_ctx* c, float* ent, float* ent_state, float* rel, float* re
         ProfScope p(c, KGE_PROF_UPDATE);
         kge_launch_update(c, ent, ent_state, rel, rel_state, ids, lr, n_loss_parts, true, st);
     }
-    KGE_HIP(c, hipGetLastError());
-    if (c->prof_on) {
-        KGE_HIP(c, hipStreamSynchronize(st));
-        for (int s = 0; s < KGE_PROF_SLOTS; ++s) {
-            float ms = 0.f;
-            if ((s == KGE_PROF_SORT && !long_lists) || (s == KGE_PROF_SCORE && front) || (s == KGE_PROF_LOSS && !run_loss) ||
-                (s == KGE_PROF_CHAIN && !run_chain) || ((s == KGE_PROF_PHI || s == KGE_PROF_REL_UPDATE) && c->cfg.model != KGE_RESCAL))
-                continue;  // that kernel did not run in this configuration
-            if (hipEventElapsedTime(&ms, c->prof_ev[s][0], c->prof_ev[s][1]) == hipSuccess) c->prof_ms[s] += ms;
-        }
-        c->prof_steps += 1;
-    }
-    return KGE_OK;
+    return end_of_step(c, st);
 }
 
 // ---- replay: kge_train_steps captures 16 or 32 consecutive steps into HIP graphs whose kernels take the step

@@ -113,6 +113,7 @@ struct kge_ctx {
     int64_t graph_captures;         // how many times they were built
     bool prof_on;                   // kge_profile: bracket every kernel with events
     hipEvent_t prof_ev[KGE_PROF_SLOTS][2];
+    uint32_t prof_launched;         // slots whose events the running step's launches carry
     double prof_ms[KGE_PROF_SLOTS];
     int64_t prof_steps;
     hipEvent_t launch_ev0, launch_ev1;  // set by a profiling scope: the next KGE_LAUNCH takes its own start/stop

@@ -31,6 +31,9 @@ int outcome(const char* call) {
     return pending = 2;  // (out of memory)
 }
 
+struct Event { bool recorded; };
+void record(void* e) { if (e) static_cast<Event*>(e)->recorded = true; }
+
 int launch(const void* f, Dim3 grid, Dim3 block) {
     const Kernel& k = kernels()[f];
     if (const int e = outcome("hipLaunchKernel")) return e;
@@ -75,7 +78,11 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** strea
     return 0;
 }
 int hipLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, size_t, void*) { return launch(f, grid, block); }
-int hipExtLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, size_t, void*, void*, void*, int) { return launch(f, grid, block); }
+int hipExtLaunchKernel(const void* f, Dim3 grid, Dim3 block, void**, size_t, void*, void* start, void* stop, int) {
+    const int e = launch(f, grid, block);
+    if (!e) { record(start); record(stop); }
+    return e;
+}
 int hipGetDeviceCount(int* n) { *n = 1; return 0; }
 int hipSetDevice(int) { return 0; }
 int hipDeviceSynchronize() { return 0; }
@@ -100,11 +107,18 @@ int hipMemcpyAsync(void*, const void*, size_t, int, void*) {
     events() += "copy\n";
     return 0;
 }
-int hipEventCreate(void** e) { *e = malloc(1); return 0; }
-int hipEventCreateWithFlags(void** e, unsigned) { *e = malloc(1); return 0; }
-int hipEventDestroy(void* e) { free(e); return 0; }
-int hipEventElapsedTime(float* ms, void*, void*) { *ms = 0.f; return 0; }
-int hipEventRecord(void*, void*) { return outcome("hipEventRecord"); }
+int hipEventCreate(void** e) { *e = new Event{}; return 0; }
+int hipEventCreateWithFlags(void** e, unsigned) { *e = new Event{}; return 0; }
+int hipEventDestroy(void* e) { delete static_cast<Event*>(e); return 0; }
+int hipEventElapsedTime(float* ms, void* start, void* stop) {  // every kernel takes 1 ms
+    if (!static_cast<Event*>(start)->recorded || !static_cast<Event*>(stop)->recorded) return pending = 400;  // (invalid handle)
+    *ms = 1.f;
+    return 0;
+}
+int hipEventRecord(void* e, void*) {
+    record(e);
+    return outcome("hipEventRecord");
+}
 int hipStreamCreateWithFlags(void** s, unsigned) { *s = malloc(1); return 0; }
 int hipStreamDestroy(void* s) { free(s); return 0; }
 int hipStreamSynchronize(void*) { return 0; }

@@ -156,6 +156,42 @@ print(json.dumps([projections(x.steps(1)[1]), plain]))
     assert all(len(k) == 1 and k == others[0] and k != forms for k in others), (forms, others)
 
 
+# (model, chunk, options, b, k of the first steps, k of the later ones): every form of the step, and changes of form on one context
+PROFILED = [(m, g, "", 64, 24, 24) for m in ("transe_l2", "transe_l1", "distmult", "complex", "rotate", "rescal", "transr") for g in (1, 16)] + [
+    ("transr", 16, "", 64, 1100, 24), ("transr", 16, "", 64, 24, 1100), ("transr", 16, "D=136, ", 64, 24, 24), ("transr", 16, "loss=1, ", 64, 24, 24),
+    ("transe_l2", 16, "adv_temperature=1.0, ", 64, 24, 24), ("rescal", 16, "D=200, ", 64, 24, 24), ("distmult", 16, "", 64, 24, 5000),
+    ("distmult", 16, "", 64, 5000, 24), ("transe_l2", 1, "D=400, ", 512, 256, 8)]
+
+
+@pytest.mark.parametrize("model,chunk,options,b,k,later", PROFILED)
+def test_profile_counts_the_kernels_that_ran(recorder, model, chunk, options, b, k, later):
+    """kge_profile's times of steps whose kernels take 1 ms each: a slot gets a millisecond from every step that launches its kernel
+    and nothing from the others, and no error is left behind."""
+    codes, rows, pending = drive(recorder, f'''
+lib.kge_profile.argtypes = [vp, i32]
+lib.kge_profile_read.argtypes = [vp, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(i64)]
+x = Library({model!r}, b={b}, g={chunk}, {options}k=max({k}, {later}))
+assert lib.kge_profile(x.ctx, 1) == 0
+def read():
+    ms, n = (ctypes.c_double * 9)(), i64()
+    assert lib.kge_profile_read(x.ctx, ms, ctypes.byref(n)) == 0
+    return list(ms) + [n.value]
+codes, rows = [], [read()]
+for k in ({k}, {later}):
+    x.k = k
+    for n in (1, 3):
+        codes.append(x.steps(n)[0])
+        rows.append(read())
+print(json.dumps([codes, rows, rec.hipGetLastError()]))
+''')
+    assert codes == [0] * 4 and pending == 0
+    for n, before, after in zip((1, 3, 1, 3), rows, rows[1:]):
+        added = [y - x for x, y in zip(before, after)]
+        assert added[9] == n and set(added[:9]) <= {0, n} and added[6] == n, added
+    first, second = ([y - x for x, y in zip(rows[i], rows[i + 1])][:9] for i in (0, 2))
+    assert (first == second) == (k == later), (first, second)
+
+
 # (b, g, k, D) and whether the tiles of the forward product are in the gather launch: the limits on tiles and on keys
 FRONT = {
     "complex": [(1024, 128, 384, 64, True), (1024, 128, 416, 64, False), (1024, 128, 384, 256, True), (1024, 128, 416, 256, False),
