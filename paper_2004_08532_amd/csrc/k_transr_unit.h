@@ -204,7 +204,8 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
             floatx4 p[NT], vsum[NT];
 #pragma unroll
             for (int ct = 0; ct < NT; ++ct) vsum[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
-            product(nf, along_rows, [&](int ct, floatx4 x) { p[ct] = x; });
+            // (zeros past column D, also where a row with an infinity has met the zeros there)
+            product(nf, along_rows, [&](int ct, floatx4 x) { p[ct] = 16 * ct + l16 < D ? x : floatx4{0.f, 0.f, 0.f, 0.f}; });
             for (int m0 = 0; m0 < n; m0 += 4) {
                 float r[4];
 #pragma unroll

@@ -161,3 +161,40 @@ def test_transr_gradients(kge, D, k):
     err = [float(np.linalg.norm(x - y) / np.linalg.norm(y)) for x, y in ((gE, wE), (gR[:, :D], wR[:, :D]), (gR[:, D:], wR[:, D:]))]
     print("\n[precision] transr", D, k, "entities %.1e translations %.1e matrices %.1e" % tuple(err))
     assert max(err) < LIMIT, err
+
+
+@gpu
+@pytest.mark.parametrize("D,k", [(20, 40), (68, 129), (100, 70), (112, 33)])
+def test_transr_infinite_corrupting_row(kge, D, k):
+    """An infinity in a corrupting row makes its scores minus infinity: nothing of it in the loss or in the other rows' gradients,
+    whether or not the columns of the projections are a multiple of the tiles."""
+    gen = np.random.default_rng(8)
+    g = 40
+    E = gen.uniform(-1, 1, (2 * g + k, D)).astype(np.float32)
+    R = gen.uniform(-1, 1, (3, D + D * D)).astype(np.float32)
+    R[:, :D] *= 0.1
+    R[:, D:] *= 3 / D  # scores of a few units, as above
+    ids = np.arange(2 * g + k)
+    bad = 2 * g + k - 2
+    E[bad, D - 1] = np.inf
+    h, r, t, neg = ids[:g], gen.integers(0, 3, g), ids[g:2 * g], ids[2 * g:]
+    dev = lambda v: torch.from_numpy(v).cuda()
+    ctx = kge.KgeContext("transr", *E.shape[:1], 3, D, D + D * D, max_batch=g, max_neg_per_chunk=k, max_chunks=1)
+    dE, dR, out = dev(E.copy()), dev(R.copy()), torch.zeros(1, device="cuda")
+    sE = torch.zeros_like(dE)
+    try:
+        ctx.train_step(dE, sE, dR, torch.zeros_like(dR), dev(h), dev(r), dev(t), dev(neg), k, g, 0, 2.0, 0.1, loss_out=out)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    others = neg[neg != bad]
+    E64, R64 = (torch.from_numpy(x).double().requires_grad_() for x in (E, R))
+    M = R64[r, D:].reshape(g, D, D)
+    o = (M @ E64[h].unsqueeze(-1)).squeeze(-1) + R64[r, :D]
+    fp = 2.0 - (o - (M @ E64[t].unsqueeze(-1)).squeeze(-1)).square().sum(-1)
+    f = 2.0 - (o[:, None] - torch.einsum("gde,ke->gkd", M, E64[others])).square().sum(-1)
+    loss = (torch.nn.functional.softplus(-fp).sum() + torch.nn.functional.softplus(f).sum() / k) / g
+    loss.backward()
+    assert abs(out.item() / loss.item() - 1) < 64 * ULP  # (roundings of the scores, a few units each)
+    got, want = sE[others].double().sqrt().cpu().numpy(), E64.grad[others].abs().numpy()
+    assert np.linalg.norm(got - want) / np.linalg.norm(want) < LIMIT
