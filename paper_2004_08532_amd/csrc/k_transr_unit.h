@@ -35,13 +35,18 @@ __device__ __forceinline__ void wave_fence() {  // LDS traffic of one wave
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-// sum over the four quarters of a wave, in every lane (vector ALU swaps, no LDS)
-__device__ __forceinline__ float sum_quads(float x) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, x);
-    const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-    const uint32_t v = __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, (uint32_t)a[0]) + __builtin_bit_cast(float, (uint32_t)a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
+// Sums over the four quarters of a wave of four values; quarter q gets that of value q (vector ALU swaps, no LDS)
+__device__ __forceinline__ double sum_quads(const double (&x)[4]) {
+    auto low = [](double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); };
+    auto high = [](double v) { return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32); };
+    auto of = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); };
+    auto halves = [&](double a, double b) {  // lanes 0 .. 31: of a, the others: of b
+        const auto l = __builtin_amdgcn_permlane32_swap(low(a), low(b), false, false), h = __builtin_amdgcn_permlane32_swap(high(a), high(b), false, false);
+        return of(l[0], h[0]) + of(l[1], h[1]);
+    };
+    const double a = halves(x[0], x[2]), b = halves(x[1], x[3]);
+    const auto l = __builtin_amdgcn_permlane16_swap(low(a), low(b), false, false), h = __builtin_amdgcn_permlane16_swap(high(a), high(b), false, false);
+    return of(l[0], h[0]) + of(l[1], h[1]);
 }
 
 // The units of range `seg` of a chunk: cut[0] .. cut[1] - 1, for every thread behind the next barrier.  Returns the chunk's number of units.
@@ -67,7 +72,7 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
     constexpr int KS = (NT + 1) / 2, W = 16 * NT, BLOCKS = (KS * KS + 7) / 8;  // K steps, columns, 32 x 32 blocks of M that a wave brings to LDS
     constexpr int PART = 32 * KS * 128;
     __shared__ __attribute__((aligned(16))) uint16_t Ms[3 * PART];
-    __shared__ __attribute__((aligned(16))) float Vs[8][16 * UVP], Os[PB * W], W2[8][4 * 16];
+    __shared__ __attribute__((aligned(16))) float Vs[8][16 * UVP], Os[PB * W];
     __shared__ int cut[2];
     __shared__ float part[8];
     const int D = a.D, tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
@@ -202,10 +207,9 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
         // from here to the next barrier every wave goes its own way
         if (active) {
             floatx4 p[NT], vsum[NT];
-#pragma unroll
-            for (int ct = 0; ct < NT; ++ct) vsum[ct] = floatx4{0.f, 0.f, 0.f, 0.f};
             // (zeros past column D, also where a row with an infinity has met the zeros there)
             product(nf, along_rows, [&](int ct, floatx4 x) { p[ct] = 16 * ct + l16 < D ? x : floatx4{0.f, 0.f, 0.f, 0.f}; });
+            float* W2 = Vs[w];  // [PB positives][16 rows]  2 W
             for (int m0 = 0; m0 < n; m0 += 4) {
                 float r[4];
 #pragma unroll
@@ -228,30 +232,46 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
                 const float s = x4 == 0 ? r[0] : x4 == 1 ? r[1] : x4 == 2 ? r[2] : r[3];
                 float w2 = 0.f;
                 if (m0 + x4 < n && jq < rows) w2 = 2.f * w_and_loss<true>(a.gamma - s, a.wk, loss);
-                W2[w][16 * x4 + 4 * quad + q4] = w2;
-                wave_fence();
+                W2[16 * (m0 + x4) + 4 * quad + q4] = w2;
+            }
+            wave_fence();
+            // V and this wave's part of dL/do, four column tiles at a time (all of them at once: 90 spills and more at D 100): products
+            // and sums over positives and rows in 64 bits.  (Sums in 32 bits leave 1.5 roundings in V of 32 positives, these 0.5; same
+            // time.)  Of the sums over rows every quarter of the wave gets those of one tile.
+            constexpr int CG = 4;
+            static_assert(16 * PB <= 16 * UVP, "W where V is staged");
 #pragma unroll
-                for (int y = 0; y < 4; ++y) {
-                    if (m0 + y >= n) break;
-                    const float* po = Os + (m0 + y) * W + l16;
-                    const float4 ww = ld4(W2[w] + 16 * y + 4 * quad);
-                    float* go = a.GOp + ((int64_t)(tile * 8 + w) * a.b + u.off + m0 + y) * D + l16;
+            for (int c0 = 0; c0 < NT; c0 += CG) {
+                doublex4 acc[CG];
 #pragma unroll
-                    for (int ct = 0; ct < NT; ++ct) {
-                        const float o = po[16 * ct];
-                        float g = 0.f;
+                for (int h = 0; h < CG; ++h) acc[h] = doublex4{0., 0., 0., 0.};
+                const int col = 16 * c0 + lane;
+                float* go = a.GOp + ((int64_t)(tile * 8 + w) * a.b + u.off) * D + col;
+#pragma unroll 1
+                for (int m = 0; m < n; ++m) {
+                    const float4 ww = ld4(W2 + 16 * m + 4 * quad);
+                    const double wd[4] = {ww.x, ww.y, ww.z, ww.w};
+                    const float* po = Os + m * W + 16 * c0 + l16;
+                    double g[CG] = {};
+#pragma unroll
+                    for (int h = 0; h < CG; ++h) {
+                        if (c0 + h >= NT) break;
+                        const float o = po[16 * h];
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const float t = (v == 0 ? ww.x : v == 1 ? ww.y : v == 2 ? ww.z : ww.w) * (o - p[ct][v]);
-                            vsum[ct][v] += t;
-                            g -= t;
+                            const double d = o - p[c0 + h][v];  // (exact where o is close to P)
+                            acc[h][v] = fma(wd[v], d, acc[h][v]);
+                            g[h] = fma(-wd[v], d, g[h]);
                         }
-                        g = sum_quads(g);
-                        if (quad == 0 && 16 * ct + l16 < D) go[16 * ct] = g;
                     }
+                    const float x = (float)sum_quads(g);
+                    if (col < D) go[(int64_t)m * D] = x;
                 }
-                wave_fence();
+#pragma unroll
+                for (int h = 0; h < CG; ++h)
+                    if (c0 + h < NT) vsum[c0 + h] = __builtin_convertvector(acc[h], floatx4);
             }
+            wave_fence();
             float* V = a.V + ((int64_t)(c * a.g + e) * a.k + j0 + 16 * w + l16) * D + 8 * quad;
             const bool mine = 16 * w + l16 < rows;
             Split8 vf[KS];
