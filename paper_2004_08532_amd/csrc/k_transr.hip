@@ -1226,11 +1226,23 @@ int back_segments(const TransrArgs& a) {
 // units (b, g, k, D, relations)  1024, 128, 256, 100, 1345 250 -> 191;  D 128 281 -> 246;  D 64 152 -> 112;  k 500, D 32 151 -> 121;  20 relations
 // 145 -> 128;  800, 400, 300, 72, 100 135 -> 109;  700, 20, 77, 96, 1345 137 -> 128;  1800, 900, 40, 124, 1000 201 -> 202.
 bool in_units(const kge_ctx* c, bool form_w) { return form_w && c->cfg.ent_dim <= BN; }
-// Ranges of a chunk's units: a workgroup per CU, at least one unit each.
+// Ranges of a chunk's units.  A workgroup has a CU to itself (rows of up to 32 floats: half of one), so a grid of a few workgroups
+// more than the chip holds takes twice the time: of the numbers that fill one to eight rounds, the one whose rounds times (units of a
+// range, and one for its start and its gradient rows) is least.  Units per chunk are known on the device only; two thirds of the most
+// there can be is what a Zipf-distributed graph has.  us per step, ceil(256 / workgroups per range) -> this (b, g, k, D, relations): 1024,
+// 256, 640, 100, 1345 425 -> 330 (260 workgroups -> 240);  1024, 128, 300, 100 274 -> 238;  1000, 200, 700, 100 472 -> 370;  1040, 16, 256, 100
+// 333 -> 301 (260 -> 390);  1600, 50, 640, 32 241 -> 215;  1000, 1000, 200, 32 78.1 -> 81.3 (256 -> 512).
 int unit_segments(const TransrArgs& a) {
-    const int base = (a.b / a.g) * ((a.k + UROWS - 1) / UROWS);
-    const int s = (KGE_TRANSR_UNIT_WGS + base - 1) / base;
-    return s > a.max_pblocks ? a.max_pblocks : s;
+    const int64_t chunks = a.b / a.g, base = chunks * ((a.k + UROWS - 1) / UROWS), slots = a.D <= 32 ? 2 * KGE_TRANSR_UNIT_WGS : KGE_TRANSR_UNIT_WGS;
+    const int64_t rows = chunks * a.k, room = (rows + (chunks + KGE_TRANSR_BACK_WGS) * BM) / rows;  // (kge_transr_back_floats)
+    const int64_t most = room < a.max_pblocks ? room : a.max_pblocks;
+    auto cost = [&](int64_t s) { return (double)((base * s + slots - 1) / slots) * (1. + 0.65 * a.max_pblocks / (double)s); };
+    int64_t best = 1;
+    for (int r = 1; r <= 8; ++r) {
+        const int64_t fill = r * slots / base, s = fill < most ? fill : most;
+        if (s > 1 && cost(s) < cost(best)) best = s;
+    }
+    return (int)best;
 }
 
 template <int NT>

@@ -250,7 +250,7 @@ void kge_launch_rescal_chain(kge_ctx* c, const float* E, float* R, const StepIds
 // RESCAL, a7 for the relation matrices: gradient of a distinct relation formed from the factor rows, then Adagrad
 void kge_launch_rescal_update(kge_ctx* c, const float* E, float* R, float* SR, const StepIds& ids, float lr, hipStream_t st);
 // TransR (k_transr.hip)
-constexpr int KGE_TRANSR_BACK_WGS = 768, KGE_TRANSR_UNIT_WGS = 256;
+constexpr int KGE_TRANSR_BACK_WGS = 768, KGE_TRANSR_UNIT_WGS = 256;  // three per CU; one
 size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* q);
 size_t kge_transr_back_floats(const kge_config& cfg);
 size_t kge_transr_go_floats(const kge_config& cfg);

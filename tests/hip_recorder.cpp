@@ -45,7 +45,9 @@ int launch(const void* f, Dim3 grid, Dim3 block) {
     if (capturing) { ++captured; return 0; }
     char line[64];
     snprintf(line, sizeof(line), "kernel %d ", k.module);
-    events() += line + k.name + "\n";
+    events() += line + k.name;
+    snprintf(line, sizeof(line), " %u\n", grid.x * grid.y * grid.z);
+    events() += line;
     return 0;
 }
 
