@@ -101,8 +101,13 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
 
     // A lane's share of M: 4 x 4 elements (rows me + i, columns md + ..) of block w + 8 q, an 8 x 8 arrangement of lanes
     struct Share { float4 m[BLOCKS][4]; };
-    auto me = [&](int q) { return (w + 8 * q) / KS * 32 + 4 * (lane >> 3); };
-    auto md = [&](int q) { return (w + 8 * q) % KS * 32 + 4 * (lane & 7); };
+    // The addresses of M's parts are formed from lx; where rows have more than 64 floats, again for every unit and product: some forty of
+    // them, kept throughout, left the products too few registers (D 128: 47 spills -> 2, FB15k-sized 242 -> 221 us per step; D 100: 10 -> 0, no
+    // change).  Shorter rows have the registers (D 64: 112.1 us, formed again 114.7).
+    int lx = lane;
+    auto again = [&]() { if (NT > 4) asm volatile("" : "+v"(lx)); };
+    auto me = [&](int q) { return (w + 8 * q) / KS * 32 + 4 * (lx >> 3); };
+    auto md = [&](int q) { return (w + 8 * q) % KS * 32 + 4 * (lx & 7); };
     auto load_m = [&](uint32_t rel) {
         const float* M = a.R + (int64_t)rel * a.rel_dim + D;
         Share s;
@@ -141,8 +146,9 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
         else store_parts(s, std::false_type());
     };
     // right operands: K along the rows of M (N M^T) ...
-    const int swz = unit_at(l16, 0) & 127;  // the permutation of row l16 (and of every row 16 further on)
     auto along_rows = [&](int ct, int ks) {
+        const int l16 = lx & 15, quad = lx >> 4;
+        const int swz = unit_at(l16, 0) & 127;  // the permutation of row l16 (and of every row 16 further on)
         const uint16_t* p = Ms + 128 * (16 * ct + l16) + ((32 * ks + 8 * quad) ^ swz);
         Split8 b;
 #pragma unroll
@@ -151,8 +157,9 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
     };
     // ... and down its columns (V M): the transposing read gives a lane of sixteen four rows of its column; lane l16 names row l16 / 4
     // and columns 4 (l16 % 4) .. of them
-    const int tr0 = unit_at(8 * quad + (l16 >> 2), 0) & 127, tr1 = unit_at(8 * quad + 4 + (l16 >> 2), 0) & 127;
     auto down_columns = [&](int ct, int ks) {
+        const int l16 = lx & 15, quad = lx >> 4;
+        const int tr0 = unit_at(8 * quad + (l16 >> 2), 0) & 127, tr1 = unit_at(8 * quad + 4 + (l16 >> 2), 0) & 127;
         typedef short shortx4 __attribute__((ext_vector_type(4)));
         typedef __attribute__((address_space(3))) shortx4* lds4;
         const int col = 16 * ct + 4 * (l16 & 3), row = 32 * ks + 8 * quad + (l16 >> 2);
@@ -198,6 +205,7 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
         const TransrBlock next = units[min(e + 1, n_units - 1)];
         const int n = u.n;
         lds_barrier();  // the unit before is done with LDS
+        again();
         store_m(share);
         for (int x = tid; x < n * (W / 4); x += UT) {  // o rows, zeros past column D
             const int m = x / (W / 4), d = 4 * (x % (W / 4));
@@ -208,6 +216,7 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
         if (active) {
             floatx4 p[NT], vsum[NT];
             // (zeros past column D, also where a row with an infinity has met the zeros there)
+            again();
             product(nf, along_rows, [&](int ct, floatx4 x) { p[ct] = 16 * ct + l16 < D ? x : floatx4{0.f, 0.f, 0.f, 0.f}; });
             float* W2 = Vs[w];  // [PB positives][16 rows]  2 W
             for (int m0 = 0; m0 < n; m0 += 4) {
@@ -235,7 +244,7 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
                 W2[16 * (m0 + x4) + 4 * quad + q4] = w2;
             }
             wave_fence();
-            // V and this wave's part of dL/do, four column tiles at a time (all of them at once: 90 spills and more at D 100): products
+            // V and this wave's part of dL/do, four column tiles at a time (all of them at once: 62 spills at D 100): products
             // and sums over positives and rows in 64 bits.  (Sums in 32 bits leave 1.5 roundings in V of 32 positives, these 0.5; same
             // time.)  Of the sums over rows every quarter of the wave gets those of one tile.
             constexpr int CG = 4;
@@ -296,8 +305,9 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
                 }
                 wave_fence();
             }
+            again();
             product(vf, down_columns, [&](int ct, floatx4 x) { sum[ct] += x; });
-            share = load_m(next.rel);  // (asked for before the product: 4244 us instead of 4088 per 20 FB15k-sized steps, spills)
+            share = load_m(next.rel);  // (asked for before the product: D 128 221 -> 232 us, spills; D 100 the same)
         } else {
             share = load_m(next.rel);
         }
