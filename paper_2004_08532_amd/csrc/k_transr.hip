@@ -63,7 +63,8 @@ struct TransrArgs {
     int out_w;       // project: store W = dL/df- instead of the score
     int train;       // project: keep the projections, scores in the order of the members; phi: likewise
     int segments;    // back, unit: ranges of a chunk's items (units)
-    int units;       // k_transr_project_units has run: gradients of the positives in parts of UROWS rows, V and matrix gradients by unit
+    int units;       // k_transr_project_units has run: gradients of the positives in parts of 16 rows, V and matrix gradients by unit
+    int unit_rows;   // unit: corrupting rows per workgroup
     TransrGroups q;
     float* O;        // [b x D]      o
     float* PP;       // [b x D]      p, then dL/dp
@@ -1205,7 +1206,7 @@ TransrArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& 
     a.max_items = transr_max_items(gsz, a.n_rel);
     a.max_pblocks = transr_max_pblocks(gsz, a.n_rel);
     a.gamma = gamma; a.wk = 1.f / ((float)(k > 0 ? k : 1) * (float)ids.b);
-    a.out_w = 0; a.train = 1; a.segments = 1; a.units = 0;
+    a.out_w = 0; a.train = 1; a.segments = 1; a.units = 0; a.unit_rows = UROWS;
     a.q = c->tr_groups;
     a.O = c->O; a.PP = c->PP; a.P = c->P3; a.V = c->P3 + (int64_t)c->cfg.max_batch * c->cfg.max_neg_per_chunk * D;
     a.N = c->Nst; a.S = c->S; a.GO = c->GO; a.GOp = c->tr_go_part;
@@ -1222,10 +1223,19 @@ int back_segments(const TransrArgs& a) {
     return s > a.max_items ? a.max_items : s;
 }
 
-// Everything between phi and the matrix gradients in k_transr_project_units?  Wherever it can be: us per step, launches of their own ->
-// units (b, g, k, D, relations)  1024, 128, 256, 100, 1345 250 -> 191;  D 128 281 -> 246;  D 64 152 -> 112;  k 500, D 32 151 -> 121;  20 relations
-// 145 -> 128;  800, 400, 300, 72, 100 135 -> 109;  700, 20, 77, 96, 1345 137 -> 128;  1800, 900, 40, 124, 1000 201 -> 202.
+// Everything between phi and the matrix gradients in k_transr_project_units?  Wherever it can be.  us per step, launches of their own ->
+// units (b, g, k, D, relations)  1024, 128, 256, 100, 1345 244 -> 193;  D 128 280 -> 223;  D 64 150 -> 112;  k 500, D 32 148 -> 122;  20 relations
+// 145 -> 130;  1024, 256, 640, 100, 1345 491 -> 330;  1024, 1024, 16, 100, 20 137 -> 102;  2000, 16, 8, 128, 1345 255 -> 253.  The only shapes found
+// where launches of their own are faster have rows of more than 96 floats, few corrupting rows, chunks of up to 128 and some ten positives
+// per relation and chunk, whose units a single wave per SIMD works through: 1024, 128, 8, 128, 5 98.6 -> 102.5;  16, 128, 10 95.8 -> 98.6;  32, 128, 20
+// 98.6 -> 101.0;  16, 100, 20 89.5 -> 90.5;  64, 100, 20 97.2 -> 96.2;  512, 64, 16, 128, 4 84.8 -> 88.7, k 40 99.9 -> 92.9.
 bool in_units(const kge_ctx* c, bool form_w) { return form_w && c->cfg.ent_dim <= BN; }
+// Corrupting rows per workgroup: 128, two waves per SIMD, which is what fills the chip; 64, one wave per SIMD, where the units are so few that
+// half as many rows still leave no workgroup to a second round.  (us per step, 128 -> 64: 1024, 1024, 72, 128, 5 132 -> 119;  1024, 128, 100, 128, 5 127 ->
+// 114, launches of their own 111;  256, 256, 256, 64, 20 71.6 -> 67.3;  32 and 16 rows: no change.)
+int unit_rows(const TransrArgs& a) {
+    return (int64_t)(a.b / a.g) * a.max_pblocks * ((a.k + UROWS / 2 - 1) / (UROWS / 2)) <= KGE_TRANSR_UNIT_WGS ? UROWS / 2 : UROWS;
+}
 // Ranges of a chunk's units.  A workgroup has a CU to itself (rows of up to 32 floats: half of one), so a grid of a few workgroups
 // more than the chip holds takes twice the time: of the numbers that fill one to eight rounds, the one whose rounds times (units of a
 // range, and one for its start and its gradient rows) is least.  Units per chunk are known on the device only; two thirds of the most
@@ -1233,7 +1243,7 @@ bool in_units(const kge_ctx* c, bool form_w) { return form_w && c->cfg.ent_dim <
 // 256, 640, 100, 1345 425 -> 330 (260 workgroups -> 240);  1024, 128, 300, 100 274 -> 238;  1000, 200, 700, 100 472 -> 370;  1040, 16, 256, 100
 // 333 -> 301 (260 -> 390);  1600, 50, 640, 32 241 -> 215;  1000, 1000, 200, 32 78.1 -> 81.3 (256 -> 512).
 int unit_segments(const TransrArgs& a) {
-    const int64_t chunks = a.b / a.g, base = chunks * ((a.k + UROWS - 1) / UROWS), slots = a.D <= 32 ? 2 * KGE_TRANSR_UNIT_WGS : KGE_TRANSR_UNIT_WGS;
+    const int64_t chunks = a.b / a.g, base = chunks * ((a.k + a.unit_rows - 1) / a.unit_rows), slots = a.D <= 32 ? 2 * KGE_TRANSR_UNIT_WGS : KGE_TRANSR_UNIT_WGS;
     const int64_t rows = chunks * a.k, room = (rows + (chunks + KGE_TRANSR_BACK_WGS) * BM) / rows;  // (kge_transr_back_floats)
     const int64_t most = room < a.max_pblocks ? room : a.max_pblocks;
     auto cost = [&](int64_t s) { return (double)((base * s + slots - 1) / slots) * (1. + 0.65 * a.max_pblocks / (double)s); };
@@ -1289,10 +1299,11 @@ int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, in
         const int chunks = ids.b / gsz;
         float* rows = a.Gent + (int64_t)2 * ids.b * a.D;
         const int64_t stride = (int64_t)chunks * k * a.D;
+        a.unit_rows = unit_rows(a);
         a.segments = unit_segments(a);
         c->neg_partial = {c->tr_back_part, rows, a.segments, stride, stride / 4};
         if (a.segments == 1) a.back_part = rows;
-        const int wgs = chunks * ((k + UROWS - 1) / UROWS) * a.segments;
+        const int wgs = chunks * ((k + a.unit_rows - 1) / a.unit_rows) * a.segments;
 #define L(NT) KGE_LAUNCH(c, k_transr_project_units<NT>, dim3(wgs), dim3(UT), 0, st, a)
         KGE_BY_COLUMNS(a.D, L);
 #undef L

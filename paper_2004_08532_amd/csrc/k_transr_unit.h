@@ -1,7 +1,7 @@
 // TransR training steps with W formed on the way (uniform weights, logistic loss), rows of up to 128 floats: everything between the
 // positives' o and p and the matrix gradients in one pass over the units, the blocks of up to 32 positives of an item.
 //
-// A workgroup of eight waves owns 128 corrupting rows of a chunk and a range of its units.  The rows, split into three bf16
+// A workgroup of eight waves owns 128 corrupting rows of a chunk (64 where units are few) and a range of its units.  The rows, split into three bf16
 // parts (k_split.h), stay in registers (16 rows per wave) for all of its units, and so do the gradient rows it adds up.  Per unit:
 //   M in three parts to LDS;  P = N M^T, scores, W, V = sum 2 W (o - P), parts of dL/do (a row per positive and wave);
 //   gradient rows += V M, with M read from LDS transposed; V goes through LDS to become the left operand
@@ -16,7 +16,7 @@
 
 namespace {
 
-constexpr int UT = 512, UROWS = 128;  // threads, corrupting rows per workgroup
+constexpr int UT = 512, UROWS = 128;  // threads, most corrupting rows per workgroup
 constexpr int UVP = 68;               // pitch of the staged V: 16-byte reads of sixteen rows free of conflicts
 
 // How a chunk's units are dealt to the workgroups: by their cost, a unit's two products (22,000 cycles) against what a positive adds.
@@ -76,9 +76,9 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
     __shared__ int cut[2];
     __shared__ float part[8];
     const int D = a.D, tid = threadIdx.x, w = tid >> 6, lane = tid & 63, l16 = lane & 15, quad = lane >> 4;
-    const int tiles = (a.k + UROWS - 1) / UROWS;
+    const int tiles = (a.k + a.unit_rows - 1) / a.unit_rows;
     const int seg = blockIdx.x % a.segments, tile = blockIdx.x / a.segments % tiles, c = blockIdx.x / a.segments / tiles;
-    const int j0 = tile * UROWS, rows = min(UROWS, a.k - j0);
+    const int j0 = tile * a.unit_rows, rows = min(a.unit_rows, a.k - j0);
     const bool active = 16 * w < rows;
     const TransrBlock* units = a.q.pblocks + (int64_t)c * a.max_pblocks;
 
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
 #pragma unroll
                 for (int h = 0; h < CG; ++h) acc[h] = doublex4{0., 0., 0., 0.};
                 const int col = 16 * c0 + lane;
-                float* go = a.GOp + ((int64_t)(tile * 8 + w) * a.b + u.off) * D + col;
+                float* go = a.GOp + ((int64_t)(j0 / 16 + w) * a.b + u.off) * D + col;
 #pragma unroll 1
                 for (int m = 0; m < n; ++m) {
                     const float4 ww = ld4(W2 + 16 * m + 4 * quad);

@@ -1137,7 +1137,9 @@ def test_train_steps_at_the_lengths_where_the_launch_schedule_changes(kge, n_ste
 # TransR steps with W formed on the way: corrupting rows around the 16 of a wave and the 128 of a workgroup, blocks of more positives
 # than one, rows around the K steps of 32 and the column tiles of 16, more ranges than a chunk has blocks
 TRANSR_UNITS = {"rows-1": (64, 64, 1, 20, 3), "rows-15": (96, 32, 15, 68, 40), "rows-129": (140, 70, 129, 100, 5), "rows-257": (66, 33, 257, 128, 2),
-                "one-relation": (140, 140, 70, 36, 1), "wide-chunk": (400, 400, 130, 84, 300), "short-rows": (48, 24, 40, 4, 7)}
+                "one-relation": (140, 140, 70, 36, 1), "wide-chunk": (400, 400, 130, 84, 300), "short-rows": (48, 24, 40, 4, 7),
+                # few units: 64 rows per workgroup; many: 128
+                "few-65": (64, 32, 65, 48, 3), "few-193": (64, 64, 193, 116, 4), "many-129": (300, 100, 129, 100, 200), "many-257": (200, 50, 257, 128, 100)}
 
 
 @pytest.mark.parametrize("side", ["tail", "head"])

@@ -192,24 +192,29 @@ print(json.dumps([codes, rows, rec.hipGetLastError()]))
     assert (first == second) == (k == later), (first, second)
 
 
-# (b, g, k, D, relations) whose (chunk, 128 corrupting rows) pairs are 24, 6, 20, 104, 130, 300 and 2
-@pytest.mark.parametrize("b,g,k,D,relations", [(1024, 128, 300, 100, 1345), (800, 400, 300, 64, 60), (1024, 256, 640, 128, 1345),
-                                               (1300, 100, 1000, 100, 1345), (1040, 16, 256, 100, 1345), (1300, 13, 300, 48, 1345),
-                                               (1000, 1000, 200, 32, 1345), (1024, 128, 256, 4, 2), (3, 1, 1, 4, 2)])
-def test_ranges_of_transr_units_fill_the_chip(recorder, b, g, k, D, relations):
+# (b, g, k, D, relations, rows per workgroup) whose (chunk, rows) pairs are 24, 6, 20, 104, 130, 300 and 2, and few units: the last
+# shape has more workgroups of 64 rows than the chip holds at a time, the one in front of it just as many
+@pytest.mark.parametrize("b,g,k,D,relations,rows", [
+    (1024, 128, 300, 100, 1345, 128), (800, 400, 300, 64, 60, 128), (1024, 256, 640, 128, 1345, 128), (1300, 100, 1000, 100, 1345, 128),
+    (1040, 16, 256, 100, 1345, 128), (1300, 13, 300, 48, 1345, 128), (1000, 1000, 200, 32, 1345, 128), (1024, 128, 256, 4, 2, 64),
+    (3, 1, 1, 4, 2, 64), (64, 32, 1024, 100, 7, 64), (512, 16, 128, 100, 4, 64), (528, 16, 128, 100, 4, 128)])
+def test_ranges_of_transr_units_fill_the_chip(recorder, b, g, k, D, relations, rows):
     """No grid whose last round of workgroups is a small part of the chip, and no more partial rows than there is room for."""
     rc, events = drive(recorder, f'''
 print(json.dumps(Library("transr", b={b}, g={g}, k={k}, D={D}, relations={relations}).steps(1)))
 ''')
-    assert rc == 0
-    wgs, = (int(e.split()[3]) for e in events if "k_transr_project_units" in e)
-    base, slots = b // g * -(-k // 128), 512 if D <= 32 else 256
+    events = [e for e in events if "k_transr_project_units" in e]
+    assert rc == 0 and (len(events) == 1 if k <= 1024 else not events)
+    if not events:
+        return
+    wgs = int(events[0].split()[3])
+    base, slots, most = b // g * -(-k // rows), 512 if D <= 32 else 256, min(g, relations) + g // 32
     segments = wgs // base
-    assert wgs == base * segments and 1 <= segments <= min(g, relations) + g // 32
+    assert wgs == base * segments and 1 <= segments <= most
     assert segments * (b // g) * k <= b // g * k + (b // g + 768) * 64
     if wgs > slots:
         assert wgs / (-(-wgs // slots) * slots) > 0.75, (wgs, slots)
-    elif segments < min(g, relations) + g // 32:
+    elif segments < most:
         assert wgs > 0.75 * slots, (wgs, slots)
 
 
