@@ -39,6 +39,7 @@
 
 #include "k_gemm_shared.h"
 #include "k_transr_items.h"
+#include "k_weights.h"
 
 namespace {
 
@@ -1208,7 +1209,7 @@ TransrArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& 
     a.gamma = gamma; a.wk = 1.f / ((float)(k > 0 ? k : 1) * (float)ids.b);
     a.out_w = 0; a.train = 1; a.segments = 1; a.units = 0; a.unit_rows = UROWS;
     a.q = c->tr_groups;
-    a.O = c->O; a.PP = c->PP; a.P = c->P3; a.V = c->P3 + (int64_t)c->cfg.max_batch * c->cfg.max_neg_per_chunk * D;
+    a.O = c->O; a.PP = c->PP; a.P = c->P3; a.V = c->P3 + kge_transr_p_floats(c->cfg);
     a.N = c->Nst; a.S = c->S; a.GO = c->GO; a.GOp = c->tr_go_part;
     a.fpos = c->fpos; a.pos_out = nullptr; a.cpos = c->cpos; a.row_loss = c->row_loss; a.loss_part = c->neg_loss_part;
     a.Gent = c->Gent; a.Gr = c->Grel; a.GM = c->Grel + (int64_t)c->cfg.max_batch * D;
@@ -1229,7 +1230,8 @@ int back_segments(const TransrArgs& a) {
 // where launches of their own are faster have rows of more than 96 floats, few corrupting rows, chunks of up to 128 and some ten positives
 // per relation and chunk, whose units a single wave per SIMD works through: 1024, 128, 8, 128, 5 98.6 -> 102.5;  16, 128, 10 95.8 -> 98.6;  32, 128, 20
 // 98.6 -> 101.0;  16, 100, 20 89.5 -> 90.5;  64, 100, 20 97.2 -> 96.2;  512, 64, 16, 128, 4 84.8 -> 88.7, k 40 99.9 -> 92.9.
-bool in_units(const kge_ctx* c, bool form_w) { return form_w && c->cfg.ent_dim <= BN; }
+bool may_take_units(const kge_config& cfg) { return cfg.adv_temperature == 0.f && cfg.loss == KGE_LOSS_LOGISTIC && cfg.ent_dim <= BN; }
+bool in_units(const kge_ctx* c, bool form_w) { return form_w && may_take_units(c->cfg); }
 // Corrupting rows per workgroup: 128, two waves per SIMD, which is what fills the chip; 64, one wave per SIMD, where the units are so few that
 // half as many rows still leave no workgroup to a second round.  (us per step, 128 -> 64: 1024, 1024, 72, 128, 5 132 -> 119;  1024, 128, 100, 128, 5 127 ->
 // 114, launches of their own 111;  256, 256, 256, 64, 20 71.6 -> 67.3;  32 and 16 rows: no change.)
@@ -1390,5 +1392,10 @@ size_t kge_transr_back_floats(const kge_config& cfg) {
     return (NR + (size_t)cfg.max_chunks * BM + (size_t)KGE_TRANSR_BACK_WGS * BM) * D;
 }
 size_t kge_transr_go_floats(const kge_config& cfg) {
-    return (size_t)cfg.max_batch * cfg.ent_dim * ((size_t)cfg.max_neg_per_chunk / (cfg.ent_dim <= BN ? 16 : BM) + 1);
+    const size_t K = cfg.max_neg_per_chunk, in_units = (K < KGE_SHORT_SCORES ? K : KGE_SHORT_SCORES) / 16 + 1, parts = K / BM + 1;
+    return (size_t)cfg.max_batch * cfg.ent_dim * (may_take_units(cfg) && in_units > parts ? in_units : parts);
+}
+// and of the projections that training steps keep: none where all of them run in units
+size_t kge_transr_p_floats(const kge_config& cfg) {
+    return may_take_units(cfg) && cfg.max_neg_per_chunk <= KGE_SHORT_SCORES ? 0 : (size_t)cfg.max_batch * cfg.max_neg_per_chunk * cfg.ent_dim;
 }

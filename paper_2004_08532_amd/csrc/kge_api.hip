@@ -501,7 +501,7 @@ int kge_create(const kge_config* cfg, kge_ctx** out) {
     const size_t sets_cap = 8 * NR * D > (size_t)64 << 20 ? 8 * NR * D : (size_t)64 << 20;
     sets_n = sets_n < sets_cap ? sets_n : sets_cap;
     const size_t o_ppo = take(pair_model ? KGE_PAIR_MAX_PARTS * B * D * 4 : 0), o_ppn = take(pair_model ? sets_n * 4 : 0);
-    const size_t o_P3 = take(transr ? 2 * B * K1 * D * 4 : 0);
+    const size_t o_P3 = take(transr ? (kge_transr_p_floats(*cfg) + B * K1 * D) * 4 : 0);
     const size_t o_tgo = take(transr ? kge_transr_go_floats(*cfg) * 4 : 0);
     const size_t o_rr = take(m == KGE_RESCAL ? kge_rescal_runs_bytes(*cfg) : 0);
     const size_t o_tbp = take(transr ? kge_transr_back_floats(*cfg) * 4 : 0);

@@ -73,7 +73,7 @@ struct kge_ctx {
     int ld_bf;       // D rounded up to 64 (rows of whole 128-byte lines)
     float* S;        // [max_batch x ld_s]   negative scores, then backward coefficients W
     float* PP;       // TransR: [max_batch x D] p_i = M_i c_i
-    float* P3;       // TransR: [max_batch x max_neg_per_chunk x D] projections of the corrupting rows; the same of dL/dP
+    float* P3;       // TransR: [max_batch x max_neg_per_chunk x D] projections of the corrupting rows (where steps keep them); the same of dL/dP
     TransrGroups tr_groups;
     float* tr_go_part;    // TransR: partial sums of dL/do
     float* tr_back_part;  //         partial gradient rows of the corrupting entities
@@ -254,6 +254,7 @@ constexpr int KGE_TRANSR_BACK_WGS = 768, KGE_TRANSR_UNIT_WGS = 256;  // three pe
 size_t kge_transr_carve_groups(const kge_config& cfg, char* base, TransrGroups* q);
 size_t kge_transr_back_floats(const kge_config& cfg);
 size_t kge_transr_go_floats(const kge_config& cfg);
+size_t kge_transr_p_floats(const kge_config& cfg);
 void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int g, float gamma, float* pos_out,
                     bool train, hipStream_t st);
 // train: keep the projections, rows in the order of the members; form_w: store W = dL/df- instead of the scores, returns the number of loss sums left

@@ -295,3 +295,13 @@ def test_workspace_holds_the_partial_rows_that_a_step_can_write(recorder, model,
 print(json.dumps(lib.kge_workspace_bytes(Library({model!r}, b={b}, g={g}, k={k}, D={D}).ctx)))
 ''')
     assert size < most
+
+
+@pytest.mark.parametrize("options,mega", [("", 675), ("adv_temperature=1.0, ", 1187), ("loss=1, ", 1187), ("D=132, ", 1226)])
+def test_transr_workspace_holds_what_its_steps_keep(recorder, options, mega):
+    """b 1024, k 1024, D 128: V takes 537 MB.  Projections (as much again) only where there are steps that keep them; the gradients of
+    the positives in parts of 16 rows (35 MB) only where a step writes such parts, of 64 rows (9 MB) elsewhere."""
+    size = drive(recorder, f'''
+print(json.dumps(lib.kge_workspace_bytes(Library("transr", b=1024, g=1024, k=1024, **dict(dict(D=128), **dict({options}))).ctx)))
+''')
+    assert 0.99 * mega < size / 1e6 < mega, size
