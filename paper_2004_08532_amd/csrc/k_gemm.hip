@@ -388,10 +388,15 @@ void set_tiling(GemmArgs& g, int chunks, bool coordinate_tiles = false) {
 //   filled ones              1024, 64, 1024, 400 29.4 -> 26.9;  2016, 63, 1000, 400 48.0 -> 42.6;  1008, 48, 1024, 200 25.2 -> 24.0; three quarters
 //                            of their 32 x 32 blocks inside the matrix 2016, 96, 1024, 400 42.4 -> 45.3, half 2048, 32, 1024, 400 64.9 ->
 //                            76.5; all, but half of the rows are not there 2013, 33, 800, 100 28.9 -> 31.3
-// kge_rank gains more (fewer atomics): 2040, 40, 1500, 64 54.9 -> 39.4, D 400 104 -> 95.6.
+//   whole rounds             a workgroup takes a CU; a few of them in the second or third round cost it for little: 1024, 1024, k, 400 k 1088 (272
+//                            workgroups) 28.7 -> 31.1, 1216 (304) 30.5 -> 31.4, 1280 (320) 31.8 -> 31.5, 1536 (384) 35.6 -> 32.5, 2112 (528) 41.7 -> 43.6, 2304
+//                            (576) 43.5 -> 43.6, 2560 (640) 45.1 -> 43.7; D 800 k 1088 42.3 -> 46.3, 1024 38.4 -> 34.0; training steps alike
+// kge_rank gains more (fewer atomics): 2040, 40, 1500, 64 54.9 -> 39.4, D 400 104 -> 95.6; 1024, 1024, 1088, 400 36.1 -> 34.5, D 800 47.2 -> 50.2.
 bool wide_tiles(const GemmArgs& g, int chunks) {
-    if (g.tiles < (g.out_mode == OUT_RANK || g.K > 128 ? 1024 : 1280)) return false;
-    const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) * chunks;
+    const bool rank = g.out_mode == OUT_RANK;
+    if (g.tiles < (rank || g.K > 128 ? 1024 : 1280)) return false;
+    const int64_t tiles = (int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) * chunks, over = tiles % 256;
+    if (over > 0 && over < 56 && (rank ? g.K > 512 && tiles < 512 : tiles < 768)) return false;
     return 8 * (int64_t)g.tiles >= 7 * 4 * tiles && 10 * (int64_t)g.M * g.N * chunks >= 6 * 64 * 64 * tiles;
 }
 

@@ -128,7 +128,8 @@ def test_bits_of_the_scores_of_positives_rescal(kge, D):
     assert np.array_equal(pos.cpu().numpy().view(np.int32), wave_sum(acc).view(np.int32))
 
 
-@pytest.mark.parametrize("b,k,D", [(1000, 1100, 400), (1025, 1057, 36), (1020, 1280, 132), (1060, 2049, 4)])
+# (336, 336, 320 and 578 tiles of 64 x 64; fewer than 320 of them, or 1280 of 32 x 32, would be scored on 32 x 32)
+@pytest.mark.parametrize("b,k,D", [(1000, 1300, 400), (1025, 1290, 36), (1020, 1280, 132), (1060, 2120, 4)])
 @pytest.mark.parametrize("model", ["transe_l2", "distmult", "complex"])
 def test_negative_scores_hang_on_the_pair_alone(kge, model, b, k, D):
     """One chunk is scored on tiles of 64 x 64, chunks of 20 (half of such tiles' rows would be missing) on tiles of 32 x 32: the
@@ -167,7 +168,7 @@ def test_training_steps_on_the_tiles_of_the_scores(kge, model, adv):
     from harness import configs
     from parity_util import Pair
     from test_gpu_parity import ragged, run_steps
-    w = ragged(model, n_entities=60_001, n_triples=20_000, batch=1020, chunk=340, neg_per_chunk=1050, ent_dim=140, rel_dim=140, steps=1,
+    w = ragged(model, n_entities=60_001, n_triples=20_000, batch=1020, chunk=340, neg_per_chunk=1100, ent_dim=140, rel_dim=140, steps=1,
                adv_temperature=adv)
     p = Pair(w, kge)
     try:

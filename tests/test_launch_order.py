@@ -261,6 +261,31 @@ print(json.dumps(Library("transe_l2", b={b}, g={g}, k={k}, D=400, {loss}).steps(
     assert any("k_gemm_fwd" in e for e in events) != split
 
 
+# (b, g, k, D) and whether scores, ranks and training steps take tiles of 64 x 64: 1024 tiles of 32 x 32 (1280 for scores of short rows), tiles
+# that are filled, no few workgroups past the first or second 256
+WIDE = [(1000, 1000, 1024, 400, 1, 1, 1), (1000, 1000, 1023, 400, 1, 1, 1), (992, 992, 1024, 400, 0, 0, 0), (1024, 1024, 1025, 400, 0, 1, 0),
+        (1024, 1024, 1216, 400, 0, 1, 0), (1024, 1024, 1280, 400, 1, 1, 1), (1024, 1024, 1088, 800, 0, 0, 0), (1024, 1024, 1280, 800, 1, 1, 1),
+        (1024, 1024, 1088, 128, 0, 1, 0), (1024, 1024, 1280, 128, 1, 1, 1), (1024, 1024, 2112, 400, 0, 1, None), (1024, 1024, 2112, 800, 0, 1, None),
+        (1024, 1024, 2304, 400, 1, 1, None), (1024, 1024, 3136, 400, 1, 1, None), (2016, 96, 1024, 400, 0, 0, None), (2013, 33, 800, 100, 0, 0, None)]
+
+
+@pytest.mark.parametrize("b,g,k,D,score,rank,step", WIDE)
+def test_wide_tiles_where_they_fill_the_chip(recorder, b, g, k, D, score, rank, step):
+    got = drive(recorder, f'''
+lib.kge_score.argtypes = [vp] * 6 + [i64, vp, i64, i64, i32, f32, vp, vp, vp]
+lib.kge_rank.argtypes = [vp] * 6 + [i64, vp, i64, i64, i32, f32, vp, vp]
+x, p, got = Library("distmult", b={b}, g={g}, k={k}, D={D}, adv_temperature=1.0), 4096, []
+for name, outputs in (("kge_score", 2), ("kge_rank", 1)):
+    rec.recorder_clear()
+    assert getattr(lib, name)(x.ctx, p, p, p, p, p, x.b, p, x.k, x.g, 0, 12.0, p, *[p] * outputs) == 0
+    got.append(rec.recorder_events().decode())
+got.append("\\n".join(x.steps(1)[1]))
+print(json.dumps([["k_gemm_fwd_wide" in e, "k_gemm_fwd" in e, "k_gemm_split_fwd" in e] for e in got]))
+''')
+    assert got[:2] == [[bool(score), True, False], [bool(rank), True, False]]
+    assert got[2] == ([False, False, True] if step is None else [bool(step), True, False])
+
+
 # chunks of one positive, steps launched one by one: (model, b, k, D) and whether the keys are sorted beside k_ind, with a fork
 # and a join: more positives than the chip holds workgroups of k_ind, and enough work
 @pytest.mark.parametrize("model,b,k,D,beside", [
