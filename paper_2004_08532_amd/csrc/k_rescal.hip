@@ -342,8 +342,10 @@ static_assert(RUNS_LDS >= PT / 64 * LT * LT + PT, "long runs share the memory");
 // four tiles per wave 62 us, with 64 columns per workgroup 66, with 64 registers (spills) 72, as workgroups that stay 75.
 // A wave takes tiles of 16 x; lane (q, l) holds n = 2 l + c, x = 4 q + i of each, which is the layout of a B operand of
 // v_mfma_f32_16x16x4_f32 for the first product (k = q, instruction i) and that of the result of the second (row 4 q + i, column l).
-template <bool HEAD, bool UPDATE, bool STREAM>
-__device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, const StepView& sv, uint32_t key, int p, int m, int slab, float* lds) {
+// ids_of(j, m, i, hid, tl, cp): position in the mini-batch, entities and dL/df+ of the j-th of m positives for lanes 0 .. 31, of the next one for
+// the others (where there is none: something valid).
+template <bool HEAD, bool UPDATE, bool STREAM, class Ids>
+__device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, Ids ids_of, uint32_t key, int m, int slab, float* lds) {
     const RescalArgs& r = a.chain;
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l = lane & 15, q = lane >> 4, D = a.D;
     const int n0 = slab * KEPT, n = n0 + 2 * l, per = ((D + 15) / 16 + PT / 64 - 1) / (PT / 64), x0 = 16 * w * per;
@@ -383,22 +385,13 @@ __device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, const St
     for (int t = 0; UPDATE && t < RUN_TILES; ++t)
         if (t < per) S[t] = load(St, t);
 
-    // a wave stages two positives, 32 lanes each; their ids are the same for the whole wave (scalar loads, which do not wait
-    // for the matrix)
+    // a wave stages two positives, 32 lanes each
     const int j = 2 * w + (lane >> 5), s32 = lane & 31;
     const bool live = j < m;
     int64_t i = 0, hid = 0, tl = 0;
     float cp = 0.f;
     if (2 * w < m) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int ju = 2 * w + u < m ? 2 * w + u : 2 * w;
-            const int64_t iu = __builtin_amdgcn_readfirstlane(a.pos[p + ju]);
-            const int64_t hu = clamp_id(sv.h[iu], r.n_ent), tu = clamp_id(sv.t[iu], r.n_ent);
-            const float cu = r.cpos[iu];
-            const bool mine = lane >> 5 == u;
-            i = mine ? iu : i; hid = mine ? hu : hid; tl = mine ? tu : tl; cp = mine ? cu : cp;
-        }
+        ids_of(2 * w, m, i, hid, tl, cp);
         const float* pa = r.E + (HEAD ? tl : hid) * (int64_t)D;
         const float* pc = r.E + (HEAD ? hid : tl) * (int64_t)D;
         float4 g4[2], c4[2];
@@ -508,11 +501,10 @@ __device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, const St
     }
 }
 
-template <bool UPDATE, bool STREAM>
-__device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, uint32_t key, int p, int m, int slab, float* lds) {
-    const StepView sv = step_view(a.chain.ids);
-    if (sv.side == KGE_NEG_HEAD) rescal_run_part<true, UPDATE, STREAM>(a, sv, key, p, m, slab, lds);
-    else rescal_run_part<false, UPDATE, STREAM>(a, sv, key, p, m, slab, lds);
+template <bool UPDATE, bool STREAM, class Ids>
+__device__ __forceinline__ void rescal_run_part(const RescalUpdArgs& a, int side, Ids ids_of, uint32_t key, int m, int slab, float* lds) {
+    if (side == KGE_NEG_HEAD) rescal_run_part<true, UPDATE, STREAM>(a, ids_of, key, m, slab, lds);
+    else rescal_run_part<false, UPDATE, STREAM>(a, ids_of, key, m, slab, lds);
 }
 
 // The runs of equal keys, in sorted order, long and short ones in lists of their own.
@@ -554,8 +546,11 @@ __device__ __forceinline__ void list_runs(const uint32_t* key, int n, RescalRuns
     if (tid < 2) out->count[tid] = count[tid];
 }
 
-// The chain rule of the long runs: workgroups of (16 sorted positions, slab), which hold positives of two long runs at most, behind
-// one that lists the runs for the launch after this.
+// The chain rule of the long runs: workgroups of (16 sorted positions, first or second long run among them, slab), behind one that lists the
+// runs for the launch after this.  Few and short for steps of few relations, whose time is that of one workgroup: key -> position -> ids -> rows.
+// Positions and ids are asked for beside the keys, and a second run does not wait for the first.  us per step, head corrupted, the chain rule
+// per positive -> one workgroup for both runs, ids after the keys -> this (b, k, D, relations):  76, 16, 160, 3 37.8 -> 41.1 -> 37.6;  312, 240, 148, 3
+// 42.6 -> 44.7 -> 41.1;  512, 64, 200, 3 49.2 -> 49.6 -> 47.7;  1024, 256, 256, 3 80.6 -> 69.5 -> 68.8.
 __global__ __launch_bounds__(PT) void k_rescal_chain_runs(RescalUpdArgs a) {
     __shared__ __attribute__((aligned(16))) float lds[RUNS_LDS];
     const int slabs = (a.D + KEPT - 1) / KEPT, wg = flat_block() - 1;
@@ -563,19 +558,29 @@ __global__ __launch_bounds__(PT) void k_rescal_chain_runs(RescalUpdArgs a) {
         list_runs(a.key, a.n, a.runs, lds);
         return;
     }
-    const int b0 = wg / slabs * LONG_RUN, slab = wg % slabs;
+    const int b0 = wg / (2 * slabs) * LONG_RUN, slab = wg % slabs;
+    int others = wg / slabs % 2;  // long runs that come before this workgroup's
     if (b0 >= a.n) return;
     // lane t: position b0 + t - 16, those of the 16 and 16 on either side
     const int lane = threadIdx.x & 63, e = b0 + lane - LONG_RUN;
     const bool in = e >= 0 && e < a.n && lane < 3 * LONG_RUN;
     const uint32_t mine = a.key[in ? e : 0];
+    // lane t: ids of position b0 + t, asked for beside the keys
+    const StepView sv = step_view(a.chain.ids);
+    const RescalArgs& r = a.chain;
+    const uint32_t pos = a.pos[min(b0 + (lane & (LONG_RUN - 1)), a.n - 1)];
+    const uint32_t hid = (uint32_t)clamp_id(sv.h[pos], r.n_ent), tl = (uint32_t)clamp_id(sv.t[pos], r.n_ent);
+    const float cp = r.cpos[pos];
     for (int s = 0; s < LONG_RUN && b0 + s < a.n;) {
         const uint32_t key = __builtin_amdgcn_readlane(mine, LONG_RUN + s);
         const unsigned long long eq = __ballot(in && mine == key);
         const int m = __builtin_ctzll(~(eq >> (LONG_RUN + s))), here = min(m, LONG_RUN - s);
-        if (__popcll(eq) >= LONG_RUN) {
-            __syncthreads();  // (the part before is done with the LDS)
-            rescal_run_part<false, false>(a, key, b0 + s, here, slab, lds);
+        if (__popcll(eq) >= LONG_RUN && others-- == 0) {
+            rescal_run_part<false, false>(a, sv.side, [&](int j, int m, int64_t& i, int64_t& h, int64_t& t, float& c) {
+                const int from = s + min(j + (lane >> 5), m - 1);
+                i = __shfl((int)pos, from, 64); h = (uint32_t)__shfl((int)hid, from, 64); t = (uint32_t)__shfl((int)tl, from, 64); c = __shfl(cp, from, 64);
+            }, key, here, slab, lds);
+            return;
         }
         s += here;
     }
@@ -606,7 +611,18 @@ __global__ __launch_bounds__(PT, 6) void k_rescal_runs(RescalUpdArgs a) {
     const int q = 8 * eight + (in & 7), slab = in >> 3;
     if (q >= a.runs->count[0]) return;
     const RescalRun run = list[q];
-    rescal_run_part<true, STREAM>(a, run.key, run.first, run.n, slab, lds);
+    const StepView sv = step_view(a.chain.ids);
+    rescal_run_part<true, STREAM>(a, sv.side, [&](int j, int m, int64_t& i, int64_t& h, int64_t& t, float& c) {
+        // (the same for the whole wave: scalar loads, which do not wait for the matrix)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int64_t iu = __builtin_amdgcn_readfirstlane(a.pos[run.first + min(j + u, m - 1)]);
+            const int64_t hu = clamp_id(sv.h[iu], a.chain.n_ent), tu = clamp_id(sv.t[iu], a.chain.n_ent);
+            const float cu = a.chain.cpos[iu];
+            const bool mine = (threadIdx.x >> 5 & 1) == u;
+            i = mine ? iu : i; h = mine ? hu : h; t = mine ? tu : t; c = mine ? cu : c;
+        }
+    }, run.key, run.n, slab, lds);
 }
 
 RescalArgs make_args(kge_ctx* c, const float* E, const float* R, const StepIds& ids) {
@@ -649,7 +665,7 @@ RescalUpdArgs make_update_args(kge_ctx* c, const float* E, float* R, float* SR, 
 void kge_launch_rescal_chain(kge_ctx* c, const float* E, float* R, const StepIds& ids, bool ordered, hipStream_t st) {
     if (kge_rescal_chain_by_runs(c)) {
         const int64_t slabs = (c->cfg.ent_dim + KEPT - 1) / KEPT;
-        KGE_LAUNCH(c, k_rescal_chain_runs, flat_grid(1 + (ids.b + LONG_RUN - 1) / LONG_RUN * slabs), dim3(PT), 0, st,
+        KGE_LAUNCH(c, k_rescal_chain_runs, flat_grid(1 + (ids.b + LONG_RUN - 1) / LONG_RUN * 2 * slabs), dim3(PT), 0, st,
                    make_update_args(c, E, R, nullptr, ids, 0.f));
         return;
     }
