@@ -36,17 +36,21 @@ __device__ __forceinline__ void wave_fence() {  // LDS traffic of one wave
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 // Sums over the four quarters of a wave of four values; quarter q gets that of value q (vector ALU swaps, no LDS)
-__device__ __forceinline__ double sum_quads(const double (&x)[4]) {
-    auto low = [](double v) { return (uint32_t)__builtin_bit_cast(uint64_t, v); };
-    auto high = [](double v) { return (uint32_t)(__builtin_bit_cast(uint64_t, v) >> 32); };
-    auto of = [](uint32_t lo, uint32_t hi) { return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo); };
-    auto halves = [&](double a, double b) {  // lanes 0 .. 31: of a, the others: of b
-        const auto l = __builtin_amdgcn_permlane32_swap(low(a), low(b), false, false), h = __builtin_amdgcn_permlane32_swap(high(a), high(b), false, false);
-        return of(l[0], h[0]) + of(l[1], h[1]);
+template <class T>
+__device__ __forceinline__ T sum_quads(const T (&x)[4]) {
+    struct Words { uint32_t w[sizeof(T) / 4]; };
+    auto exchanged = [](T a, T b, auto swap) {  // a and b with what swap exchanges of them, added
+        Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
+#pragma unroll
+        for (size_t i = 0; i < sizeof(T) / 4; ++i) {
+            const auto r = swap(u.w[i], v.w[i]);
+            u.w[i] = r[0]; v.w[i] = r[1];
+        }
+        return __builtin_bit_cast(T, u) + __builtin_bit_cast(T, v);
     };
-    const double a = halves(x[0], x[2]), b = halves(x[1], x[3]);
-    const auto l = __builtin_amdgcn_permlane16_swap(low(a), low(b), false, false), h = __builtin_amdgcn_permlane16_swap(high(a), high(b), false, false);
-    return of(l[0], h[0]) + of(l[1], h[1]);
+    auto halves = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_permlane32_swap(a, b, false, false); };
+    auto rows = [](uint32_t a, uint32_t b) { return __builtin_amdgcn_permlane16_swap(a, b, false, false); };
+    return exchanged(exchanged(x[0], x[2], halves), exchanged(x[1], x[3], halves), rows);
 }
 
 // The units of range `seg` of a chunk: cut[0] .. cut[1] - 1, for every thread behind the next barrier.  Returns the chunk's number of units.
@@ -244,42 +248,46 @@ __global__ __launch_bounds__(UT) void k_transr_project_units(TransrArgs a) {
                 W2[16 * (m0 + x4) + 4 * quad + q4] = w2;
             }
             wave_fence();
-            // V and this wave's part of dL/do, four column tiles at a time (all of them at once: 62 spills at D 100): products
-            // and sums over positives and rows in 64 bits.  (Sums in 32 bits leave 1.5 roundings in V of 32 positives, these 0.5; same
-            // time.)  Of the sums over rows every quarter of the wave gets those of one tile.
-            constexpr int CG = 4;
+            // V and this wave's part of dL/do, four column tiles at a time, which leaves 64-bit sums the registers.  Of the sums over rows
+            // every quarter of the wave gets those of one tile.
             static_assert(16 * PB <= 16 * UVP, "W where V is staged");
+            auto v_and_go = [&](auto zero) {
+                typedef decltype(zero) Sum;
+                typedef Sum Sumx4 __attribute__((ext_vector_type(4)));
 #pragma unroll
-            for (int c0 = 0; c0 < NT; c0 += CG) {
-                doublex4 acc[CG];
-#pragma unroll
-                for (int h = 0; h < CG; ++h) acc[h] = doublex4{0., 0., 0., 0.};
-                const int col = 16 * c0 + lane;
-                float* go = a.GOp + ((int64_t)(j0 / 16 + w) * a.b + u.off) * D + col;
+                for (int c0 = 0; c0 < NT; c0 += 4) {
+                    Sumx4 acc[4] = {};
+                    const int col = 16 * c0 + lane;
+                    float* go = a.GOp + ((int64_t)(j0 / 16 + w) * a.b + u.off) * D + col;
 #pragma unroll 1
-                for (int m = 0; m < n; ++m) {
-                    const float4 ww = ld4(W2 + 16 * m + 4 * quad);
-                    const double wd[4] = {ww.x, ww.y, ww.z, ww.w};
-                    const float* po = Os + m * W + 16 * c0 + l16;
-                    double g[CG] = {};
+                    for (int m = 0; m < n; ++m) {
+                        const float4 ww = ld4(W2 + 16 * m + 4 * quad);
+                        const Sum ws[4] = {ww.x, ww.y, ww.z, ww.w};
+                        const float* po = Os + m * W + 16 * c0 + l16;
+                        Sum g[4] = {};
 #pragma unroll
-                    for (int h = 0; h < CG; ++h) {
-                        if (c0 + h >= NT) break;
-                        const float o = po[16 * h];
+                        for (int h = 0; h < 4; ++h) {
+                            if (c0 + h >= NT) break;
+                            const float o = po[16 * h];
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const double d = o - p[c0 + h][v];  // (exact where o is close to P)
-                            acc[h][v] = fma(wd[v], d, acc[h][v]);
-                            g[h] = fma(-wd[v], d, g[h]);
+                            for (int v = 0; v < 4; ++v) {
+                                const Sum d = o - p[c0 + h][v];  // (a difference in 32 bits, exact where o is close to P)
+                                acc[h][v] = __builtin_elementwise_fma(ws[v], d, (Sum)acc[h][v]);
+                                g[h] = __builtin_elementwise_fma(-ws[v], d, g[h]);
+                            }
                         }
+                        const float x = (float)sum_quads(g);
+                        if (col < D) go[(int64_t)m * D] = x;
                     }
-                    const float x = (float)sum_quads(g);
-                    if (col < D) go[(int64_t)m * D] = x;
-                }
 #pragma unroll
-                for (int h = 0; h < CG; ++h)
-                    if (c0 + h < NT) vsum[c0 + h] = __builtin_convertvector(acc[h], floatx4);
-            }
+                    for (int h = 0; h < 4; ++h)
+                        if (c0 + h < NT) vsum[c0 + h] = __builtin_convertvector(acc[h], floatx4);
+                }
+            };
+            // items of many positives: products and sums in 64 bits, as k_transr_dp has them (32 positives in 32 bits: 1.5 roundings in V, in
+            // 64 bits 0.5; FB15k-sized 190 -> 194 us where that is done for every item)
+            if (u.all > DP_FEW) v_and_go(0.);
+            else v_and_go(0.f);
             wave_fence();
             float* V = a.V + ((int64_t)(c * a.g + e) * a.k + j0 + 16 * w + l16) * D + 8 * quad;
             const bool mine = 16 * w + l16 < rows;
