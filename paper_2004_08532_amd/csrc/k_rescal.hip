@@ -558,9 +558,9 @@ __global__ __launch_bounds__(PT) void k_rescal_chain_runs(RescalUpdArgs a) {
         list_runs(a.key, a.n, a.runs, lds);
         return;
     }
-    const int b0 = wg / (2 * slabs) * LONG_RUN, slab = wg % slabs;
-    int others = wg / slabs % 2;  // long runs that come before this workgroup's
-    if (b0 >= a.n) return;
+    const int blocks = (a.n + LONG_RUN - 1) / LONG_RUN, b0 = wg / slabs % blocks * LONG_RUN, slab = wg % slabs;
+    int others = wg / slabs / blocks;  // long runs that come before this workgroup's
+    if (others > 1) return;
     // lane t: position b0 + t - 16, those of the 16 and 16 on either side
     const int lane = threadIdx.x & 63, e = b0 + lane - LONG_RUN;
     const bool in = e >= 0 && e < a.n && lane < 3 * LONG_RUN;
