@@ -88,7 +88,8 @@ def algorithmic_work(w, h, r, t, neg, rowwise=False):
         "neg_score": {"flops": pair_fwd * b * k * coords if pair_fwd else 2.0 * b * k * D * (D if transr else 1)},
         "neg_backward": {"flops": pair_bwd * b * k * coords if pair_bwd else
                          (2.0 * b * k * D * D if transr else 4.0 * b * k * D)},
-        "chain": {"bytes": 4.0 * (8 * chain_b * D + chain_m * Dr) if rescal else 4.0 * (6 * b * D + 2 * b * Dr)},
+        # (TransR: o and p read, dL/do, dL/dp and the translation's gradient written)
+        "chain": {"bytes": 4.0 * 5 * b * D if transr else 4.0 * (8 * chain_b * D + chain_m * Dr) if rescal else 4.0 * (6 * b * D + 2 * b * Dr)},
         "loss": {"bytes": 8.0 * b * k},
         "sort": {"bytes": 8.0 * (n_keys + b)},
         "unique_entity_rows": float(ue), "unique_relation_rows": float(ur),
@@ -99,7 +100,8 @@ def kernel_report(w, ms, nsteps, work):
     """Average time of every kernel and what it achieves of the card's peaks.  In steps of few tiles the gather launch forms
     the negative scores too: it is then rated by its bytes and by the flops of the scoring product, the closer of the two to
     its peak first ("other" is the other one), and "neg_score", which has no launch of its own, carries the rate of the
-    product over that whole launch."""
+    product over that whole launch.  Where TransR forms scores and the negatives' gradient rows in one launch, timed as
+    "neg_score", that is rated by both products and "neg_backward" has neither time nor rate."""
     gemm = w.model in ("transe_l2", "distmult", "complex", "rescal", "transr")
     flop_peak = (BF16_MATRIX_PEAK_TFLOPS if w.bf16_inputs else FP32_MATRIX_PEAK_TFLOPS) if gemm else FP32_VECTOR_PEAK_TFLOPS
 
@@ -117,9 +119,12 @@ def kernel_report(w, ms, nsteps, work):
     avg_us = {name: 1e3 * total / max(nsteps, 1) for name, total in ms.items()}
     # (chunks of one positive have one kernel for scores and gradients, timed as neg_backward)
     merged = avg_us.get("neg_score") == 0 and avg_us.get("gather", 0) > 0 and w.chunk > 1
+    one_pass = w.model == "transr" and avg_us.get("neg_score", 0) > 0 and avg_us.get("neg_backward") == 0
     kernels = {}
     for name, us in avg_us.items():
         work_of = work.get(name, {})
+        if one_pass and name == "neg_score":
+            work_of = {"flops": work_of["flops"] + work["neg_backward"]["flops"]}
         if merged and name == "gather":
             work_of = {**work_of, **work["neg_score"]}
         found = rates(work_of, us)

@@ -41,3 +41,16 @@ def test_scoring_product_in_a_launch_of_its_own():
 def test_elementwise_models_are_rated_by_the_vector_units():
     _, work, k = report("medium", {"gather": 8.0, "neg_score": 14.8, "neg_backward": 29.0, "chain": 7.0, "update": 14.0})
     assert k["neg_score"]["bound"] == "alu" and k["neg_score"]["peak"] == bench.FP32_VECTOR_PEAK_TFLOPS
+
+
+@pytest.mark.parametrize("us", [{"neg_score": 75.0, "chain": 5.0}, {"neg_score": 60.0, "neg_backward": 65.0, "chain": 30.0}])
+def test_transr_products_in_one_launch_or_two(us):
+    w, _, k = report("small-transr", {"gather": 10.7, "update": 8.3, "phi": 16.6, "rel_update": 15.7, **us})
+    product = 2.0 * w.batch * w.neg_per_chunk * w.ent_dim ** 2
+    if "neg_backward" in us:
+        assert k["neg_backward"]["achieved"] == pytest.approx(product / 65e-6 / 1e12)
+        assert k["neg_score"]["achieved"] == pytest.approx(product / 60e-6 / 1e12)
+    else:
+        assert "achieved" not in k["neg_backward"]
+        assert k["neg_score"]["achieved"] == pytest.approx(2 * product / 75e-6 / 1e12)
+    assert k["chain"]["achieved"] == pytest.approx(20.0 * w.batch * w.ent_dim / us["chain"] / 1e3)  # GB/s
