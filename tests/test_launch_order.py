@@ -131,29 +131,33 @@ print(json.dumps([one, got]))
         assert rc == 0 and run_kernels(events) == n_steps * len(one[1])
 
 
-def test_transr_calls_that_form_no_v_launch_a_projection_without_it(recorder):
-    """The projection that forms V and dL/do too needs more registers: kge_score, kge_rank, steps with a loss kernel and steps of
-    rows of more than 128 floats have one without that code."""
-    forms, others = drive(recorder, '''
+def test_transr_projections_in_one_launch_with_the_gradients_where_no_kernel_comes_between(recorder):
+    """Steps with the logistic loss and uniform weights, rows of up to 128 floats and at most 1024 scores per row run in units; kge_score, kge_rank
+    and all other steps have the projections in a launch of their own, and those steps a kernel for V and one for the back-projection."""
+    units, others, scores = drive(recorder, '''
 lib.kge_score.argtypes = [vp] * 6 + [i64, vp, i64, i64, i32, f32, vp, vp, vp]
 lib.kge_rank.argtypes = [vp] * 6 + [i64, vp, i64, i64, i32, f32, vp, vp]
 
-def projections(events):
-    return sorted({e.split()[2] for e in events if "k_transr_project" in e})
+def kernels(events):
+    return sorted({k for e in events for k in ("project_units", "k_transr_projectI", "transr_dp", "transr_back") if k in e})
 
 def forward(x, name, outputs):
     p = 4096
     rec.recorder_clear()
     assert getattr(lib, name)(x.ctx, p, p, p, p, p, x.b, p, x.k, x.g, 0, 12.0, p, *[p] * outputs) == 0
-    return projections(rec.recorder_events().decode().splitlines())
+    return kernels(rec.recorder_events().decode().splitlines())
+
+def step(**kw):
+    return kernels(Library("transr", **{"k": 64, **kw}).steps(1)[1])
 
 x = Library("transr", k=64)
-plain = [forward(x, "kge_score", 2), forward(x, "kge_rank", 1), projections(Library("transr", k=64, adv_temperature=1.0).steps(1)[1]),
-         projections(Library("transr", k=64, loss=1).steps(1)[1])]
-print(json.dumps([projections(x.steps(1)[1]), plain]))
+print(json.dumps([[step(), step(D=128), step(k=1024), step(k=1, D=4), step(relations=1)],
+                  [step(adv_temperature=1.0), step(loss=1), step(D=132), step(k=1025)],
+                  [forward(x, "kge_score", 2), forward(x, "kge_rank", 1)]]))
 ''')
-    assert len(forms) == 1 and len(others) == 4
-    assert all(len(k) == 1 and k == others[0] and k != forms for k in others), (forms, others)
+    assert units == 5 * [["project_units"]]
+    assert others == 4 * [["k_transr_projectI", "transr_back", "transr_dp"]]
+    assert scores == 2 * [["k_transr_projectI"]]
 
 
 # (model, chunk, options, b, k of the first steps, k of the later ones): every form of the step, and changes of form on one context
