@@ -5,11 +5,11 @@
 // share the rows of a 64 x 64 tile through LDS (half the bytes), and a wave owns a 32 x 32 block of it over the whole of K.  A rank
 // hangs on the last bit of a score (split_forward in k_gemm.hip), so the sums keep their order: block kb of K goes into
 // accumulator kb mod 4, as it would into that wave of k_gemm_fwd, and the four are added up in order.
-// What bounds it: matrix instructions.  1000 x 2000 x 400 (two workgroups per CU): 49.1 -> 34.5 us for kge_rank with its metrics, the
+// What bounds it: matrix instructions.  1000 x 2000 x 400 (two workgroups per CU): 46.4 -> 30.4 us for kge_rank with its metrics, the
 // product 36 -> 22 by itself, of which the matrix instructions take 13 at the 2.07 GHz that the clock shows in it (2048 of about
 // 2550 cycles per block of K); 4000 cycles pass before the first block is there, 3600 behind the last.  Ranks: one global atomic per row
-// and tile instead of one per row and 32 columns (D 64: 35.9 -> 16.9 us).  Tiles of 64 x 128 (a CU each at this size) 35.5 us, of 128 x
-// 128 46 (half of the CUs), of 32 x 128 36.0; operands read from LDS before they are multiplied, without the second set: 37.1.
+// and tile instead of one per row and 32 columns (D 64: 35.9 -> 16.9 us).  Tiles of 64 x 128 (a CU each at this size) take 1 us more, of 128 x
+// 128 11.5 (half of the CUs), of 32 x 128 1.5; operands read from LDS before they are multiplied, without the second set: 2.6.
 #include "k_gemm_shared.h"
 
 namespace {

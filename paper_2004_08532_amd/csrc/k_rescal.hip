@@ -201,7 +201,7 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 constexpr int LT = 32;        // ... in tiles of LT x LT elements of the matrix
 
 // Runs of LONG_RUN positives and more.  dL/dM = U^T W over the run is a matrix product whose inner length is the run:
-// a workgroup owns one 32 x 32 tile of the matrix, its four waves take blocks of 16 positives in turn (16 loads in
+// a workgroup owns one 32 x 32 tile of the matrix, its waves (four, in k_rescal_runs eight) take blocks of 16 positives in turn (16 loads in
 // flight per lane, straight into fragments: a half-wave's load is 128 consecutive bytes of one factor row), their
 // sums meet in LDS in wave order, and Adagrad is applied to the tile.  What this avoids is the serial chain of the
 // slabs below, one round of loads per 4 positives (a relation with a quarter of the batch: 64 rounds and more).  From 16
@@ -338,7 +338,7 @@ static_assert(RUNS_LDS >= PT / 64 * LT * LT + PT, "long runs share the memory");
 // so that a workgroup that holds this part in registers does both, and Adagrad, from one read of it (UPDATE: the m positives are
 // all that the relation has; without it y and the factor rows).  Bound by memory: matrices and state, 235 MB per step at b 1024,
 // D 200 on the FB15k-sized graph, in 58 us (4.1 TB/s; a large copy reaches 5.2 to 6.0); with the longer runs' chain rule (7) in place of
-// the chain rule positive by positive (17) and an update of the matrices alone (55).  512 threads and 76 registers (three workgroups per CU): with 256 threads and
+// the chain rule positive by positive (17) and an update of the matrices alone (55).  512 threads and 78 registers (three workgroups per CU): with 256 threads and
 // four tiles per wave 62 us, with 64 columns per workgroup 66, with 64 registers (spills) 72, as workgroups that stay 75.
 // A wave takes tiles of 16 x; lane (q, l) holds n = 2 l + c, x = 4 q + i of each, which is the layout of a B operand of
 // v_mfma_f32_16x16x4_f32 for the first product (k = q, instruction i) and that of the result of the second (row 4 q + i, column l).

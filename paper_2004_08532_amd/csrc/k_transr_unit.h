@@ -7,11 +7,12 @@
 //   gradient rows += V M, with M read from LDS transposed; V goes through LDS to become the left operand
 // V is stored for k_transr_mgrad; P, scores and W are not.  (Launches of their own read N, M and V again, split all of them again for
 // every 64 rows, and stored P or V in between.)
-// What bounds it: one workgroup per CU (150 KB of LDS, 256 registers), two waves per SIMD whose phases hardly overlap.  FB15k-sized
-// (D 100, 667 units x 2, 5.2 per workgroup): 84 us; of about 26,000 cycles per unit M in three parts takes 2,800, the first product
-// 3,900 (its matrix instructions 2,700 per wave), scores, W and V 4,100, V through LDS and the second product 9,000, barriers 4,000.
+// What bounds it: one workgroup per CU (90 to 150 KB of LDS and 170 to 256 registers for rows of more than 32 floats), two waves per SIMD
+// whose phases hardly overlap.  FB15k-sized (D 100, 1332 units, 5.2 per workgroup, 1.5 positives per unit): 75 us; cycles per unit: M in three
+// parts and o to LDS 3,100, first product 4,500 (its matrix instructions 2,700 per wave), scores and W 1,800, V and dL/do 1,900, V through LDS and
+// into parts 2,300, second product 4,900, barriers 4,200, the next M asked for 800; 23,500 in all.  (D 128 26,100, D 64 9,500.)
 // Tried: M stored a second time, transposed, for the second product, and the sums of both products in registers throughout (104
-// spills) 152 us; M of the next unit asked for ahead of the second product (28 spills) 92 us; sums of four positives first 102 us.
+// spills) 152 us instead of 84; sums of four positives first 102 us.
 #pragma once
 
 namespace {
@@ -19,7 +20,8 @@ namespace {
 constexpr int UT = 512, UROWS = 128;  // threads, most corrupting rows per workgroup
 constexpr int UVP = 68;               // pitch of the staged V: 16-byte reads of sixteen rows free of conflicts
 
-// How a chunk's units are dealt to the workgroups: by their cost, a unit's two products (22,000 cycles) against what a positive adds.
+// How a chunk's units are dealt to the workgroups: by their cost, what a unit takes but for its positives (20,000 cycles at D 100) against what
+// one of these adds (2,400).
 constexpr int UNIT_COST = 8, POSITIVE_COST = 1;
 
 // LDS position (bf16 elements) of column `col` (a multiple of 4) of row `row` of a part of M: rows of 128 columns, 16-byte groups
