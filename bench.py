@@ -72,7 +72,8 @@ def algorithmic_work(w, h, r, t, neg, rowwise=False):
     pair_bwd = {"rotate": 2 * 9.0, "transe_l1": 2 * 3.0}.get(w.model)
     coords = D // 2 if w.model == "rotate" else D
     rescal = w.model in ("rescal", "transr")  # relation rows hold D x D matrices, read by their own kernels
-    transr = w.model == "transr"  # three products batched over the positives, 2 b k D^2 flops each
+    transr = w.model == "transr"  # products batched over the items, the (chunk, relation) that occur: 2 items k D^2 flops each
+    items = np.mean([sum(np.unique(c).size for c in r[s].reshape(C, -1)) for s in range(n)]) if transr else 0
     # RESCAL: matrices that the chain rule reads for how many positives.  Rows of 148 to 256 floats: once for each relation of 16
     # positives and more (the update does the others)
     chain_b, chain_m = b, b
@@ -85,9 +86,9 @@ def algorithmic_work(w, h, r, t, neg, rowwise=False):
         "rel_update": {"bytes": ur * 16.0 * Dr + 8.0 * b * D},
         "update": {"bytes": ue * (8.0 * D + 8.0 if rowwise else 16.0 * D) + n_keys * 4.0 * D +
                             (0 if rescal else ur * (8.0 * Dr + 8.0 if rowwise else 16.0 * Dr) + b * 4.0 * Dr)},
-        "neg_score": {"flops": pair_fwd * b * k * coords if pair_fwd else 2.0 * b * k * D * (D if transr else 1)},
+        "neg_score": {"flops": pair_fwd * b * k * coords if pair_fwd else 2.0 * k * D * (items * D if transr else b)},
         "neg_backward": {"flops": pair_bwd * b * k * coords if pair_bwd else
-                         (2.0 * b * k * D * D if transr else 4.0 * b * k * D)},
+                         (2.0 * items * k * D * D if transr else 4.0 * b * k * D)},
         # (TransR: o and p read, dL/do, dL/dp and the translation's gradient written)
         "chain": {"bytes": 4.0 * 5 * b * D if transr else 4.0 * (8 * chain_b * D + chain_m * Dr) if rescal else 4.0 * (6 * b * D + 2 * b * Dr)},
         "loss": {"bytes": 8.0 * b * k},

@@ -45,8 +45,9 @@ def test_elementwise_models_are_rated_by_the_vector_units():
 
 @pytest.mark.parametrize("us", [{"neg_score": 75.0, "chain": 5.0}, {"neg_score": 60.0, "neg_backward": 65.0, "chain": 30.0}])
 def test_transr_products_in_one_launch_or_two(us):
-    w, _, k = report("small-transr", {"gather": 10.7, "update": 8.3, "phi": 16.6, "rel_update": 15.7, **us})
-    product = 2.0 * w.batch * w.neg_per_chunk * w.ent_dim ** 2
+    w, work, k = report("small-transr", {"gather": 10.7, "update": 8.3, "phi": 16.6, "rel_update": 15.7, **us})
+    product = work["neg_score"]["flops"]  # 2 k D^2 per (chunk, relation) that occurs
+    assert w.batch / 4 < product / (2.0 * w.neg_per_chunk * w.ent_dim ** 2) < w.batch
     if "neg_backward" in us:
         assert k["neg_backward"]["achieved"] == pytest.approx(product / 65e-6 / 1e12)
         assert k["neg_score"]["achieved"] == pytest.approx(product / 60e-6 / 1e12)
