@@ -548,8 +548,8 @@ __device__ __forceinline__ void list_runs(const uint32_t* key, int n, RescalRuns
 
 // The chain rule of the long runs: workgroups of (16 sorted positions, first or second long run among them, slab), behind one that lists the
 // runs for the launch after this.  Few and short for steps of few relations, whose time is that of one workgroup: key -> position -> ids -> rows.
-// Positions and ids are asked for beside the keys, and a second run does not wait for the first.  us per step, head corrupted, the chain rule
-// per positive -> one workgroup for both runs, ids after the keys -> this (b, k, D, relations):  76, 16, 160, 3 37.8 -> 41.1 -> 37.6;  312, 240, 148, 3
+// Positions are asked for beside the keys, and a second run does not wait for the first.  us per step, head corrupted, the chain rule
+// per positive -> one workgroup for both runs, positions after the keys -> this (b, k, D, relations):  76, 16, 160, 3 37.8 -> 41.1 -> 37.6;  312, 240, 148, 3
 // 42.6 -> 44.7 -> 41.1;  512, 64, 200, 3 49.2 -> 49.6 -> 47.7;  1024, 256, 256, 3 80.6 -> 69.5 -> 68.8.
 __global__ __launch_bounds__(PT) void k_rescal_chain_runs(RescalUpdArgs a) {
     __shared__ __attribute__((aligned(16))) float lds[RUNS_LDS];
@@ -565,17 +565,16 @@ __global__ __launch_bounds__(PT) void k_rescal_chain_runs(RescalUpdArgs a) {
     const int lane = threadIdx.x & 63, e = b0 + lane - LONG_RUN;
     const bool in = e >= 0 && e < a.n && lane < 3 * LONG_RUN;
     const uint32_t mine = a.key[in ? e : 0];
-    // lane t: ids of position b0 + t, asked for beside the keys
+    const uint32_t pos = a.pos[min(b0 + (lane & (LONG_RUN - 1)), a.n - 1)];  // lane t: of b0 + t
     const StepView sv = step_view(a.chain.ids);
-    const RescalArgs& r = a.chain;
-    const uint32_t pos = a.pos[min(b0 + (lane & (LONG_RUN - 1)), a.n - 1)];
-    const uint32_t hid = (uint32_t)clamp_id(sv.h[pos], r.n_ent), tl = (uint32_t)clamp_id(sv.t[pos], r.n_ent);
-    const float cp = r.cpos[pos];
     for (int s = 0; s < LONG_RUN && b0 + s < a.n;) {
         const uint32_t key = __builtin_amdgcn_readlane(mine, LONG_RUN + s);
         const unsigned long long eq = __ballot(in && mine == key);
         const int m = __builtin_ctzll(~(eq >> (LONG_RUN + s))), here = min(m, LONG_RUN - s);
         if (__popcll(eq) >= LONG_RUN && others-- == 0) {
+            // (ahead of the matrix, which what waits for them would wait for too)
+            const uint32_t hid = (uint32_t)clamp_id(sv.h[pos], a.chain.n_ent), tl = (uint32_t)clamp_id(sv.t[pos], a.chain.n_ent);
+            const float cp = a.chain.cpos[pos];
             rescal_run_part<false, false>(a, sv.side, [&](int j, int m, int64_t& i, int64_t& h, int64_t& t, float& c) {
                 const int from = s + min(j + (lane >> 5), m - 1);
                 i = __shfl((int)pos, from, 64); h = (uint32_t)__shfl((int)hid, from, 64); t = (uint32_t)__shfl((int)tl, from, 64); c = __shfl(cp, from, 64);
