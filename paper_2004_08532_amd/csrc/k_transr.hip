@@ -33,7 +33,7 @@
 // K in blocks of 32 staged in LDS for its four waves (16 rows each), the next block's global loads in flight while one is
 // multiplied.  (128 rows per workgroup were measured: equal or slower, half as many waves fit a SIMD.)  All sums have a
 // fixed order.
-// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 191 us per step; 250 with projection, V M and M^T dL/do
+// FB15k-sized (b 1024, g 128, k 256, D 100; 667 items of the 1024 positives): 190 us per step; 250 with projection, V M and M^T dL/do
 // in launches of their own, 292 with all products in fp32 and V in a launch too (450 with three products per positive on 32x32 tiles).
 #include <type_traits>
 
@@ -64,7 +64,7 @@ struct TransrArgs {
     int out_w;       // project: store W = dL/df- instead of the score
     int train;       // project: keep the projections, scores in the order of the members; phi: likewise
     int segments;    // back, unit: ranges of a chunk's items (units)
-    int units;       // k_transr_project_units has run: gradients of the positives in parts of 16 rows, V and matrix gradients by unit
+    int units;       // k_transr_project_units runs, or has run: gradients of the positives in parts of 16 rows, V and matrix gradients by unit
     int unit_rows;   // unit: corrupting rows per workgroup
     TransrGroups q;
     float* O;        // [b x D]      o
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(RT) void k_transr_phi(TransrArgs a) {
         pa[it] = a.E + id * D;
         if (tid % 8 == 0 && row == tid / 8 + 32 * it) a.q.ent[2 * blk.off + row] = (uint32_t)id;
     }
-    if (a.train && tid < n) a.q.unit_of[a.q.members[blk.off + tid]] = tid > 0 ? -1 : c * a.g + (int)blockIdx.x - c * a.max_pblocks;
+    if (a.units && tid < n) a.q.unit_of[a.q.members[blk.off + tid]] = tid > 0 ? -1 : c * a.g + (int)blockIdx.x - c * a.max_pblocks;
     const float sigma = head ? -1.f : 1.f;
     const int l16 = tid & 15, quad = (tid & 63) >> 4;
     float ss[2] = {0.f, 0.f};
@@ -1225,7 +1225,7 @@ int back_segments(const TransrArgs& a) {
 }
 
 // Everything between phi and the matrix gradients in k_transr_project_units?  Wherever it can be.  us per step, launches of their own ->
-// units (b, g, k, D, relations)  1024, 128, 256, 100, 1345 244 -> 193;  D 128 280 -> 223;  D 64 150 -> 112;  k 500, D 32 148 -> 122;  20 relations
+// units (b, g, k, D, relations)  1024, 128, 256, 100, 1345 244 -> 190;  D 128 280 -> 220;  D 64 150 -> 111;  k 500, D 32 148 -> 120;  20 relations
 // 145 -> 130;  1024, 256, 640, 100, 1345 491 -> 330;  1024, 1024, 16, 100, 20 137 -> 102;  2000, 16, 8, 128, 1345 255 -> 253.  The only shapes found
 // where launches of their own are faster have rows of more than 96 floats, few corrupting rows, chunks of up to 128 and some ten positives
 // per relation and chunk, whose units a single wave per SIMD works through: 1024, 128, 8, 128, 5 98.6 -> 102.5;  16, 128, 10 95.8 -> 98.6;  32, 128, 20
@@ -1286,9 +1286,9 @@ auto mgrad_kernel() {
 
 // train: what later launches read stays in the order of the items' positives; otherwise the outputs are the caller's
 void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int gsz, float gamma, float* pos_out, bool train,
-                    hipStream_t st) {
+                    bool form_w, hipStream_t st) {
     TransrArgs a = make_args(c, E, R, ids, 0, gsz, gamma);
-    a.pos_out = pos_out; a.train = train;
+    a.pos_out = pos_out; a.train = train; a.units = train && in_units(c, form_w);
 #define L(NT) KGE_LAUNCH(c, k_transr_phi<NT>, dim3(ids.b / gsz * a.max_pblocks), dim3(RT), 0, st, a)
     KGE_BY_COLUMNS(a.D, L);
 #undef L

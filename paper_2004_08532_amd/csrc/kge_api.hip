@@ -106,7 +106,7 @@ void forward(kge_ctx* c, const float* ent, const float* rel, const StepIds& ids,
         return;
     }
     kge_launch_gather(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
-    if (c->cfg.model == KGE_TRANSR) kge_transr_phi(c, ent, rel, ids, chunk, gamma, pos_out, false, st);
+    if (c->cfg.model == KGE_TRANSR) kge_transr_phi(c, ent, rel, ids, chunk, gamma, pos_out, false, false, st);
     if (neg_out && k > 0) {
         if (c->cfg.model == KGE_TRANSR) {
             kge_transr_project(c, rel, ids, k, chunk, gamma, neg_out, ld_out, false, false, st);
@@ -158,7 +158,7 @@ int enqueue_transr_rest(kge_ctx* c, float* ent, float* ent_state, float* rel, fl
     int n_loss_parts;
     {
         ProfScope p(c, KGE_PROF_PHI);
-        kge_transr_phi(c, ent, rel, ids, G, gamma, nullptr, true, st);
+        kge_transr_phi(c, ent, rel, ids, G, gamma, nullptr, true, form_w, st);
     }
     {
         ProfScope p(c, KGE_PROF_SCORE);

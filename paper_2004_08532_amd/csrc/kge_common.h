@@ -256,7 +256,7 @@ size_t kge_transr_back_floats(const kge_config& cfg);
 size_t kge_transr_go_floats(const kge_config& cfg);
 size_t kge_transr_p_floats(const kge_config& cfg);
 void kge_transr_phi(kge_ctx* c, const float* E, const float* R, const StepIds& ids, int g, float gamma, float* pos_out,
-                    bool train, hipStream_t st);
+                    bool train, bool form_w, hipStream_t st);
 // train: keep the projections, rows in the order of the members; form_w: store W = dL/df- instead of the scores, returns the number of loss sums left
 int kge_transr_project(kge_ctx* c, const float* R, const StepIds& ids, int k, int g, float gamma, float* out, int ld_out,
                        bool train, bool form_w, hipStream_t st);
